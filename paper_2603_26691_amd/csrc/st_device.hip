@@ -1499,17 +1499,46 @@ __global__ void k_stage(int64_t n, const double *x, const double *up, const doub
 // ---------------------------------------------------------------------------
 // outputs
 // ---------------------------------------------------------------------------
+// Where the read-out goes (any may be null); particle k's row k of each.
+struct ParticleOut {
+    double *x, *up, *d;
+    int64_t *id;
+    int32_t *cell;
+};
+
+// Writes particle k of chunk c with stored position o, velocity v, diameter dd.
+template <class T>
+__device__ __forceinline__ void put_particle(const ParticleOut &out, const Params &p, int64_t k,
+                                             int64_t c, const T (&o)[3], const T (&v)[3], T dd)
+{
+    const int32_t cc[3] = {(int32_t)(c % p.nc[0]), (int32_t)((c / p.nc[0]) % p.nc[1]),
+                           (int32_t)(c / ((int64_t)p.nc[0] * p.nc[1]))};
+    for (int a = 0; a < 3; ++a) {
+        const double org = (double)((int64_t)cc[a] * p.E);
+        if (p.global) {   // binary32 metres
+            if (out.x) out.x[3 * k + a] = (double)o[a];
+            if (out.cell) out.cell[3 * k + a] = gcell((float)o[a], p.inv_hf[a], p.n[a]);
+        } else {
+            if (out.x) out.x[3 * k + a] = (org + (double)o[a]) * p.h[a];
+            if (out.cell)
+                out.cell[3 * k + a] = cc[a] * p.E + min(max((int)o[a], 0), p.E - 1);
+        }
+        if (out.up) out.up[3 * k + a] = (double)v[a];
+    }
+    if (out.d) out.d[k] = (double)dd;
+    if (out.id) out.id[k] = k;
+}
+
+// Read-out straight from the store: a particle's row of each output lies
+// wherever its id does, so each is a partial-line write.
 template <class T>
 __global__ void __launch_bounds__(256) k_get_particles(View<T> V, const int32_t *items,
                                                        const int32_t *nitems, Params p,
-                                                       int64_t count, double *x, double *up,
-                                                       double *d, int64_t *id, int32_t *cell)
+                                                       int64_t count, ParticleOut out)
 {
     const int64_t ni = *nitems;
     for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
         const int64_t c = items[2 * it], seg = items[2 * it + 1];
-        const int64_t cc[3] = {c % p.nc[0], (c / p.nc[0]) % p.nc[1],
-                               c / ((int64_t)p.nc[0] * p.nc[1])};
         const int64_t s0 = V.base[c] + seg * kSeg;
         const int64_t s1 = min(s0 + (int64_t)kSeg, V.base[c] + (int64_t)V.cnt[c]);
         for (int64_t q = s0 + threadIdx.x; q < s1; q += blockDim.x) {
@@ -1518,21 +1547,95 @@ __global__ void __launch_bounds__(256) k_get_particles(View<T> V, const int32_t 
             if (k < 0 || k >= count) continue;  // never in a consistent store
             const T o[3] = {V.ox[q], V.oy[q], V.oz[q]};
             const T v[3] = {V.vx[q], V.vy[q], V.vz[q]};
-            for (int a = 0; a < 3; ++a) {
-                const double org = (double)(cc[a] * p.E);
-                if (p.global) {   // binary32 metres
-                    if (x) x[3 * k + a] = (double)o[a];
-                    if (cell) cell[3 * k + a] = gcell((float)o[a], p.inv_hf[a], p.n[a]);
-                } else {
-                    if (x) x[3 * k + a] = (org + (double)o[a]) * p.h[a];
-                    if (cell)
-                        cell[3 * k + a] = (int32_t)(cc[a] * p.E + min(max((int)o[a], 0), p.E - 1));
-                }
-                if (up) up[3 * k + a] = (double)v[a];
-            }
-            if (d) d[k] = (double)V.d[q];
-            if (id) id[k] = k;
+            put_particle<T>(out, p, k, c, o, v, V.d[q]);
         }
+    }
+}
+
+// Read-out of many particles in two passes: one scattered write per particle
+// (its record with its chunk, by id), then the records in id order into the
+// outputs, whole lines at a time.  The records lie in the re-bin's second
+// store, which holds nothing between re-bins: seven arrays of slots T, each a
+// run of slots / 8 records of eight T, together at least 7/8 * 5/4 of the
+// capacity.  1e7 binary32 particles, all outputs: 0.67 ms (0.075 ms clearing,
+// 0.38 ms the scattered records, 0.22 ms out), against 2.06 ms directly.
+template <class T>
+struct RecordArrays {
+    T *a[7];
+    int64_t per;   // records per array
+
+    __device__ __forceinline__ MoverRec<T> *at(int64_t k) const
+    {
+        T *b = a[0];
+        int64_t j = k;
+#pragma unroll
+        for (int i = 1; i < 7; ++i)
+            if (k >= i * per) {
+                b = a[i];
+                j = k - i * per;
+            }
+        return reinterpret_cast<MoverRec<T> *>(b) + j;
+    }
+};
+
+template <class T>
+__global__ void __launch_bounds__(256) k_records_clear(RecordArrays<T> r, int64_t count)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < count) *r.at(k) = MoverRec<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), -1};
+}
+
+template <class T>
+__global__ void __launch_bounds__(256) k_records_by_id(View<T> V, const int32_t *items,
+                                                       const int32_t *nitems, int64_t count,
+                                                       RecordArrays<T> r)
+{
+    const int64_t ni = *nitems;
+    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
+        const int64_t c = items[2 * it], seg = items[2 * it + 1];
+        const int64_t s0 = V.base[c] + seg * kSeg;
+        const int64_t s1 = min(s0 + (int64_t)kSeg, V.base[c] + (int64_t)V.cnt[c]);
+        for (int64_t q = s0 + threadIdx.x; q < s1; q += blockDim.x) {
+            const MoverRec<T> m{V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q],
+                                (int32_t)c};
+            const int64_t k = V.id[q];
+            if (!occupied(m.ox, m.d) || k < 0 || k >= count) continue;
+            *r.at(k) = m;
+        }
+    }
+}
+
+// A workgroup's 256 rows of the [count][3] outputs pass through LDS, so that
+// the lanes' stores are consecutive.
+template <class T>
+__global__ void __launch_bounds__(256) k_records_out(RecordArrays<T> r, Params p, int64_t count,
+                                                     ParticleOut out)
+{
+    __shared__ double sx[768], su[768];
+    __shared__ int32_t sc[768];
+    __shared__ int there[256];
+    const int64_t k0 = (int64_t)blockIdx.x * 256;
+    const int64_t k = k0 + threadIdx.x;
+    MoverRec<T> m;
+    m.id = -1;
+    if (k < count) m = *r.at(k);
+    there[threadIdx.x] = m.id >= 0;   // else no slot holds it (never in a consistent store)
+    if (m.id >= 0) {
+        const T o[3] = {m.ox, m.oy, m.oz};
+        const T v[3] = {m.vx, m.vy, m.vz};
+        const ParticleOut rows{sx, su, nullptr, nullptr, sc};
+        put_particle<T>(rows, p, threadIdx.x, m.id, o, v, m.d);
+        if (out.d) out.d[k] = (double)m.d;
+        if (out.id) out.id[k] = k;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int e = threadIdx.x + 256 * j;
+        if (!there[e / 3]) continue;
+        if (out.x) out.x[3 * k0 + e] = sx[e];
+        if (out.up) out.up[3 * k0 + e] = su[e];
+        if (out.cell) out.cell[3 * k0 + e] = sc[e];
     }
 }
 
@@ -1766,6 +1869,7 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 {
     const RebinArgs<T> a = rebin_args<T>(c, npend);
     const int64_t C = c->C;
+    c->store_stream = s;
     // a thread per mover for the arrivals (at most mcap of them); the count
     // (rare) strides over the items
     int64_t g = std::max<int64_t>((c->mcap + kArriveBlock - 1) / kArriveBlock, c->max_items);
@@ -1923,14 +2027,35 @@ hipError_t launch_stage_inject(st_ctx *c, int64_t n, const double *x, const doub
     });
 }
 
+// The two-pass read-out from this many particles on (below it the outputs stay
+// in the caches and its two launches more cost more than they save).
+constexpr int64_t kRecordsMin = 1 << 16;
+
 hipError_t launch_get_particles(st_ctx *c, double *x, double *up, double *d, int64_t *id,
                                 int32_t *cell, hipStream_t s)
 {
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         const int64_t gi = c->max_items < 65536 ? c->max_items : 65536;
-        hipLaunchKernelGGL((k_get_particles<T>), dim3(gi), dim3(256), 0, s, view_of<T>(c, 0),
-                           c->items, c->flags + F_NITEMS, c->prm, c->count, x, up, d, id, cell);
+        const View<T> V = view_of<T>(c, 0);
+        const int32_t *ni = c->flags + F_NITEMS;
+        const ParticleOut out{x, up, d, id, cell};
+        // The second store is this stream's to use when this stream wrote the
+        // store last: whoever writes the store or reads it from another
+        // stream has ordered that stream against this one first.
+        if (c->count < kRecordsMin || s != c->store_stream) {
+            hipLaunchKernelGGL((k_get_particles<T>), dim3(gi), dim3(256), 0, s, V, c->items, ni,
+                               c->prm, c->count, out);
+            return hipGetLastError();
+        }
+        RecordArrays<T> r;
+        for (int k = 0; k < 7; ++k) r.a[k] = (T *)c->store[1][k];
+        r.per = c->slots / 8;
+        const dim3 g((c->count + 255) / 256);
+        hipLaunchKernelGGL((k_records_clear<T>), g, dim3(256), 0, s, r, c->count);
+        hipLaunchKernelGGL((k_records_by_id<T>), dim3(gi), dim3(256), 0, s, V, c->items, ni,
+                           c->count, r);
+        hipLaunchKernelGGL((k_records_out<T>), g, dim3(256), 0, s, r, c->prm, c->count, out);
         return hipGetLastError();
     });
 }
@@ -2054,6 +2179,7 @@ hipError_t launch_snapshot(st_ctx *c, void *dst, int restore, hipStream_t s)
         return hipGetLastError();
     });
     if (e != hipSuccess || !restore) return e;
+    c->store_stream = s;
     return launch_items(c, s);
 }
 

@@ -154,6 +154,7 @@ struct st_ctx {
     int64_t pending = 0;       // injected particles waiting in the staging area
     int64_t next_id = 0;
     int32_t epoch = 0;         // tag of the last step or flush launched
+    hipStream_t store_stream = nullptr;   // stream of the last launch that wrote the store
 
     // device memory
     void *store[2][8] = {};    // SoA arrays: [0] the store, [1] re-bin target
