@@ -17,6 +17,7 @@
 // returns them).
 #include "st_internal.h"
 
+#include <algorithm>
 #include <mutex>
 
 // Partial results of st_bounding_boxes_noalloc (the min and max bounds of up
@@ -128,9 +129,118 @@ struct BoxArgs {
     unsigned long long *box;
 };
 
-// One workgroup per work item.  When every particle of a wave that belongs
-// to a partition belongs to the same one (the usual case while partitions are
-// compact), the wave reduces first and one lane updates the box.
+// The partition (below nparts, else -1) and position of slot q of chunk
+// (cx, cy, cz) E cells.
+template <class T>
+__device__ __forceinline__ int64_t box_particle(const BoxArgs<T> &a, int32_t id, T x, T y, T z,
+                                                T d, const int64_t (&cc)[3], double (&xg)[3])
+{
+    const Params &p = a.p;
+    // a hole has a -1 offset (binary32) or a negated diameter (binary64)
+    if (!(x >= T(0) && d > T(0)) || id < a.id0) return -1;
+    const int64_t rel = id - a.id0;    // below 2^31
+    const int64_t part = a.per_part > 0x7fffffff ? 0 : (uint32_t)rel / (uint32_t)a.per_part;
+    if (part >= a.nparts) return -1;
+    const T o[3] = {x, y, z};
+    for (int ax = 0; ax < 3; ++ax)   // binary32 metres in the FP32-everywhere form
+        xg[ax] = p.global ? (double)o[ax] : ((double)(cc[ax] * p.E) + (double)o[ax]) * p.h[ax];
+    return part;
+}
+
+// The boxes of up to kBoxTable partitions in LDS, workgroup by workgroup: a
+// workgroup takes every gridDim.x-th work item, four consecutive slots a
+// thread, and keeps its own table of the partitions [blockIdx.y Kp,
+// (blockIdx.y + 1) Kp).  A particle inside its partition's box as the table
+// has it adds nothing (of n particles about ln n per bound do), so the atomics
+// are few; the tables are then reduced over the workgroups.  Atomics on the
+// boxes in memory are served beyond the XCD's own L2 (six a particle: 2.46 ms
+// for 1e7 droplets in 4096 partitions, against 0.17 ms this way: 0.133 ms here,
+// 0.037 ms the reduction).
+constexpr int kBoxTable = 3328;      // 48 B each: 156 KB of the CU's 160 KB LDS
+constexpr int kBoxPasses = 4;        // tables' worth of partitions (the store is read once each)
+constexpr int kBoxGroups = 256;      // workgroups per table: one a CU
+
+template <class T>
+__global__ void __launch_bounds__(1024) k_bbox_tables(BoxArgs<T> a, int32_t Kp,
+                                                      unsigned long long *tables)
+{
+    extern __shared__ unsigned long long tab[];   // [Kp][6]
+    constexpr int G = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(G)));
+    typedef int32_t ivec __attribute__((ext_vector_type(G)));
+    static_assert(kAlign % G == 0, "chunk rooms must hold whole particle groups");
+    const Params &p = a.p;
+    const int32_t first = blockIdx.y * Kp;
+    for (int t = threadIdx.x; t < 6 * Kp; t += 1024) tab[t] = (t % 6) < 3 ? kPosInf : 0ull;
+    __syncthreads();
+    const int64_t ni = *a.nitems;
+    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
+        const int64_t c = a.items[2 * it], seg = a.items[2 * it + 1];
+        const int64_t cc[3] = {c % p.nc[0], (c / p.nc[0]) % p.nc[1],
+                               c / ((int64_t)p.nc[0] * p.nc[1])};
+        const int64_t s0 = a.V.base[c] + seg * kSeg;
+        const int64_t s1 = min(s0 + (int64_t)kSeg, a.V.base[c] + (int64_t)a.V.cnt[c]);
+        // a group that runs past s1 stays inside the chunk's room
+        for (int64_t q = s0 + G * (int64_t)threadIdx.x; q < s1; q += 1024 * G) {
+            const vec x = *(const vec *)(a.V.ox + q), y = *(const vec *)(a.V.oy + q),
+                      z = *(const vec *)(a.V.oz + q), d = *(const vec *)(a.V.d + q);
+            const ivec id = *(const ivec *)(a.V.id + q);
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                double xg[3];
+                int64_t part = -1;
+                if (q + k < s1) part = box_particle<T>(a, id[k], x[k], y[k], z[k], d[k], cc, xg);
+                part -= first;
+                if (part < 0 || part >= Kp) continue;
+                unsigned long long *b = tab + 6 * part;
+                for (int ax = 0; ax < 3; ++ax) {
+                    const unsigned long long v = (unsigned long long)__double_as_longlong(xg[ax]);
+                    if (v < b[ax]) atomicMin(b + ax, v);
+                    if (v > b[3 + ax]) atomicMax(b + 3 + ax, v);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    unsigned long long *out = tables + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 6 * Kp;
+    for (int t = threadIdx.x; t < 6 * Kp; t += 1024) out[t] = tab[t];
+}
+
+// the tables of `groups` workgroups into the boxes
+__global__ void __launch_bounds__(256) k_bbox_reduce(const unsigned long long *tables,
+                                                     int32_t groups, int32_t Kp, int64_t nparts,
+                                                     unsigned long long *box)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= 6 * nparts) return;
+    const int64_t part = t / 6, b = t - 6 * part;
+    const int64_t pass = part / Kp;
+    const unsigned long long *v = tables + (pass * groups * Kp + (part - pass * Kp)) * 6;
+    unsigned long long lo = kPosInf, hi = 0ull;
+#pragma unroll 8
+    for (int32_t g = 0; g < groups; ++g) {
+        const unsigned long long w = v[(int64_t)g * 6 * Kp + b];
+        lo = w < lo ? w : lo;
+        hi = w > hi ? w : hi;
+    }
+    // an empty partition keeps min = +inf; its max becomes -inf (positions are
+    // non-negative, and 0.0 is the bit pattern 0, so its min tells)
+    if (b >= 3) {
+        unsigned long long m = kPosInf;
+#pragma unroll 8
+        for (int32_t g = 0; g < groups; ++g) {
+            const unsigned long long w = v[(int64_t)g * 6 * Kp];
+            m = w < m ? w : m;
+        }
+        if (m == kPosInf) hi = kNegInf;
+    }
+    box[t] = b < 3 ? lo : hi;
+}
+
+// One workgroup per work item, updating the boxes in memory.  When every
+// particle of a wave that belongs to a partition belongs to the same one (the
+// usual case while partitions are compact), the wave reduces first and one
+// lane updates the box.
 template <class T>
 __global__ void __launch_bounds__(256) k_bbox(BoxArgs<T> a)
 {
@@ -147,17 +257,9 @@ __global__ void __launch_bounds__(256) k_bbox(BoxArgs<T> a)
             const int64_t q = q0 + threadIdx.x;
             int64_t part = -1;
             double xg[3] = {0.0, 0.0, 0.0};
-            // a hole has a -1 offset (binary32) or a negated diameter (binary64)
-            if (q < s1 && a.V.ox[q] >= T(0) && a.V.d[q] > T(0)) {
-                const int64_t id = a.V.id[q];
-                if (id >= a.id0 && (id - a.id0) / a.per_part < a.nparts) {
-                    part = (id - a.id0) / a.per_part;
-                    const T o[3] = {a.V.ox[q], a.V.oy[q], a.V.oz[q]};
-                    for (int ax = 0; ax < 3; ++ax)   // binary32 metres in the FP32-everywhere form
-                        xg[ax] = p.global ? (double)o[ax]
-                                          : ((double)(cc[ax] * p.E) + (double)o[ax]) * p.h[ax];
-                }
-            }
+            if (q < s1)
+                part = box_particle<T>(a, a.V.id[q], a.V.ox[q], a.V.oy[q], a.V.oz[q], a.V.d[q],
+                                       cc, xg);
             const uint64_t has = __ballot(part >= 0);
             if (has == 0) continue;
             const int lead = __ffsll((unsigned long long)has) - 1;
@@ -231,18 +333,40 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
                                  double *box, hipStream_t s)
 {
     unsigned long long *b = (unsigned long long *)box;
-    hipLaunchKernelGGL(k_bbox_init, dim3(blocks_for(6 * nparts)), dim3(256), 0, s, b, nparts);
-    const int64_t gi = c->max_items < 65536 ? c->max_items : 65536;
-    auto run = [&](auto t) {
+    // Tables when the partitions fit a few of them and the re-bin's second
+    // store (nothing lies in it between re-bins; it is this stream's to use when
+    // this stream wrote the store last) has room for at least 32 workgroups'.
+    // Beyond that each further table reads the store again, and a store too
+    // small for the tables has few atomics to make.
+    const int64_t passes = (nparts + kBoxTable - 1) / kBoxTable;
+    const int64_t Kp = (nparts + passes - 1) / passes;
+    const int64_t room = c->slots * (int64_t)c->tsize / (passes * Kp * 48);
+    const int64_t groups = std::min(std::min<int64_t>(kBoxGroups, room), c->max_items);
+    const bool tables = passes <= kBoxPasses && s == c->store_stream &&
+                        groups >= std::min<int64_t>(32, c->max_items);
+    auto run = [&](auto t) -> hipError_t {
         using T = decltype(t);
         BoxArgs<T> a{store_view<T>(c), c->items, c->flags + F_NITEMS, c->prm, id0, per_part,
                      nparts, b};
+        if (tables) {
+            unsigned long long *w = (unsigned long long *)c->store[1][0];
+            hipError_t e = hipFuncSetAttribute((const void *)k_bbox_tables<T>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               kBoxTable * 48);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((k_bbox_tables<T>), dim3(groups, passes), dim3(1024),
+                               (size_t)Kp * 48, s, a, (int32_t)Kp, w);
+            hipLaunchKernelGGL(k_bbox_reduce, dim3((6 * nparts + 255) / 256), dim3(256), 0, s, w,
+                               (int32_t)groups, (int32_t)Kp, nparts, b);
+            return hipGetLastError();
+        }
+        hipLaunchKernelGGL(k_bbox_init, dim3(blocks_for(6 * nparts)), dim3(256), 0, s, b, nparts);
+        const int64_t gi = c->max_items < 65536 ? c->max_items : 65536;
         hipLaunchKernelGGL((k_bbox<T>), dim3(gi), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_bbox_finish, dim3(blocks_for(nparts)), dim3(256), 0, s, b, nparts);
+        return hipGetLastError();
     };
-    if (c->form == ST_FORM_FP64) run(double(0));
-    else run(float(0));
-    hipLaunchKernelGGL(k_bbox_finish, dim3(blocks_for(nparts)), dim3(256), 0, s, b, nparts);
-    return hipGetLastError();
+    return c->form == ST_FORM_FP64 ? run(double(0)) : run(float(0));
 }
 
 namespace {
