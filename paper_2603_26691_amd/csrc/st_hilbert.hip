@@ -31,57 +31,96 @@ static __device__ __align__(256) unsigned long long scratch[st::kNoAllocMaxParts
 namespace st {
 namespace {
 
-// Hilbert curve position h -> voxel: the index is split into its transpose
-// (bit level l of axis i is bit 3 l + 2 - i of h), then Skilling's
+// bits 0, 3, 6, ... 27 of v, packed
+__device__ __forceinline__ uint32_t every_third(uint32_t v)
+{
+    v &= 0x09249249u;
+    v = (v | (v >> 2)) & 0x030C30C3u;
+    v = (v | (v >> 4)) & 0x0300F00Fu;
+    v = (v | (v >> 8)) & 0x030000FFu;
+    return (v | (v >> 16)) & 0x3FFu;
+}
+
+// Hilbert curve position h (below 2^30) -> voxel: the index is split into its
+// transpose (bit level l of axis i is bit 3 l + 2 - i of h), then Skilling's
 // transpose-to-axes (AIP Conf. Proc. 707, 2004): Gray decode, then undo the
 // reflections and exchanges from the least significant level up.
-__device__ void hilbert_voxel(int order, int64_t h, int32_t c[3])
+__device__ __forceinline__ void hilbert_voxel(int order, uint32_t h, uint32_t (&X)[3])
 {
-    uint32_t X[3] = {0u, 0u, 0u};
-    for (int l = 0; l < order; ++l)
-        for (int i = 0; i < 3; ++i)
-            X[i] |= (uint32_t)((h >> (3 * l + 2 - i)) & 1) << l;
-    const uint32_t N = 2u << (order - 1);
-    uint32_t t = X[2] >> 1;
-    for (int i = 2; i > 0; --i) X[i] ^= X[i - 1];
-    X[0] ^= t;
-    for (uint32_t Q = 2; Q != N; Q <<= 1) {
-        const uint32_t P = Q - 1;
+    X[0] = every_third(h >> 2);
+    X[1] = every_third(h >> 1);
+    X[2] = every_third(h);
+    const uint32_t top = X[2] >> 1;
+    X[2] ^= X[1];
+    X[1] ^= X[0];
+    X[0] ^= top;
+    for (int l = 1; l < order; ++l) {
+        const uint32_t P = (1u << l) - 1u;
+#pragma unroll
         for (int i = 2; i >= 0; --i) {
-            if (X[i] & Q) {
-                X[0] ^= P;
-            } else {
-                t = (X[0] ^ X[i]) & P;
-                X[0] ^= t;
-                X[i] ^= t;
-            }
+            // all ones when the axis has bit l: the first axis is reflected,
+            // else the low bits of the two axes are exchanged
+            const uint32_t m = (uint32_t)-(int32_t)((X[i] >> l) & 1u);
+            const uint32_t t = (X[0] ^ X[i]) & P & ~m;
+            X[0] ^= (P & m) | t;
+            if (i > 0) X[i] ^= t;
         }
     }
-    for (int i = 0; i < 3; ++i) c[i] = (int32_t)X[i];
 }
 
 struct HilbertArgs {
     int32_t order;
     int64_t nseg, seg_begin, per_seg;
+    int64_t q, r;        // V / nseg and V % nseg, V = 8^order voxels
     double hv[3];        // voxel width per axis, L / 2^order
 };
 
-// positions of particles first .. first + n - 1 of the call (particle g of the
-// call is particle g mod per_seg of segment seg_begin + g / per_seg)
-__global__ void k_hilbert_positions(HilbertArgs a, int64_t first, int64_t n, const double *u,
-                                    double *x)
+// the first voxel of segment s: floor(s V / nseg) = s q + floor(s r / nseg)
+template <class I>
+__device__ __forceinline__ I segment_voxel(const HilbertArgs &a, I s)
 {
-    const int64_t V = (int64_t)1 << (3 * a.order);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t g = first + i;
-        const int64_t s = a.seg_begin + g / a.per_seg, k = g % a.per_seg;
-        const int64_t v0 = s * V / a.nseg, v1 = (s + 1) * V / a.nseg;
-        const int64_t v = v0 + k * (v1 - v0) / a.per_seg;
-        int32_t c[3];
-        hilbert_voxel(a.order, v, c);
-        for (int ax = 0; ax < 3; ++ax)
-            x[3 * i + ax] = ((double)c[ax] + u[3 * i + ax]) * a.hv[ax];
+    return s * (I)a.q + s * (I)a.r / (I)a.nseg;
+}
+
+// positions of particles first .. first + n - 1 of the call (particle g of the
+// call is particle g mod per_seg of segment seg_begin + g / per_seg).  I: the
+// integer type of the divisions; 32 bits where every product fits (a 64-bit
+// division is a long sequence on this chip, and there are four a particle).
+// The uniforms and positions pass through LDS, so that the lanes' accesses to
+// the [n][3] arrays are consecutive.
+// Bound by HBM (48 B a particle): 1e7 particles in 0.095 ms, 5.1 TB/s, against
+// 0.135 ms with 64-bit divisions, bit-by-bit splitting and direct accesses.
+template <class I>
+__global__ void __launch_bounds__(256) k_hilbert_positions(HilbertArgs a, int64_t first,
+                                                           int64_t n, const double *u, double *x)
+{
+    __shared__ double sh[3 * 256];
+    for (int64_t b = (int64_t)blockIdx.x * 256; b < n; b += (int64_t)gridDim.x * 256) {
+        const int nb = (int)(n - b < 256 ? n - b : 256);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int e = threadIdx.x + 256 * j;
+            if (e < 3 * nb) sh[e] = u[3 * b + e];
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < nb) {
+            const I g = (I)(first + b + threadIdx.x);
+            const I sl = g / (I)a.per_seg, k = g - sl * (I)a.per_seg;
+            const I s = sl + (I)a.seg_begin;
+            const I v0 = segment_voxel<I>(a, s), v1 = segment_voxel<I>(a, s + 1);
+            const I v = v0 + k * (v1 - v0) / (I)a.per_seg;
+            uint32_t c[3];
+            hilbert_voxel(a.order, (uint32_t)v, c);
+            for (int ax = 0; ax < 3; ++ax)
+                sh[3 * threadIdx.x + ax] = ((double)c[ax] + sh[3 * threadIdx.x + ax]) * a.hv[ax];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int e = threadIdx.x + 256 * j;
+            if (e < 3 * nb) x[3 * b + e] = sh[e];
+        }
+        __syncthreads();
     }
 }
 
@@ -323,9 +362,19 @@ hipError_t launch_hilbert_positions(int32_t order, int64_t nseg, int64_t seg_beg
     a.nseg = nseg;
     a.seg_begin = seg_begin;
     a.per_seg = per_seg;
+    const int64_t V = (int64_t)1 << (3 * order);
+    a.q = V / nseg;
+    a.r = V % nseg;
     for (int ax = 0; ax < 3; ++ax) a.hv[ax] = L[ax] / (double)((int64_t)1 << order);
-    hipLaunchKernelGGL(k_hilbert_positions, dim3(blocks_for(n)), dim3(256), 0, s, a, first, n, u,
-                       x);
+    const dim3 g(blocks_for(n, 1 << 20));
+    // every product and index of the kernel below 2^32: s r with s <= nseg and
+    // r < nseg, k (v1 - v0) with k < per_seg and v1 - v0 <= q + 1
+    const int64_t lim = (int64_t)1 << 32;
+    const bool narrow = first + n < lim && nseg < (1 << 16) && per_seg < lim / (a.q + 1);
+    if (narrow)
+        hipLaunchKernelGGL(k_hilbert_positions<uint32_t>, g, dim3(256), 0, s, a, first, n, u, x);
+    else
+        hipLaunchKernelGGL(k_hilbert_positions<int64_t>, g, dim3(256), 0, s, a, first, n, u, x);
     return hipGetLastError();
 }
 
