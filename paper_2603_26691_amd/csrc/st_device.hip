@@ -1639,23 +1639,52 @@ __global__ void __launch_bounds__(256) k_records_out(RecordArrays<T> r, Params p
     }
 }
 
-template <class A>
-__global__ void k_get_sources(A *src, Params p, double *out, int reset)
+// Chunk-major sources into the field layout, and their reset.  A thread takes
+// two neighbouring cells along x in all E rows (j) of one chunk row, its loads
+// issued before its stores: a wave's stores are whole rows of up to 128 cells,
+// and the 64-byte rows it reads from a chunk are consecutive (a chunk's E rows
+// of one k), so every line is used whole by one wave.  128^3 cells with reset:
+// 21.9 us (150 MB), against 36.0 us with a thread per output value and its
+// 64-bit divisions; 256^3: 281 against 343 us.
+template <class A, int E>
+__global__ void __launch_bounds__(256) k_get_sources(A *src, Params p, double *out, int reset)
 {
-    const int64_t nx = p.n[0], ny = p.n[1], nz = p.n[2];
-    const int64_t ncell = nx * ny * nz;
-    const int E = p.E;
-    const int64_t E3 = (int64_t)E * E * E;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < 3 * ncell;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t comp = t / ncell;
-        const int64_t r = t - comp * ncell;
-        const int64_t i = r % nx, j = (r / nx) % ny, k = r / (nx * ny);
-        const int64_t c = ((k / E) * p.nc[1] + (j / E)) * p.nc[0] + (i / E);
-        const int64_t l = ((k % E) * E + (j % E)) * E + (i % E);
-        A *s = src + c * 3 * E3 + comp * E3 + l;
-        out[t] = (double)*s;
-        if (reset) *s = A(0);
+    typedef A pair __attribute__((ext_vector_type(2)));
+    typedef double dpair __attribute__((ext_vector_type(2)));
+    constexpr int E3 = E * E * E;
+    const int64_t nx2 = p.n[0] / 2, total = 3 * nx2 * p.nc[1] * p.n[2];
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= total) return;
+    int64_t row;       // (comp, k, chunk row)
+    int32_t i;
+    if (total <= 0xffffffffll) {   // one 32-bit division
+        row = (uint32_t)t / (uint32_t)nx2;
+        i = (int32_t)((uint32_t)t - (uint32_t)row * (uint32_t)nx2) * 2;
+    } else {
+        row = t / nx2;
+        i = (int32_t)(t - row * nx2) * 2;
+    }
+    const int64_t ck = row / p.nc[1];
+    const int32_t cy = (int32_t)(row - ck * p.nc[1]);
+    const int32_t comp = (int32_t)(ck / p.n[2]);
+    const int32_t k = (int32_t)(ck - (int64_t)comp * p.n[2]);
+    const int64_t c = ((int64_t)(k / E) * p.nc[1] + cy) * p.nc[0] + i / E;
+    A *s = src + (c * 3 + comp) * E3 + (k % E) * (E * E) + i % E;
+    double *o = out + (((int64_t)comp * p.n[2] + k) * p.n[1] + cy * E) * p.n[0] + i;
+    pair v[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = *(const pair *)(s + j * E);
+    const bool whole = ((uintptr_t)out & 15) == 0;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        const dpair w = {(double)v[j][0], (double)v[j][1]};
+        if (whole) {
+            *(dpair *)(o + (int64_t)j * p.n[0]) = w;
+        } else {
+            o[(int64_t)j * p.n[0]] = w[0];
+            o[(int64_t)j * p.n[0] + 1] = w[1];
+        }
+        if (reset) *(pair *)(s + j * E) = pair{A(0), A(0)};
     }
 }
 
@@ -2064,9 +2093,15 @@ hipError_t launch_get_sources(st_ctx *c, double *out, int reset, hipStream_t s)
 {
     return dispatch(c, [&](auto, auto acc) -> hipError_t {
         using A = decltype(acc);
-        const int64_t n = 3 * (int64_t)c->prm.n[0] * c->prm.n[1] * c->prm.n[2];
-        hipLaunchKernelGGL((k_get_sources<A>), dim3(grid_for(n, 16384)), dim3(256), 0, s,
-                           (A *)c->src, c->prm, out, reset);
+        const Params &p = c->prm;
+        const int64_t n = 3 * (int64_t)(p.n[0] / 2) * p.nc[1] * p.n[2];
+        const dim3 g((n + 255) / 256);
+        A *src = (A *)c->src;
+        switch (p.E) {
+        case 2: hipLaunchKernelGGL((k_get_sources<A, 2>), g, dim3(256), 0, s, src, p, out, reset); break;
+        case 4: hipLaunchKernelGGL((k_get_sources<A, 4>), g, dim3(256), 0, s, src, p, out, reset); break;
+        default: hipLaunchKernelGGL((k_get_sources<A, 8>), g, dim3(256), 0, s, src, p, out, reset); break;
+        }
         return hipGetLastError();
     });
 }
