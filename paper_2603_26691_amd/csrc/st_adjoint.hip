@@ -46,12 +46,11 @@ namespace {
 
 template <class T>
 struct AdjArgs {
-    // saved store of the step (pointers into a snapshot)
-    const T *ox, *oy, *oz, *vx, *vy, *vz, *d;
-    const int32_t *id;
-    const int64_t *base;
-    const int32_t *cnt;
-    const int32_t *items;
+    // saved store of the step: pointers into a snapshot (both views the same),
+    // or the store and the re-bin's target (then F_CUR of flags says which)
+    Views<T> V;
+    const int32_t *flags;    // or null
+    const RunItem *items;
     const int32_t *nitems;
     const T *u;              // field of the step [3][n2][n1][n0]
     const double *lamC;      // dL/dSu_int by chunk [C][3][E^3]
@@ -113,8 +112,8 @@ __device__ __forceinline__ void stage_tile(const Params &p, const T *u, int cx, 
 }
 
 // A saved slot holds a particle unless its anchor is -1 (no particle at
-// that slot of the checkpoint) or it is a hole (a -1 offset in binary32, a
-// negated diameter in binary64).
+// that slot of the checkpoint) or it is a hole (its mark for an offset in
+// binary32, a negated diameter in binary64).
 template <class T>
 __device__ __forceinline__ bool adj_live(int64_t anchor, int64_t nrec, const T (&st)[7])
 {
@@ -250,9 +249,9 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
     const int64_t item = blockIdx.x;
     if (item >= *a.nitems) return;
     const Params &p = a.p;
-    const int64_t c = a.items[2 * item], seg = a.items[2 * item + 1];
-    const int64_t s0 = a.base[c] + seg * kSeg;
-    const int64_t s1 = min(s0 + (int64_t)kSeg, a.base[c] + (int64_t)a.cnt[c]);
+    const RunItem run = a.items[item];
+    const View<T> V = a.V.pick(a.flags ? a.flags[F_CUR] : 0);
+    const int64_t c = run.c, s0 = run.s0, s1 = s0 + run.cnt;
     const int cx = (int)(c % p.nc[0]);
     const int cy = (int)((c / p.nc[0]) % p.nc[1]);
     const int cz = (int)(c / ((int64_t)p.nc[0] * p.nc[1]));
@@ -262,7 +261,7 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
     // continue those of the steps reversed before (kept per chunk), and go
     // back to them at the end; a chunk split over several items adds its
     // sums to dL/du atomically
-    const bool own = a.tacc != nullptr && a.cnt[c] <= kSeg;
+    const bool own = a.tacc != nullptr && run.k == 1;
     double *const tacc_c = own ? a.tacc + c * 3 * S3 : nullptr;
     stage_tile<T, E, kAdjBlock>(p, a.u, cx, cy, cz, tile);
     for (int t = threadIdx.x; t < 3 * S3; t += kAdjBlock) nacc[t] = own ? tacc_c[t] : 0.0;
@@ -285,14 +284,14 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
             const int64_t q = q0 + threadIdx.x + (int64_t)u * kAdjBlock;
             an[u] = -1;
             if (u < np && q < s1) {
-                an[u] = a.id[q];
-                st[u][0] = a.ox[q];
-                st[u][1] = a.oy[q];
-                st[u][2] = a.oz[q];
-                st[u][3] = a.vx[q];
-                st[u][4] = a.vy[q];
-                st[u][5] = a.vz[q];
-                st[u][6] = a.d[q];
+                an[u] = V.id[q];
+                st[u][0] = V.ox[q];
+                st[u][1] = V.oy[q];
+                st[u][2] = V.oz[q];
+                st[u][3] = V.vx[q];
+                st[u][4] = V.vy[q];
+                st[u][5] = V.vz[q];
+                st[u][6] = V.d[q];
             }
         }
         bool live[PPT];
@@ -376,9 +375,9 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     const int64_t item = blockIdx.x;
     if (item >= *a.nitems) return;
     const Params &p = a.p;
-    const int64_t c = a.items[2 * item], seg = a.items[2 * item + 1];
-    const int64_t s0 = a.base[c] + seg * kSeg;
-    const int64_t s1 = min(s0 + (int64_t)kSeg, a.base[c] + (int64_t)a.cnt[c]);
+    const RunItem run = a.items[item];
+    const View<T> V = a.V.pick(a.flags ? a.flags[F_CUR] : 0);
+    const int64_t c = run.c, s0 = run.s0, s1 = s0 + run.cnt;
     const int cx = (int)(c % p.nc[0]);
     const int cy = (int)((c / p.nc[0]) % p.nc[1]);
     const int cz = (int)(c / ((int64_t)p.nc[0] * p.nc[1]));
@@ -389,8 +388,8 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     __syncthreads();
     const double *lam = a.lamC + c * 3 * E3;
     for (int64_t q = s0 + threadIdx.x; q < s1; q += kAdjBlock) {
-        const int64_t an = a.id[q];
-        const T st[7] = {a.ox[q], a.oy[q], a.oz[q], a.vx[q], a.vy[q], a.vz[q], a.d[q]};
+        const int64_t an = V.id[q];
+        const T st[7] = {V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q]};
         if (!adj_live(an, a.nrec, st)) continue;
         double rc[7];
         for (int k = 0; k < 7; ++k) rc[k] = (double)a.adj[8 * an + k];
@@ -404,7 +403,7 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     __syncthreads();
     // a chunk that is one work item adds its sums to those it keeps over the
     // steps; a chunk split over several items adds them to dL/du atomically
-    const bool own = a.tacc != nullptr && a.cnt[c] <= kSeg;
+    const bool own = a.tacc != nullptr && run.k == 1;
     for (int t = threadIdx.x; t < 3 * S3; t += kAdjBlock) {
         const double v = (double)ubt[t];
         if (own) {
@@ -456,7 +455,7 @@ __device__ __forceinline__ bool ck_particle(int32_t id, int64_t count, T ox, T d
     return id >= 0 && id < count && ox >= T(0) && d > T(0);
 }
 
-// The checkpoint's particles, a workgroup per chunk.  Mode bits: kAnchor
+// The checkpoint's particles, a workgroup per container.  Mode bits: kAnchor
 // replaces the restored store's ids by anchors (every other slot of a run
 // gets -1), kToAnchor takes each particle's record from the array by id into
 // the array by anchor, kToId puts it back.  With a second checkpoint (ok,
@@ -467,23 +466,25 @@ __device__ __forceinline__ bool ck_particle(int32_t id, int64_t count, T ox, T d
 constexpr int kAnchor = 1, kToAnchor = 2, kToId = 4;
 template <class T>
 __global__ void k_checkpoint_records(const char *ck, const char *ok, SnapLayout L, int64_t slots,
-                                     int64_t C, int64_t count, int32_t *store_id, T *by_id,
-                                     T *rec, int mode)
+                                     int64_t count, int32_t *id0, int32_t *id1,
+                                     const int32_t *flags, T *by_id, T *rec, int mode)
 {
+    int32_t *const store_id = flags[F_CUR] ? id1 : id0;
     const T *ox = reinterpret_cast<const T *>(ck + L.state);
     const T *d = ox + 6 * slots;
     const int32_t *sid = reinterpret_cast<const int32_t *>(ck + L.id);
-    const int64_t *base = reinterpret_cast<const int64_t *>(ck + L.base);
-    const int32_t *cnt = reinterpret_cast<const int32_t *>(ck + L.cnt);
+    const RunItem *runs = reinterpret_cast<const RunItem *>(ck + L.items);
+    const int32_t ni = *reinterpret_cast<const int32_t *>(ck + L.nitems);
     const char *const oc = ok ? ok : ck;   // (not read without ok)
     const T *o_ox = reinterpret_cast<const T *>(oc + L.state);
     const T *o_d = o_ox + 6 * slots;
     const int32_t *o_sid = reinterpret_cast<const int32_t *>(oc + L.id);
-    const int64_t *o_base = reinterpret_cast<const int64_t *>(oc + L.base);
-    const int32_t *o_cnt = reinterpret_cast<const int32_t *>(oc + L.cnt);
-    for (int64_t c = blockIdx.x; c < C; c += gridDim.x) {
-        const int64_t q0 = base[c], q1 = q0 + cnt[c];
-        const int64_t p0 = ok ? o_base[c] : 0, p1 = ok ? p0 + o_cnt[c] : 0;
+    const RunItem *o_runs = reinterpret_cast<const RunItem *>(oc + L.items);
+    const int32_t o_ni = *reinterpret_cast<const int32_t *>(oc + L.nitems);
+    for (int32_t j = blockIdx.x; j < ni; j += gridDim.x) {
+        const int64_t q0 = runs[j].s0, q1 = q0 + runs[j].cnt;
+        const bool both = ok && j < o_ni;
+        const int64_t p0 = both ? o_runs[j].s0 : 0, p1 = both ? p0 + o_runs[j].cnt : 0;
         for (int64_t q = q0 + threadIdx.x; q < q1; q += blockDim.x) {
             const int32_t k = sid[q];
             const bool live = ck_particle(k, count, ox[q], d[q]);
@@ -512,9 +513,10 @@ hipError_t launch_checkpoint_records(st_ctx *c, const char *ck, const char *ok, 
                                      T *rec, int mode, hipStream_t s)
 {
     const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
-    const int64_t g = c->C < 16384 ? c->C : 16384;
-    hipLaunchKernelGGL((k_checkpoint_records<T>), dim3(g > 0 ? g : 1), dim3(256), 0, s, ck, ok,
-                       L, c->slots, c->C, c->count, (int32_t *)c->store[0][7], by_id, rec, mode);
+    const int64_t g = c->max_items < 16384 ? c->max_items : 16384;
+    hipLaunchKernelGGL((k_checkpoint_records<T>), dim3(g), dim3(256), 0, s, ck, ok, L, c->slots,
+                       c->count, (int32_t *)c->store[0][7], (int32_t *)c->store[1][7], c->flags,
+                       by_id, rec, mode);
     return hipGetLastError();
 }
 
@@ -529,38 +531,25 @@ __global__ void k_take_dbar(const T *adj, int64_t P, double *dd)
 
 
 template <class T>
-AdjArgs<T> adj_args(st_ctx *c, const char *snap, const TapeStep &ts, const double *lamC,
-                    T *adj, double *Ubar, double *tacc)
+AdjArgs<T> adj_args(st_ctx *c, char *snap, const RunItem *runs, const int32_t *nruns,
+                    const TapeStep &ts, const double *lamC, T *adj, double *Ubar, double *tacc)
 {
     AdjArgs<T> a;
+    const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
     if (snap) {
-        const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
-        const T *st = reinterpret_cast<const T *>(snap + L.state);
-        a.ox = st;
-        a.oy = st + c->slots;
-        a.oz = st + 2 * c->slots;
-        a.vx = st + 3 * c->slots;
-        a.vy = st + 4 * c->slots;
-        a.vz = st + 5 * c->slots;
-        a.d = st + 6 * c->slots;
-        a.id = reinterpret_cast<const int32_t *>(snap + L.id);
-        a.base = reinterpret_cast<const int64_t *>(snap + L.base);
-        a.cnt = reinterpret_cast<const int32_t *>(snap + L.cnt);
-        a.items = reinterpret_cast<const int32_t *>(snap + L.items);
+        T *st = reinterpret_cast<T *>(snap + L.state);
+        const int64_t n = c->slots;
+        const View<T> v{st, st + n, st + 2 * n, st + 3 * n, st + 4 * n, st + 5 * n, st + 6 * n,
+                        reinterpret_cast<int32_t *>(snap + L.id)};
+        a.V = Views<T>{v, v};
+        a.flags = nullptr;
+        a.items = reinterpret_cast<const RunItem *>(snap + L.items);
         a.nitems = reinterpret_cast<const int32_t *>(snap + L.nitems);
-    } else {   // the store itself, with its layout and work items
-        a.ox = (const T *)c->store[0][0];
-        a.oy = (const T *)c->store[0][1];
-        a.oz = (const T *)c->store[0][2];
-        a.vx = (const T *)c->store[0][3];
-        a.vy = (const T *)c->store[0][4];
-        a.vz = (const T *)c->store[0][5];
-        a.d = (const T *)c->store[0][6];
-        a.id = (const int32_t *)c->store[0][7];
-        a.base = c->base;
-        a.cnt = c->cnt;
-        a.items = c->items;
-        a.nitems = c->flags + F_NITEMS;
+    } else {   // the store itself, its runs in the workspace
+        a.V = views_of<T>(c);
+        a.flags = c->flags;
+        a.items = runs;
+        a.nitems = nruns;
     }
     a.u = reinterpret_cast<const T *>(ts.u);
     a.lamC = lamC;
@@ -606,7 +595,7 @@ namespace {
 // dL/du when they fit in a GiB (else each step adds its sums to dL/du
 // atomically).
 struct BwdLayout {
-    size_t step_bytes, o_steps, o_lam, o_rid, o_adj, o_tacc, tbytes, bytes;
+    size_t step_bytes, o_steps, o_lam, o_rid, o_adj, o_runs, o_tacc, tbytes, bytes;
 };
 
 BwdLayout bwd_layout(const st_ctx *c, int64_t K)
@@ -622,7 +611,8 @@ BwdLayout bwd_layout(const st_ctx *c, int64_t K)
     W.o_lam = W.o_steps + (size_t)(K > 1 ? K - 1 : 0) * W.step_bytes;
     W.o_rid = W.o_lam + up256((size_t)c->C * 3 * E3 * 8);
     W.o_adj = W.o_rid + up256((size_t)(P > 0 ? P : 1) * rbytes);
-    W.o_tacc = W.o_adj + up256((size_t)c->slots * rbytes);
+    W.o_runs = W.o_adj + up256((size_t)c->slots * rbytes);
+    W.o_tacc = W.o_runs + up256((size_t)c->max_items * sizeof(RunItem) + 4);
     W.tbytes = (size_t)c->C * 3 * S3 * 8;
     if (W.tbytes > ((size_t)1 << 30)) W.tbytes = 0;
     W.bytes = W.o_tacc + W.tbytes;
@@ -668,6 +658,8 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
     void *rid = ws + W.o_rid;
     void *adj = ws + W.o_adj;
     double *tacc = W.tbytes ? (double *)(ws + W.o_tacc) : nullptr;
+    RunItem *runs = (RunItem *)(ws + W.o_runs);
+    int32_t *nruns = (int32_t *)(runs + c->max_items);
     const bool fp64 = c->form == ST_FORM_FP64;
 
     // an error return first drains the stream
@@ -710,17 +702,21 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
             e = launch_step(c, c->tape[(size_t)k].u, c->tape[(size_t)k].dt, 0, s, step_buf(k - k0));
             if (e != hipSuccess) return fail(e);
         }
-        // and reverse it, newest step first
+        // and reverse it, newest step first (the arrivals of the last
+        // recomputed step placed, the store's runs listed)
+        e = launch_settle(c, s);
+        if (e == hipSuccess) e = launch_runs(c, runs, nruns, s);
+        if (e != hipSuccess) return fail(e);
         for (int64_t k = k1 - 1; k >= k0; --k) {
-            const char *snap = k + 1 < k1 ? (const char *)step_buf(k - k0) : nullptr;
+            char *snap = k + 1 < k1 ? (char *)step_buf(k - k0) : nullptr;
             if (fp64)
                 e = launch_adjoint_step<double>(
-                    c, adj_args<double>(c, snap, c->tape[(size_t)k], lamC, (double *)adj, dU,
-                                          tacc), s);
+                    c, adj_args<double>(c, snap, runs, nruns, c->tape[(size_t)k], lamC,
+                                        (double *)adj, dU, tacc), s);
             else
                 e = launch_adjoint_step<float>(
-                    c, adj_args<float>(c, snap, c->tape[(size_t)k], lamC, (float *)adj, dU,
-                                         tacc), s);
+                    c, adj_args<float>(c, snap, runs, nruns, c->tape[(size_t)k], lamC,
+                                       (float *)adj, dU, tacc), s);
             if (e != hipSuccess) return fail(e);
         }
         // the records of the particles the earlier checkpoint does not hold at

@@ -48,11 +48,9 @@ void free_all(st_ctx *c)
 {
     for (int b = 0; b < 2; ++b)
         for (int k = 0; k < 8; ++k) (void)hipFree(c->store_raw[b][k]);
-    for (int k = 0; k < 3; ++k) (void)hipFree(c->mov[k]);
-    void *singles[] = {c->base, c->room, c->cnt, c->ndead, c->out_cnt, c->in_cnt, c->cursor,
-                       c->new_cnt, c->nbase, c->nroom, c->hole, c->items, c->nseg,
-                       c->scan_tmp, c->room_denom, c->flags, c->src, c->stage64, c->fieldbuf[0],
-                       c->fieldbuf[1], c->ec_prev, c->ec_ext};
+    void *singles[] = {c->cont[0], c->cont[1], c->first[0], c->first[1], c->rec, c->stage_dest,
+                       c->cursor, c->new_cnt, c->lay, c->flags, c->spread, c->src, c->stage64,
+                       c->fieldbuf[0], c->fieldbuf[1], c->ec_prev, c->ec_ext};
     for (void *p : singles) (void)hipFree(p);
     for (auto &sn : c->snaps) (void)hipFree(sn.buf);
     c->snaps.clear();
@@ -151,13 +149,18 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
 
     c->C = p.C;
     c->cap = d.capacity;
+    // containers: one per chunk and one more per kSeg particles (rounded up to
+    // the step's launch grid)
+    c->max_items = p.C + (d.capacity + st::kSeg - 1) / st::kSeg;
     // spare slots: a quarter of the capacity (at least kSlackMin per chunk),
     // plus what rounding every room up to kAlign can take
     c->slots = d.capacity + std::max<int64_t>(d.capacity / 4, (int64_t)st::kSlackMin * p.C) +
-               (int64_t)st::kAlign * p.C;
-    c->mcap = std::max<int64_t>(std::min<int64_t>(d.capacity, 1 << 16), d.capacity / 8);
-    c->max_items = p.C + (d.capacity + st::kSeg - 1) / st::kSeg;
-    if (c->slots >= ((int64_t)1 << 31) - 1 || c->max_items >= ((int64_t)1 << 30))
+               (int64_t)st::kAlign * c->max_items;
+    // inboxes: whole rooms in a small store, else an eighth of them
+    c->whole_inbox = c->slots <= (1 << 17);
+    c->nrec = c->whole_inbox ? c->slots : c->slots / 8 + 16 * c->max_items;
+    c->mcap = std::min<int64_t>(d.capacity, 2 * c->nrec);
+    if (c->slots >= ((int64_t)1 << 31) - 1 || c->max_items >= ((int64_t)1 << 26))
         return bad("capacity too large for 32-bit slot indices");
 
     auto dev_bad = [&](st_status st, const std::string &m) {
@@ -181,26 +184,18 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
             if (c->store_raw[b][k]) c->store[b][k] = (char *)c->store_raw[b][k] + off;
         }
     }
-    A(&c->base, (size_t)(C + 1) * 8);
-    A(&c->room, (size_t)C * 4);
-    A(&c->cnt, (size_t)C * 4);
-    A(&c->ndead, (size_t)C * 4);
-    A(&c->mov[0], (size_t)c->mcap * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
-                                                   : sizeof(st::MoverRec<float>)));
-    A(&c->mov[1], (size_t)c->mcap * 4);
-    A(&c->mov[2], (size_t)c->mcap * 4);
-    A(&c->out_cnt, (size_t)C * 4);
-    A(&c->in_cnt, (size_t)C * 4);
+    for (int b = 0; b < 2; ++b) {
+        A(&c->cont[b], (size_t)c->max_items * sizeof(st::Cont));
+        A(&c->first[b], (size_t)(C + 1) * 4);
+    }
+    A(&c->rec, (size_t)(2 * c->nrec) * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
+                                                      : sizeof(st::MoverRec<float>)));
+    A(&c->stage_dest, (size_t)c->mcap * 4);
     A(&c->cursor, (size_t)C * 4);
     A(&c->new_cnt, (size_t)C * 4);
-    A(&c->nbase, (size_t)(C + 1) * 8);
-    A(&c->nroom, (size_t)C * 4);
-    A(&c->hole, (size_t)c->slots * 4);
-    A(&c->items, (size_t)c->max_items * 8);
-    A(&c->nseg, (size_t)(C + 1) * 4);
-    A(&c->scan_tmp, (size_t)(C / 1024 + 4) * 8);
-    A(&c->room_denom, 8);
+    A(&c->lay, (size_t)C * 16);
     A(&c->flags, (size_t)st::F_COUNT * 4);
+    A(&c->spread, (size_t)st::kSpreadInts * 4);
     A(&c->src, (size_t)3 * ncell * c->asize);
     if (ok != hipSuccess)
         return dev_bad(ST_ERR_OOM, "device allocation failed after " + std::to_string(total) +
@@ -262,6 +257,8 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
         if (on_device) {
             ST_HIP(st::launch_zero_i32(c->flags + st::F_BADINPUT, 1, s));
         }
+        // the staging area is the inboxes' memory
+        if (c->pending == 0) ST_HIP(st::launch_settle(c, s));
         const int64_t stage_batch = std::min<int64_t>(c->mcap, 1 << 22);
         if (!on_device && !c->stage64) {
             size_t bytes = (size_t)stage_batch * 7 * 8;
@@ -301,6 +298,7 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
                 // only possible when no flush happened in between (n <= mcap);
                 // otherwise the state already holds the batch
                 if (c->count == count0) {
+                    ST_HIP(st::launch_unstage(c, pend0, s));
                     c->pending = pend0;
                     c->next_id = id0;
                     return fail(c, ST_ERR_INVALID, "st_inject: non-finite value or d <= 0");
@@ -649,14 +647,15 @@ st_status st_stats(st_ctx *c, int64_t *last_movers, int64_t *repacks, int64_t *p
     ST_HIP(hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)hip_stream;
     int32_t f[st::F_COUNT];
+    ST_HIP(st::launch_stats(c, s));
     ST_HIP(hipMemcpyAsync(f, c->flags, sizeof f, hipMemcpyDeviceToHost, s));
     ST_HIP(hipStreamSynchronize(s));
     if (last_movers) *last_movers = f[st::F_LASTMOV];
     if (repacks) *repacks = f[st::F_REPACKS];
     if (particles) *particles = c->count + c->pending;
     if (slots) *slots = c->slots;
-    if (items) *items = f[st::F_NITEMS];
-    if (holes) *holes = f[st::F_DEAD];
+    if (items) *items = f[st::F_STAT_ITEMS];
+    if (holes) *holes = f[st::F_STAT_HOLES];
     return ST_OK;
 }
 

@@ -2,43 +2,29 @@
 //
 // One step of the particle method (paper Sec. 2.1 equations of motion and
 // momentum source, Sec. 2.5 interpolation, deposit and time integration)
-// is five launches:
-//   step      one workgroup per work item (a run of at most kSeg slots of
-//             one chunk): stage the chunk's fluid tile with a one-cell halo
-//             in LDS, gather, integrate, deposit into an LDS accumulator of
-//             the chunk's cells, write every particle back in place, collect
-//             the chunk crossers ("movers") in LDS by direction and emit
-//             them as whole records, with one atomic instruction for all of
-//             a workgroup's reservations (mover list, the chunk's hole list,
-//             one arrival count per neighbouring chunk), and flush the
-//             accumulator with one read-modify-write (or one atomic, for
-//             chunks split over several items) per cell.  A mover's slot
-//             becomes a hole of its chunk (binary32: a -1 offset, written by
-//             the step's own store; binary64: its diameter negated, its
-//             state left in place) and goes onto the chunk's hole list; its
-//             record carries its destination and its rank among the
-//             destination's arrivals.  Arrivals that do not fit the
-//             destination's free slots force the full re-bin;
-//   arrive    one thread per mover: each arrival takes a hole of its
-//             destination (the newest first) or, when there are none left,
-//             the next slot past the destination's last (when a full re-bin
-//             is due, nothing: the re-bin takes the movers from their
-//             records);
-//   counts    one thread per chunk: the new slot and hole counts; holes no
-//             arrival took are skipped by every kernel until the next full
-//             re-bin (forced once they exceed a sixteenth of the particles);
-//   layout    work items of the next step from the counts, the reset of the
-//             counters, and, when a full re-bin is due, the rooms and bases
-//             of its layout (one workgroup; it also takes the counts step
-//             when the mesh has few enough chunks);
-//   scatter, commit
-//             only when a chunk ran out of room, the mover list overflowed
-//             or particles were injected: a full counting-sort re-bin into
-//             the second store, copied back (decided on the device).
-// (Meshes of more than kScan1Max chunks count and scan with several
-// launches.)
-// Device flags that decide between the two re-bins hold the tag (epoch) of
-// the step that raised them, so nothing has to clear them between steps.
+// is three launches:
+//   step      one workgroup per container (a run of the slots of one chunk):
+//             stage the chunk's fluid tile with a one-cell halo in LDS,
+//             gather, integrate, deposit into an LDS accumulator of the
+//             chunk's cells, write every particle back in place, collect the
+//             chunk crossers ("movers") in LDS by direction and emit them as
+//             whole records into the inboxes of the neighbouring chunks'
+//             containers, with one atomic instruction for all of a
+//             workgroup's reservations, and flush the accumulator with one
+//             read-modify-write (or one atomic, for chunks of several
+//             containers) per cell.  A mover's slot becomes a hole (binary32:
+//             an offset no particle has, written by the step's own store;
+//             binary64: its diameter negated, its state left in place).  The container's
+//             own arrivals of the step before are taken from its inbox into
+//             the holes the stream passes, then past its last slot, where the
+//             step's own vector stores write them: no pass of their own, and
+//             no scattered writes but their diameters and ids;
+//   gate      one workgroup: the next tick; and, when a container ran out of
+//             room, an inbox was too small, particles were injected or too
+//             many holes gathered, the layout of a full re-bin (counts per
+//             chunk, rooms, containers);
+//   scatter   only then: a counting sort into the second store, which becomes
+//             the store.
 #include "st_internal.h"
 
 #include <hip/hip_ext.h>
@@ -49,28 +35,6 @@
 
 namespace st {
 namespace {
-
-constexpr int kScan1Max = 1 << 13;  // largest scan done by one workgroup
-constexpr int kScanBlock = 1024;    // elements per block of the multi-block scan
-
-enum Gate { G_ALWAYS = 0, G_FULL = 1, G_MOVERS = 2 };
-
-__device__ __forceinline__ bool full_rebin(const int32_t *flags, int32_t epoch)
-{
-    return flags[F_OVERFLOW] == epoch || flags[F_FORCE] == epoch;
-}
-
-__device__ __forceinline__ bool gate_open(const int32_t *flags, int gate, int32_t epoch)
-{
-    if (gate == G_ALWAYS) return true;
-    return (gate == G_FULL) == full_rebin(flags, epoch);
-}
-
-// movers of the step tagged `epoch` are counted in one of two slots
-__host__ __device__ __forceinline__ int nmov_slot(int32_t epoch)
-{
-    return (epoch & 1) ? F_NMOV_ODD : F_NMOV;
-}
 
 __device__ __forceinline__ int64_t wrapi(int64_t i, int64_t n)
 {
@@ -111,205 +75,6 @@ __device__ V block_excl_scan(V v, V &total)
     const V ex = (wave ? ws[wave - 1] : V(0)) + incl - v;
     __syncthreads();
     return ex;
-}
-
-// ---------------------------------------------------------------------------
-// exclusive scans of f(i), i < n: out[i] = sum_{j<i} f(j), out[n] = total
-// ---------------------------------------------------------------------------
-
-// whole scan in one workgroup of 1024 threads, 4096 elements per round
-template <class TO, class F>
-__device__ void block_scan_all(const F &f, int64_t n, TO *out)
-{
-    TO carry = 0;
-    for (int64_t r0 = 0; r0 < n; r0 += 4096) {
-        TO v[4];
-        TO s = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t i = r0 + 4 * (int64_t)threadIdx.x + k;
-            v[k] = i < n ? f(i) : TO(0);
-            s += v[k];
-        }
-        TO total;
-        TO ex = carry + block_excl_scan<TO>(s, total);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t i = r0 + 4 * (int64_t)threadIdx.x + k;
-            if (i < n) out[i] = ex;
-            ex += v[k];
-        }
-        carry += total;
-    }
-    if (threadIdx.x == 0) out[n] = carry;
-}
-
-template <class TO, class F>
-__global__ void __launch_bounds__(1024) k_scan1(F f, int64_t n, TO *out, const int32_t *flags,
-                                                int gate, int32_t epoch)
-{
-    if (!gate_open(flags, gate, epoch)) return;
-    block_scan_all<TO>(f, n, out);
-}
-
-template <class TO, class F>
-__global__ void __launch_bounds__(256) k_scan_partials(F f, int64_t n, TO *part,
-                                                       const int32_t *flags, int gate,
-                                                       int32_t epoch)
-{
-    if (!gate_open(flags, gate, epoch)) return;
-    const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
-    TO s = 0;
-    for (int k = 0; k < kScanBlock / 256; ++k) {
-        const int64_t i = b0 + k * 256 + threadIdx.x;
-        if (i < n) s += f(i);
-    }
-    TO tot;
-    block_excl_scan<TO>(s, tot);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
-}
-
-template <class TO>
-__global__ void __launch_bounds__(1024) k_scan_spine(TO *part, int64_t nb, const int32_t *flags,
-                                                     int gate, int32_t epoch)
-{
-    if (!gate_open(flags, gate, epoch)) return;
-    struct Id {
-        const TO *p;
-        __device__ TO operator()(int64_t i) const { return p[i]; }
-    };
-    // in place: the spine is short (n / 1024 entries)
-    TO carry = 0;
-    for (int64_t r0 = 0; r0 < nb; r0 += 1024) {
-        const int64_t i = r0 + threadIdx.x;
-        const TO v = i < nb ? part[i] : TO(0);
-        TO total;
-        const TO ex = block_excl_scan<TO>(v, total);
-        if (i < nb) part[i] = carry + ex;
-        carry += total;
-    }
-}
-
-template <class TO, class F>
-__global__ void __launch_bounds__(256) k_scan_final(F f, int64_t n, const TO *part, TO *out,
-                                                    const int32_t *flags, int gate, int32_t epoch)
-{
-    if (!gate_open(flags, gate, epoch)) return;
-    const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
-    constexpr int K = kScanBlock / 256;
-    TO v[K];
-    TO s = 0;
-    for (int k = 0; k < K; ++k) {
-        const int64_t i = b0 + (int64_t)threadIdx.x * K + k;
-        v[k] = i < n ? f(i) : TO(0);
-        s += v[k];
-    }
-    TO tot;
-    TO ex = block_excl_scan<TO>(s, tot) + part[blockIdx.x];
-    for (int k = 0; k < K; ++k) {
-        const int64_t i = b0 + (int64_t)threadIdx.x * K + k;
-        if (i < n) out[i] = ex;
-        ex += v[k];
-        if (i == n - 1) out[n] = ex;
-    }
-}
-
-// multi-block scan (three launches), for n > kScan1Max
-template <class TO, class F>
-hipError_t scan_multi(F f, int64_t n, TO *out, TO *part, const int32_t *flags, int gate,
-                      int32_t epoch, hipStream_t s)
-{
-    const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-    hipLaunchKernelGGL((k_scan_partials<TO, F>), dim3(nb), dim3(256), 0, s, f, n, part, flags,
-                       gate, epoch);
-    hipLaunchKernelGGL((k_scan_spine<TO>), dim3(1), dim3(1024), 0, s, part, nb, flags, gate,
-                       epoch);
-    hipLaunchKernelGGL((k_scan_final<TO, F>), dim3(nb), dim3(256), 0, s, f, n, part, out, flags,
-                       gate, epoch);
-    return hipGetLastError();
-}
-
-template <class TO, class F>
-hipError_t scan(F f, int64_t n, TO *out, TO *part, const int32_t *flags, int gate, int32_t epoch,
-                hipStream_t s)
-{
-    if (n <= kScan1Max) {
-        hipLaunchKernelGGL((k_scan1<TO, F>), dim3(1), dim3(1024), 0, s, f, n, out, flags, gate,
-                           epoch);
-        return hipGetLastError();
-    }
-    return scan_multi<TO>(f, n, out, part, flags, gate, epoch, s);
-}
-
-// work items per chunk
-struct Segments {
-    const int32_t *cnt;
-    __device__ int32_t operator()(int64_t i) const { return (cnt[i] + kSeg - 1) / kSeg; }
-};
-
-// Share of the spare slots a chunk asks for in a re-binned layout: the
-// largest count among the chunk and its six face neighbours (periodic), plus
-// kSlackMin.  What a chunk can gain before the next re-bin is bounded by what
-// its neighbours can send, so a sparse chunk at the edge of a dense region
-// gets room for the arrivals from the dense side.
-struct RoomWeight {
-    const int32_t *cnt;
-    int32_t nc[3];
-    __device__ int64_t operator()(int64_t i) const
-    {
-        const int64_t x = i % nc[0], y = (i / nc[0]) % nc[1], z = i / ((int64_t)nc[0] * nc[1]);
-        const int64_t sx = 1, sy = nc[0], sz = (int64_t)nc[0] * nc[1];
-        const int64_t nb[6] = {
-            i + (x == nc[0] - 1 ? -(nc[0] - 1) * sx : sx), i + (x == 0 ? (nc[0] - 1) * sx : -sx),
-            i + (y == nc[1] - 1 ? -(nc[1] - 1) * sy : sy), i + (y == 0 ? (nc[1] - 1) * sy : -sy),
-            i + (z == nc[2] - 1 ? -(nc[2] - 1) * sz : sz), i + (z == 0 ? (nc[2] - 1) * sz : -sz)};
-        int32_t m = cnt[i];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) m = max(m, cnt[nb[k]]);
-        return (int64_t)m + kSlackMin;
-    }
-};
-
-// rooms of a re-binned layout: the spare slots are shared out in proportion
-// to the chunks' weights (denom = their sum), rounded down to whole groups of
-// kAlign slots, on top of the count rounded up to kAlign; also records the
-// room
-struct Rooms {
-    RoomWeight w;
-    int64_t spare, denom;
-    int32_t *nroom;
-    __device__ int64_t operator()(int64_t i) const
-    {
-        const int64_t n = w.cnt[i];
-        const int64_t extra = denom > 0 ? spare * w(i) / denom : 0;
-        const int64_t r = (n + kAlign - 1) / kAlign * kAlign + extra / kAlign * kAlign;
-        nroom[i] = (int32_t)r;
-        return r;
-    }
-};
-
-// the same, with the sum of the weights read from device memory (several
-// workgroups; written by k_room_denom)
-struct RoomsDev {
-    Rooms r;
-    const int64_t *denom;
-    __device__ int64_t operator()(int64_t i) const
-    {
-        Rooms q = r;
-        q.denom = *denom;
-        return q(i);
-    }
-};
-
-// sum of f(i), i < n, over one workgroup of 1024 threads (every thread gets it)
-template <class F>
-__device__ int64_t block_sum_all(const F &f, int64_t n)
-{
-    int64_t s = 0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) s += f(i);
-    int64_t tot;
-    block_excl_scan<int64_t>(s, tot);
-    return tot;
 }
 
 // ---------------------------------------------------------------------------
@@ -372,216 +137,166 @@ __device__ __forceinline__ int64_t chunk_of_stored(const Params &p, int64_t c, T
 }
 
 // ---------------------------------------------------------------------------
-// work items of the next step, and the reset of the per-step counters
+// after the step: the next tick, and the layout of a full re-bin
 // ---------------------------------------------------------------------------
-struct ItemArgs {
+struct GateArgs {
+    Cont *cont0, *cont1;
+    int32_t *first0, *first1;
+    int32_t *new_cnt, *cursor;
+    int4 *lay;
+    int32_t *flags, *spread;
     int64_t C;
-    int32_t *noff;       // [C+1] exclusive scan of the items per chunk
-    int32_t *items;
-    int32_t *out_cnt, *in_cnt, *new_cnt, *cursor;
-    int32_t *flags;
-    int32_t epoch;
-    int32_t dead_limit;  // more holes than this force a full re-bin at the next step
+    int32_t nc[3];
+    int64_t spare;           // slots to share out beyond the particles
+    int32_t whole;           // inboxes hold whole rooms
+    int32_t hole_limit;      // more holes than this force a full re-bin at the next step
+    int32_t advance;         // after a step (not after an injection)
 };
 
-// chunk c's work items [o, e) (its offsets in the item list), and the reset
-// of its counters
-__device__ __forceinline__ void write_items_at(const ItemArgs &a, int64_t c, int32_t o, int32_t e)
+// Share of the spare slots a chunk asks for in a re-binned layout: the
+// largest count among the chunk and its six face neighbours (periodic), plus
+// kSlackMin.  What a chunk can gain before the next re-bin is bounded by what
+// its neighbours can send, so a sparse chunk at the edge of a dense region
+// gets room for the arrivals from the dense side.
+__device__ __forceinline__ int64_t room_weight(const int32_t *cnt, const int32_t (&nc)[3],
+                                               int64_t i)
 {
-    for (int32_t s = 0; s < e - o; ++s) {
-        a.items[2 * (int64_t)(o + s)] = (int32_t)c;
-        a.items[2 * (int64_t)(o + s) + 1] = s;
+    const int32_t j = (int32_t)i;
+    const int32_t sx = 1, sy = nc[0], sz = nc[0] * nc[1];
+    const int32_t x = j % nc[0], y = (j / nc[0]) % nc[1], z = j / sz;
+    const int32_t nb[6] = {
+        j + (x == nc[0] - 1 ? -(nc[0] - 1) * sx : sx), j + (x == 0 ? (nc[0] - 1) * sx : -sx),
+        j + (y == nc[1] - 1 ? -(nc[1] - 1) * sy : sy), j + (y == 0 ? (nc[1] - 1) * sy : -sy),
+        j + (z == nc[2] - 1 ? -(nc[2] - 1) * sz : sz), j + (z == 0 ? (nc[2] - 1) * sz : -sz)};
+    int32_t m = cnt[j];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) m = max(m, cnt[nb[k]]);
+    return (int64_t)m + kSlackMin;
+}
+
+// One workgroup.  Without a full re-bin (nearly always) it only turns the
+// tick and sums the spread counters.  With one: each chunk's particles are
+// those of its containers (their holes out, their inboxes in); the chunk gets
+// k containers of at most kSeg particles, equal rooms of whole groups of
+// kAlign slots, the spare slots shared out in proportion to the chunks'
+// weights and rounded down.
+__global__ void __launch_bounds__(1024) k_gate(GateArgs a)
+{
+    int32_t *const f = a.flags;
+    const int32_t t = f[F_TICK], cur = f[F_CUR];
+    const bool full = (f[F_OVERFLOW] | f[F_FORCE]) != 0;
+    __syncthreads();   // every thread has read the flags before one writes them
+    if (threadIdx.x < 64) {
+        int32_t *const l = a.spread + 16 * threadIdx.x;
+        int32_t holes = l[0], movers = l[1];
+        for (int o = 32; o > 0; o >>= 1) {
+            holes += __shfl_xor(holes, o);
+            movers += __shfl_xor(movers, o);
+        }
+        l[1] = 0;
+        if (full) l[0] = 0;
+        if (threadIdx.x == 0) {
+            if (a.advance) {
+                f[F_LASTMOV] = movers;
+                f[F_TICK] = t == 5 ? 0 : t + 1;
+            }
+            // holes are streamed like particles until a full re-bin drops them
+            f[F_FORCE] = !full && holes - movers > a.hole_limit;
+            if (full) {
+                f[F_OVERFLOW] = 0;
+                f[F_TICKET] = 0;
+                f[F_GO] = 1;
+            }
+        }
     }
-    a.out_cnt[c] = 0;
-    a.in_cnt[c] = 0;
-}
+    if (!full) return;
 
-__device__ __forceinline__ void write_items(const ItemArgs &a, int64_t c)
-{
-    write_items_at(a, c, a.noff[c], a.noff[c + 1]);
-}
-
-__device__ __forceinline__ void finish_flags_n(const ItemArgs &a, int32_t nitems)
-{
-    a.flags[F_NITEMS] = nitems;
-    a.flags[F_LASTMOV] = a.flags[nmov_slot(a.epoch)];
-    a.flags[nmov_slot(a.epoch + 1)] = 0;
-    // holes are streamed like particles until a full re-bin drops them
-    if (a.flags[F_DEAD] > a.dead_limit) a.flags[F_FORCE] = a.epoch + 1;
-}
-
-__device__ __forceinline__ void finish_flags(const ItemArgs &a)
-{
-    finish_flags_n(a, a.noff[a.C]);
-}
-
-// one workgroup: scan, items and reset (C <= kScan1Max)
-__global__ void __launch_bounds__(1024) k_items1(Segments f, ItemArgs a)
-{
-    block_scan_all<int32_t>(f, a.C, a.noff);
+    const int m = a.advance ? t % 3 : (t + 2) % 3;   // state index after the step
+    const Cont *const ct = cur ? a.cont1 : a.cont0;
+    const int32_t *const cf = cur ? a.first1 : a.first0;
+    Cont *const nct = cur ? a.cont0 : a.cont1;
+    int32_t *const ncf = cur ? a.first0 : a.first1;
+    for (int64_t c = threadIdx.x; c < a.C; c += 1024) {
+        int32_t n = 0;
+        for (int32_t j = cf[c]; j < cf[c + 1]; ++j) n += ct[j].s[m].cnt - ct[j].s[m].h + ct[j].in[m];
+        a.new_cnt[c] = n;
+        a.cursor[c] = 0;
+    }
     __syncthreads();
-    for (int64_t c = threadIdx.x; c < a.C; c += blockDim.x) write_items(a, c);
-    if (threadIdx.x == 0) finish_flags(a);
-}
-
-__global__ void k_items(ItemArgs a)
-{
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.C;
-         c += (int64_t)gridDim.x * blockDim.x)
-        write_items(a, c);
-    if (blockIdx.x == 0 && threadIdx.x == 0) finish_flags(a);
-}
-
-// After the arrivals: chunk c's new slot and hole counts.  With h holes
-// (older ones plus the step's departures) and `in` arrivals, the arrivals
-// took the top min(h, in) holes and the rest of them extended the chunk;
-// holes no arrival took stay listed (and marked: a -1 offset or a negated
-// diameter).  Returns the chunk's holes.
-// chunk c's slot count after the arrivals (as count_chunk_from sets it)
-__device__ __forceinline__ int32_t chunk_count_after(int32_t out, int32_t in, int32_t nd,
-                                                     int32_t cnt)
-{
-    const int32_t h = nd + out;
-    return in >= h ? cnt + in - h : cnt;
-}
-
-template <class T>
-__device__ __forceinline__ int32_t count_chunk_from(const View<T> &V, int32_t out, int32_t in,
-                                                    int32_t nd, int32_t cnt, int64_t c)
-{
-    const int32_t h = nd + out;
-    if (out == 0 && in == 0) return nd;
-    if (in >= h) {
-        V.cnt[c] = cnt + in - h;
-        V.ndead[c] = 0;
-        return 0;
-    }
-    V.ndead[c] = h - in;
-    return h - in;
-}
-
-template <class T>
-__device__ __forceinline__ int32_t count_chunk(const View<T> &V, const int32_t *out_cnt,
-                                               const int32_t *in_cnt, int64_t c)
-{
-    return count_chunk_from(V, out_cnt[c], in_cnt[c], V.ndead[c], V.cnt[c], c);
-}
-
-// one workgroup, after the arrivals or the re-keyed count (C <= kScan1Max).
-// After the arrivals: the chunks' new counts (one wave per chunk), the work
-// items of the next step and the reset of the counters.  When a full re-bin
-// is due: the rooms and bases of its layout and the item offsets from the
-// re-keyed counts; the scatter still walks the current items, so the commit
-// writes the new ones.
-template <class T>
-__global__ void __launch_bounds__(1024) k_layout1(Rooms rooms, int64_t *nbase,
-                                                  Segments rekeyed, ItemArgs a, View<T> V,
-                                                  const int32_t *flags)
-{
-    if (full_rebin(flags, a.epoch)) {
-        rooms.denom = block_sum_all(rooms.w, a.C);
-        block_scan_all<int64_t>(rooms, a.C, nbase);
-        __syncthreads();
-        block_scan_all<int32_t>(rekeyed, a.C, a.noff);
-        return;
-    }
-    // a thread's chunks c = k 1024 + threadIdx.x (at most kScan1Max / 1024):
-    // every load is issued before the first store, so that the latencies
-    // overlap, and the new counts, item offsets and totals stay in registers
-    constexpr int PT = kScan1Max / 1024;
-    int32_t out[PT], in[PT], nd[PT], cn[PT];
-#pragma unroll
-    for (int k = 0; k < PT; ++k) {
-        const int64_t c = k * 1024 + threadIdx.x;
-        out[k] = in[k] = nd[k] = cn[k] = 0;
+    int64_t w = 0, denom;
+    for (int64_t c = threadIdx.x; c < a.C; c += 1024) w += room_weight(a.new_cnt, a.nc, c);
+    block_excl_scan<int64_t>(w, denom);
+    int64_t slot0 = 0;
+    int32_t cont_0 = 0, rec0 = 0;
+    for (int64_t r0 = 0; r0 < a.C; r0 += 1024) {
+        const int64_t c = r0 + threadIdx.x;
+        int32_t n = 0, k = 0, per = 0, room = 0;
         if (c < a.C) {
-            out[k] = a.out_cnt[c];
-            in[k] = a.in_cnt[c];
-            nd[k] = V.ndead[c];
-            cn[k] = V.cnt[c];
+            n = a.new_cnt[c];
+            k = n > kSeg ? (n + kSeg - 1) / kSeg : 1;
+            per = ((n + k - 1) / k + kAlign - 1) / kAlign * kAlign;
+            const int64_t extra = a.spare * room_weight(a.new_cnt, a.nc, c) / denom / k;
+            room = (int32_t)min((int64_t)kRoomMax, per + extra / kAlign * kAlign);
         }
-    }
-    int32_t dead = 0, nseg[PT];
-#pragma unroll
-    for (int k = 0; k < PT; ++k) {
-        const int64_t c = k * 1024 + threadIdx.x;
-        nseg[k] = 0;
+        const int32_t icap = c < a.C ? inbox_cap(room, a.whole) : 0;
+        int64_t slots_r;
+        int32_t conts_r, recs_r;
+        const int64_t base = slot0 + block_excl_scan<int64_t>((int64_t)k * room, slots_r);
+        const int32_t j0 = cont_0 + block_excl_scan<int32_t>(k, conts_r);
+        const int32_t ib = rec0 + block_excl_scan<int32_t>(k * icap, recs_r);
         if (c < a.C) {
-            dead += count_chunk_from(V, out[k], in[k], nd[k], cn[k], c);
-            nseg[k] = (chunk_count_after(out[k], in[k], nd[k], cn[k]) + kSeg - 1) / kSeg;
+            ncf[c] = j0;
+            a.lay[c] = int4{(int32_t)base, per, room, k};
+            for (int32_t i = 0; i < k; ++i) {
+                Cont d;
+                d.c = (int32_t)c;
+                d.base = (int32_t)base + i * room;
+                d.room = room;
+                d.ibase = ib + i * icap;
+                d.k = k;
+                for (int u = 0; u < 3; ++u) {
+                    d.in[u] = 0;
+                    d.s[u].cnt = u == m ? min(max(n - i * per, 0), per) : 0;
+                    d.s[u].h = 0;
+                }
+                d.pad[0] = d.pad[1] = 0;
+                nct[j0 + i] = d;
+            }
         }
-    }
-    int32_t total;
-    block_excl_scan<int32_t>(dead, total);
-    if (threadIdx.x == 0) a.flags[F_DEAD] = total;
-    // the item offsets in chunk order, a round of 1024 chunks at a time
-    int32_t carry = 0;
-#pragma unroll
-    for (int k = 0; k < PT; ++k) {
-        if ((int64_t)k * 1024 >= a.C) break;   // uniform
-        int32_t rt;
-        const int32_t o = carry + block_excl_scan<int32_t>(nseg[k], rt);
-        const int64_t c = k * 1024 + threadIdx.x;
-        if (c < a.C) {
-            a.noff[c] = o;
-            write_items_at(a, c, o, o + nseg[k]);
-        }
-        carry += rt;
+        slot0 += slots_r;
+        cont_0 += conts_r;
+        rec0 += recs_r;
     }
     if (threadIdx.x == 0) {
-        a.noff[a.C] = carry;
-        finish_flags_n(a, carry);
+        ncf[a.C] = cont_0;
+        f[cur ? F_NITEMS : F_NITEMS1] = cont_0;
     }
 }
 
 __global__ void k_set_flag(int32_t *flags, int which, int32_t v) { flags[which] = v; }
-
-// when a full re-bin is due on a mesh of more than kScan1Max chunks: the sum
-// of the chunks' room weights, kScanBlock chunks per workgroup
-__global__ void __launch_bounds__(256) k_room_denom(RoomWeight w, int64_t C, int64_t *denom,
-                                                    const int32_t *flags, int32_t epoch)
-{
-    if (!full_rebin(flags, epoch)) return;
-    const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
-    int64_t s = 0;
-    for (int k = 0; k < kScanBlock / 256; ++k) {
-        const int64_t i = b0 + k * 256 + threadIdx.x;
-        if (i < C) s += w(i);
-    }
-    int64_t tot;
-    block_excl_scan<int64_t>(s, tot);
-    if (threadIdx.x == 0) atomicAdd((unsigned long long *)denom, (unsigned long long)tot);
-}
 
 // ---------------------------------------------------------------------------
 // the step kernel
 // ---------------------------------------------------------------------------
 template <class T, class A>
 struct StepArgs {
-    View<T> V;
-    const int32_t *items;
-    const int32_t *nitems;
+    Views<T> V;
+    Cont *cont0, *cont1;
+    const int32_t *first0, *first1;
     const T *u;              // field [3][n2][n1][n0]
     A *src;                  // [C][3][E^3]
-    Movers<T> mv;
-    int32_t *nmov;
-    int64_t mcap;
-    int32_t *out_cnt;
-    int32_t *in_cnt;
-    int32_t *hole;           // holes of chunk c, relative to base[c], from hole[base[c]]
-    int32_t *flags;
+    MoverRec<T> *rec;        // inboxes [2][nrec]
+    int64_t nrec;
+    int32_t *flags, *spread;
+    int32_t whole;           // inboxes hold whole rooms
     int32_t deposit;         // 0: move and re-bin only (tape recompute)
-    int32_t epoch;           // tag of this step in the device flags
     // tape recompute: what the reverse of the step reads, saved into a
     // snapshot buffer at the store's slot indices: the state each slot
-    // starts the step with, its id, and the step's layout (its work items,
-    // and the first slot and slot count of every chunk that has one)
+    // starts the step with, its id, and the containers' runs
     T *sv[7];
     int32_t *sid;
-    int32_t *sitems;
+    RunItem *sitems;
     int32_t *snitems;
-    int64_t *sbase;
-    int32_t *scnt;
     Params p;
     T dt;
     T dt_h[3];               // dt / h per axis
@@ -660,63 +375,69 @@ __device__ __forceinline__ const T *at_byte(const T *base, uint32_t byte_off)
     return (const T *)((const char *)base + byte_off);
 }
 
-// Slots of chunk c free for arrivals whatever the step's departures: those
-// past its last slot and its holes from earlier steps.
-template <class T>
-__device__ __forceinline__ int32_t free_slots(const View<T> &V, int64_t c)
-{
-    return V.room[c] - V.cnt[c] + V.ndead[c];
-}
-
-// A slot holds a particle unless its offset is negative (binary32 forms:
-// the step kernel stores -1 for a particle that left) or its diameter is not
+// A slot holds a particle unless its offset is the hole mark (binary32 forms:
+// the step kernel stores it for a particle that left) or its diameter is not
 // positive (binary64 form: the diameter of a particle that left is negated).
+// (A particle whose inbox was full stays in place with the un-rebased, perhaps
+// negative, offsets of its new position.)
 template <class T>
 __device__ __forceinline__ bool occupied(T ox, T d)
 {
-    return ox >= T(0) && d > T(0);
+    return ox > T(kHoleMark) && d > T(0);
 }
 
-// A mover not staged in LDS (more movers than the stage holds), from its
-// new state in registers (un-rebased offsets, relative to chunk c): lists
-// its slot q among the chunk's holes at hpos and copies the particle,
-// re-based onto its destination chunk, into the mover list at m with its
-// destination and its rank among the destination's arrivals.  Returns false
-// when the mover list is full: the particle then stays in place (the full
-// re-bin that the overflow forces takes it from there).
-template <class T, class A>
-__device__ __forceinline__ bool emit_mover(const StepArgs<T, A> &a, int64_t c, int64_t base,
-                                           int64_t q, int64_t m, int64_t hpos, T x, T y, T z,
-                                           T vx, T vy, T vz, T dd)
+// Where a container takes arrivals of the step with state index m (the state
+// before it: index pm): slots free for them whatever the step's departures
+// (more force the full re-bin), the records its inbox holds, and its first.
+struct Inbox {
+    int32_t free, cap, base;
+};
+__device__ __forceinline__ Inbox inbox_of(const Cont *d, int pm, int32_t whole)
 {
-    const View<T> &V = a.V;
-    const int32_t id = V.id[q];
+    const int32_t room = d->room;
+    return Inbox{room - (d->s[pm].cnt - d->s[pm].h) - d->in[pm], inbox_cap(room, whole), d->ibase};
+}
+
+// The container of chunk c that container `item` sends its movers to.
+__device__ __forceinline__ int32_t container_for(const int32_t *first, int64_t c, int32_t item)
+{
+    const int32_t f = first[c], k = first[c + 1] - f;
+    return f + (k > 1 ? item % k : 0);
+}
+
+// A mover sent by itself (farther than one chunk, or more movers than the LDS
+// stage holds): x, y, z its new position as stored (un-rebased offsets,
+// relative to chunk c).  Returns false when the inbox is full: the particle
+// then stays in place (the full re-bin that this forces takes it from there).
+template <class T, class A>
+__device__ __forceinline__ bool send_mover(const StepArgs<T, A> &a, Cont *ct,
+                                           const int32_t *first, MoverRec<T> *rec, int m, int pm,
+                                           int32_t item, int64_t c, T x, T y, T z, T vx, T vy,
+                                           T vz, T dd, int32_t id)
+{
     const int64_t cn = chunk_of_stored(a.p, c, x, y, z);
-    a.hole[base + hpos] = (int32_t)(q - base);
-    if (m >= a.mcap) {
-        a.flags[F_OVERFLOW] = a.epoch;
+    const int32_t j = container_for(first, cn, item);
+    const Inbox in = inbox_of(ct + j, pm, a.whole);
+    const int32_t r = atomicAdd(&ct[j].in[m], 1);
+    if (r >= in.free) a.flags[F_OVERFLOW] = 1;
+    if (r >= in.cap) {
+        a.flags[F_OVERFLOW] = 1;
         return false;
     }
-    a.mv.rec[m] = MoverRec<T>{x, y, z, vx, vy, vz, dd, id};
-    a.mv.dest[m] = (int32_t)cn;
-    const int32_t r = atomicAdd(&a.in_cnt[cn], 1);
-    a.mv.rank[m] = r;
-    // arrivals must fit the destination's free slots; one that does not
-    // forces the full re-bin, which places every recorded mover itself
-    if (r >= free_slots(V, cn)) a.flags[F_OVERFLOW] = a.epoch;
+    rec[in.base + r] = MoverRec<T>{x, y, z, vx, vy, vz, dd, id};
     return true;
 }
 
-// Staged mover: its slot within the work item (below kSeg, 14 bits), its
+// Staged mover: its slot within the container (below kRoomMax, 15 bits), its
 // direction class (0..26 the neighbouring chunks, 27 farther; 5 bits) and its
 // rank within that class (below kMoverStage, 9 bits).
-constexpr int kSlotBits = 14, kDirBits = 5;
-static_assert(kSeg <= (1 << kSlotBits) && kMoverStage <= (1 << (32 - 1 - kSlotBits - kDirBits)),
+constexpr int kSlotBits = 15, kDirBits = 5;
+static_assert(kRoomMax <= (1 << kSlotBits) && kMoverStage <= (1 << (32 - 1 - kSlotBits - kDirBits)),
               "staged mover fields must fit one int32");
 static_assert(kDirBits * 4 <= 32, "direction classes of a group must fit one uint32");
 
-template <class T, class A, int E, int INTERP, int DRAG, bool SAVE>
-__global__ void __launch_bounds__(kBlock)
+template <class T, class A, int E, int INTERP, int DRAG, bool SAVE, int NB>
+__global__ void __launch_bounds__(NB)
      k_step(StepArgs<T, A> a)
 {
     constexpr int S = E + 2;            // tile edge with the halo
@@ -727,77 +448,84 @@ __global__ void __launch_bounds__(kBlock)
     __shared__ T tile[3 * S3];
     __shared__ A acc[3 * E3];
     __shared__ int32_t mstage[kMoverStage];
-    // binary32 state: the staged movers' new positions and velocities (12 KB,
-    // which still lets four workgroups share a CU; the binary64 form re-reads
-    // them instead)
+    // binary32 state: the staged movers' new positions and velocities (9 KB,
+    // which with the arrivals still lets four workgroups share a CU; the
+    // binary64 form re-reads them instead)
     constexpr bool kStageVals = sizeof(T) == 4;
     __shared__ T mval[kStageVals ? 6 * kMoverStage : 1];
-    __shared__ int32_t mcount, mbase_sh, hbase_sh;
-    __shared__ int32_t dcount[28], doff[28], dbase[27];
+    __shared__ MoverRec<T> pool[kPool];   // the first arrivals
+    __shared__ int32_t mcount, apop;
+    __shared__ int32_t dcount[28], dbase[27];
+    __shared__ int32_t nbj[27];           // the neighbouring chunks' containers
+    __shared__ Inbox nbin[27];
 
-    // the grid covers the most items a layout can have, rounded up to whole
-    // rounds of the remap
+    // the grid covers the most containers a layout can have, rounded up to
+    // whole rounds of the remap
     const int64_t item = xcd_remap(blockIdx.x);
+    const int32_t cur = a.flags[F_CUR], tick = a.flags[F_TICK];
+    const int32_t ni = cur ? a.flags[F_NITEMS1] : a.flags[F_NITEMS];
     if constexpr (SAVE)
-        if (blockIdx.x == 0 && threadIdx.x == 0) *a.snitems = *a.nitems;
-    if (item >= *a.nitems) return;
-    const View<T> &V = a.V;
-    const int64_t c = a.items[2 * item];
-    const int64_t seg = a.items[2 * item + 1];
-    const int64_t base = V.base[c];
-    const int32_t cnt = V.cnt[c];
-    if constexpr (SAVE) {
-        if (threadIdx.x == 0) {
-            a.sitems[2 * item] = (int32_t)c;
-            a.sitems[2 * item + 1] = (int32_t)seg;
-            if (seg == 0) {
-                a.sbase[c] = base;
-                a.scnt[c] = cnt;
-            }
-        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.snitems = ni;
+    if (item >= ni) return;
+    Cont *const ct = cur ? a.cont1 : a.cont0;
+    const int32_t *const first = cur ? a.first1 : a.first0;
+    const View<T> V = a.V.pick(cur);
+    // state indices of this step, the one before and the one after
+    const int m = tick >= 3 ? tick - 3 : tick, pm = m == 0 ? 2 : m - 1, qm = m == 2 ? 0 : m + 1;
+    MoverRec<T> *const rec_in = a.rec + (tick & 1 ? 0 : a.nrec);    // written by the last step
+    MoverRec<T> *const rec_out = a.rec + (tick & 1 ? a.nrec : 0);
+    const ContState me = state_of(ct + item, pm);
+    const int64_t c = me.c;
+    const int64_t s0 = me.base;
+    const int32_t n_in = me.in, nq_old = me.cnt, h_old = me.h;
+    // the arrivals take the holes, then slots past the last
+    const int nq = nq_old + max(0, n_in - h_old);
+    const int32_t h_left = max(0, h_old - n_in);
+    const bool multi = me.k > 1;
+    if constexpr (SAVE)
+        if (threadIdx.x == 0) a.sitems[item] = RunItem{me.c, me.base, nq, me.k};
+    if (threadIdx.x == 0) ct[item].in[qm] = 0;
+    if (nq == 0) {
+        if (threadIdx.x == 0) ct[item].s[m] = {0, 0};
+        return;
     }
-    const int32_t nd_c = V.ndead[c];   // this step's holes are listed after these
-    const int64_t s0 = base + seg * kSeg;
-    const int64_t s1 = min(s0 + (int64_t)kSeg, base + (int64_t)cnt);
-    const bool multi = cnt > kSeg;
     const Params &p = a.p;
-    const int cx = (int)(c % p.nc[0]);
-    const int cy = (int)((c / p.nc[0]) % p.nc[1]);
-    const int cz = (int)(c / ((int64_t)p.nc[0] * p.nc[1]));
+    const int row = me.c / p.nc[0], cx = me.c - row * p.nc[0];
+    const int cz = row / p.nc[1], cy = row - cz * p.nc[1];
     const int64_t ncell = (int64_t)p.n[0] * p.n[1] * p.n[2];
 
-    // The work item's slots are read in groups of G consecutive slots through
-    // uniform base pointers and 32-bit offsets (at most kSeg).  s0 is a
-    // multiple of G (chunk bases and kSeg are), and a group that runs past s1
-    // stays inside the chunk's room.
-    const int nq = (int)(s1 - s0);
+    // The container's slots are read in groups of G consecutive slots through
+    // uniform base pointers and 32-bit offsets (below kRoomMax).  s0 is a
+    // multiple of G, and a group that runs past the last slot stays inside the
+    // container's room.
     const int ngroups = (nq + G - 1) / G;
     T *const pox = V.ox + s0, *const poy = V.oy + s0, *const poz = V.oz + s0;
     T *const pvx = V.vx + s0, *const pvy = V.vy + s0, *const pvz = V.vz + s0;
-    const T *const pd = V.d + s0;
+    T *const pd = V.d + s0;
+    int32_t *const pid = V.id + s0;
     auto load_group = [&](int gi, T (&X)[G], T (&Y)[G], T (&Z)[G], T (&UX)[G], T (&UY)[G],
                           T (&UZ)[G], T (&DD)[G]) {
         const uint32_t ob = (uint32_t)gi * G * (uint32_t)sizeof(T);
-        vld<T, G>(at_byte(pox, ob), X);
-        vld<T, G>(at_byte(poy, ob), Y);
-        vld<T, G>(at_byte(poz, ob), Z);
-        vld<T, G>(at_byte(pvx, ob), UX);
-        vld<T, G>(at_byte(pvy, ob), UY);
-        vld<T, G>(at_byte(pvz, ob), UZ);
-        vld<T, G>(at_byte(pd, ob), DD);
+        vld<T, G>(at_byte((const T *)pox, ob), X);
+        vld<T, G>(at_byte((const T *)poy, ob), Y);
+        vld<T, G>(at_byte((const T *)poz, ob), Z);
+        vld<T, G>(at_byte((const T *)pvx, ob), UX);
+        vld<T, G>(at_byte((const T *)pvy, ob), UY);
+        vld<T, G>(at_byte((const T *)pvz, ob), UZ);
+        vld<T, G>(at_byte((const T *)pd, ob), DD);
     };
 
     // Stage the fluid tile: cells E*c - 1 .. E*c + E per axis, wrapped.  The
     // main loop is software-pipelined: a group's loads are issued before the
     // arithmetic of the previous one, and the first group's right after the
     // tile's loads, so that memory latency overlaps work.
-    constexpr int NT = (3 * S3 + kBlock - 1) / kBlock;
+    constexpr int NT = (3 * S3 + NB - 1) / NB;
     T vals[NT];
     {
         const int ox0 = cx * E - 1, oy0 = cy * E - 1, oz0 = cz * E - 1;
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
-            const int t = threadIdx.x + u * kBlock;
+            const int t = threadIdx.x + u * NB;
             if (t < 3 * S3) {
                 const int comp = t / S3;
                 const int r = t - comp * S3;
@@ -815,18 +543,45 @@ __global__ void __launch_bounds__(kBlock)
             }
         }
     }
+    // the container's first arrivals, in 16-byte pieces
+    constexpr int RV = sizeof(MoverRec<T>) / 16;
+    int4 arr[RV];
+    const bool have_arr = (int)threadIdx.x < min(n_in, kPool);
+#pragma unroll
+    for (int u = 0; u < RV; ++u)
+        arr[u] = have_arr ? reinterpret_cast<const int4 *>(rec_in + me.ibase + threadIdx.x)[u]
+                          : int4{0, 0, 0, 0};
     int gi = threadIdx.x;
     T X[G], Y[G], Z[G], UX[G], UY[G], UZ[G], DD[G];
     if (gi < ngroups) load_group(gi, X, Y, Z, UX, UY, UZ, DD);
+    // the neighbouring chunks' inboxes, needed after the loop
+    int32_t nb = 0, nb_free = 0, nb_cap = 0, nb_base = 0;
+    if (threadIdx.x < 27) {
+        const int l = threadIdx.x;
+        auto wrap1 = [](int i, int n) { return i < 0 ? i + n : i >= n ? i - n : i; };
+        const int64_t dc = chunk_index(p, wrap1(cx + l % 3 - 1, p.nc[0]),
+                                       wrap1(cy + (l / 3) % 3 - 1, p.nc[1]),
+                                       wrap1(cz + l / 9 - 1, p.nc[2]));
+        nb = ni == (int32_t)p.C ? (int32_t)dc : container_for(first, dc, (int32_t)item);
+        const Inbox in = inbox_of(ct + nb, pm, a.whole);
+        nb_free = in.free;
+        nb_cap = in.cap;
+        nb_base = in.base;
+    }
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-        const int t = threadIdx.x + u * kBlock;
+        const int t = threadIdx.x + u * NB;
         if (t < 3 * S3) tile[t] = vals[u];
     }
-    for (int t = threadIdx.x; t < 3 * E3; t += kBlock) acc[t] = A(0);
+    for (int t = threadIdx.x; t < 3 * E3; t += NB) acc[t] = A(0);
     if (threadIdx.x < 28) dcount[threadIdx.x] = 0;
-    if (threadIdx.x == 0) mcount = 0;
+    if (have_arr) {
+#pragma unroll
+        for (int u = 0; u < RV; ++u) reinterpret_cast<int4 *>(pool + threadIdx.x)[u] = arr[u];
+    }
+    if (threadIdx.x == 0) mcount = apop = 0;
     __syncthreads();
+    bool pool_open = n_in > 0;   // of the wave: arrivals may be left
 
     const T dt = a.dt;
     const T fe = T(E), inv_e = T(1) / T(E);
@@ -834,11 +589,62 @@ __global__ void __launch_bounds__(kBlock)
     // in binary32 (the chunk origin in cells is exact)
     constexpr bool GLOBAL = sizeof(A) == 4;
     const T org[3] = {T(cx * E), T(cy * E), T(cz * E)};
-    for (; gi < ngroups; gi += kBlock) {
+    for (; gi < ngroups; gi += NB) {
         T Xn[G], Yn[G], Zn[G], UXn[G], UYn[G], UZn[G], DDn[G];
-        if (gi + kBlock < ngroups) load_group(gi + kBlock, Xn, Yn, Zn, UXn, UYn, UZn, DDn);
+        if (gi + NB < ngroups) load_group(gi + NB, Xn, Yn, Zn, UXn, UYn, UZn, DDn);
         const uint32_t o = (uint32_t)gi * G;
         const uint32_t ob = o * (uint32_t)sizeof(T);
+        int32_t I[G];
+        if constexpr (SAVE) vld<int32_t, G>(at_byte((const int32_t *)pid, o * 4u), I);
+        if (pool_open) {
+            // holes of the run, and its slots past the last step's last, take
+            // arrivals while there are any: one LDS reservation per wave, the
+            // lanes' shares from a ballot per bit of their counts (at most 4)
+            uint32_t holes = 0;
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                const int q = (int)o + k;
+                if (q < nq && (q >= nq_old || !occupied(X[k], DD[k]))) holes |= 1u << k;
+            }
+            if (__ballot(holes != 0)) {
+                const int mine = __popc(holes);
+                const uint64_t below = lanes_below_mask();
+                int ex = 0, tot = 0;
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const uint64_t bal = __ballot((mine >> b) & 1);
+                    ex += __popcll(bal & below) << b;
+                    tot += __popcll(bal) << b;
+                }
+                const int lead = __ffsll((long long)__ballot(1)) - 1;
+                int r0 = 0;
+                if (__lane_id() == lead) r0 = atomicAdd(&apop, tot);
+                r0 = __shfl(r0, lead);
+                pool_open = r0 + tot < n_in;
+                int r = r0 + ex;
+#pragma unroll
+                for (int k = 0; k < G; ++k) {
+                    if (!((holes >> k) & 1)) continue;
+                    if (r < n_in) {
+                        auto take = [&](const MoverRec<T> &rc) {
+                            X[k] = rc.ox;
+                            Y[k] = rc.oy;
+                            Z[k] = rc.oz;
+                            UX[k] = rc.vx;
+                            UY[k] = rc.vy;
+                            UZ[k] = rc.vz;
+                            DD[k] = rc.d;
+                            if constexpr (SAVE) I[k] = rc.id;
+                            pd[o + k] = rc.d;
+                            pid[o + k] = rc.id;
+                        };
+                        if (r < kPool) take(pool[r]);
+                        else take(rec_in[me.ibase + r]);
+                    }
+                    ++r;
+                }
+            }
+        }
         if constexpr (SAVE) {   // the group as the step finds it, with its ids
             vst<T, G>(at_byte(a.sv[0] + s0, ob), X);
             vst<T, G>(at_byte(a.sv[1] + s0, ob), Y);
@@ -847,8 +653,6 @@ __global__ void __launch_bounds__(kBlock)
             vst<T, G>(at_byte(a.sv[4] + s0, ob), UY);
             vst<T, G>(at_byte(a.sv[5] + s0, ob), UZ);
             vst<T, G>(at_byte(a.sv[6] + s0, ob), DD);
-            int32_t I[G];
-            vld<int32_t, G>(at_byte((const int32_t *)V.id + s0, o * 4u), I);
             vst<int32_t, G>(at_byte(a.sid + s0, o * 4u), I);
         }
         uint32_t movers = 0, dirs = 0;   // mover bits and 5-bit direction classes
@@ -962,7 +766,7 @@ __global__ void __launch_bounds__(kBlock)
                 mover = xn[0] < T(0) || xn[0] >= fe || xn[1] < T(0) || xn[1] >= fe ||
                         xn[2] < T(0) || xn[2] >= fe;
             }
-            if (valid) {   // a hole keeps what it holds (binary32: the -1 offset)
+            if (valid) {   // a hole keeps what it holds (binary32: its mark)
                 X[k] = xn[0];
                 Y[k] = xn[1];
                 Z[k] = xn[2];
@@ -999,10 +803,10 @@ __global__ void __launch_bounds__(kBlock)
                 ex += __popcll(bal & below) << b;
                 tot += __popcll(bal) << b;
             }
-            const int first = __ffsll((long long)__ballot(1)) - 1;
+            const int lead = __ffsll((long long)__ballot(1)) - 1;
             int j0 = 0;
-            if (__lane_id() == first) j0 = atomicAdd(&mcount, tot);
-            int j = __shfl(j0, first) + ex;
+            if (__lane_id() == lead) j0 = atomicAdd(&mcount, tot);
+            int j = __shfl(j0, lead) + ex;
             if constexpr (kStageVals) {
                 // binary32: the new state too, so that it need not be re-read
 #pragma unroll
@@ -1017,13 +821,11 @@ __global__ void __launch_bounds__(kBlock)
                         mval[3 * kMoverStage + j] = UX[k];
                         mval[4 * kMoverStage + j] = UY[k];
                         mval[5 * kMoverStage + j] = UZ[k];
-                        X[k] = T(-1);   // the slot becomes a hole
-                    } else {  // more movers than the LDS stage holds: emit directly
-                        const int64_t m = atomicAdd(a.nmov, 1);
-                        const int64_t h = atomicAdd(&a.out_cnt[c], 1);
-                        if (emit_mover(a, c, base, s0 + o + k, m, nd_c + h, X[k], Y[k], Z[k],
-                                       UX[k], UY[k], UZ[k], DD[k]))
-                            X[k] = T(-1);
+                        X[k] = T(2 * kHoleMark);   // the slot becomes a hole
+                    } else {  // more movers than the LDS stage holds
+                        if (send_mover(a, ct, first, rec_out, m, pm, (int32_t)item, c, X[k], Y[k],
+                                       Z[k], UX[k], UY[k], UZ[k], DD[k], pid[o + k]))
+                            X[k] = T(2 * kHoleMark);
                     }
                     ++j;
                 }
@@ -1034,19 +836,17 @@ __global__ void __launch_bounds__(kBlock)
                     if (j < kMoverStage) {
                         const int dir = (dirs >> (kDirBits * k)) & ((1 << kDirBits) - 1);
                         mstage[j] = (int32_t)(o + k) | (dir << kSlotBits);
-                    } else {  // more movers than the LDS stage holds: emit directly
-                        const int64_t m = atomicAdd(a.nmov, 1);
-                        const int64_t h = atomicAdd(&a.out_cnt[c], 1);
+                    } else {  // more movers than the LDS stage holds
                         // binary64: the negated diameter marks the hole
-                        if (emit_mover(a, c, base, s0 + o + k, m, nd_c + h, X[k], Y[k], Z[k],
-                                       UX[k], UY[k], UZ[k], DD[k]))
-                            a.V.d[s0 + o + k] = -DD[k];
+                        if (send_mover(a, ct, first, rec_out, m, pm, (int32_t)item, c, X[k], Y[k],
+                                       Z[k], UX[k], UY[k], UZ[k], DD[k], pid[o + k]))
+                            pd[o + k] = -DD[k];
                     }
                     ++j;
                 }
             }
         }
-        // slots past s1 in the last group are dead; writing them is harmless
+        // slots past the run in the last group are dead; writing them is harmless
         vst<T, G>(at_byte(pox, ob), X);
         vst<T, G>(at_byte(poy, ob), Y);
         vst<T, G>(at_byte(poz, ob), Z);
@@ -1064,45 +864,45 @@ __global__ void __launch_bounds__(kBlock)
             DD[k] = DDn[k];
         }
     }
+    // The chunk's source cells are read while the other waves finish (a chunk
+    // of one container adds its sum to them; one of several adds atomically).
+    A *const src_c = a.src + c * (3 * E3);
+    constexpr int NF = (3 * E3 + NB - 1) / NB;
+    A old[NF];
+    const bool rmw = a.deposit && !multi;
+    if (rmw) {
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            const int t = threadIdx.x + u * NB;
+            old[u] = t < 3 * E3 ? src_c[t] : A(0);
+        }
+    }
+    if (threadIdx.x < 27) {
+        nbj[threadIdx.x] = nb;
+        nbin[threadIdx.x] = Inbox{nb_free, nb_cap, nb_base};
+    }
     __syncthreads();
 
-    // Mover reservations, all issued by one wave at once: the workgroup's
-    // slots in the mover list (ordered by direction class, movers farther
-    // than one chunk last, so that the arrivals a destination receives from
-    // this chunk sit in consecutive records), its entries in the chunk's
-    // vacated-slot list, and one arrival-count reservation per neighbouring
-    // destination instead of one per mover, which would serialise on the
-    // counters of crowded chunks.  The movers' state is read in the same
-    // round trip.
+    // Mover reservations, all issued by one wave at once: one reservation per
+    // neighbouring destination instead of one per mover, which would serialise
+    // on the counters of crowded chunks, and the workgroup's share of the
+    // spread counters.  The movers' state is read in the same round trip.
     const int nm = min(mcount, kMoverStage);
     // ranks of the staged movers within their direction classes
     if (nm > 0) {
-        for (int j = threadIdx.x; j < nm; j += kBlock) {
+        for (int j = threadIdx.x; j < nm; j += NB) {
             const int32_t w = mstage[j];
             const int dir = (w >> kSlotBits) & ((1 << kDirBits) - 1);
             mstage[j] = w | (atomicAdd(&dcount[dir], 1) << (kSlotBits + kDirBits));
         }
         __syncthreads();
     }
-    // The chunk's source cells are read first (a chunk that is one work item
-    // adds its sum to them; one split over several items adds atomically).
-    A *const src_c = a.src + c * (3 * E3);
-    constexpr int NF = (3 * E3 + kBlock - 1) / kBlock;
-    A old[NF];
-    const bool rmw = a.deposit && !multi;
-    if (rmw) {
-#pragma unroll
-        for (int u = 0; u < NF; ++u) {
-            const int t = threadIdx.x + u * kBlock;
-            old[u] = t < 3 * E3 ? src_c[t] : A(0);
-        }
-    }
-    constexpr int NM = kMoverStage / kBlock;   // staged movers per thread
+    constexpr int NM = (kMoverStage + NB - 1) / NB;   // staged movers per thread
     T mx[NM], my[NM], mz[NM], mvx[NM], mvy[NM], mvz[NM], md[NM];
     int32_t mid[NM];
 #pragma unroll
     for (int u = 0; u < NM; ++u) {
-        const int j = threadIdx.x + u * kBlock;
+        const int j = threadIdx.x + u * NB;
         if (j < nm) {
             const int64_t q = s0 + (mstage[j] & ((1 << kSlotBits) - 1));
             if constexpr (kStageVals) {
@@ -1124,34 +924,32 @@ __global__ void __launch_bounds__(kBlock)
             mid[u] = V.id[q];
         }
     }
-    if (nm > 0 && threadIdx.x < 64) {
+    if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
-        const int n = lane < 28 ? dcount[lane] : 0;
-        int incl = n;
-        for (int off = 1; off < 32; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            if (lane >= off) incl += v;
+        const int n = lane < 27 ? dcount[lane] : 0;
+        const int32_t h_new = h_left + mcount;
+        if (lane == 0) ct[item].s[m] = {nq, h_new};
+        // one atomic instruction (the counters differ per lane)
+        int32_t *ctr = nullptr;
+        int add = n;
+        if (n > 0) ctr = &ct[nbj[lane]].in[m];
+        int32_t *const line = a.spread + 16 * (blockIdx.x % kSpread);
+        if (lane == 32) {
+            ctr = line;
+            add = h_new - h_old;
         }
-        if (lane < 28) doff[lane] = incl - n;
-        // one atomic instruction for all reservations (the counters differ
-        // per lane): lanes 0..26 the arrival counts of the neighbouring
-        // chunks, lane 32 the mover list, lane 33 the vacated-slot list
-        const bool nb = lane < 27 && n > 0;
-        const int64_t dc = chunk_index(p, wrapi(cx + lane % 3 - 1, p.nc[0]),
-                                       wrapi(cy + (lane / 3) % 3 - 1, p.nc[1]),
-                                       wrapi(cz + (lane / 9) % 3 - 1, p.nc[2]));
-        int32_t *ctr = nb ? &a.in_cnt[dc] : lane == 32 ? a.nmov : &a.out_cnt[c];
-        const int add = nb ? n : nm;
-        if (nb || lane == 32 || lane == 33) {
+        if (lane == 33) {
+            ctr = line + 1;
+            add = mcount;
+        }
+        if (add != 0) {
             const int32_t r = atomicAdd(ctr, add);
-            if (nb) {
+            if (n > 0) {
                 dbase[lane] = r;
-                // arrivals must fit the destination's free slots (a bound
-                // that ignores its departures), else the full re-bin runs
-                if (r + n > free_slots(V, dc)) a.flags[F_OVERFLOW] = a.epoch;
+                // arrivals must fit the destination's free slots, else the
+                // full re-bin runs
+                if (r + n > nbin[lane].free) a.flags[F_OVERFLOW] = 1;
             }
-            if (lane == 32) mbase_sh = r;
-            if (lane == 33) hbase_sh = r;
         }
     }
 
@@ -1159,11 +957,11 @@ __global__ void __launch_bounds__(kBlock)
     if (rmw) {
 #pragma unroll
         for (int u = 0; u < NF; ++u) {
-            const int t = threadIdx.x + u * kBlock;
+            const int t = threadIdx.x + u * NB;
             if (t < 3 * E3) src_c[t] = old[u] + acc[t];
         }
     } else if (a.deposit) {
-        for (int t = threadIdx.x; t < 3 * E3; t += kBlock) {
+        for (int t = threadIdx.x; t < 3 * E3; t += NB) {
             const A v = acc[t];
             if (v != A(0)) atomicAdd(src_c + t, v);
         }
@@ -1171,281 +969,272 @@ __global__ void __launch_bounds__(kBlock)
     if (nm == 0) return;
     __syncthreads();
 
-    // emit the staged movers into their records and the arrival lists
+    // emit the staged movers into their destinations' inboxes
 #pragma unroll
     for (int u = 0; u < NM; ++u) {
-        const int j = threadIdx.x + u * kBlock;
+        const int j = threadIdx.x + u * NB;
         if (j >= nm) continue;
         const int32_t w = mstage[j];
         const int32_t off = w & ((1 << kSlotBits) - 1);
         const int dir = (w >> kSlotBits) & ((1 << kDirBits) - 1);
         const int rank = w >> (kSlotBits + kDirBits);
-        const int64_t m = (int64_t)mbase_sh + doff[dir] + rank;
-        // re-base the offsets into the destination chunk (FP32-everywhere
-        // form: positions in metres stay as they are)
-        T rx = mx[u], ry = my[u], rz = mz[u];
-        const int64_t cfar = chunk_of_stored(p, c, rx, ry, rz);
-        int64_t dest;
-        int32_t r;
+        bool sent;
         if (dir < 27) {   // within the direction's reservation
-            dest = chunk_index(p, wrapi(cx + dir % 3 - 1, p.nc[0]),
-                               wrapi(cy + (dir / 3) % 3 - 1, p.nc[1]),
-                               wrapi(cz + dir / 9 - 1, p.nc[2]));
-            r = dbase[dir] + rank;
+            // re-base the offsets into the destination chunk (FP32-everywhere
+            // form: positions in metres stay as they are)
+            T rx = mx[u], ry = my[u], rz = mz[u];
+            chunk_of_stored(p, c, rx, ry, rz);
+            const int32_t r = dbase[dir] + rank;
+            sent = r < nbin[dir].cap;
+            if (sent)
+                rec_out[nbin[dir].base + r] =
+                    MoverRec<T>{rx, ry, rz, mvx[u], mvy[u], mvz[u], md[u], mid[u]};
+            else
+                a.flags[F_OVERFLOW] = 1;
         } else {          // farther than one chunk: a reservation of its own
-            dest = cfar;
-            r = atomicAdd(&a.in_cnt[dest], 1);
-            if (r >= free_slots(V, dest)) a.flags[F_OVERFLOW] = a.epoch;
+            sent = send_mover(a, ct, first, rec_out, m, pm, (int32_t)item, c, mx[u], my[u], mz[u],
+                              mvx[u], mvy[u], mvz[u], md[u], mid[u]);
         }
-        // the slot becomes a hole of this chunk (binary32: the step stored a
-        // -1 offset; binary64: the diameter is negated)
-        a.hole[base + nd_c + hbase_sh + j] = (int32_t)(s0 + off - base);
-        if (m < a.mcap) {
-            a.mv.rec[m] = MoverRec<T>{rx, ry, rz, mvx[u], mvy[u], mvz[u], md[u], mid[u]};
-            a.mv.dest[m] = (int32_t)dest;
-            // a rank beyond the destination's free slots has forced the full
-            // re-bin, which places every recorded mover itself
-            a.mv.rank[m] = r;
-            if constexpr (!kStageVals) V.d[s0 + off] = -md[u];
+        // the slot becomes a hole (binary32: the step stored its mark;
+        // binary64: the diameter is negated); a particle whose inbox is full
+        // stays in place (its un-rebased offsets) for the full re-bin
+        if constexpr (kStageVals) {
+            if (!sent) pox[off] = mx[u];
         } else {
-            // the mover list is full: the particle stays in place (its
-            // un-rebased offsets) for the full re-bin that this forces
-            a.flags[F_OVERFLOW] = a.epoch;
-            if constexpr (kStageVals) V.ox[s0 + off] = mx[u];
+            if (sent) pd[off] = -md[u];
         }
     }
 }
 
 
 // ---------------------------------------------------------------------------
-// re-bin after the step: the arrivals or the full counting sort
+// the full re-bin's scatter, and the placement of the last step's arrivals
 // ---------------------------------------------------------------------------
 template <class T>
-__device__ __forceinline__ void place_mover(const View<T> &V, int64_t dst, const Movers<T> &mv,
-                                            int64_t m)
+__device__ __forceinline__ void put_slot(const View<T> &V, int64_t q, const MoverRec<T> &r)
 {
-    const MoverRec<T> r = mv.rec[m];
-    V.ox[dst] = r.ox;
-    V.oy[dst] = r.oy;
-    V.oz[dst] = r.oz;
-    V.vx[dst] = r.vx;
-    V.vy[dst] = r.vy;
-    V.vz[dst] = r.vz;
-    V.d[dst] = r.d;
-    V.id[dst] = r.id;
+    V.ox[q] = r.ox;
+    V.oy[q] = r.oy;
+    V.oz[q] = r.oz;
+    V.vx[q] = r.vx;
+    V.vy[q] = r.vy;
+    V.vz[q] = r.vz;
+    V.d[q] = r.d;
+    V.id[q] = r.id;
 }
 
 template <class T>
-struct RebinArgs {
-    View<T> V;
-    View<T> W;               // second store (target of the full re-bin)
-    Movers<T> mv;
-    int64_t C;
-    const int32_t *out_cnt, *in_cnt;
-    int32_t *hole;
-    const int32_t *items, *nitems;
-    Params p;
-    int64_t npend;           // staged injected particles (full re-bin only)
-    int64_t mcap;            // mover list capacity
-    int32_t *new_cnt, *cursor;
-    const int64_t *nbase;
-    const int32_t *nroom;
-    int64_t *room_denom;     // sum of the room weights (zeroed by the count)
-    int64_t slots;
+struct ScatterArgs {
+    Views<T> V;
+    const Cont *cont0, *cont1;
+    const MoverRec<T> *rec;  // inboxes [2][nrec], or staged injections
+    int64_t nrec;
+    const int32_t *dest;     // chunks of the staged injections
+    int64_t npend;           // staged injections (then no inbox holds any)
+    const int4 *lay;
+    int32_t *cursor;
     int32_t *flags;
-    int32_t epoch;
+    int64_t C;
+    int32_t whole;
+    Params p;
 };
 
-constexpr int kArriveBlock = 256;   // threads per workgroup of the arrivals
-
-// One thread per mover of the step: its arrival of rank r in chunk c takes
-// the hole r places from the top of the chunk's hole list (the step's own
-// departures first, then the older holes), or, past the holes, the slot
-// r - holes past the chunk's last.  Counts are those of the step's start
-// (the counts pass runs after this one).
-template <class T>
-__device__ void arrive(const RebinArgs<T> &a)
+// the slot of a chunk's particle number `rank` in the new layout
+__device__ __forceinline__ int64_t slot_of_rank(const int4 &l, int32_t rank)
 {
-    const View<T> &V = a.V;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    // a thread's first destination and rank are read together with the
-    // count (the list's entries below its capacity can all be read), the
-    // next ones while the current mover is placed; a record is read beside
-    // its destination's counts
-    int32_t c = 0, r = 0;
-    if (m < a.mcap) {
-        c = a.mv.dest[m];
-        r = a.mv.rank[m];
-    }
-    const int64_t nm = a.flags[nmov_slot(a.epoch)];
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.flags[F_DEAD] = 0;   // summed by the counts
-    for (; m < nm; m += stride) {
-        const MoverRec<T> cur = a.mv.rec[m];
-        const int64_t base = V.base[c];
-        const int32_t h = V.ndead[c] + a.out_cnt[c];
-        const int64_t slot = r < h ? base + a.hole[base + h - 1 - r]
-                                   : base + V.cnt[c] + (r - h);
-        if (m + stride < nm && m + stride < a.mcap) {
-            c = a.mv.dest[m + stride];
-            r = a.mv.rank[m + stride];
+    const int32_t i = rank < l.y ? 0 : rank / l.y;
+    return (int64_t)l.x + (int64_t)i * l.z + (rank - i * l.y);
+}
+
+constexpr int kScatterBlock = 1024;
+constexpr int kScatterGroups = 512;   // they run every step and usually exit at the gate
+
+// Staged injections per chunk are counted, and placed, in tiles of kTile per
+// workgroup through LDS counters of every chunk while there are at most
+// kHistMax chunks, so that the counter of a crowded chunk is taken once per
+// tile: device atomics on one address are served one after the other (8 x
+// 375e3 droplets in two plumes on 1728 chunks: 0.53 ms a count and 0.57 ms a
+// scatter with an atomic per droplet).  With more chunks the counters are
+// less crowded, and a droplet takes its own atomic.
+constexpr int kHistMax = 8192;
+constexpr int kTilePer = 8, kTile = kTilePer * kScatterBlock;
+
+// Full re-bin: the occupied slots and the records, chunk by chunk, into the
+// second store, which the last workgroup makes the store.  A container's
+// particles that stay in its chunk get consecutive places (one reservation
+// per container), and so do its arrivals.
+template <class T>
+__global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
+{
+    if (!a.flags[F_GO]) return;
+    __shared__ int32_t stay0, in0, pos, hist[kHistMax];
+    __shared__ bool last;
+    const int cur = a.flags[F_CUR], t = a.flags[F_TICK];
+    const int32_t ni = cur ? a.flags[F_NITEMS1] : a.flags[F_NITEMS];
+    const View<T> V = a.V.pick(cur), W = a.V.pick(cur ^ 1);
+    const Cont *const ct = cur ? a.cont1 : a.cont0;
+    const int m = (t + 2) % 3;
+    const MoverRec<T> *const rec = a.rec + ((t + 1) & 1) * a.nrec;
+    for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) {
+        const ContState me = state_of(ct + it, m);
+        const int32_t c = me.c, cnt = me.cnt, stays = cnt - me.h;
+        const int32_t nin = a.npend ? 0 : min(me.in, inbox_cap(me.room, a.whole));
+        if (cnt == 0 && nin == 0) continue;   // uniform
+        const int4 l = a.lay[c];
+        if (threadIdx.x == 0) {
+            stay0 = stays > 0 ? atomicAdd(&a.cursor[c], stays) : 0;
+            in0 = nin > 0 ? atomicAdd(&a.cursor[c], nin) : 0;
+            pos = 0;
         }
-        V.ox[slot] = cur.ox;
-        V.oy[slot] = cur.oy;
-        V.oz[slot] = cur.oz;
-        V.vx[slot] = cur.vx;
-        V.vy[slot] = cur.vy;
-        V.vz[slot] = cur.vz;
-        V.d[slot] = cur.d;
-        V.id[slot] = cur.id;
-    }
-}
-
-// Records the full re-bin places: the staged injections, or the movers the
-// step recorded (all of them unless the mover list overflowed; those it
-// could not record stayed in place).
-template <class T>
-__device__ __forceinline__ int64_t records(const RebinArgs<T> &a)
-{
-    const int64_t nm = a.flags[nmov_slot(a.epoch)];
-    return a.npend + (nm < a.mcap ? nm : a.mcap);
-}
-
-// Full re-bin, first pass: particles per destination chunk, from the
-// occupied slots (holes skipped) and the records.
-template <class T>
-__device__ void rekey_count(const RebinArgs<T> &a)
-{
-    const View<T> &V = a.V;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.room_denom = 0;
-    const int64_t ni = *a.nitems;
-    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const int64_t c = a.items[2 * it], seg = a.items[2 * it + 1];
-        const int64_t s0 = V.base[c] + seg * kSeg;
-        const int64_t s1 = min(s0 + (int64_t)kSeg, V.base[c] + (int64_t)V.cnt[c]);
-        for (int64_t q = s0 + threadIdx.x; q < s1; q += blockDim.x) {
-            T x = V.ox[q], y = V.oy[q], z = V.oz[q];
-            const bool live = occupied(x, V.d[q]);
-            const int64_t cn = live ? chunk_of_stored(a.p, c, x, y, z) : -1;
-            // one atomic per wave for the lanes that stay in chunk c
-            const uint64_t stay = __ballot(cn == c);
-            if (cn == c) {
-                if (__lane_id() == __ffsll((unsigned long long)stay) - 1)
-                    atomicAdd(&a.new_cnt[c], __popcll(stay));
-            } else if (live) {
-                atomicAdd(&a.new_cnt[cn], 1);
+        __syncthreads();
+        const int64_t s0 = me.base;
+        for (int32_t o = 0; o < cnt; o += kScatterBlock) {   // every lane the same rounds
+            const int32_t o1 = o + threadIdx.x;
+            const int64_t q = s0 + o1;
+            MoverRec<T> r;
+            int64_t cn = -1;
+            bool home = false;
+            if (o1 < cnt) {
+                r = MoverRec<T>{V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q],
+                                V.id[q]};
+                if (occupied(r.ox, r.d)) {
+                    // (a particle can leave its chunk and still be in it: one
+                    // chunk along a periodic axis)
+                    const T fe = T(a.p.E);
+                    home = a.p.global || (r.ox >= T(0) && r.ox < fe && r.oy >= T(0) &&
+                                          r.oy < fe && r.oz >= T(0) && r.oz < fe);
+                    cn = chunk_of_stored(a.p, c, r.ox, r.oy, r.oz);
+                    home = home && cn == c;
+                }
             }
+            const uint64_t stay = __ballot(home);
+            int32_t b = 0;
+            if (__lane_id() == 0) b = stay ? atomicAdd(&pos, __popcll(stay)) : 0;
+            b = __shfl(b, 0);
+            if (home)
+                put_slot(W, slot_of_rank(l, stay0 + b + __popcll(stay & lanes_below_mask())), r);
+            else if (cn >= 0)   // a mover whose inbox was full
+                put_slot(W, slot_of_rank(a.lay[cn], atomicAdd(&a.cursor[cn], 1)), r);
+        }
+        for (int32_t r = threadIdx.x; r < nin; r += kScatterBlock)
+            put_slot(W, slot_of_rank(l, in0 + r), rec[me.ibase + r]);
+        __syncthreads();
+    }
+    for (int64_t r0 = (int64_t)blockIdx.x * kTile; r0 < a.npend;
+         r0 += (int64_t)gridDim.x * kTile) {
+        int32_t cn[kTilePer], rank[kTilePer];
+        if (a.C <= kHistMax) {
+            __syncthreads();
+            for (int32_t i = threadIdx.x; i < a.C; i += kScatterBlock) hist[i] = 0;
+            __syncthreads();
+        }
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j) {
+            const int64_t r = r0 + j * kScatterBlock + threadIdx.x;
+            cn[j] = r < a.npend ? a.dest[r] : -1;
+            rank[j] = cn[j] < 0 ? 0
+                                : atomicAdd(a.C <= kHistMax ? &hist[cn[j]] : &a.cursor[cn[j]], 1);
+        }
+        if (a.C <= kHistMax) {
+            __syncthreads();
+            for (int32_t i = threadIdx.x; i < a.C; i += kScatterBlock)
+                if (hist[i]) hist[i] = atomicAdd(&a.cursor[i], hist[i]);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j) {
+            if (cn[j] < 0) continue;
+            if (a.C <= kHistMax) rank[j] += hist[cn[j]];
+            put_slot(W, slot_of_rank(a.lay[cn[j]], rank[j]),
+                     a.rec[r0 + j * kScatterBlock + threadIdx.x]);
         }
     }
-    const int64_t nr = records(a);
-    for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < nr;
-         m += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&a.new_cnt[a.mv.dest[m]], 1);
-}
-
-template <class T>
-__global__ void __launch_bounds__(kArriveBlock) k_arrive_or_count(RebinArgs<T> a)
-{
-    if (full_rebin(a.flags, a.epoch)) rekey_count(a);
-    else arrive(a);
-}
-
-template <class T>
-__global__ void __launch_bounds__(256) k_counts(View<T> V, const int32_t *out_cnt,
-                                                const int32_t *in_cnt, int64_t C, int32_t *flags,
-                                                int32_t epoch)
-{
-    if (full_rebin(flags, epoch)) return;
-    int32_t dead = 0;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < C;
-         c += (int64_t)gridDim.x * blockDim.x)
-        dead += count_chunk(V, out_cnt, in_cnt, c);
-    int32_t total;
-    block_excl_scan<int32_t>(dead, total);
-    if (threadIdx.x == 0 && total) atomicAdd(&flags[F_DEAD], total);
-}
-
-// Full re-bin, second pass: scatter into the second store.
-template <class T>
-__global__ void __launch_bounds__(256) k_rekey_scatter(RebinArgs<T> a)
-{
-    if (!full_rebin(a.flags, a.epoch)) return;
-    const View<T> &V = a.V;
-    const View<T> &W = a.W;
-    const int64_t ni = *a.nitems;
-    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const int64_t c = a.items[2 * it], seg = a.items[2 * it + 1];
-        const int64_t s0 = V.base[c] + seg * kSeg;
-        const int64_t s1 = min(s0 + (int64_t)kSeg, V.base[c] + (int64_t)V.cnt[c]);
-        for (int64_t q = s0 + threadIdx.x; q < s1; q += blockDim.x) {
-            T x = V.ox[q], y = V.oy[q], z = V.oz[q];
-            const T dd = V.d[q];
-            const bool live = occupied(x, dd);      // holes are dropped
-            const int64_t cn = live ? chunk_of_stored(a.p, c, x, y, z) : -1;
-            int64_t dst = -1;
-            const uint64_t stay = __ballot(cn == c);
-            if (cn == c) {
-                const int leader = __ffsll((unsigned long long)stay) - 1;
-                int32_t b = 0;
-                if (__lane_id() == leader) b = atomicAdd(&a.cursor[c], __popcll(stay));
-                b = __shfl(b, leader, 64);
-                dst = a.nbase[c] + b + __popcll(stay & lanes_below_mask());
-            } else if (live) {
-                dst = a.nbase[cn] + atomicAdd(&a.cursor[cn], 1);
-            }
-            if (!live) continue;
-            W.ox[dst] = x;
-            W.oy[dst] = y;
-            W.oz[dst] = z;
-            W.vx[dst] = V.vx[q];
-            W.vy[dst] = V.vy[q];
-            W.vz[dst] = V.vz[q];
-            W.d[dst] = dd;
-            W.id[dst] = V.id[q];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(&a.flags[F_TICKET], 1) == (int32_t)gridDim.x - 1;
+        if (last) {   // every workgroup has passed the gate and read the flags
+            a.flags[F_CUR] = cur ^ 1;
+            a.flags[F_GO] = 0;
+            a.flags[F_REPACKS] += 1;
         }
     }
-    const int64_t nr = records(a);
-    for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < nr;
-         m += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t cn = a.mv.dest[m];
-        const int64_t dst = a.nbase[cn] + atomicAdd(&a.cursor[cn], 1);
-        place_mover(W, dst, a.mv, m);
+}
+
+// Places the last step's arrivals, as the next step's kernel would (for
+// calls that need the store whole): into the holes, then past the last slot.
+template <class T>
+__global__ void __launch_bounds__(256) k_settle(Views<T> VV, Cont *cont0, Cont *cont1,
+                                                const MoverRec<T> *recs, int64_t nrec,
+                                                int32_t *flags, int32_t *spread)
+{
+    __shared__ int32_t apop;
+    const int cur = flags[F_CUR], t = flags[F_TICK];
+    const int32_t ni = cur ? flags[F_NITEMS1] : flags[F_NITEMS];
+    const View<T> V = VV.pick(cur);
+    Cont *const ct = cur ? cont1 : cont0;
+    const int m = (t + 2) % 3;
+    const MoverRec<T> *const rec = recs + ((t + 1) & 1) * nrec;
+    for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) {
+        const ContState me = state_of(ct + it, m);
+        const int32_t n_in = me.in;
+        if (n_in == 0) continue;   // uniform
+        const int32_t nq_old = me.cnt, h = me.h;
+        const int32_t nq = nq_old + max(0, n_in - h);
+        __syncthreads();
+        if (threadIdx.x == 0) apop = 0;
+        __syncthreads();
+        for (int32_t o = threadIdx.x; o < nq; o += 256) {
+            const int64_t q = (int64_t)me.base + o;
+            if (o < nq_old && occupied(V.ox[q], V.d[q])) continue;
+            const int32_t r = atomicAdd(&apop, 1);
+            if (r < n_in) put_slot(V, q, rec[me.ibase + r]);
+        }
+        if (threadIdx.x == 0) {
+            ct[it].in[m] = 0;
+            ct[it].s[m] = {nq, max(0, h - n_in)};
+            atomicAdd(&spread[16 * (it % kSpread)], max(0, h - n_in) - h);
+        }
     }
 }
 
-// Full re-bin, last pass: the second store and the new layout become the store.
-template <class T>
-__global__ void k_rekey_commit(RebinArgs<T> a, ItemArgs ia, int items_here)
+// non-empty containers and holes (as they are once the arrivals are placed)
+// (without the inboxes when these count staged injections)
+__global__ void __launch_bounds__(256) k_stats(const Cont *cont0, const Cont *cont1,
+                                               int32_t *flags, int arrivals)
 {
-    if (!full_rebin(a.flags, a.epoch)) return;
-    const View<T> &V = a.V;
-    const View<T> &W = a.W;
-    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t gs = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t q = g0; q < a.slots; q += gs) {
-        V.ox[q] = W.ox[q];
-        V.oy[q] = W.oy[q];
-        V.oz[q] = W.oz[q];
-        V.vx[q] = W.vx[q];
-        V.vy[q] = W.vy[q];
-        V.vz[q] = W.vz[q];
-        V.d[q] = W.d[q];
-        V.id[q] = W.id[q];
+    const int cur = flags[F_CUR], t = flags[F_TICK];
+    const int32_t ni = cur ? flags[F_NITEMS1] : flags[F_NITEMS];
+    const Cont *const ct = cur ? cont1 : cont0;
+    const int m = (t + 2) % 3;
+    int32_t items = 0, holes = 0;
+    for (int32_t j = blockIdx.x * 256 + threadIdx.x; j < ni; j += gridDim.x * 256) {
+        const int32_t in = arrivals ? ct[j].in[m] : 0;
+        items += ct[j].s[m].cnt - ct[j].s[m].h + in > 0;
+        holes += max(0, ct[j].s[m].h - in);
     }
-    for (int64_t c = g0; c < a.C; c += gs) {
-        V.cnt[c] = a.new_cnt[c];
-        V.ndead[c] = 0;
-        V.base[c] = a.nbase[c];
-        V.room[c] = a.nroom[c];
-        a.new_cnt[c] = 0;   // ready for the next full re-bin
-        a.cursor[c] = 0;
-        if (items_here) write_items(ia, c);
+    for (int o = 32; o > 0; o >>= 1) {
+        items += __shfl_xor(items, o);
+        holes += __shfl_xor(holes, o);
     }
-    if (g0 == 0) {
-        a.flags[F_DEAD] = 0;
-        if (items_here) finish_flags(ia);
-        a.flags[F_REPACKS] += 1;
+    if (__lane_id() == 0) {
+        atomicAdd(&flags[F_STAT_ITEMS], items);
+        atomicAdd(&flags[F_STAT_HOLES], holes);
     }
+}
+
+// the runs of a settled store's containers
+__global__ void __launch_bounds__(256) k_runs(const Cont *cont0, const Cont *cont1,
+                                              const int32_t *flags, RunItem *items,
+                                              int32_t *nitems)
+{
+    const int cur = flags[F_CUR], t = flags[F_TICK];
+    const int32_t ni = cur ? flags[F_NITEMS1] : flags[F_NITEMS];
+    const Cont *const ct = cur ? cont1 : cont0;
+    const int m = (t + 2) % 3;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nitems = ni;
+    for (int32_t j = blockIdx.x * 256 + threadIdx.x; j < ni; j += gridDim.x * 256)
+        items[j] = RunItem{ct[j].c, ct[j].base, ct[j].s[m].cnt, ct[j].k};
 }
 
 // ---------------------------------------------------------------------------
@@ -1453,7 +1242,8 @@ __global__ void k_rekey_commit(RebinArgs<T> a, ItemArgs ia, int items_here)
 // ---------------------------------------------------------------------------
 template <class T>
 __global__ void k_stage(int64_t n, const double *x, const double *up, const double *d,
-                        int64_t at, int64_t id0, Params p, Movers<T> mv, int32_t *flags)
+                        int64_t at, int64_t id0, Params p, MoverRec<T> *rec, int32_t *dest,
+                        int32_t *flags)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -1489,10 +1279,49 @@ __global__ void k_stage(int64_t n, const double *x, const double *up, const doub
             if (!isfinite(v[a])) ok = false;
         if (!isfinite(dd) || !(dd > 0.0)) ok = false;
         const int64_t m = at + i;
-        mv.rec[m] = MoverRec<T>{loc[0], loc[1], loc[2], (T)v[0], (T)v[1], (T)v[2], (T)dd,
+        rec[m] = MoverRec<T>{loc[0], loc[1], loc[2], (T)v[0], (T)v[1], (T)v[2], (T)dd,
                                 (int32_t)(id0 + i)};
-        mv.dest[m] = (int32_t)chunk_index(p, ch[0], ch[1], ch[2]);
+        dest[m] = (int32_t)chunk_index(p, ch[0], ch[1], ch[2]);
         if (!ok) flags[F_BADINPUT] = 1;
+    }
+}
+
+// (after a rejected injection)
+__global__ void k_clear_staged(Cont *cont0, Cont *cont1, const int32_t *flags)
+{
+    const int cur = flags[F_CUR], m = (flags[F_TICK] + 2) % 3;
+    const int32_t ni = cur ? flags[F_NITEMS1] : flags[F_NITEMS];
+    Cont *const ct = cur ? cont1 : cont0;
+    for (int32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < ni; j += gridDim.x * blockDim.x)
+        ct[j].in[m] = 0;
+}
+
+// Adds the staged injections to the inbox counts of their chunks' first
+// containers (a full re-bin's layout counts a chunk's particles from these).
+__global__ void __launch_bounds__(kScatterBlock) k_count_staged(Cont *cont0, Cont *cont1,
+                                                                const int32_t *first0,
+                                                                const int32_t *first1,
+                                                                const int32_t *flags,
+                                                                const int32_t *dest, int64_t n,
+                                                                int64_t C)
+{
+    __shared__ int32_t hist[kHistMax];
+    const int cur = flags[F_CUR], t = flags[F_TICK];
+    Cont *const ct = cur ? cont1 : cont0;
+    const int32_t *const first = cur ? first1 : first0;
+    const int m = (t + 2) % 3;
+    const bool lds = C <= kHistMax;
+    if (lds) {
+        for (int32_t i = threadIdx.x; i < C; i += kScatterBlock) hist[i] = 0;
+        __syncthreads();
+    }
+    for (int64_t i = (int64_t)blockIdx.x * kScatterBlock + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kScatterBlock)
+        atomicAdd(lds ? &hist[dest[i]] : &ct[first[dest[i]]].in[m], 1);
+    if (lds) {
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < C; i += kScatterBlock)
+            if (hist[i]) atomicAdd(&ct[first[i]].in[m], hist[i]);
     }
 }
 
@@ -1529,27 +1358,38 @@ __device__ __forceinline__ void put_particle(const ParticleOut &out, const Param
     if (out.id) out.id[k] = k;
 }
 
+// Calls f(chunk, record) for every particle: the occupied slots of the
+// containers' runs and the arrivals waiting in their inboxes.
+template <class T, class F>
+__device__ __forceinline__ void each_particle(const Current<T> &S, const F &f)
+{
+    const View<T> &V = S.V;
+    for (int32_t it = blockIdx.x; it < S.ni; it += gridDim.x) {
+        const ContState me = state_of(S.cont + it, S.m);
+        for (int32_t o = threadIdx.x; o < me.cnt; o += blockDim.x) {
+            const int64_t q = (int64_t)me.base + o;
+            const MoverRec<T> r{V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q],
+                                V.id[q]};
+            if (occupied(r.ox, r.d)) f(me.c, r);
+        }
+        for (int32_t j = threadIdx.x; j < me.in; j += blockDim.x)
+            f(me.c, S.rec[me.ibase + j]);
+    }
+}
+
 // Read-out straight from the store: a particle's row of each output lies
 // wherever its id does, so each is a partial-line write.
 template <class T>
-__global__ void __launch_bounds__(256) k_get_particles(View<T> V, const int32_t *items,
-                                                       const int32_t *nitems, Params p,
-                                                       int64_t count, ParticleOut out)
+__global__ void __launch_bounds__(256) k_get_particles(Store<T> st, Params p, int64_t count,
+                                                       ParticleOut out)
 {
-    const int64_t ni = *nitems;
-    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const int64_t c = items[2 * it], seg = items[2 * it + 1];
-        const int64_t s0 = V.base[c] + seg * kSeg;
-        const int64_t s1 = min(s0 + (int64_t)kSeg, V.base[c] + (int64_t)V.cnt[c]);
-        for (int64_t q = s0 + threadIdx.x; q < s1; q += blockDim.x) {
-            if (!occupied(V.ox[q], V.d[q])) continue;   // a hole
-            const int64_t k = V.id[q];
-            if (k < 0 || k >= count) continue;  // never in a consistent store
-            const T o[3] = {V.ox[q], V.oy[q], V.oz[q]};
-            const T v[3] = {V.vx[q], V.vy[q], V.vz[q]};
-            put_particle<T>(out, p, k, c, o, v, V.d[q]);
-        }
-    }
+    const Current<T> S(st);
+    each_particle(S, [&](int32_t c, const MoverRec<T> &r) {
+        if (r.id < 0 || r.id >= count) return;   // never in a consistent store
+        const T o[3] = {r.ox, r.oy, r.oz};
+        const T v[3] = {r.vx, r.vy, r.vz};
+        put_particle<T>(out, p, r.id, c, o, v, r.d);
+    });
 }
 
 // Read-out of many particles in two passes: one scattered write per particle
@@ -1561,11 +1401,16 @@ __global__ void __launch_bounds__(256) k_get_particles(View<T> V, const int32_t 
 // 0.38 ms the scattered records, 0.22 ms out), against 2.06 ms directly.
 template <class T>
 struct RecordArrays {
-    T *a[7];
+    View<T> W;
     int64_t per;   // records per array
 
+    __device__ __forceinline__ RecordArrays(const Store<T> &s, int64_t slots)
+        : W(s.V.pick(s.flags[F_CUR] ^ 1)), per(slots / 8)
+    {
+    }
     __device__ __forceinline__ MoverRec<T> *at(int64_t k) const
     {
+        T *const a[7] = {W.ox, W.oy, W.oz, W.vx, W.vy, W.vz, W.d};
         T *b = a[0];
         int64_t j = k;
 #pragma unroll
@@ -1579,41 +1424,36 @@ struct RecordArrays {
 };
 
 template <class T>
-__global__ void __launch_bounds__(256) k_records_clear(RecordArrays<T> r, int64_t count)
+__global__ void __launch_bounds__(256) k_records_clear(Store<T> st, int64_t slots, int64_t count)
 {
+    const RecordArrays<T> r(st, slots);
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < count) *r.at(k) = MoverRec<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), -1};
 }
 
 template <class T>
-__global__ void __launch_bounds__(256) k_records_by_id(View<T> V, const int32_t *items,
-                                                       const int32_t *nitems, int64_t count,
-                                                       RecordArrays<T> r)
+__global__ void __launch_bounds__(256) k_records_by_id(Store<T> st, int64_t slots, int64_t count)
 {
-    const int64_t ni = *nitems;
-    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const int64_t c = items[2 * it], seg = items[2 * it + 1];
-        const int64_t s0 = V.base[c] + seg * kSeg;
-        const int64_t s1 = min(s0 + (int64_t)kSeg, V.base[c] + (int64_t)V.cnt[c]);
-        for (int64_t q = s0 + threadIdx.x; q < s1; q += blockDim.x) {
-            const MoverRec<T> m{V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q],
-                                (int32_t)c};
-            const int64_t k = V.id[q];
-            if (!occupied(m.ox, m.d) || k < 0 || k >= count) continue;
-            *r.at(k) = m;
-        }
-    }
+    const RecordArrays<T> to(st, slots);
+    const Current<T> S(st);
+    each_particle(S, [&](int32_t c, MoverRec<T> r) {
+        const int64_t k = r.id;
+        if (k < 0 || k >= count) return;
+        r.id = c;
+        *to.at(k) = r;
+    });
 }
 
 // A workgroup's 256 rows of the [count][3] outputs pass through LDS, so that
 // the lanes' stores are consecutive.
 template <class T>
-__global__ void __launch_bounds__(256) k_records_out(RecordArrays<T> r, Params p, int64_t count,
-                                                     ParticleOut out)
+__global__ void __launch_bounds__(256) k_records_out(Store<T> st, int64_t slots, Params p,
+                                                     int64_t count, ParticleOut out)
 {
     __shared__ double sx[768], su[768];
     __shared__ int32_t sc[768];
     __shared__ int there[256];
+    const RecordArrays<T> r(st, slots);
     const int64_t k0 = (int64_t)blockIdx.x * 256;
     const int64_t k = k0 + threadIdx.x;
     MoverRec<T> m;
@@ -1723,55 +1563,66 @@ __global__ void k_rotate(const T *u0, T *u, int64_t ncell, double cs, double sn)
     }
 }
 
-// checkpoint copy of the store (all slots), its hole lists and its layout
+// checkpoint copy of the (settled) store, all slots, and its containers; or
+// back (into the current store, whichever of the two it is by then)
 template <class T>
-__global__ void k_snapshot(View<T> V, int32_t *hole, int64_t slots, int64_t C, char *buf,
-                           SnapLayout L, int32_t *items, const int32_t *nitems, int64_t max_items,
-                           int restore)
+__global__ void k_snapshot(Views<T> VV, Cont *cont0, Cont *cont1, int32_t *first0,
+                           int32_t *first1, int64_t slots, int64_t C, char *buf, SnapLayout L,
+                           int32_t *flags, int32_t *spread, int restore)
 {
+    const int cur = flags[F_CUR], t = flags[F_TICK];
+    const View<T> V = VV.pick(cur);
+    Cont *const ct = cur ? cont1 : cont0;
+    int32_t *const first = cur ? first1 : first0;
+    const int m = (t + 2) % 3;
     T *arr[7] = {V.ox, V.oy, V.oz, V.vx, V.vy, V.vz, V.d};
     T *sT = reinterpret_cast<T *>(buf + L.state);
     int32_t *sid = reinterpret_cast<int32_t *>(buf + L.id);
-    int32_t *shole = reinterpret_cast<int32_t *>(buf + L.hole);
-    int64_t *sbase = reinterpret_cast<int64_t *>(buf + L.base);
-    int32_t *sroom = reinterpret_cast<int32_t *>(buf + L.room);
-    int32_t *scnt = reinterpret_cast<int32_t *>(buf + L.cnt);
-    int32_t *sndead = reinterpret_cast<int32_t *>(buf + L.ndead);
-    int32_t *sitems = reinterpret_cast<int32_t *>(buf + L.items);
+    RunItem *sitems = reinterpret_cast<RunItem *>(buf + L.items);
     int32_t *snitems = reinterpret_cast<int32_t *>(buf + L.nitems);
+    Cont *scont = reinterpret_cast<Cont *>(buf + L.cont);
+    int32_t *sfirst = reinterpret_cast<int32_t *>(buf + L.first);
+    int32_t *const nitems = flags + (cur ? F_NITEMS1 : F_NITEMS);
     const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (!restore) {  // the work items of this layout travel with it
-        const int64_t ni = *nitems;
-        for (int64_t k = g0; k < 2 * ni; k += (int64_t)gridDim.x * blockDim.x)
-            sitems[k] = items[k];
-        if (g0 == 0) *snitems = (int32_t)ni;
-    }
-    (void)max_items;
     const int64_t gs = (int64_t)gridDim.x * blockDim.x;
+    const int32_t ni = restore ? *snitems : *nitems;
     for (int64_t q = g0; q < slots; q += gs) {
         if (restore) {
             for (int a = 0; a < 7; ++a) arr[a][q] = sT[a * slots + q];
             V.id[q] = sid[q];
-            hole[q] = shole[q];
         } else {
             for (int a = 0; a < 7; ++a) sT[a * slots + q] = arr[a][q];
             sid[q] = V.id[q];
-            shole[q] = hole[q];
         }
     }
-    for (int64_t c = g0; c < C; c += gs) {
+    for (int64_t j = g0; j < ni; j += gs) {
+        const ContState me = state_of((restore ? scont : ct) + j, restore ? 0 : m);
+        const int32_t cnt = me.cnt, h = me.h;
+        const int at = restore ? m : 0;    // a saved container's state is its first
+        Cont d = {};
+        d.c = me.c;
+        d.base = me.base;
+        d.room = me.room;
+        d.ibase = me.ibase;
+        d.k = me.k;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            d.s[u].cnt = u == at ? cnt : 0;
+            d.s[u].h = u == at ? h : 0;
+        }
         if (restore) {
-            V.base[c] = sbase[c];
-            V.room[c] = sroom[c];
-            V.cnt[c] = scnt[c];
-            V.ndead[c] = sndead[c];
+            ct[j] = d;
+            if (h) atomicAdd(&spread[16 * (j % kSpread)], h);   // (cleared before)
         } else {
-            sbase[c] = V.base[c];
-            sroom[c] = V.room[c];
-            scnt[c] = V.cnt[c];
-            sndead[c] = V.ndead[c];
+            scont[j] = d;
+            sitems[j] = RunItem{d.c, d.base, cnt, d.k};
         }
     }
+    for (int64_t c = g0; c <= C; c += gs) {
+        if (restore) first[c] = sfirst[c];
+        else sfirst[c] = first[c];
+    }
+    if (g0 == 0) *(restore ? nitems : snitems) = ni;
 }
 
 // ---------------------------------------------------------------------------
@@ -1782,35 +1633,6 @@ inline int64_t grid_for(int64_t n, int64_t cap = 8192)
     int64_t g = (n + 255) / 256;
     if (g < 1) g = 1;
     return g > cap ? cap : g;
-}
-
-template <class T>
-View<T> view_of(st_ctx *c, int b)
-{
-    View<T> v;
-    v.ox = (T *)c->store[b][0];
-    v.oy = (T *)c->store[b][1];
-    v.oz = (T *)c->store[b][2];
-    v.vx = (T *)c->store[b][3];
-    v.vy = (T *)c->store[b][4];
-    v.vz = (T *)c->store[b][5];
-    v.d = (T *)c->store[b][6];
-    v.id = (int32_t *)c->store[b][7];
-    v.base = c->base;
-    v.room = c->room;
-    v.cnt = c->cnt;
-    v.ndead = c->ndead;
-    return v;
-}
-
-template <class T>
-Movers<T> movers_of(st_ctx *c)
-{
-    Movers<T> m;
-    m.rec = (MoverRec<T> *)c->mov[0];
-    m.dest = (int32_t *)c->mov[1];
-    m.rank = (int32_t *)c->mov[2];
-    return m;
 }
 
 // more holes than this force a full re-bin (a sixteenth of the particles)
@@ -1835,19 +1657,20 @@ hipError_t dispatch(st_ctx *c, F &&f)
 template <class T, class A, int E, int I, int D>
 hipError_t launch_step_t(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipEvent_t *ev)
 {
+    constexpr int NB = 256;
     const int64_t round = 8 * kXcdBlock;
     const int64_t grid = (c->max_items + round - 1) / round * round;
     if constexpr (sizeof(A) == 8) {   // only the forms that tape save
         if (a.sv[0]) {
-            hipLaunchKernelGGL((k_step<T, A, E, I, D, true>), dim3(grid), dim3(kBlock), 0, s, a);
+            hipLaunchKernelGGL((k_step<T, A, E, I, D, true, NB>), dim3(grid), dim3(NB), 0, s, a);
             return hipGetLastError();
         }
     }
     if (ev[0])
-        hipExtLaunchKernelGGL((k_step<T, A, E, I, D, false>), dim3(grid), dim3(kBlock), 0, s,
+        hipExtLaunchKernelGGL((k_step<T, A, E, I, D, false, NB>), dim3(grid), dim3(NB), 0, s,
                               ev[0], ev[1], 0, a);
     else
-        hipLaunchKernelGGL((k_step<T, A, E, I, D, false>), dim3(grid), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((k_step<T, A, E, I, D, false, NB>), dim3(grid), dim3(NB), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1865,75 +1688,26 @@ hipError_t launch_step_e(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
                               : launch_step_d<T, A, E, 0>(c, a, s, ev);
 }
 
-template <class T>
-RebinArgs<T> rebin_args(st_ctx *c, int64_t npend)
-{
-    RebinArgs<T> a;
-    a.V = view_of<T>(c, 0);
-    a.W = view_of<T>(c, 1);
-    a.mv = movers_of<T>(c);
-    a.C = c->C;
-    a.out_cnt = c->out_cnt;
-    a.in_cnt = c->in_cnt;
-    a.hole = c->hole;
-    a.items = c->items;
-    a.nitems = c->flags + F_NITEMS;
-    a.p = c->prm;
-    a.npend = npend;
-    a.mcap = c->mcap;
-    a.new_cnt = c->new_cnt;
-    a.cursor = c->cursor;
-    a.nbase = c->nbase;
-    a.nroom = c->nroom;
-    a.room_denom = c->room_denom;
-    a.slots = c->slots;
-    a.flags = c->flags;
-    a.epoch = c->epoch;
-    return a;
-}
-
-// everything after the step kernel: arrivals or full re-bin, then the items
+// everything after the step kernel (or, npend > 0, after staged injections):
+// the gate, and the full re-bin's scatter
 template <class T>
 hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 {
-    const RebinArgs<T> a = rebin_args<T>(c, npend);
-    const int64_t C = c->C;
     c->store_stream = s;
-    // a thread per mover for the arrivals (at most mcap of them); the count
-    // (rare) strides over the items
-    int64_t g = std::max<int64_t>((c->mcap + kArriveBlock - 1) / kArriveBlock, c->max_items);
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL((k_arrive_or_count<T>), dim3(g), dim3(kArriveBlock), 0, s, a);
     const int64_t total = c->count + npend;
-    const RoomWeight rw{c->new_cnt, {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]}};
-    const Rooms rooms{rw, c->slots - total - (int64_t)kAlign * C, 0, c->nroom};
-    // the full re-bin launches run every step and usually exit at their gate:
-    // grids of at most 2048 workgroups (strided loops) keep that cheap
-    const int64_t gs = c->max_items < 2048 ? c->max_items : 2048;
-    ItemArgs ia{C, c->nseg, c->items, c->out_cnt, c->in_cnt, c->new_cnt, c->cursor, c->flags,
-                c->epoch, dead_limit(c)};
-    if (C <= kScan1Max) {
-        // counts, rooms (when due) and the next items in one workgroup
-        hipLaunchKernelGGL((k_layout1<T>), dim3(1), dim3(1024), 0, s, rooms, c->nbase,
-                           Segments{c->new_cnt}, ia, a.V, c->flags);
-        hipLaunchKernelGGL((k_rekey_scatter<T>), dim3(gs), dim3(256), 0, s, a);
-        hipLaunchKernelGGL((k_rekey_commit<T>), dim3(grid_for(c->slots, 2048)), dim3(256), 0, s,
-                           a, ia, 1);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((k_counts<T>), dim3(grid_for(C)), dim3(256), 0, s, a.V, c->out_cnt,
-                       c->in_cnt, C, c->flags, c->epoch);
-    hipLaunchKernelGGL(k_room_denom, dim3((C + kScanBlock - 1) / kScanBlock), dim3(256), 0, s, rw,
-                       C, c->room_denom, c->flags, c->epoch);
-    hipError_t e = scan<int64_t>(RoomsDev{rooms, c->room_denom}, C, c->nbase, c->scan_tmp,
-                                 c->flags, G_FULL, c->epoch, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rekey_scatter<T>), dim3(gs), dim3(256), 0, s, a);
-    hipLaunchKernelGGL((k_rekey_commit<T>), dim3(grid_for(c->slots, 2048)), dim3(256), 0, s, a,
-                       ia, 0);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_items(c, s);
+    const GateArgs g{c->cont[0], c->cont[1], c->first[0], c->first[1], c->new_cnt, c->cursor,
+                     c->lay, c->flags, c->spread, c->C,
+                     {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]},
+                     c->slots - total - (int64_t)kAlign * c->max_items, c->whole_inbox,
+                     dead_limit(c), npend == 0};
+    hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
+    const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
+                           (const MoverRec<T> *)c->rec, c->nrec, c->stage_dest, npend, c->lay,
+                           c->cursor, c->flags, c->C, c->whole_inbox, c->prm};
+    const int64_t n = std::max(c->max_items, npend / kTile);
+    hipLaunchKernelGGL((k_scatter<T>), dim3(std::min<int64_t>(kScatterGroups, n)),
+                       dim3(kScatterBlock), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -1941,69 +1715,103 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_items(st_ctx *c, hipStream_t s)
+namespace {
+// no particles: a container without slots for every chunk
+__global__ void k_init(Cont *cont, int32_t *first, int32_t *flags, int64_t C)
 {
-    ItemArgs a{c->C, c->nseg, c->items, c->out_cnt, c->in_cnt, c->new_cnt, c->cursor, c->flags,
-               c->epoch, dead_limit(c)};
-    if (c->C <= kScan1Max) {
-        hipLaunchKernelGGL(k_items1, dim3(1), dim3(1024), 0, s, Segments{c->cnt}, a);
-        return hipGetLastError();
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c <= C;
+         c += (int64_t)gridDim.x * blockDim.x) {
+        first[c] = (int32_t)c;
+        if (c < C) {
+            Cont d = {};
+            d.c = (int32_t)c;
+            d.k = 1;
+            cont[c] = d;
+        }
+        if (c == 0) flags[F_NITEMS] = (int32_t)C;
     }
-    hipError_t e = scan_multi<int32_t>(Segments{c->cnt}, c->C, c->nseg, (int32_t *)c->scan_tmp,
-                                       c->flags, G_ALWAYS, c->epoch, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_items, dim3(grid_for(c->C)), dim3(256), 0, s, a);
-    return hipGetLastError();
 }
+}  // namespace
 
 hipError_t launch_init(st_ctx *c, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->cnt, c->C, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->room, c->C, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->ndead, c->C, 0);
-    hipLaunchKernelGGL(k_fill_i64, dim3(grid_for(c->C + 1)), dim3(256), 0, s, c->base, c->C + 1,
-                       (int64_t)0);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, s, c->flags, (int64_t)F_COUNT, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->new_cnt, c->C, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->cursor, c->C, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_items(c, s);
+    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(kSpreadInts)), dim3(256), 0, s, c->spread,
+                       (int64_t)kSpreadInts, 0);
+    hipLaunchKernelGGL(k_init, dim3(grid_for(c->C + 1)), dim3(256), 0, s, c->cont[0], c->first[0],
+                       c->flags, c->C);
+    return hipGetLastError();
+}
+
+hipError_t launch_settle(st_ctx *c, hipStream_t s)
+{
+    c->store_stream = s;
+    return dispatch(c, [&](auto t, auto) -> hipError_t {
+        using T = decltype(t);
+        hipLaunchKernelGGL((k_settle<T>), dim3(std::min<int64_t>(c->max_items, 4096)), dim3(256), 0,
+                           s, views_of<T>(c), c->cont[0], c->cont[1],
+                           (const MoverRec<T> *)c->rec, c->nrec, c->flags, c->spread);
+        return hipGetLastError();
+    });
+}
+
+namespace {
+hipError_t count_staged(st_ctx *c, int64_t at, int64_t n, hipStream_t s)
+{
+    if (n > 0) {
+        const int64_t g = std::min<int64_t>((n + kTile - 1) / kTile, 512);
+        hipLaunchKernelGGL(k_count_staged, dim3(g), dim3(kScatterBlock), 0, s, c->cont[0],
+                           c->cont[1], c->first[0], c->first[1], c->flags, c->stage_dest + at, n,
+                           c->C);
+    }
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_stats(st_ctx *c, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, c->flags + F_STAT_ITEMS, (int64_t)2, 0);
+    hipLaunchKernelGGL(k_stats, dim3(grid_for(c->max_items, 1024)), dim3(256), 0, s, c->cont[0],
+                       c->cont[1], c->flags, c->pending == 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_runs(st_ctx *c, RunItem *items, int32_t *nitems, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_runs, dim3(grid_for(c->max_items, 1024)), dim3(256), 0, s, c->cont[0],
+                       c->cont[1], c->flags, items, nitems);
+    return hipGetLastError();
 }
 
 hipError_t launch_step(st_ctx *c, const void *u, double dt, int deposit, hipStream_t s,
                        void *save)
 {
-    c->epoch += 1;
     return dispatch(c, [&](auto t, auto acc) -> hipError_t {
         using T = decltype(t);
         using A = decltype(acc);
         StepArgs<T, A> a;
-        a.V = view_of<T>(c, 0);
+        a.V = views_of<T>(c);
+        a.cont0 = c->cont[0];
+        a.cont1 = c->cont[1];
+        a.first0 = c->first[0];
+        a.first1 = c->first[1];
         for (int k = 0; k < 7; ++k) a.sv[k] = nullptr;
         if (save) {
             const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
             char *b = (char *)save;
             for (int k = 0; k < 7; ++k) a.sv[k] = (T *)(b + L.state) + k * c->slots;
             a.sid = (int32_t *)(b + L.id);
-            a.sitems = (int32_t *)(b + L.items);
+            a.sitems = (RunItem *)(b + L.items);
             a.snitems = (int32_t *)(b + L.nitems);
-            a.sbase = (int64_t *)(b + L.base);
-            a.scnt = (int32_t *)(b + L.cnt);
         }
-        a.items = c->items;
-        a.nitems = c->flags + F_NITEMS;
         a.u = (const T *)u;
         a.src = (A *)c->src;
-        a.mv = movers_of<T>(c);
-        a.nmov = c->flags + nmov_slot(c->epoch);
-        a.mcap = c->mcap;
-        a.out_cnt = c->out_cnt;
-        a.in_cnt = c->in_cnt;
-        a.hole = c->hole;
+        a.rec = (MoverRec<T> *)c->rec;
+        a.nrec = c->nrec;
         a.flags = c->flags;
+        a.spread = c->spread;
+        a.whole = c->whole_inbox;
         a.deposit = deposit;
-        a.epoch = c->epoch;
         a.p = c->prm;
         a.dt = (T)dt;
         for (int ax = 0; ax < 3; ++ax) {
@@ -2037,8 +1845,7 @@ hipError_t launch_step(st_ctx *c, const void *u, double dt, int deposit, hipStre
 
 hipError_t launch_flush_pending(st_ctx *c, hipStream_t s)
 {
-    c->epoch += 1;
-    hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(1), 0, s, c->flags, (int)F_FORCE, c->epoch);
+    hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(1), 0, s, c->flags, (int)F_FORCE, 1);
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         return launch_rebin<T>(c, c->pending, s);
@@ -2051,9 +1858,16 @@ hipError_t launch_stage_inject(st_ctx *c, int64_t n, const double *x, const doub
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         hipLaunchKernelGGL((k_stage<T>), dim3(grid_for(n)), dim3(256), 0, s, n, x, up, d, at,
-                           c->next_id, c->prm, movers_of<T>(c), c->flags);
-        return hipGetLastError();
+                           c->next_id, c->prm, (MoverRec<T> *)c->rec, c->stage_dest, c->flags);
+        return count_staged(c, at, n, s);
     });
+}
+
+hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_clear_staged, dim3(grid_for(c->max_items)), dim3(256), 0, s, c->cont[0],
+                       c->cont[1], c->flags);
+    return count_staged(c, 0, keep, s);
 }
 
 // The two-pass read-out from this many particles on (below it the outputs stay
@@ -2066,25 +1880,22 @@ hipError_t launch_get_particles(st_ctx *c, double *x, double *up, double *d, int
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         const int64_t gi = c->max_items < 65536 ? c->max_items : 65536;
-        const View<T> V = view_of<T>(c, 0);
-        const int32_t *ni = c->flags + F_NITEMS;
+        const Store<T> st = store_of<T>(c);
         const ParticleOut out{x, up, d, id, cell};
         // The second store is this stream's to use when this stream wrote the
         // store last: whoever writes the store or reads it from another
         // stream has ordered that stream against this one first.
         if (c->count < kRecordsMin || s != c->store_stream) {
-            hipLaunchKernelGGL((k_get_particles<T>), dim3(gi), dim3(256), 0, s, V, c->items, ni,
-                               c->prm, c->count, out);
+            hipLaunchKernelGGL((k_get_particles<T>), dim3(gi), dim3(256), 0, s, st, c->prm,
+                               c->count, out);
             return hipGetLastError();
         }
-        RecordArrays<T> r;
-        for (int k = 0; k < 7; ++k) r.a[k] = (T *)c->store[1][k];
-        r.per = c->slots / 8;
         const dim3 g((c->count + 255) / 256);
-        hipLaunchKernelGGL((k_records_clear<T>), g, dim3(256), 0, s, r, c->count);
-        hipLaunchKernelGGL((k_records_by_id<T>), dim3(gi), dim3(256), 0, s, V, c->items, ni,
-                           c->count, r);
-        hipLaunchKernelGGL((k_records_out<T>), g, dim3(256), 0, s, r, c->prm, c->count, out);
+        hipLaunchKernelGGL((k_records_clear<T>), g, dim3(256), 0, s, st, c->slots, c->count);
+        hipLaunchKernelGGL((k_records_by_id<T>), dim3(gi), dim3(256), 0, s, st, c->slots,
+                           c->count);
+        hipLaunchKernelGGL((k_records_out<T>), g, dim3(256), 0, s, st, c->slots, c->prm, c->count,
+                           out);
         return hipGetLastError();
     });
 }
@@ -2201,21 +2012,26 @@ size_t snapshot_bytes(const st_ctx *c)
     return snap_layout(c->slots, c->tsize, c->C, c->max_items).bytes;
 }
 
-// Saves the store, its layout and its work items into dst, or (restore)
-// puts a saved store and layout back and rebuilds the work items.
+// Saves the store (its arrivals placed first) and its containers into dst, or
+// (restore) puts a saved store back.
 hipError_t launch_snapshot(st_ctx *c, void *dst, int restore, hipStream_t s)
 {
     const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
-    hipError_t e = dispatch(c, [&](auto t, auto) -> hipError_t {
+    if (!restore) {
+        const hipError_t e = launch_settle(c, s);
+        if (e != hipSuccess) return e;
+    } else {
+        c->store_stream = s;
+        hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(kSpreadInts)), dim3(256), 0, s, c->spread,
+                           (int64_t)kSpreadInts, 0);
+    }
+    return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         hipLaunchKernelGGL((k_snapshot<T>), dim3(grid_for(c->slots, 16384)), dim3(256), 0, s,
-                           view_of<T>(c, 0), c->hole, c->slots, c->C, (char *)dst, L, c->items,
-                           c->flags + F_NITEMS, c->max_items, restore);
+                           views_of<T>(c), c->cont[0], c->cont[1], c->first[0], c->first[1],
+                           c->slots, c->C, (char *)dst, L, c->flags, c->spread, restore);
         return hipGetLastError();
     });
-    if (e != hipSuccess || !restore) return e;
-    c->store_stream = s;
-    return launch_items(c, s);
 }
 
 }  // namespace st

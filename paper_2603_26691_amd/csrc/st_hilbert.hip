@@ -160,23 +160,20 @@ __device__ __forceinline__ double wave_max(double v)
 
 template <class T>
 struct BoxArgs {
-    View<T> V;
-    const int32_t *items;
-    const int32_t *nitems;
+    Store<T> st;
     Params p;
     int64_t id0, per_part, nparts;
     unsigned long long *box;
 };
 
-// The partition (below nparts, else -1) and position of slot q of chunk
-// (cx, cy, cz) E cells.
+// The partition (below nparts, else -1) and position of a slot of chunk cc.
 template <class T>
 __device__ __forceinline__ int64_t box_particle(const BoxArgs<T> &a, int32_t id, T x, T y, T z,
                                                 T d, const int64_t (&cc)[3], double (&xg)[3])
 {
     const Params &p = a.p;
-    // a hole has a -1 offset (binary32) or a negated diameter (binary64)
-    if (!(x >= T(0) && d > T(0)) || id < a.id0) return -1;
+    // a hole has the mark for an offset (binary32) or a negated diameter (binary64)
+    if (!(x > T(kHoleMark) && d > T(0)) || id < a.id0) return -1;
     const int64_t rel = id - a.id0;    // below 2^31
     const int64_t part = a.per_part > 0x7fffffff ? 0 : (uint32_t)rel / (uint32_t)a.per_part;
     if (part >= a.nparts) return -1;
@@ -186,8 +183,15 @@ __device__ __forceinline__ int64_t box_particle(const BoxArgs<T> &a, int32_t id,
     return part;
 }
 
+// The tables lie in the re-bin's second store.
+template <class T>
+__device__ __forceinline__ unsigned long long *box_tables(const Store<T> &s)
+{
+    return reinterpret_cast<unsigned long long *>(s.V.pick(s.flags[F_CUR] ^ 1).ox);
+}
+
 // The boxes of up to kBoxTable partitions in LDS, workgroup by workgroup: a
-// workgroup takes every gridDim.x-th work item, four consecutive slots a
+// workgroup takes every gridDim.x-th container, four consecutive slots a
 // thread, and keeps its own table of the partitions [blockIdx.y Kp,
 // (blockIdx.y + 1) Kp).  A particle inside its partition's box as the table
 // has it adds nothing (of n particles about ln n per bound do), so the atomics
@@ -200,56 +204,65 @@ constexpr int kBoxPasses = 4;        // tables' worth of partitions (the store i
 constexpr int kBoxGroups = 256;      // workgroups per table: one a CU
 
 template <class T>
-__global__ void __launch_bounds__(1024) k_bbox_tables(BoxArgs<T> a, int32_t Kp,
-                                                      unsigned long long *tables)
+__global__ void __launch_bounds__(1024) k_bbox_tables(BoxArgs<T> a, int32_t Kp)
 {
     extern __shared__ unsigned long long tab[];   // [Kp][6]
     constexpr int G = 16 / sizeof(T);
     typedef T vec __attribute__((ext_vector_type(G)));
     typedef int32_t ivec __attribute__((ext_vector_type(G)));
-    static_assert(kAlign % G == 0, "chunk rooms must hold whole particle groups");
+    static_assert(kAlign % G == 0, "container rooms must hold whole particle groups");
     const Params &p = a.p;
+    const Current<T> S(a.st);
+    const View<T> &V = S.V;
     const int32_t first = blockIdx.y * Kp;
     for (int t = threadIdx.x; t < 6 * Kp; t += 1024) tab[t] = (t % 6) < 3 ? kPosInf : 0ull;
     __syncthreads();
-    const int64_t ni = *a.nitems;
-    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const int64_t c = a.items[2 * it], seg = a.items[2 * it + 1];
+    auto take = [&](int64_t part, const double (&xg)[3]) {
+        part -= first;
+        if (part < 0 || part >= Kp) return;
+        unsigned long long *b = tab + 6 * part;
+        for (int ax = 0; ax < 3; ++ax) {
+            const unsigned long long v = (unsigned long long)__double_as_longlong(xg[ax]);
+            if (v < b[ax]) atomicMin(b + ax, v);
+            if (v > b[3 + ax]) atomicMax(b + 3 + ax, v);
+        }
+    };
+    for (int32_t it = blockIdx.x; it < S.ni; it += gridDim.x) {
+        const ContState me = state_of(S.cont + it, S.m);
+        const int64_t c = me.c;
         const int64_t cc[3] = {c % p.nc[0], (c / p.nc[0]) % p.nc[1],
                                c / ((int64_t)p.nc[0] * p.nc[1])};
-        const int64_t s0 = a.V.base[c] + seg * kSeg;
-        const int64_t s1 = min(s0 + (int64_t)kSeg, a.V.base[c] + (int64_t)a.V.cnt[c]);
-        // a group that runs past s1 stays inside the chunk's room
+        const int64_t s0 = me.base, s1 = s0 + me.cnt;
+        // a group that runs past s1 stays inside the container's room
         for (int64_t q = s0 + G * (int64_t)threadIdx.x; q < s1; q += 1024 * G) {
-            const vec x = *(const vec *)(a.V.ox + q), y = *(const vec *)(a.V.oy + q),
-                      z = *(const vec *)(a.V.oz + q), d = *(const vec *)(a.V.d + q);
-            const ivec id = *(const ivec *)(a.V.id + q);
+            const vec x = *(const vec *)(V.ox + q), y = *(const vec *)(V.oy + q),
+                      z = *(const vec *)(V.oz + q), d = *(const vec *)(V.d + q);
+            const ivec id = *(const ivec *)(V.id + q);
 #pragma unroll
             for (int k = 0; k < G; ++k) {
                 double xg[3];
-                int64_t part = -1;
-                if (q + k < s1) part = box_particle<T>(a, id[k], x[k], y[k], z[k], d[k], cc, xg);
-                part -= first;
-                if (part < 0 || part >= Kp) continue;
-                unsigned long long *b = tab + 6 * part;
-                for (int ax = 0; ax < 3; ++ax) {
-                    const unsigned long long v = (unsigned long long)__double_as_longlong(xg[ax]);
-                    if (v < b[ax]) atomicMin(b + ax, v);
-                    if (v > b[3 + ax]) atomicMax(b + 3 + ax, v);
-                }
+                if (q + k < s1)
+                    take(box_particle<T>(a, id[k], x[k], y[k], z[k], d[k], cc, xg), xg);
             }
+        }
+        for (int32_t j = threadIdx.x; j < me.in; j += 1024) {
+            const MoverRec<T> r = S.rec[me.ibase + j];
+            double xg[3];
+            take(box_particle<T>(a, r.id, r.ox, r.oy, r.oz, r.d, cc, xg), xg);
         }
     }
     __syncthreads();
-    unsigned long long *out = tables + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 6 * Kp;
+    unsigned long long *out = box_tables(a.st) +
+                              ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 6 * Kp;
     for (int t = threadIdx.x; t < 6 * Kp; t += 1024) out[t] = tab[t];
 }
 
 // the tables of `groups` workgroups into the boxes
-__global__ void __launch_bounds__(256) k_bbox_reduce(const unsigned long long *tables,
-                                                     int32_t groups, int32_t Kp, int64_t nparts,
+template <class T>
+__global__ void __launch_bounds__(256) k_bbox_reduce(Store<T> st, int32_t groups, int32_t Kp, int64_t nparts,
                                                      unsigned long long *box)
 {
+    const unsigned long long *const tables = box_tables(st);
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= 6 * nparts) return;
     const int64_t part = t / 6, b = t - 6 * part;
@@ -276,29 +289,34 @@ __global__ void __launch_bounds__(256) k_bbox_reduce(const unsigned long long *t
     box[t] = b < 3 ? lo : hi;
 }
 
-// One workgroup per work item, updating the boxes in memory.  When every
+// One workgroup per container, updating the boxes in memory.  When every
 // particle of a wave that belongs to a partition belongs to the same one (the
 // usual case while partitions are compact), the wave reduces first and one
 // lane updates the box.
 template <class T>
 __global__ void __launch_bounds__(256) k_bbox(BoxArgs<T> a)
 {
-    const int64_t ni = *a.nitems;
     const Params &p = a.p;
-    for (int64_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const int64_t c = a.items[2 * it], seg = a.items[2 * it + 1];
+    const Current<T> S(a.st);
+    const View<T> &V = S.V;
+    for (int32_t it = blockIdx.x; it < S.ni; it += gridDim.x) {
+        const ContState me = state_of(S.cont + it, S.m);
+        const int64_t c = me.c;
         const int64_t cc[3] = {c % p.nc[0], (c / p.nc[0]) % p.nc[1],
                                c / ((int64_t)p.nc[0] * p.nc[1])};
-        const int64_t s0 = a.V.base[c] + seg * kSeg;
-        const int64_t s1 = min(s0 + (int64_t)kSeg, a.V.base[c] + (int64_t)a.V.cnt[c]);
+        const int32_t cnt = me.cnt, all = cnt + me.in;   // the arrivals last
         // every lane of the workgroup runs the same number of rounds
-        for (int64_t q0 = s0; q0 < s1; q0 += blockDim.x) {
-            const int64_t q = q0 + threadIdx.x;
+        for (int32_t o0 = 0; o0 < all; o0 += blockDim.x) {
+            const int32_t o = o0 + threadIdx.x;
             int64_t part = -1;
             double xg[3] = {0.0, 0.0, 0.0};
-            if (q < s1)
-                part = box_particle<T>(a, a.V.id[q], a.V.ox[q], a.V.oy[q], a.V.oz[q], a.V.d[q],
-                                       cc, xg);
+            if (o < cnt) {
+                const int64_t q = (int64_t)me.base + o;
+                part = box_particle<T>(a, V.id[q], V.ox[q], V.oy[q], V.oz[q], V.d[q], cc, xg);
+            } else if (o < all) {
+                const MoverRec<T> r = S.rec[me.ibase + (o - cnt)];
+                part = box_particle<T>(a, r.id, r.ox, r.oy, r.oz, r.d, cc, xg);
+            }
             const uint64_t has = __ballot(part >= 0);
             if (has == 0) continue;
             const int lead = __ffsll((unsigned long long)has) - 1;
@@ -324,25 +342,6 @@ __global__ void __launch_bounds__(256) k_bbox(BoxArgs<T> a)
             }
         }
     }
-}
-
-template <class T>
-View<T> store_view(st_ctx *c)
-{
-    View<T> v;
-    v.ox = (T *)c->store[0][0];
-    v.oy = (T *)c->store[0][1];
-    v.oz = (T *)c->store[0][2];
-    v.vx = (T *)c->store[0][3];
-    v.vy = (T *)c->store[0][4];
-    v.vz = (T *)c->store[0][5];
-    v.d = (T *)c->store[0][6];
-    v.id = (int32_t *)c->store[0][7];
-    v.base = c->base;
-    v.room = c->room;
-    v.cnt = c->cnt;
-    v.ndead = c->ndead;
-    return v;
 }
 
 inline int64_t blocks_for(int64_t n, int64_t cap = 8192)
@@ -395,18 +394,16 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
                         groups >= std::min<int64_t>(32, c->max_items);
     auto run = [&](auto t) -> hipError_t {
         using T = decltype(t);
-        BoxArgs<T> a{store_view<T>(c), c->items, c->flags + F_NITEMS, c->prm, id0, per_part,
-                     nparts, b};
+        BoxArgs<T> a{store_of<T>(c), c->prm, id0, per_part, nparts, b};
         if (tables) {
-            unsigned long long *w = (unsigned long long *)c->store[1][0];
             hipError_t e = hipFuncSetAttribute((const void *)k_bbox_tables<T>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                kBoxTable * 48);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL((k_bbox_tables<T>), dim3(groups, passes), dim3(1024),
-                               (size_t)Kp * 48, s, a, (int32_t)Kp, w);
-            hipLaunchKernelGGL(k_bbox_reduce, dim3((6 * nparts + 255) / 256), dim3(256), 0, s, w,
-                               (int32_t)groups, (int32_t)Kp, nparts, b);
+                               (size_t)Kp * 48, s, a, (int32_t)Kp);
+            hipLaunchKernelGGL((k_bbox_reduce<T>), dim3((6 * nparts + 255) / 256), dim3(256), 0, s,
+                               a.st,                               (int32_t)groups, (int32_t)Kp, nparts, b);
             return hipGetLastError();
         }
         hipLaunchKernelGGL(k_bbox_init, dim3(blocks_for(6 * nparts)), dim3(256), 0, s, b, nparts);

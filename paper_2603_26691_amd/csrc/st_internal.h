@@ -1,18 +1,23 @@
 // Internal declarations of the scaletrack HIP library (not part of the ABI).
 //
 // Particle store: structure of arrays, kept sorted by chunk (a cube of
-// E^3 cells, E = chunk_edge).  Chunk c owns the slot range
-// [base[c], base[c] + room[c]); its particles sit in the first cnt[c] slots
-// of that range, among ndead[c] holes: slots a particle left (a -1 offset in
-// binary32, a negative diameter in binary64), listed (relative to base[c])
-// at hole[base[c] .. base[c] + ndead[c]).  Arrivals fill holes first.
+// E^3 cells, E = chunk_edge).  A chunk's particles lie in one or more
+// containers (one per kSeg particles at the last full re-bin): container j
+// owns the slot range [base, base + room); its particles sit in the first cnt
+// slots of that range, among h holes: slots a particle left (an offset of
+// kHoleMark or below in binary32, a negative diameter in binary64).  Particles that crossed into the
+// chunk in the last step wait as `in` records in the container's inbox; the
+// next step's kernel takes them up as it streams the container (into the
+// holes, then past the last slot).
 // Positions are stored as chunk-local offsets in cell units, xi in [0, E)
 // per axis; the chunk origin is exact (the chunk index times E cells).  The
 // FP32-everywhere form stores binary32 coordinates in metres instead, and
-// takes the cell from their binary32 product with n / L.  Kernels get the
-// store's pointers as arguments (so
-// every access is a global-memory instruction); a full re-bin scatters into
-// a second store and copies back.
+// takes the cell from their binary32 product with n / L.  A full re-bin
+// scatters into a second store, which then becomes the store: the device flag
+// F_CUR says which of the two it is, and every kernel gets both stores'
+// pointers as arguments (so every access is a global-memory instruction).
+// All of the state that a step reads and writes lives on the device (the
+// flags, the step's tick), so a captured step can be replayed.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -25,11 +30,14 @@
 
 namespace st {
 
-constexpr int kBlock = 256;       // threads per workgroup of the step kernels
-constexpr int kSeg = 16384;       // max particles per step work item
+constexpr int kSeg = 16384;       // particles per container at a full re-bin, at most
+constexpr int kRoomMax = 32768;   // slots per container, at most
 constexpr int kSlackMin = 32;     // spare-slot weight per chunk in the room formula
-constexpr int kMoverStage = 512;  // movers per workgroup staged in LDS
-constexpr int kAlign = 4;         // chunk rooms are whole multiples of this
+constexpr int kMoverStage = 384;  // movers per workgroup staged in LDS
+constexpr int kPool = 128;        // arrivals per workgroup staged in LDS
+constexpr int kAlign = 4;         // container rooms are whole multiples of this
+// binary32: an offset at or below this marks a hole
+constexpr float kHoleMark = -1e30f;
 // The state arrays are streamed together at equal slot indices; array k of
 // store b starts (8 b + k) kStagger bytes into its allocation, so that equal
 // indices of different arrays do not fall on the same HBM channels (aligned
@@ -46,11 +54,43 @@ struct View {
     T *d;              // diameter [m]; binary64: -d marks a hole (the state
                        // of the particle that left it is still in place)
     int32_t *id;       // particle id
-    int64_t *base;     // [C] first slot of the chunk
-    int32_t *room;     // [C] slots owned by the chunk
-    int32_t *cnt;      // [C] slots in use: particles and holes
-    int32_t *ndead;    // [C] holes among them
 };
+
+// The store and the re-bin's target; F_CUR says which is which.
+template <class T>
+struct Views {
+    View<T> a, b;
+    __host__ __device__ __forceinline__ View<T> pick(int cur) const
+    {
+        return View<T>{cur ? b.ox : a.ox, cur ? b.oy : a.oy, cur ? b.oz : a.oz,
+                       cur ? b.vx : a.vx, cur ? b.vy : a.vy, cur ? b.vz : a.vz,
+                       cur ? b.d : a.d,   cur ? b.id : a.id};
+    }
+};
+
+// A container: its place, and its state after each of the last three steps,
+// by the tick modulo 3.  A step at tick t reads the state t - 1 of its own
+// container and of its neighbours, adds its movers to in[t] of theirs, and
+// writes cnt[t] and h[t] of its own and the zero of in[t + 1]: no two of
+// these are the same words, so a step needs no order among its workgroups.
+// 64 bytes, so that one scalar load takes all of it.
+struct alignas(64) Cont {
+    int32_t c;             // chunk
+    int32_t base, room;    // slots
+    int32_t ibase;         // first record of its inbox
+    int32_t k;             // containers of the chunk
+    int32_t in[3];         // records in the inbox (arrivals of the step)
+    struct { int32_t cnt, h; } s[3];   // slots in use, holes among them
+    int32_t pad[2];
+};
+static_assert(sizeof(Cont) == 64, "a container is one 64-byte line");
+
+// records an inbox holds: a container's whole room in a small store, else an
+// eighth of it (more arrivals in one step take the full re-bin)
+__host__ __device__ __forceinline__ int32_t inbox_cap(int32_t room, int32_t whole)
+{
+    return whole ? room : room / 8 + 16;
+}
 
 // One particle in flight between chunks (also the staging area of
 // st_inject), kept together so that moving it reads and writes whole
@@ -62,13 +102,6 @@ struct alignas(16) MoverRec {
 };
 static_assert(sizeof(MoverRec<float>) == 32, "binary32 mover record is 32 bytes");
 static_assert(sizeof(MoverRec<double>) == 64, "binary64 mover record is 64 bytes");
-
-template <class T>
-struct Movers {
-    MoverRec<T> *rec;
-    int32_t *dest;     // destination chunk
-    int32_t *rank;     // rank among the destination's arrivals of the step
-};
 
 // Scalars of the mesh and material used by the kernels.
 struct Params {
@@ -95,12 +128,19 @@ struct Params {
     int32_t pad2_;
 };
 
-// Flags and counters on the device (one int32 each).  F_OVERFLOW and
-// F_FORCE hold the tag (epoch) of the step or flush that raised them; the
-// movers of a step are counted in F_NMOV or F_NMOV_ODD by the tag's parity.
-// F_DEAD counts the holes of the store after the last arrivals.
-enum DevFlag { F_OVERFLOW = 0, F_NMOV = 1, F_NITEMS = 2, F_FORCE = 3, F_BADINPUT = 4,
-               F_REPACKS = 5, F_LASTMOV = 6, F_NMOV_ODD = 7, F_DEAD = 8, F_COUNT = 9 };
+// Flags and counters on the device (one int32 each).  F_OVERFLOW: the step
+// needs a full re-bin; F_FORCE: so does the next one; F_GO: the full re-bin's
+// layout is made, its scatter is due; F_TICKET counts the scatter's finished
+// workgroups; F_CUR: the store (0 or 1); F_TICK: the tick of the next step,
+// modulo 6; F_NITEMS, F_NITEMS1: the containers of either store's layout.
+enum DevFlag { F_OVERFLOW = 0, F_FORCE = 1, F_GO = 2, F_CUR = 3, F_TICK = 4, F_NITEMS = 5,
+               F_NITEMS1 = 6, F_BADINPUT = 7, F_REPACKS = 8, F_LASTMOV = 9, F_TICKET = 10,
+               F_STAT_ITEMS = 11, F_STAT_HOLES = 12, F_COUNT = 16 };
+
+// Counts of holes and of a step's movers, spread over kSpread 64-byte lines
+// (hundreds of thousands of workgroups add to them).
+constexpr int kSpread = 64;
+constexpr int kSpreadInts = kSpread * 16;   // line i: holes at 16 i, movers at 16 i + 1
 
 struct TapeStep {
     const void *u;     // field of the step (borrowed)
@@ -112,27 +152,29 @@ struct Snapshot {      // particle store and layout at a checkpoint
     size_t bytes = 0;
 };
 
+// One container's run in a saved step or checkpoint.
+struct alignas(16) RunItem {
+    int32_t c, s0, cnt, k;   // chunk, first slot, slots in use, containers of the chunk
+};
+
 // Byte offsets inside a snapshot: the 7 state arrays ([7][slots] of the
-// state scalar), ids, the hole lists, the chunk layout (base, room, cnt,
-// ndead) and the work items of that layout with their count.
+// state scalar), ids, the containers' runs with their count, the containers
+// themselves and the chunks' first containers.
 struct SnapLayout {
-    size_t state, id, hole, base, room, cnt, ndead, items, nitems, bytes;
+    size_t state, id, items, nitems, cont, first, bytes;
 };
 
 inline SnapLayout snap_layout(int64_t slots, size_t tsize, int64_t C, int64_t max_items)
 {
-    auto up8 = [](size_t v) { return (v + 7) & ~(size_t)7; };
+    auto up64 = [](size_t v) { return (v + 63) & ~(size_t)63; };
     SnapLayout l;
     l.state = 0;
     l.id = 7 * (size_t)slots * tsize;
-    l.hole = l.id + (size_t)slots * 4;
-    l.base = up8(l.hole + (size_t)slots * 4);
-    l.room = l.base + (size_t)C * 8;
-    l.cnt = l.room + (size_t)C * 4;
-    l.ndead = l.cnt + (size_t)C * 4;
-    l.items = up8(l.ndead + (size_t)C * 4);
-    l.nitems = l.items + (size_t)max_items * 8;
-    l.bytes = up8(l.nitems + 4);
+    l.items = up64(l.id + (size_t)slots * 4);
+    l.nitems = l.items + (size_t)max_items * sizeof(RunItem);
+    l.cont = up64(l.nitems + 4);
+    l.first = l.cont + (size_t)max_items * sizeof(Cont);
+    l.bytes = up64(l.first + (size_t)(C + 1) * 4);
     return l;
 }
 
@@ -148,33 +190,28 @@ struct st_ctx {
     int64_t C = 0;             // chunks
     int64_t cap = 0;           // particle capacity
     int64_t slots = 0;         // slots per store
-    int64_t mcap = 0;          // mover / staging capacity
-    int64_t max_items = 0;     // upper bound of step work items
+    int64_t mcap = 0;          // staging capacity of injections
+    int64_t nrec = 0;          // records of one tick's inboxes
+    int32_t whole_inbox = 0;   // inboxes hold their containers' whole rooms
+    int64_t max_items = 0;     // upper bound of containers
     int64_t count = 0;         // particles in the store (host mirror)
     int64_t pending = 0;       // injected particles waiting in the staging area
     int64_t next_id = 0;
-    int32_t epoch = 0;         // tag of the last step or flush launched
     hipStream_t store_stream = nullptr;   // stream of the last launch that wrote the store
 
     // device memory
-    void *store[2][8] = {};    // SoA arrays: [0] the store, [1] re-bin target
+    void *store[2][8] = {};    // SoA arrays of the store and the re-bin's target (F_CUR)
     void *store_raw[2][8] = {};  // their allocations (the arrays start past a stagger)
-    int64_t *base = nullptr;   // [C+1] layout of the store
-    int32_t *room = nullptr;   // [C]
-    int32_t *cnt = nullptr;    // [C]
-    int32_t *ndead = nullptr;  // [C]
-    void *mov[3] = {};         // Movers: records, destination chunks, ranks
-    int32_t *out_cnt = nullptr, *in_cnt = nullptr;
+    st::Cont *cont[2] = {};    // [max_items] containers of either store
+    int32_t *first[2] = {};    // [C+1] first container of each chunk
+    void *rec = nullptr;       // [2][nrec] inboxes, by the tick's parity; also the
+                               // staging area of injections
+    int32_t *stage_dest = nullptr; // [mcap] chunks of the staged injections
     int32_t *cursor = nullptr;     // [C] scatter cursors of the full re-bin
-    int32_t *new_cnt = nullptr;    // [C]
-    int64_t *nbase = nullptr;      // [C+1] first slots of the re-binned layout
-    int32_t *nroom = nullptr;      // [C]   rooms of the re-binned layout
-    int32_t *hole = nullptr;       // [slots] holes of chunk c from base[c]
-    int32_t *items = nullptr;      // [max_items][2]
-    int32_t *nseg = nullptr;       // [C+1] offsets of the work items per chunk
-    int64_t *scan_tmp = nullptr;   // block partials of the scans
-    int64_t *room_denom = nullptr; // [1] sum of the chunks' room weights
-    int32_t *flags = nullptr;      // DevFlag counters
+    int32_t *new_cnt = nullptr;    // [C] particles per chunk at a full re-bin
+    int4 *lay = nullptr;           // [C] its layout: first slot, per container, room, containers
+    int32_t *flags = nullptr;      // DevFlag
+    int32_t *spread = nullptr;     // spread counters
     void *src = nullptr;           // [C][3][E^3] accumulator (double or float)
     double *stage64 = nullptr;     // staging for host-side injects ([batch][7])
 
@@ -208,9 +245,16 @@ struct st_ctx {
 
 namespace st {
 
-// Kernel launchers (st_kernels.hip).  All enqueue on `s`.
+// Kernel launchers (st_device.hip).  All enqueue on `s`.
 hipError_t launch_init(st_ctx *c, hipStream_t s);
-hipError_t launch_items(st_ctx *c, hipStream_t s);
+// places the last step's arrivals (else the next step does)
+hipError_t launch_settle(st_ctx *c, hipStream_t s);
+// counts the non-empty containers and the holes into F_STAT_*
+hipError_t launch_stats(st_ctx *c, hipStream_t s);
+// the runs of the (settled) store's containers and their count
+hipError_t launch_runs(st_ctx *c, RunItem *items, int32_t *nitems, hipStream_t s);
+// takes staged injections from `keep` on out of the inbox counts again
+hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s);
 hipError_t launch_flush_pending(st_ctx *c, hipStream_t s);
 hipError_t launch_zero_sources(st_ctx *c, hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t s);
@@ -244,5 +288,69 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
 hipError_t noalloc_scratch_init(int device);
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStream_t s);
 hipError_t noalloc_scratch(int device, double **ptr);
+
+template <class T>
+Views<T> views_of(const st_ctx *c)
+{
+    auto v = [&](int b) {
+        return View<T>{(T *)c->store[b][0], (T *)c->store[b][1], (T *)c->store[b][2],
+                       (T *)c->store[b][3], (T *)c->store[b][4], (T *)c->store[b][5],
+                       (T *)c->store[b][6], (int32_t *)c->store[b][7]};
+    };
+    return Views<T>{v(0), v(1)};
+}
+
+// What a kernel that reads the particles gets: both stores, their containers,
+// the inboxes and the flags.
+template <class T>
+struct Store {
+    Views<T> V;
+    const Cont *cont0, *cont1;
+    const MoverRec<T> *rec;   // [2][nrec]
+    int64_t nrec;
+    const int32_t *flags;
+};
+
+template <class T>
+Store<T> store_of(const st_ctx *c)
+{
+    return Store<T>{views_of<T>(c), c->cont[0], c->cont[1], (const MoverRec<T> *)c->rec, c->nrec,
+                    c->flags};
+}
+
+#ifdef __HIPCC__
+// A container's place and its state with index m.
+struct ContState {
+    int32_t c, base, room, ibase, k, in, cnt, h;
+};
+__device__ __forceinline__ ContState state_of(const Cont *p, int m)
+{
+    const Cont d = *p;   // (constant indices: the copy stays in registers)
+    return ContState{d.c, d.base, d.room, d.ibase, d.k,
+                     m == 0 ? d.in[0] : m == 1 ? d.in[1] : d.in[2],
+                     m == 0 ? d.s[0].cnt : m == 1 ? d.s[1].cnt : d.s[2].cnt,
+                     m == 0 ? d.s[0].h : m == 1 ? d.s[1].h : d.s[2].h};
+}
+
+// The current state of a store: its arrays and containers, and where the
+// last step's arrivals are.
+template <class T>
+struct Current {
+    View<T> V;
+    const Cont *cont;
+    const MoverRec<T> *rec;
+    int32_t ni;          // containers
+    int32_t m;           // state index of the last step
+    __device__ __forceinline__ explicit Current(const Store<T> &s)
+    {
+        const int cur = s.flags[F_CUR], t = s.flags[F_TICK];
+        V = s.V.pick(cur);
+        cont = cur ? s.cont1 : s.cont0;
+        ni = cur ? s.flags[F_NITEMS1] : s.flags[F_NITEMS];
+        m = (t + 2) % 3;
+        rec = s.rec + ((t + 1) & 1) * s.nrec;
+    }
+};
+#endif
 
 }  // namespace st
