@@ -185,10 +185,10 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
     int32_t *const f = a.flags;
     const int32_t t = f[F_TICK], cur = f[F_CUR];
     const bool full = (f[F_OVERFLOW] | f[F_FORCE]) != 0;
+    int32_t *const l = a.spread + 16 * (threadIdx.x & 63);
+    int32_t holes = l[0], movers = l[1];
     __syncthreads();   // every thread has read the flags before one writes them
     if (threadIdx.x < 64) {
-        int32_t *const l = a.spread + 16 * threadIdx.x;
-        int32_t holes = l[0], movers = l[1];
         for (int o = 32; o > 0; o >>= 1) {
             holes += __shfl_xor(holes, o);
             movers += __shfl_xor(movers, o);
@@ -1654,10 +1654,9 @@ hipError_t dispatch(st_ctx *c, F &&f)
 
 // ev[0], ev[1] (when not null) take the start and end of the kernel's own
 // execution (not of the commands around it)
-template <class T, class A, int E, int I, int D>
-hipError_t launch_step_t(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipEvent_t *ev)
+template <class T, class A, int E, int I, int D, int NB>
+hipError_t launch_step_n(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipEvent_t *ev)
 {
-    constexpr int NB = 256;
     const int64_t round = 8 * kXcdBlock;
     const int64_t grid = (c->max_items + round - 1) / round * round;
     if constexpr (sizeof(A) == 8) {   // only the forms that tape save
@@ -1672,6 +1671,19 @@ hipError_t launch_step_t(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
     else
         hipLaunchKernelGGL((k_step<T, A, E, I, D, false, NB>), dim3(grid), dim3(NB), 0, s, a);
     return hipGetLastError();
+}
+
+template <class T, class A, int E, int I, int D>
+hipError_t launch_step_t(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipEvent_t *ev)
+{
+    // Twice the threads where the containers fill at most half of the 256 CUs
+    // and hold more than one pass of 256 threads (32^3 mesh, 1e5 droplets in
+    // binary64: 24.7 against 27.4 us a step with its sources; with 270
+    // containers and more the larger workgroups lose 3 % and more).
+    if constexpr (E == 8)
+        if (c->max_items <= 128 && c->count > c->C * 256 * (16 / (int64_t)sizeof(T)))
+            return launch_step_n<T, A, E, I, D, 512>(c, a, s, ev);
+    return launch_step_n<T, A, E, I, D, 256>(c, a, s, ev);
 }
 
 template <class T, class A, int E, int I>
