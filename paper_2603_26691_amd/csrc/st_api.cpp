@@ -49,7 +49,7 @@ void free_all(st_ctx *c)
     for (int b = 0; b < 2; ++b)
         for (int k = 0; k < 8; ++k) (void)hipFree(c->store_raw[b][k]);
     void *singles[] = {c->cont[0], c->cont[1], c->first[0], c->first[1], c->rec, c->stage_dest,
-                       c->cursor, c->new_cnt, c->lay, c->flags, c->spread, c->src, c->stage64,
+                       c->cursor, c->new_cnt, c->lay, c->flags, c->spread, c->src, c->written, c->stage64,
                        c->fieldbuf[0], c->fieldbuf[1], c->ec_prev, c->ec_ext};
     for (void *p : singles) (void)hipFree(p);
     for (auto &sn : c->snaps) (void)hipFree(sn.buf);
@@ -160,7 +160,7 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
     c->whole_inbox = c->slots <= (1 << 17);
     c->nrec = c->whole_inbox ? c->slots : c->slots / 8 + 16 * c->max_items;
     c->mcap = std::min<int64_t>(d.capacity, 2 * c->nrec);
-    if (c->slots >= ((int64_t)1 << 31) - 1 || c->max_items >= ((int64_t)1 << 26))
+    if (c->slots >= ((int64_t)1 << 31) - 1 || c->max_items >= ((int64_t)1 << 30))
         return bad("capacity too large for 32-bit slot indices");
 
     auto dev_bad = [&](st_status st, const std::string &m) {
@@ -197,6 +197,7 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
     A(&c->flags, (size_t)st::F_COUNT * 4);
     A(&c->spread, (size_t)st::kSpreadInts * 4);
     A(&c->src, (size_t)3 * ncell * c->asize);
+    A(&c->written, (size_t)C * 4);
     if (ok != hipSuccess)
         return dev_bad(ST_ERR_OOM, "device allocation failed after " + std::to_string(total) +
                                        " bytes");

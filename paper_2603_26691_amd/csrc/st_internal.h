@@ -213,6 +213,7 @@ struct st_ctx {
     int32_t *flags = nullptr;      // DevFlag
     int32_t *spread = nullptr;     // spread counters
     void *src = nullptr;           // [C][3][E^3] accumulator (double or float)
+    int32_t *written = nullptr;    // [C] it holds something (else the chunk's is zero)
     double *stage64 = nullptr;     // staging for host-side injects ([batch][7])
 
     // tape

@@ -77,6 +77,47 @@ def test_sources_any_alignment(form, edge):
 
 
 @pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("n,edge,P", [((24, 16, 40), 8, 3000), ((40, 16, 16), 4, 20000),
+                                      ((6, 10, 36), 2, 2000), ((16, 16, 16), 8, 60000)])
+def test_sources_cleared_between_steps(form, n, edge, P):
+    """Sources read and cleared after every step (a reset only marks a chunk;
+    empty chunks, chunks that droplets enter and leave, and chunks of several
+    containers) add up to those left to accumulate, and a read-out without a
+    reset changes nothing."""
+    import torch
+    w = workload("plume256", n=n, L=tuple(0.1 * v / 32 for v in n), P=P, plumes=1, noise=0.3,
+                 plume_sigma=0.08, chunk_edge=edge)
+    x, up, d = w.particles()
+    a, b = tracker(w, form, capacity=2 * P), tracker(w, form, capacity=2 * P)
+    U = torch.from_numpy(w.field()).cuda().to(a.field_dtype)
+    total = torch.zeros(a.field_shape, dtype=torch.float64, device="cuda")
+    size = torch.zeros_like(total)
+    for t in (a, b):
+        t.inject(x, up, d)
+    assert float(a.sources(reset=True).abs().max()) == 0.0
+    for k in range(12):
+        a.step(U, 1e-3)
+        b.step(U, 1e-3)
+        if k == 5:     # more containers: half the droplets again, in one chunk
+            for t in (a, b):
+                t.inject(x[: P // 2] * 0.2, up[: P // 2], d[: P // 2])
+        S = a.sources()
+        assert torch.equal(a.sources(reset=k % 4 != 3), S)
+        if k % 4 != 3:
+            assert float(a.sources().abs().max()) == 0.0
+            total += S
+            size += S.abs()
+    total += a.sources(reset=True)
+    size += total.abs()
+    eps = 2.0 ** -22 if form == "fp32" else 2.0 ** -50
+    # sums of the same terms in another order: at most P roundings of the sum
+    # of their sizes in one cell, and far fewer in all but the fullest
+    assert float((total - b.sources()).abs().max()) <= 64 * eps * float(size.max())
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("per_part", [1, 7, 700, 20001])
 def test_boxes_of_scattered_partitions(form, per_part):
     import torch
