@@ -212,15 +212,28 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
     if (!full) return;
 
     const int m = a.advance ? t % 3 : (t + 2) % 3;   // state index after the step
-    const Cont *const ct = cur ? a.cont1 : a.cont0;
+    Cont *const ct = cur ? a.cont1 : a.cont0;
     const int32_t *const cf = cur ? a.first1 : a.first0;
     Cont *const nct = cur ? a.cont0 : a.cont1;
     int32_t *const ncf = cur ? a.first0 : a.first1;
     for (int64_t c = threadIdx.x; c < a.C; c += 1024) {
-        int32_t n = 0;
-        for (int32_t j = cf[c]; j < cf[c + 1]; ++j) n += ct[j].s[m].cnt - ct[j].s[m].h + ct[j].in[m];
-        a.new_cnt[c] = n;
-        a.cursor[c] = 0;
+        // the places of a chunk's particles: those that stay in its containers,
+        // container by container, then its inboxes' records, then (from the
+        // cursor on) injections and the movers whose inbox was full
+        const int32_t j0 = cf[c], j1 = cf[c + 1];
+        int32_t n = 0, all = 0;
+        for (int32_t j = j0; j < j1; ++j) {
+            ct[j].place[0] = n;
+            n += ct[j].s[m].cnt - ct[j].s[m].h;
+        }
+        all = n;
+        for (int32_t j = j0; j < j1; ++j) {
+            ct[j].place[1] = n;
+            n += a.advance ? min(ct[j].in[m], inbox_cap(ct[j].room, a.whole)) : 0;
+            all += ct[j].in[m];
+        }
+        a.new_cnt[c] = all;
+        a.cursor[c] = n;
     }
     __syncthreads();
     int64_t w = 0, denom;
@@ -259,7 +272,7 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
                     d.s[u].cnt = u == m ? min(max(n - i * per, 0), per) : 0;
                     d.s[u].h = 0;
                 }
-                d.pad[0] = d.pad[1] = 0;
+                d.place[0] = d.place[1] = 0;
                 nct[j0 + i] = d;
             }
         }
@@ -1056,8 +1069,8 @@ __device__ __forceinline__ int64_t slot_of_rank(const int4 &l, int32_t rank)
     return (int64_t)l.x + (int64_t)i * l.z + (rank - i * l.y);
 }
 
-constexpr int kScatterBlock = 1024;
-constexpr int kScatterGroups = 512;   // they run every step and usually exit at the gate
+constexpr int kScatterBlock = 256;
+constexpr int kScatterGroups = 2048;   // they run every step and usually exit at the gate
 
 // Staged injections per chunk are counted, and placed, in tiles of kTile per
 // workgroup through LDS counters of every chunk while there are at most
@@ -1067,7 +1080,7 @@ constexpr int kScatterGroups = 512;   // they run every step and usually exit at
 // scatter with an atomic per droplet).  With more chunks the counters are
 // less crowded, and a droplet takes its own atomic.
 constexpr int kHistMax = 8192;
-constexpr int kTilePer = 8, kTile = kTilePer * kScatterBlock;
+constexpr int kTilePer = 16, kTile = kTilePer * kScatterBlock;
 
 // Full re-bin: the occupied slots and the records, chunk by chunk, into the
 // second store, which the last workgroup makes the store.  A container's
@@ -1077,7 +1090,7 @@ template <class T>
 __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
 {
     if (!a.flags[F_GO]) return;
-    __shared__ int32_t stay0, in0, pos, hist[kHistMax];
+    __shared__ int32_t pos, hist[kHistMax];
     __shared__ bool last;
     const int cur = a.flags[F_CUR], t = a.flags[F_TICK];
     const int32_t ni = cur ? a.flags[F_NITEMS1] : a.flags[F_NITEMS];
@@ -1087,15 +1100,12 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
     const MoverRec<T> *const rec = a.rec + ((t + 1) & 1) * a.nrec;
     for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) {
         const ContState me = state_of(ct + it, m);
-        const int32_t c = me.c, cnt = me.cnt, stays = cnt - me.h;
+        const int32_t c = me.c, cnt = me.cnt;
         const int32_t nin = a.npend ? 0 : min(me.in, inbox_cap(me.room, a.whole));
         if (cnt == 0 && nin == 0) continue;   // uniform
         const int4 l = a.lay[c];
-        if (threadIdx.x == 0) {
-            stay0 = stays > 0 ? atomicAdd(&a.cursor[c], stays) : 0;
-            in0 = nin > 0 ? atomicAdd(&a.cursor[c], nin) : 0;
-            pos = 0;
-        }
+        if (threadIdx.x == 0) pos = ct[it].place[0];
+        const int32_t in0 = ct[it].place[1];
         __syncthreads();
         const int64_t s0 = me.base;
         for (int32_t o = 0; o < cnt; o += kScatterBlock) {   // every lane the same rounds
@@ -1122,7 +1132,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
             if (__lane_id() == 0) b = stay ? atomicAdd(&pos, __popcll(stay)) : 0;
             b = __shfl(b, 0);
             if (home)
-                put_slot(W, slot_of_rank(l, stay0 + b + __popcll(stay & lanes_below_mask())), r);
+                put_slot(W, slot_of_rank(l, b + __popcll(stay & lanes_below_mask())), r);
             else if (cn >= 0)   // a mover whose inbox was full
                 put_slot(W, slot_of_rank(a.lay[cn], atomicAdd(&a.cursor[cn], 1)), r);
         }

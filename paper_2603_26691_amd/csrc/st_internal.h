@@ -81,7 +81,7 @@ struct alignas(64) Cont {
     int32_t k;             // containers of the chunk
     int32_t in[3];         // records in the inbox (arrivals of the step)
     struct { int32_t cnt, h; } s[3];   // slots in use, holes among them
-    int32_t pad[2];
+    int32_t place[2];      // full re-bin: places in the chunk of its particles, its records
 };
 static_assert(sizeof(Cont) == 64, "a container is one 64-byte line");
 
