@@ -109,7 +109,10 @@ typedef struct {
 st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out);
 
 /* Outside the paper (lifetime of a context).
- * Frees every buffer of the context (after synchronising its device). */
+ * Frees every buffer of the context (after synchronising its device).  Up to
+ * 512 MiB of device memory that contexts free, here and in st_tape_clear, are
+ * kept for the buffers of later ones; they are given back when later frees
+ * pass them by, or when device memory runs out. */
 st_status st_destroy(st_ctx *ctx);
 
 /* Outside the paper (error reporting).

@@ -621,14 +621,13 @@ BwdLayout bwd_layout(const st_ctx *c, int64_t K)
 
 hipError_t ensure_bwd_workspace(st_ctx *c, const BwdLayout &W)
 {
-    if (c->bwd_ws_bytes >= W.bytes) return hipSuccess;
-    (void)hipFree(c->bwd_ws);
-    c->bwd_ws = nullptr;
-    c->bwd_ws_bytes = 0;
-    hipError_t e = hipMalloc(&c->bwd_ws, W.bytes);
-    if (e != hipSuccess) return e;
-    c->bwd_ws_bytes = W.bytes;
-    return hipSuccess;
+    if (c->bwd_ws.bytes >= W.bytes) return hipSuccess;
+    if (c->bwd_ws.buf) {
+        const hipError_t e = hipDeviceSynchronize();
+        if (e != hipSuccess) return e;
+        block_free(c->device, &c->bwd_ws);
+    }
+    return block_alloc(c->device, W.bytes, &c->bwd_ws);
 }
 
 }  // namespace
@@ -651,7 +650,7 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
     const BwdLayout W = bwd_layout(c, K);
     hipError_t e0 = ensure_bwd_workspace(c, W);
     if (e0 != hipSuccess) return e0;
-    char *ws = (char *)c->bwd_ws;
+    char *ws = (char *)c->bwd_ws.buf;
     void *final_state = ws;
     auto step_buf = [&](int64_t k) -> void * { return ws + W.o_steps + (size_t)k * W.step_bytes; };
     double *lamC = (double *)(ws + W.o_lam);

@@ -7,11 +7,114 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
 
 #include "st_internal.h"
+
+// ---------------------------------------------------------------------------
+// device memory
+// ---------------------------------------------------------------------------
+namespace st {
+namespace {
+
+// Blocks kept for the next context: at most kKeepBytes in all, for all devices
+// and threads, and none that the last kKeepFrees calls of block_free have passed
+// by; all of them are given back when the device has no memory left.  Making
+// and freeing device memory can cost more than a short-lived context's work:
+// memory is cleared on its way through the driver, so a program that makes a
+// context per iteration waits for that.  3e6 droplets put in, read back and
+// closed: 5.1 ms with an allocation per array (4.1 ms of them in hipFree), 22.6
+// ms in a process that has just freed large buffers; 1.1 ms with kept blocks.
+constexpr size_t kKeepBytes = (size_t)512 << 20;
+constexpr uint64_t kKeepFrees = 64;
+
+struct Kept {
+    int device;
+    Block b;
+    uint64_t at;     // the count of block_free calls when it was kept
+};
+struct Keeper {
+    std::mutex mu;
+    std::vector<Kept> kept;   // oldest first
+    size_t bytes = 0;
+    uint64_t frees = 0;
+};
+// (never destroyed: contexts may be closed while the process ends)
+Keeper &keeper()
+{
+    static Keeper *const k = new Keeper();
+    return *k;
+}
+
+void drop(Keeper &k, size_t i)
+{
+    (void)hipFree(k.kept[i].b.buf);
+    k.bytes -= k.kept[i].b.bytes;
+    k.kept.erase(k.kept.begin() + (ptrdiff_t)i);
+}
+
+}  // namespace
+
+hipError_t block_alloc(int device, size_t bytes, Block *out)
+{
+    if (bytes == 0) bytes = 8;
+    if (bytes <= kKeepBytes) {
+        Keeper &k = keeper();
+        std::lock_guard<std::mutex> lock(k.mu);
+        // the smallest that fits and wastes at most a quarter
+        size_t best = k.kept.size();
+        for (size_t i = 0; i < k.kept.size(); ++i) {
+            const Kept &e = k.kept[i];
+            if (e.device == device && e.b.bytes >= bytes && e.b.bytes <= bytes + bytes / 4 &&
+                (best == k.kept.size() || e.b.bytes < k.kept[best].b.bytes))
+                best = i;
+        }
+        if (best < k.kept.size()) {
+            *out = k.kept[best].b;
+            k.bytes -= out->bytes;
+            k.kept.erase(k.kept.begin() + (ptrdiff_t)best);
+            return hipSuccess;
+        }
+    }
+    void *p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        Keeper &k = keeper();
+        std::lock_guard<std::mutex> lock(k.mu);
+        while (!k.kept.empty()) drop(k, 0);
+        e = hipMalloc(&p, bytes);
+    }
+    if (e == hipSuccess) *out = Block{p, bytes};
+    return e;
+}
+
+void block_free(int device, Block *b)
+{
+    if (!b->buf) return;
+    const Block mine = *b;
+    *b = Block{};
+    Keeper &k = keeper();
+    std::lock_guard<std::mutex> lock(k.mu);
+    k.frees += 1;
+    while (!k.kept.empty() && (k.kept[0].at + kKeepFrees < k.frees ||
+                               (mine.bytes <= kKeepBytes && k.bytes + mine.bytes > kKeepBytes)))
+        drop(k, 0);
+    if (mine.bytes <= kKeepBytes) {
+        try {
+            k.kept.push_back(Kept{device, mine, k.frees});
+            k.bytes += mine.bytes;
+            return;
+        } catch (...) {   // no host memory to remember it by
+        }
+    }
+    (void)hipFree(mine.buf);
+}
+
+}  // namespace st
 
 namespace {
 
@@ -37,28 +140,52 @@ st_status dev_fail(st_ctx *c, hipError_t e, const char *what)
         if (e_ != hipSuccess) return dev_fail(c, e_, #call); \
     } while (0)
 
-template <class P>
-hipError_t dalloc(P **p, size_t bytes, size_t &total)
+// A context's buffers up to this much are one block (each array at 256 bytes,
+// large ones at 2 MiB, as separate allocations start); larger contexts live
+// long, and are allocated array by array.
+constexpr size_t kOneBlock = (size_t)4 << 30;
+
+struct Wanted {
+    void **ptr;
+    size_t bytes;
+};
+
+hipError_t allocate(st_ctx *c, const std::vector<Wanted> &want, size_t &total)
 {
-    total += bytes;
-    return hipMalloc((void **)p, bytes ? bytes : 8);
+    constexpr size_t kLarge = (size_t)2 << 20;
+    size_t at = 0;
+    std::vector<size_t> off;
+    for (const Wanted &w : want) {
+        const size_t align = w.bytes >= kLarge ? kLarge : 256;
+        at = (at + align - 1) / align * align;
+        off.push_back(at);
+        at += w.bytes ? w.bytes : 8;
+    }
+    total = at;
+    const bool one = at <= kOneBlock;
+    c->blocks.reserve(one ? 1 : want.size());
+    for (size_t k = 0; k < (one ? 1 : want.size()); ++k) {
+        st::Block b;
+        const hipError_t e = st::block_alloc(c->device, one ? at : want[k].bytes, &b);
+        if (e != hipSuccess) return e;
+        c->blocks.push_back(b);
+        *want[k].ptr = b.buf;
+    }
+    if (one)
+        for (size_t k = 0; k < want.size(); ++k) *want[k].ptr = (char *)c->blocks[0].buf + off[k];
+    return hipSuccess;
 }
 
 void free_all(st_ctx *c)
 {
-    for (int b = 0; b < 2; ++b)
-        for (int k = 0; k < 8; ++k) (void)hipFree(c->store_raw[b][k]);
-    void *singles[] = {c->cont[0], c->cont[1], c->first[0], c->first[1], c->rec, c->stage_dest,
-                       c->cursor, c->new_cnt, c->lay, c->flags, c->spread, c->src, c->written, c->stage64,
-                       c->fieldbuf[0], c->fieldbuf[1], c->ec_prev, c->ec_ext};
+    for (auto *v : {&c->blocks, &c->snaps, &c->spare}) {
+        for (auto &b : *v) st::block_free(c->device, &b);
+        v->clear();
+    }
+    st::block_free(c->device, &c->stage64);
+    st::block_free(c->device, &c->bwd_ws);
+    void *singles[] = {c->fieldbuf[0], c->fieldbuf[1], c->ec_prev, c->ec_ext};
     for (void *p : singles) (void)hipFree(p);
-    for (auto &sn : c->snaps) (void)hipFree(sn.buf);
-    c->snaps.clear();
-    for (auto &sn : c->spare) (void)hipFree(sn.buf);
-    c->spare.clear();
-    (void)hipFree(c->bwd_ws);
-    c->bwd_ws = nullptr;
-    c->bwd_ws_bytes = 0;
     for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
     c->tev.clear();
     if (c->side) (void)hipStreamDestroy(c->side);
@@ -164,6 +291,7 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
         return bad("capacity too large for 32-bit slot indices");
 
     auto dev_bad = [&](st_status st, const std::string &m) {
+        (void)hipDeviceSynchronize();
         free_all(c);
         delete c;
         g_create_err = "st_create_mesh: " + m;
@@ -173,34 +301,36 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
     if (e != hipSuccess) return dev_bad(ST_ERR_DEVICE, hipGetErrorString(e));
     size_t total = 0;
     const int64_t C = p.C;
-    hipError_t ok = hipSuccess;
-    auto A = [&](auto **ptr, size_t bytes) {
-        if (ok == hipSuccess) ok = dalloc(ptr, bytes, total);
-    };
-    for (int b = 0; b < 2; ++b) {
-        for (int k = 0; k < 8; ++k) {
-            const size_t off = (size_t)(8 * b + k) * st::kStagger;
-            A(&c->store_raw[b][k], (size_t)c->slots * (k < 7 ? c->tsize : 4) + off);
-            if (c->store_raw[b][k]) c->store[b][k] = (char *)c->store_raw[b][k] + off;
+    auto stagger = [](int b, int k) { return (size_t)(8 * b + k) * st::kStagger; };
+    hipError_t ok = hipErrorOutOfMemory;
+    try {
+        std::vector<Wanted> want;
+        auto A = [&](auto **ptr, size_t bytes) { want.push_back({(void **)ptr, bytes}); };
+        for (int b = 0; b < 2; ++b)
+            for (int k = 0; k < 8; ++k)
+                A(&c->store[b][k], (size_t)c->slots * (k < 7 ? c->tsize : 4) + stagger(b, k));
+        for (int b = 0; b < 2; ++b) {
+            A(&c->cont[b], (size_t)c->max_items * sizeof(st::Cont));
+            A(&c->first[b], (size_t)(C + 1) * 4);
         }
+        A(&c->rec, (size_t)(2 * c->nrec) * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
+                                                          : sizeof(st::MoverRec<float>)));
+        A(&c->stage_dest, (size_t)c->mcap * 4);
+        A(&c->cursor, (size_t)C * 4);
+        A(&c->new_cnt, (size_t)C * 4);
+        A(&c->lay, (size_t)C * 16);
+        A(&c->flags, (size_t)st::F_COUNT * 4);
+        A(&c->spread, (size_t)st::kSpreadInts * 4);
+        A(&c->src, (size_t)3 * ncell * c->asize);
+        A(&c->written, (size_t)C * 4);
+        ok = allocate(c, want, total);
+    } catch (...) {   // host memory
     }
-    for (int b = 0; b < 2; ++b) {
-        A(&c->cont[b], (size_t)c->max_items * sizeof(st::Cont));
-        A(&c->first[b], (size_t)(C + 1) * 4);
-    }
-    A(&c->rec, (size_t)(2 * c->nrec) * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
-                                                      : sizeof(st::MoverRec<float>)));
-    A(&c->stage_dest, (size_t)c->mcap * 4);
-    A(&c->cursor, (size_t)C * 4);
-    A(&c->new_cnt, (size_t)C * 4);
-    A(&c->lay, (size_t)C * 16);
-    A(&c->flags, (size_t)st::F_COUNT * 4);
-    A(&c->spread, (size_t)st::kSpreadInts * 4);
-    A(&c->src, (size_t)3 * ncell * c->asize);
-    A(&c->written, (size_t)C * 4);
     if (ok != hipSuccess)
-        return dev_bad(ST_ERR_OOM, "device allocation failed after " + std::to_string(total) +
-                                       " bytes");
+        return dev_bad(ST_ERR_OOM, "device allocation of " + std::to_string(total) +
+                                       " bytes failed");
+    for (int b = 0; b < 2; ++b)
+        for (int k = 0; k < 8; ++k) c->store[b][k] = (char *)c->store[b][k] + stagger(b, k);
     // this device's address of the fixed scratch of st_bounding_boxes_noalloc
     e = st::noalloc_scratch_init(device);
     if (e != hipSuccess) return dev_bad(ST_ERR_DEVICE, hipGetErrorString(e));
@@ -261,9 +391,9 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
         // the staging area is the inboxes' memory
         if (c->pending == 0) ST_HIP(st::launch_settle(c, s));
         const int64_t stage_batch = std::min<int64_t>(c->mcap, 1 << 22);
-        if (!on_device && !c->stage64) {
+        if (!on_device && !c->stage64.buf) {
             size_t bytes = (size_t)stage_batch * 7 * 8;
-            hipError_t e = hipMalloc((void **)&c->stage64, bytes);
+            hipError_t e = st::block_alloc(c->device, bytes, &c->stage64);
             if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_inject: staging buffer");
         }
         const int64_t pend0 = c->pending, id0 = c->next_id, count0 = c->count;
@@ -277,7 +407,7 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
             if (!on_device) k = std::min<int64_t>(k, stage_batch);
             const double *xs = x + 3 * done, *us = up + 3 * done, *ds = d + done;
             if (!on_device) {
-                double *sx = c->stage64, *su = sx + 3 * stage_batch, *sd = su + 3 * stage_batch;
+                double *sx = (double *)c->stage64.buf, *su = sx + 3 * stage_batch, *sd = su + 3 * stage_batch;
                 ST_HIP(hipMemcpyAsync(sx, xs, (size_t)k * 24, hipMemcpyHostToDevice, s));
                 ST_HIP(hipMemcpyAsync(su, us, (size_t)k * 24, hipMemcpyHostToDevice, s));
                 ST_HIP(hipMemcpyAsync(sd, ds, (size_t)k * 8, hipMemcpyHostToDevice, s));
@@ -342,8 +472,7 @@ st_status st_step(st_ctx *c, const void *u_cells, double dt, int32_t nsub, int32
                         sn = c->spare.back();
                         c->spare.pop_back();
                     } else {
-                        sn.bytes = st::snapshot_bytes(c);
-                        hipError_t e = hipMalloc(&sn.buf, sn.bytes);
+                        hipError_t e = st::block_alloc(c->device, st::snapshot_bytes(c), &sn);
                         if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_step: checkpoint");
                     }
                     c->snaps.push_back(sn);
@@ -426,15 +555,13 @@ void tape_reset(st_ctx *c, bool keep_buffers)
     (void)hipDeviceSynchronize();
     for (auto &sn : c->snaps) {
         if (keep_buffers) c->spare.push_back(sn);
-        else (void)hipFree(sn.buf);
+        else st::block_free(c->device, &sn);
     }
     c->snaps.clear();
     if (!keep_buffers) {
-        for (auto &sn : c->spare) (void)hipFree(sn.buf);
+        for (auto &sn : c->spare) st::block_free(c->device, &sn);
         c->spare.clear();
-        (void)hipFree(c->bwd_ws);
-        c->bwd_ws = nullptr;
-        c->bwd_ws_bytes = 0;
+        st::block_free(c->device, &c->bwd_ws);
     }
     c->tape.clear();
     c->tape_every = 0;
@@ -463,8 +590,7 @@ st_status st_tape_reserve(st_ctx *c, int32_t tape, int64_t substeps)
         const int64_t need = (substeps + tape - 1) / tape;
         while ((int64_t)c->spare.size() < need) {
             st::Snapshot sn;
-            sn.bytes = st::snapshot_bytes(c);
-            if (hipMalloc(&sn.buf, sn.bytes) != hipSuccess)
+            if (st::block_alloc(c->device, st::snapshot_bytes(c), &sn) != hipSuccess)
                 return fail(c, ST_ERR_OOM, "st_tape_reserve: checkpoint");
             c->spare.push_back(sn);
         }

@@ -147,10 +147,17 @@ struct TapeStep {
     double dt;         // sub-step length
 };
 
-struct Snapshot {      // particle store and layout at a checkpoint
+struct Block {         // device memory from block_alloc
     void *buf = nullptr;
     size_t bytes = 0;
 };
+using Snapshot = Block;   // particle store and layout at a checkpoint
+
+// Device memory of the current device, at least `bytes` of it, perhaps one that
+// block_free kept (its contents are anything).
+hipError_t block_alloc(int device, size_t bytes, Block *b);
+// Takes a block back; nothing on the device may use it any more.
+void block_free(int device, Block *b);
 
 // One container's run in a saved step or checkpoint.
 struct alignas(16) RunItem {
@@ -201,7 +208,8 @@ struct st_ctx {
 
     // device memory
     void *store[2][8] = {};    // SoA arrays of the store and the re-bin's target (F_CUR)
-    void *store_raw[2][8] = {};  // their allocations (the arrays start past a stagger)
+                               // (array k of store b starts past a stagger)
+    std::vector<st::Block> blocks;  // allocations that hold the buffers below
     st::Cont *cont[2] = {};    // [max_items] containers of either store
     int32_t *first[2] = {};    // [C+1] first container of each chunk
     void *rec = nullptr;       // [2][nrec] inboxes, by the tick's parity; also the
@@ -214,7 +222,7 @@ struct st_ctx {
     int32_t *spread = nullptr;     // spread counters
     void *src = nullptr;           // [C][3][E^3] accumulator (double or float)
     int32_t *written = nullptr;    // [C] it holds something (else the chunk's is zero)
-    double *stage64 = nullptr;     // staging for host-side injects ([batch][7])
+    st::Block stage64;             // staging for host-side injects ([batch][7] double)
 
     // tape
     int tape_every = 0;
@@ -225,8 +233,7 @@ struct st_ctx {
     // (the state at the end of the forward run, the saved states of one
     // segment, the adjoint records and dL/dS by chunk)
     std::vector<st::Snapshot> spare;
-    void *bwd_ws = nullptr;
-    size_t bwd_ws_bytes = 0;
+    st::Block bwd_ws;
 
     // coupled run
     void *fieldbuf[2] = {};
