@@ -460,7 +460,10 @@ __global__ void __launch_bounds__(NB)
     constexpr int G = 16 / sizeof(T);   // consecutive particles per thread
     static_assert(kAlign % G == 0, "chunk rooms must hold whole particle groups");
     __shared__ T tile[3 * S3];
-    __shared__ A acc[3 * E3];
+    // (binary64 in every form: LDS adds of binary32 values take twice as long on
+    // this chip; 777777 droplets with Schiller-Naumann drag in the FP32-everywhere
+    // form: 47 against 55 us)
+    __shared__ double acc[3 * E3];
     __shared__ int32_t mstage[kMoverStage];
     // binary32 state: the staged movers' new positions and velocities (9 KB,
     // which with the arrivals still lets four workgroups share a CU; the
@@ -591,7 +594,7 @@ __global__ void __launch_bounds__(NB)
         const int t = threadIdx.x + u * NB;
         if (t < 3 * S3) tile[t] = vals[u];
     }
-    for (int t = threadIdx.x; t < 3 * E3; t += NB) acc[t] = A(0);
+    for (int t = threadIdx.x; t < 3 * E3; t += NB) acc[t] = 0.0;
     if (threadIdx.x < 28) dcount[threadIdx.x] = 0;
     if (have_arr) {
 #pragma unroll
@@ -749,7 +752,7 @@ __global__ void __launch_bounds__(NB)
                 const int cell = (cl[2] * E + cl[1]) * E + cl[0];
                 for (int ax = 0; ax < 3; ++ax) {
                     const T slip = (uf[ax] - up[ax]) - a.g_dt[ax];
-                    atomicAdd(&acc[ax * E3 + cell], (A)(coef * slip));
+                    atomicAdd(&acc[ax * E3 + cell], (double)(coef * slip));
                 }
             }
 
@@ -977,12 +980,12 @@ __global__ void __launch_bounds__(NB)
 #pragma unroll
         for (int u = 0; u < NF; ++u) {
             const int t = threadIdx.x + u * NB;
-            if (t < 3 * E3) src_c[t] = old[u] + acc[t];
+            if (t < 3 * E3) src_c[t] = (A)(old[u] + acc[t]);
         }
         if (!add && threadIdx.x == 0) a.written[c] = 1;
     } else if (a.deposit) {
         for (int t = threadIdx.x; t < 3 * E3; t += NB) {
-            const A v = acc[t];
+            const A v = (A)acc[t];
             if (v != A(0)) atomicAdd(src_c + t, v);
         }
     }
