@@ -185,11 +185,13 @@ st_status st_get_particles(st_ctx *ctx, double *x, double *up, double *d,
  * dL/du (device, [3][n2][n1][n0] binary64; the sum over the taped steps'
  * fields, which are one tensor when every step used the same field) and
  * dL/dd (device, [count] binary64, by id; may be NULL when count is 0).
- * Checkpoints are restored and
- * the steps between them recomputed.  The tape is consumed; its checkpoint
- * buffers and the call's workspace (about tape + 1 copies of the particle
- * store, plus the adjoint records: 8 values of the state precision per
- * particle and per slot) stay allocated for the next taped run until
+ * The states of the steps between checkpoints are kept by the forward run, one
+ * more copy of the store each, up to 2 GiB in all and while device memory
+ * lasts; where they are not kept, the checkpoint is restored and the steps
+ * after it recomputed.  The tape is consumed; its checkpoint and state buffers
+ * and the call's workspace (the adjoint records: 8 values of the state precision
+ * per particle and per slot; where steps are recomputed, about tape copies of
+ * the particle store more) stay allocated for the next taped run until
  * st_tape_clear or st_destroy.  Returns when the results are written and the
  * store holds the state the taped run ended in (the call synchronises
  * hip_stream); after a HIP error the store's contents are undefined.
@@ -203,8 +205,8 @@ st_status st_tape_clear(st_ctx *ctx);
 
 /* Outside the paper (see st_backward).  Allocates ahead of time what a taped
  * run of `substeps` sub-steps with a checkpoint every `tape` sub-steps and
- * its st_backward need (the checkpoint buffers and the backward's workspace,
- * for the particles held now), so that neither st_step nor st_backward
+ * its st_backward need (the checkpoint and state buffers and the backward's
+ * workspace, for the particles held now), so that neither st_step nor st_backward
  * allocates during that run: for callers that time or capture it.  The
  * buffers are kept like those of a consumed tape (released by st_tape_clear
  * or st_destroy).  ST_ERR_INVALID for tape <= 0, substeps < 0 or the FP32

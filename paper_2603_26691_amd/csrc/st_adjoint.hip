@@ -20,8 +20,14 @@
 // (zero slip contributes no Re term).
 // The cell c0 and the periodic wrap are piecewise constant (zero derivative).
 //
-// Checkpoints of the particle store are kept every `tape_every` taped steps;
-// each segment is recomputed from its checkpoint (deposit off), each step
+// Checkpoints of the particle store are kept every `tape_every` taped steps,
+// and, up to a bound in memory, the states of the steps between them, as the
+// forward run's own step kernel streams them.  A segment with all its steps'
+// states is reversed from these, and consecutive such segments share the
+// anchors of the newest one's checkpoint (below), looked up by particle id (the
+// records by id itself would be scattered over the whole array: 69 us a step
+// against 55 us on 1e6 particles; in a recomputed segment, whose
+// ids are the anchors, 45 us).  Any other segment is recomputed from its checkpoint (deposit off), each step
 // saving the state it starts from, the ids and its layout as it streams
 // them, and then reversed newest first (the newest from the store itself).
 // The per-particle adjoint state is kept in one record of eight values of
@@ -57,6 +63,8 @@ struct AdjArgs {
     T *adj;                  // adjoint records by anchor, [nrec][8]: xbar[3], ubar[3], dbar, unused
     double *Ubar;            // dL/du [3][n2][n1][n0]
     double *tacc;            // per-chunk tile sums of dL/du over the steps, [C][3][S3], or null
+    const int32_t *anchor;   // anchors by id of the saved ids, or null (these are anchors)
+    int64_t nids;            // particles
     int64_t nrec;            // records (the store's slots)
     Params p;
     double dt;
@@ -131,6 +139,14 @@ __device__ __forceinline__ void stencil(const double (&xi)[3], int (&i0)[3], dou
         i0[ax] = min(max((int)fl, -1), E - 1);
         fr[ax] = sx - fl;
     }
+}
+
+// the anchor of a saved slot's particle
+template <class T>
+__device__ __forceinline__ int64_t anchor_of(const AdjArgs<T> &a, int32_t id)
+{
+    if (!a.anchor) return id;
+    return id >= 0 && id < a.nids ? a.anchor[id] : -1;
 }
 
 // The reverse of one particle's step.  st: its saved state (chunk-local
@@ -284,7 +300,7 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
             const int64_t q = q0 + threadIdx.x + (int64_t)u * kAdjBlock;
             an[u] = -1;
             if (u < np && q < s1) {
-                an[u] = V.id[q];
+                an[u] = anchor_of(a, V.id[q]);
                 st[u][0] = V.ox[q];
                 st[u][1] = V.oy[q];
                 st[u][2] = V.oz[q];
@@ -360,9 +376,9 @@ __global__ void k_fold_tiles(const double *tacc, Params p, int64_t C, double *Ub
 }
 
 // Nearest grid point: the reverse of each particle adds its ufbar to its
-// cell of the tile with one LDS atomic per component, in the state
-// precision; per chunk each tile cell's sum goes to the chunk's binary64 tile
-// sums (or, for a chunk split over several items, to dL/du with one atomic).
+// cell of the tile with one LDS atomic per component, in binary64 (LDS adds of
+// binary32 values take longer on this chip); per chunk each tile cell's
+// sum goes to the chunk's binary64 tile sums (or, for a chunk split over several items, to dL/du with one atomic).
 template <class T, int E>
 __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
 {
@@ -370,7 +386,7 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     constexpr int S3 = S * S * S;
     constexpr int E3 = E * E * E;
     __shared__ T tile[3 * S3];
-    __shared__ T ubt[3 * S3];
+    __shared__ double ubt[3 * S3];
 
     const int64_t item = blockIdx.x;
     if (item >= *a.nitems) return;
@@ -384,11 +400,11 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     const int64_t ncell = (int64_t)p.n[0] * p.n[1] * p.n[2];
 
     stage_tile<T, E, kAdjBlock>(p, a.u, cx, cy, cz, tile);
-    for (int t = threadIdx.x; t < 3 * S3; t += kAdjBlock) ubt[t] = T(0);
+    for (int t = threadIdx.x; t < 3 * S3; t += kAdjBlock) ubt[t] = 0.0;
     __syncthreads();
     const double *lam = a.lamC + c * 3 * E3;
     for (int64_t q = s0 + threadIdx.x; q < s1; q += kAdjBlock) {
-        const int64_t an = V.id[q];
+        const int64_t an = anchor_of(a, V.id[q]);
         const T st[7] = {V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q]};
         if (!adj_live(an, a.nrec, st)) continue;
         double rc[7];
@@ -396,7 +412,7 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
         double ufb[3], fr[3];
         int i0[3], t0;
         reverse_particle<T, E, false>(p, a.dt, tile, lam, st, rc, ufb, i0, fr, t0);
-        for (int comp = 0; comp < 3; ++comp) atomicAdd(&ubt[comp * S3 + t0], (T)ufb[comp]);
+        for (int comp = 0; comp < 3; ++comp) atomicAdd(&ubt[comp * S3 + t0], ufb[comp]);
         T *rec = a.adj + 8 * an;
         for (int k = 0; k < 7; ++k) rec[k] = (T)rc[k];
     }
@@ -405,7 +421,7 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     // steps; a chunk split over several items adds them to dL/du atomically
     const bool own = a.tacc != nullptr && run.k == 1;
     for (int t = threadIdx.x; t < 3 * S3; t += kAdjBlock) {
-        const double v = (double)ubt[t];
+        const double v = ubt[t];
         if (own) {
             a.tacc[c * 3 * S3 + t] += v;
         } else if (v != 0.0) {
@@ -457,17 +473,19 @@ __device__ __forceinline__ bool ck_particle(int32_t id, int64_t count, T ox, T d
 
 // The checkpoint's particles, a workgroup per container.  Mode bits: kAnchor
 // replaces the restored store's ids by anchors (every other slot of a run
-// gets -1), kToAnchor takes each particle's record from the array by id into
+// gets -1), kMap writes each particle's anchor by its id, kToAnchor takes each
+// particle's record from the array by id into
 // the array by anchor, kToId puts it back.  With a second checkpoint (ok,
 // the neighbouring segment's), only the particles that it does not hold at
 // the same slot of the same chunk's run move: their records change place
 // between the two segments' arrays by anchor, which are one array, so the
 // others' records are already where the next segment reads them.
-constexpr int kAnchor = 1, kToAnchor = 2, kToId = 4;
+constexpr int kAnchor = 1, kToAnchor = 2, kToId = 4, kMap = 8;
 template <class T>
 __global__ void k_checkpoint_records(const char *ck, const char *ok, SnapLayout L, int64_t slots,
                                      int64_t count, int32_t *id0, int32_t *id1,
-                                     const int32_t *flags, T *by_id, T *rec, int mode)
+                                     const int32_t *flags, T *by_id, T *rec, int32_t *map,
+                                     int mode)
 {
     int32_t *const store_id = flags[F_CUR] ? id1 : id0;
     const T *ox = reinterpret_cast<const T *>(ck + L.state);
@@ -489,6 +507,7 @@ __global__ void k_checkpoint_records(const char *ck, const char *ok, SnapLayout 
             const int32_t k = sid[q];
             const bool live = ck_particle(k, count, ox[q], d[q]);
             if (mode & kAnchor) store_id[q] = live ? (int32_t)q : -1;
+            if ((mode & kMap) && live) map[k] = (int32_t)q;
             if (!live || !(mode & (kToAnchor | kToId))) continue;
             if (ok && q >= p0 && q < p1 && o_sid[q] == k && ck_particle(k, count, o_ox[q], o_d[q]))
                 continue;   // the same slot in both
@@ -509,14 +528,14 @@ __global__ void k_checkpoint_records(const char *ck, const char *ok, SnapLayout 
 }
 
 template <class T>
-hipError_t launch_checkpoint_records(st_ctx *c, const char *ck, const char *ok, T *by_id,
-                                     T *rec, int mode, hipStream_t s)
+hipError_t launch_checkpoint_records(st_ctx *c, const char *ck, const char *ok, void *by_id,
+                                     void *rec, int32_t *map, int mode, hipStream_t s)
 {
     const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
     const int64_t g = c->max_items < 16384 ? c->max_items : 16384;
     hipLaunchKernelGGL((k_checkpoint_records<T>), dim3(g), dim3(256), 0, s, ck, ok, L, c->slots,
                        c->count, (int32_t *)c->store[0][7], (int32_t *)c->store[1][7], c->flags,
-                       by_id, rec, mode);
+                       (T *)by_id, (T *)rec, map, mode);
     return hipGetLastError();
 }
 
@@ -532,7 +551,8 @@ __global__ void k_take_dbar(const T *adj, int64_t P, double *dd)
 
 template <class T>
 AdjArgs<T> adj_args(st_ctx *c, char *snap, const RunItem *runs, const int32_t *nruns,
-                    const TapeStep &ts, const double *lamC, T *adj, double *Ubar, double *tacc)
+                    const int32_t *anchor, const TapeStep &ts, const double *lamC, T *adj,
+                    double *Ubar, double *tacc)
 {
     AdjArgs<T> a;
     const SnapLayout L = snap_layout(c->slots, c->tsize, c->C, c->max_items);
@@ -556,6 +576,8 @@ AdjArgs<T> adj_args(st_ctx *c, char *snap, const RunItem *runs, const int32_t *n
     a.adj = adj;
     a.Ubar = Ubar;
     a.tacc = tacc;
+    a.anchor = anchor;
+    a.nids = c->count;
     a.nrec = c->slots;
     a.p = c->prm;
     a.dt = ts.dt;
@@ -588,17 +610,17 @@ hipError_t launch_adjoint_step(st_ctx *c, const AdjArgs<T> &a, hipStream_t s)
 
 namespace {
 
-// One workspace, kept in the context for the next call: the state the
-// forward run ended in, the saved states of one segment (K - 1 steps; the
-// newest is the store itself), dL/dS by chunk, the adjoint records by id and
-// those of the current segment by anchor, and the per-chunk tile sums of
-// dL/du when they fit in a GiB (else each step adds its sums to dL/du
-// atomically).
+// One workspace, kept in the context for the next call: dL/dS by chunk, the
+// adjoint records by id and by anchor, the anchors by id, and the per-chunk tile
+// sums of dL/du when they fit in a GiB (else each step adds its sums to dL/du
+// atomically); and for segments to be recomputed the state the forward run
+// ended in and the saved states of one segment (K - 1 steps; the newest is
+// the store itself).
 struct BwdLayout {
-    size_t step_bytes, o_steps, o_lam, o_rid, o_adj, o_runs, o_tacc, tbytes, bytes;
+    size_t step_bytes, o_steps, o_lam, o_rid, o_adj, o_map, o_runs, o_tacc, tbytes, bytes;
 };
 
-BwdLayout bwd_layout(const st_ctx *c, int64_t K)
+BwdLayout bwd_layout(const st_ctx *c, int64_t K, bool recompute)
 {
     auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
     const int64_t P = c->count;
@@ -606,12 +628,13 @@ BwdLayout bwd_layout(const st_ctx *c, int64_t K)
     const int64_t S3 = (int64_t)(c->prm.E + 2) * (c->prm.E + 2) * (c->prm.E + 2);
     const size_t rbytes = 8 * c->tsize;   // a record: eight state-precision values
     BwdLayout W;
-    W.step_bytes = up256(snapshot_bytes(c));
+    W.step_bytes = recompute ? up256(snapshot_bytes(c)) : 0;
     W.o_steps = W.step_bytes;
     W.o_lam = W.o_steps + (size_t)(K > 1 ? K - 1 : 0) * W.step_bytes;
     W.o_rid = W.o_lam + up256((size_t)c->C * 3 * E3 * 8);
     W.o_adj = W.o_rid + up256((size_t)(P > 0 ? P : 1) * rbytes);
-    W.o_runs = W.o_adj + up256((size_t)c->slots * rbytes);
+    W.o_map = W.o_adj + up256((size_t)c->slots * rbytes);
+    W.o_runs = W.o_map + up256((size_t)(P > 0 ? P : 1) * 4);
     W.o_tacc = W.o_runs + up256((size_t)c->max_items * sizeof(RunItem) + 4);
     W.tbytes = (size_t)c->C * 3 * S3 * 8;
     if (W.tbytes > ((size_t)1 << 30)) W.tbytes = 0;
@@ -630,12 +653,22 @@ hipError_t ensure_bwd_workspace(st_ctx *c, const BwdLayout &W)
     return block_alloc(c->device, W.bytes, &c->bwd_ws);
 }
 
+// whether every step of a segment has its state: the first the checkpoint, the
+// others one of their own
+bool segment_saved(const st_ctx *c, int64_t sg)
+{
+    const int64_t K = c->tape_every, n = (int64_t)c->tape.size();
+    for (int64_t k = sg * K + 1; k < std::min((sg + 1) * K, n); ++k)
+        if (!c->saved[(size_t)k].buf) return false;
+    return true;
+}
+
 }  // namespace
 
-hipError_t reserve_backward(st_ctx *c, int64_t K)
+hipError_t reserve_backward(st_ctx *c, int64_t K, bool recompute)
 {
     if (K <= 0) return hipErrorInvalidValue;
-    return ensure_bwd_workspace(c, bwd_layout(c, K));
+    return ensure_bwd_workspace(c, bwd_layout(c, K, recompute));
 }
 
 hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd, hipStream_t s)
@@ -647,8 +680,19 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
     const int64_t P = c->count;
     const int64_t ncell = (int64_t)c->prm.n[0] * c->prm.n[1] * c->prm.n[2];
 
-    const BwdLayout W = bwd_layout(c, K);
+    auto recomputes = [&]() {
+        for (int64_t sg = 0; sg < nseg; ++sg)
+            if (!segment_saved(c, sg)) return true;
+        return false;
+    };
+    bool recompute = recomputes();
+    BwdLayout W = bwd_layout(c, K, recompute);
     hipError_t e0 = ensure_bwd_workspace(c, W);
+    if (e0 == hipErrorOutOfMemory && drop_saved(c)) {   // room for the recomputation instead
+        recompute = recomputes();
+        W = bwd_layout(c, K, recompute);
+        e0 = ensure_bwd_workspace(c, W);
+    }
     if (e0 != hipSuccess) return e0;
     char *ws = (char *)c->bwd_ws.buf;
     void *final_state = ws;
@@ -657,6 +701,7 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
     void *rid = ws + W.o_rid;
     void *adj = ws + W.o_adj;
     double *tacc = W.tbytes ? (double *)(ws + W.o_tacc) : nullptr;
+    int32_t *map = (int32_t *)(ws + W.o_map);
     RunItem *runs = (RunItem *)(ws + W.o_runs);
     int32_t *nruns = (int32_t *)(runs + c->max_items);
     const bool fp64 = c->form == ST_FORM_FP64;
@@ -667,7 +712,8 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
         return err;
     };
     // keep the state the forward run ended in
-    hipError_t e = launch_snapshot(c, final_state, 0, s);
+    hipError_t e = hipSuccess;
+    if (recompute) e = launch_snapshot(c, final_state, 0, s);
     if (e != hipSuccess) return fail(e);
     hipLaunchKernelGGL(k_lambda_to_chunks, dim3(grid_of(3 * ncell)), dim3(256), 0, s, lam, c->prm,
                        lamC);
@@ -680,20 +726,51 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
     e = hipGetLastError();
     if (e != hipSuccess) return fail(e);
 
+    // the records of a checkpoint's particles between the two arrays
+    auto records = [&](const char *ck, const char *ok, int mode) {
+        return fp64 ? launch_checkpoint_records<double>(c, ck, ok, rid, adj, map, mode, s)
+                    : launch_checkpoint_records<float>(c, ck, ok, rid, adj, map, mode, s);
+    };
+    // the reverse of step k from its saved state (null: the store)
+    auto reverse = [&](char *snap, const int32_t *anchor, int64_t k) {
+        const TapeStep &ts = c->tape[(size_t)k];
+        return fp64 ? launch_adjoint_step<double>(
+                          c, adj_args<double>(c, snap, runs, nruns, anchor, ts, lamC, (double *)adj,
+                                              dU, tacc), s)
+                    : launch_adjoint_step<float>(
+                          c, adj_args<float>(c, snap, runs, nruns, anchor, ts, lamC, (float *)adj,
+                                             dU, tacc), s);
+    };
+    const char *group = nullptr;   // the checkpoint whose anchors a run of saved segments uses
     for (int64_t sg = nseg - 1; sg >= 0; --sg) {
         const int64_t k0 = sg * K, k1 = std::min(k0 + K, ntape);
+        if (segment_saved(c, sg)) {
+            if (!group) {   // the newest of some
+                group = (const char *)c->snaps[(size_t)sg].buf;
+                e = records(group, nullptr, kMap | kToAnchor);
+            }
+            for (int64_t k = k1 - 1; k >= k0 && e == hipSuccess; --k)
+                e = reverse((char *)(k == k0 ? c->snaps[(size_t)sg] : c->saved[(size_t)k]).buf, map,
+                            k);
+            if (e == hipSuccess && (sg == 0 || !segment_saved(c, sg - 1))) {
+                e = records(group, nullptr, kToId);
+                group = nullptr;
+            }
+            if (e != hipSuccess) return fail(e);
+            continue;
+        }
         // the checkpoint, with anchors in place of its ids, and the records of
         // its particles by anchor (those the later checkpoint held at the
         // same slot are there already)
         const char *ck = (const char *)c->snaps[(size_t)sg].buf;
-        const char *later = sg + 1 < nseg ? (const char *)c->snaps[(size_t)sg + 1].buf : nullptr;
-        const char *earlier = sg > 0 ? (const char *)c->snaps[(size_t)sg - 1].buf : nullptr;
+        auto neighbour = [&](int64_t o) {   // a recomputed one
+            return o >= 0 && o < nseg && !segment_saved(c, o)
+                       ? (const char *)c->snaps[(size_t)o].buf : nullptr;
+        };
+        const char *later = neighbour(sg + 1), *earlier = neighbour(sg - 1);
         e = launch_snapshot(c, c->snaps[(size_t)sg].buf, 1, s);
         if (e != hipSuccess) return fail(e);
-        e = fp64 ? launch_checkpoint_records<double>(c, ck, later, (double *)rid, (double *)adj,
-                                                     kAnchor | kToAnchor, s)
-                 : launch_checkpoint_records<float>(c, ck, later, (float *)rid, (float *)adj,
-                                                    kAnchor | kToAnchor, s);
+        e = records(ck, later, kAnchor | kToAnchor);
         if (e != hipSuccess) return fail(e);
         // recompute the segment, each step saving what its reverse reads; the
         // last step's start is the store itself, reversed from there
@@ -707,23 +784,12 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
         if (e == hipSuccess) e = launch_runs(c, runs, nruns, s);
         if (e != hipSuccess) return fail(e);
         for (int64_t k = k1 - 1; k >= k0; --k) {
-            char *snap = k + 1 < k1 ? (char *)step_buf(k - k0) : nullptr;
-            if (fp64)
-                e = launch_adjoint_step<double>(
-                    c, adj_args<double>(c, snap, runs, nruns, c->tape[(size_t)k], lamC,
-                                        (double *)adj, dU, tacc), s);
-            else
-                e = launch_adjoint_step<float>(
-                    c, adj_args<float>(c, snap, runs, nruns, c->tape[(size_t)k], lamC,
-                                       (float *)adj, dU, tacc), s);
+            e = reverse(k + 1 < k1 ? (char *)step_buf(k - k0) : nullptr, nullptr, k);
             if (e != hipSuccess) return fail(e);
         }
         // the records of the particles the earlier checkpoint does not hold at
         // the same slot (after the first segment, all) go to the array by id
-        e = fp64 ? launch_checkpoint_records<double>(c, ck, earlier, (double *)rid, (double *)adj,
-                                                     kToId, s)
-                 : launch_checkpoint_records<float>(c, ck, earlier, (float *)rid, (float *)adj,
-                                                    kToId, s);
+        e = records(ck, earlier, kToId);
         if (e != hipSuccess) return fail(e);
     }
     if (tacc) {
@@ -742,7 +808,7 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
                            (const float *)rid, P, dd);
     e = hipGetLastError();
     if (e != hipSuccess) return fail(e);
-    e = launch_snapshot(c, final_state, 1, s);
+    if (recompute) e = launch_snapshot(c, final_state, 1, s);
     if (e != hipSuccess) return fail(e);
     // the tape's buffers are handed back when this returns: finish first
     return hipStreamSynchronize(s);

@@ -29,7 +29,7 @@ namespace {
 // closed: 5.1 ms with an allocation per array (4.1 ms of them in hipFree), 22.6
 // ms in a process that has just freed large buffers; 1.1 ms with kept blocks.
 constexpr size_t kKeepBytes = (size_t)512 << 20;
-constexpr uint64_t kKeepFrees = 64;
+constexpr uint64_t kKeepFrees = 512;
 
 struct Kept {
     int device;
@@ -114,6 +114,30 @@ void block_free(int device, Block *b)
     (void)hipFree(mine.buf);
 }
 
+Block take_saved(st_ctx *c)
+{
+    Block b;
+    if (!c->saved_spare.empty()) {
+        b = c->saved_spare.back();
+        c->saved_spare.pop_back();
+    } else if (c->saved_bytes + snapshot_bytes(c) <= kSavedBytes) {
+        if (block_alloc(c->device, snapshot_bytes(c), &b) == hipSuccess) c->saved_bytes += b.bytes;
+        else (void)hipGetLastError();
+    }
+    return b;
+}
+
+bool drop_saved(st_ctx *c)
+{
+    const bool any = c->saved_bytes > 0;
+    if (!any || hipDeviceSynchronize() != hipSuccess) return false;
+    for (auto *v : {&c->saved, &c->saved_spare})
+        for (auto &b : *v) block_free(c->device, &b);
+    c->saved_spare.clear();
+    c->saved_bytes = 0;
+    return true;
+}
+
 }  // namespace st
 
 namespace {
@@ -178,7 +202,7 @@ hipError_t allocate(st_ctx *c, const std::vector<Wanted> &want, size_t &total)
 
 void free_all(st_ctx *c)
 {
-    for (auto *v : {&c->blocks, &c->snaps, &c->spare}) {
+    for (auto *v : {&c->blocks, &c->snaps, &c->spare, &c->saved, &c->saved_spare}) {
         for (auto &b : *v) st::block_free(c->device, &b);
         v->clear();
     }
@@ -466,19 +490,28 @@ st_status st_step(st_ctx *c, const void *u_cells, double dt, int32_t nsub, int32
         const double dts = dt / nsub;
         for (int32_t k = 0; k < nsub; ++k) {
             if (tape > 0) {
-                if (c->tape.size() % (size_t)c->tape_every == 0) {
+                st::Block state;   // the step's, for the reverse
+                const size_t pos = c->tape.size() % (size_t)c->tape_every;
+                if (pos == 0) {
                     st::Snapshot sn;
                     if (!c->spare.empty()) {   // a buffer of a consumed tape
                         sn = c->spare.back();
                         c->spare.pop_back();
                     } else {
                         hipError_t e = st::block_alloc(c->device, st::snapshot_bytes(c), &sn);
+                        if (e == hipErrorOutOfMemory && st::drop_saved(c))
+                            e = st::block_alloc(c->device, st::snapshot_bytes(c), &sn);
                         if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_step: checkpoint");
                     }
                     c->snaps.push_back(sn);
                     ST_HIP(st::launch_snapshot(c, sn.buf, 0, s));
+                } else if (pos == 1 || c->saved.back().buf) {   // a segment's states, or none
+                    state = st::take_saved(c);
                 }
+                c->saved.push_back(state);
                 c->tape.push_back(st::TapeStep{u_cells, dts});
+                ST_HIP(st::launch_step(c, u_cells, dts, 1, s, state.buf));
+                continue;
             }
             ST_HIP(st::launch_step(c, u_cells, dts, 1, s));
         }
@@ -563,6 +596,10 @@ void tape_reset(st_ctx *c, bool keep_buffers)
         c->spare.clear();
         st::block_free(c->device, &c->bwd_ws);
     }
+    for (auto &b : c->saved)
+        if (b.buf) c->saved_spare.push_back(b);
+    c->saved.clear();
+    if (!keep_buffers) (void)st::drop_saved(c);
     c->tape.clear();
     c->tape_every = 0;
 }
@@ -594,7 +631,17 @@ st_status st_tape_reserve(st_ctx *c, int32_t tape, int64_t substeps)
                 return fail(c, ST_ERR_OOM, "st_tape_reserve: checkpoint");
             c->spare.push_back(sn);
         }
-        if (st::reserve_backward(c, tape) != hipSuccess)
+        // the states of the steps between the checkpoints, as far as they are kept
+        const int64_t between = substeps - need;
+        while ((int64_t)c->saved_spare.size() < between) {
+            std::vector<st::Block> held;
+            held.swap(c->saved_spare);
+            const st::Block b = st::take_saved(c);
+            held.swap(c->saved_spare);
+            if (!b.buf) break;
+            c->saved_spare.push_back(b);
+        }
+        if (st::reserve_backward(c, tape, (int64_t)c->saved_spare.size() < between) != hipSuccess)
             return fail(c, ST_ERR_OOM, "st_tape_reserve: backward workspace");
         return ST_OK;
     } catch (...) {

@@ -304,8 +304,8 @@ struct StepArgs {
     int32_t *flags, *spread;
     int32_t whole;           // inboxes hold whole rooms
     int32_t deposit;         // 0: move and re-bin only (tape recompute)
-    // tape recompute: what the reverse of the step reads, saved into a
-    // snapshot buffer at the store's slot indices: the state each slot
+    // taped steps and their recomputation: what the reverse of the step reads,
+    // saved into a snapshot buffer at the store's slot indices: the state each slot
     // starts the step with, its id, and the containers' runs
     T *sv[7];
     int32_t *sid;
@@ -1699,7 +1699,12 @@ hipError_t launch_step_n(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
     const int64_t grid = (c->max_items + round - 1) / round * round;
     if constexpr (sizeof(A) == 8) {   // only the forms that tape save
         if (a.sv[0]) {
-            hipLaunchKernelGGL((k_step<T, A, E, I, D, true, NB>), dim3(grid), dim3(NB), 0, s, a);
+            if (ev[0])
+                hipExtLaunchKernelGGL((k_step<T, A, E, I, D, true, NB>), dim3(grid), dim3(NB), 0,
+                                      s, ev[0], ev[1], 0, a);
+            else
+                hipLaunchKernelGGL((k_step<T, A, E, I, D, true, NB>), dim3(grid), dim3(NB), 0, s,
+                                   a);
             return hipGetLastError();
         }
     }

@@ -233,6 +233,10 @@ struct st_ctx {
     // (the state at the end of the forward run, the saved states of one
     // segment, the adjoint records and dL/dS by chunk)
     std::vector<st::Snapshot> spare;
+    // the states of the taped steps between checkpoints, by step (no buffer:
+    // not kept), and buffers for them from a consumed tape; their bytes in all
+    std::vector<st::Block> saved, saved_spare;
+    size_t saved_bytes = 0;
     st::Block bwd_ws;
 
     // coupled run
@@ -283,7 +287,13 @@ hipError_t launch_zero_f64(double *p, int64_t n, hipStream_t s);
 size_t snapshot_bytes(const st_ctx *c);
 hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd, hipStream_t s);
 // allocates st_backward's workspace for checkpoints every K sub-steps, if smaller
-hipError_t reserve_backward(st_ctx *c, int64_t K);
+hipError_t reserve_backward(st_ctx *c, int64_t K, bool recompute);
+// A buffer for one more taped step's state, or none when they would take more
+// than kSavedBytes or memory has run out.
+constexpr size_t kSavedBytes = (size_t)2 << 30;
+Block take_saved(st_ctx *c);
+// Gives all of them up (their steps are recomputed); whether there were any.
+bool drop_saved(st_ctx *c);
 hipError_t launch_hilbert_positions(int32_t order, int64_t nseg, int64_t seg_begin,
                                     int64_t per_seg, const double L[3], int64_t first, int64_t n,
                                     const double *u, double *x, hipStream_t s);
