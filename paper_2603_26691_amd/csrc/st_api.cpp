@@ -412,8 +412,11 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
         if (on_device) {
             ST_HIP(st::launch_zero_i32(c->flags + st::F_BADINPUT, 1, s));
         }
-        // the staging area is the inboxes' memory
-        if (c->pending == 0) ST_HIP(st::launch_settle(c, s));
+        // the staging area is the inboxes' memory, or the store while it is empty
+        if (c->pending == 0) {
+            c->stage_in_store = c->count == 0;
+            if (c->count > 0) ST_HIP(st::launch_settle(c, s));
+        }
         const int64_t stage_batch = std::min<int64_t>(c->mcap, 1 << 22);
         if (!on_device && !c->stage64.buf) {
             size_t bytes = (size_t)stage_batch * 7 * 8;
@@ -423,11 +426,15 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
         const int64_t pend0 = c->pending, id0 = c->next_id, count0 = c->count;
         int64_t done = 0;
         while (done < n) {
-            if (c->pending == c->mcap) {
+            // (an empty store's 7 slots / 8 records are more than the capacity)
+            int64_t room = c->stage_in_store ? c->slots / 8 * 7 : c->mcap;
+            if (c->pending >= room) {
                 st_status r = ensure_flushed(c, s);
                 if (r != ST_OK) return r;
+                c->stage_in_store = 0;
+                room = c->mcap;
             }
-            int64_t k = std::min<int64_t>(n - done, c->mcap - c->pending);
+            int64_t k = std::min<int64_t>(n - done, room - c->pending);
             if (!on_device) k = std::min<int64_t>(k, stage_batch);
             const double *xs = x + 3 * done, *us = up + 3 * done, *ds = d + done;
             if (!on_device) {
@@ -462,6 +469,8 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
                             "st_inject: non-finite value or d <= 0 (partially injected)");
             }
         }
+        // no more than the inboxes' memory holds is left for the next call to place
+        if (c->stage_in_store && c->pending > c->mcap) return ensure_flushed(c, s);
         return ST_OK;
     } catch (...) {
         return fail(c, ST_ERR_OOM, "st_inject: host allocation failed");

@@ -1046,13 +1046,68 @@ __device__ __forceinline__ void put_slot(const View<T> &V, int64_t q, const Move
     V.id[q] = r.id;
 }
 
+// Records in a store's arrays: seven arrays of slots T, each a run of slots / 8
+// records of eight T, together at least 7/8 * 5/4 of the capacity.
+template <class T>
+struct RecordArrays {
+    View<T> W;
+    int64_t per;   // records per array
+
+    __device__ __forceinline__ RecordArrays(const View<T> &v, int64_t slots) : W(v), per(slots / 8)
+    {
+    }
+    __device__ __forceinline__ MoverRec<T> *at(int64_t k) const
+    {
+        T *const a[7] = {W.ox, W.oy, W.oz, W.vx, W.vy, W.vz, W.d};
+        T *b = a[0];
+        int64_t j = k;
+#pragma unroll
+        for (int i = 1; i < 7; ++i)
+            if (k >= i * per) {
+                b = a[i];
+                j = k - i * per;
+            }
+        return reinterpret_cast<MoverRec<T> *>(b) + j;
+    }
+};
+
+// Where injections are staged: the inboxes' memory (no arrivals wait there
+// then), or, while no particle has been placed, the empty store's own arrays,
+// which hold them all, so that a first load in one call takes one re-bin (3e6
+// droplets: 0.45 to 0.12 ms).  Their chunks beside them (the store's id array).
+template <class T>
+struct Staging {
+    Views<T> V;
+    const int32_t *flags;
+    MoverRec<T> *rec;
+    int32_t *dest;
+    int64_t slots;
+    int32_t in_store;
+};
+template <class T>
+struct StagingAt {
+    RecordArrays<T> own;
+    MoverRec<T> *rec;
+    int32_t *dest;
+    bool in_store;
+    __device__ __forceinline__ explicit StagingAt(const Staging<T> &s)
+        : own(s.V.pick(s.flags[F_CUR]), s.slots), rec(s.rec), in_store(s.in_store != 0)
+    {
+        dest = in_store ? own.W.id : s.dest;
+    }
+    __device__ __forceinline__ MoverRec<T> *at(int64_t k) const
+    {
+        return in_store ? own.at(k) : rec + k;
+    }
+};
+
 template <class T>
 struct ScatterArgs {
     Views<T> V;
     const Cont *cont0, *cont1;
-    const MoverRec<T> *rec;  // inboxes [2][nrec], or staged injections
+    const MoverRec<T> *rec;  // inboxes [2][nrec]
     int64_t nrec;
-    const int32_t *dest;     // chunks of the staged injections
+    Staging<T> staged;
     int64_t npend;           // staged injections (then no inbox holds any)
     const int4 *lay;
     int32_t *cursor;
@@ -1143,6 +1198,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
             put_slot(W, slot_of_rank(l, in0 + r), rec[me.ibase + r]);
         __syncthreads();
     }
+    const StagingAt<T> staged(a.staged);
     for (int64_t r0 = (int64_t)blockIdx.x * kTile; r0 < a.npend;
          r0 += (int64_t)gridDim.x * kTile) {
         int32_t cn[kTilePer], rank[kTilePer];
@@ -1154,7 +1210,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
 #pragma unroll
         for (int j = 0; j < kTilePer; ++j) {
             const int64_t r = r0 + j * kScatterBlock + threadIdx.x;
-            cn[j] = r < a.npend ? a.dest[r] : -1;
+            cn[j] = r < a.npend ? staged.dest[r] : -1;
             rank[j] = cn[j] < 0 ? 0
                                 : atomicAdd(a.C <= kHistMax ? &hist[cn[j]] : &a.cursor[cn[j]], 1);
         }
@@ -1169,7 +1225,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
             if (cn[j] < 0) continue;
             if (a.C <= kHistMax) rank[j] += hist[cn[j]];
             put_slot(W, slot_of_rank(a.lay[cn[j]], rank[j]),
-                     a.rec[r0 + j * kScatterBlock + threadIdx.x]);
+                     *staged.at(r0 + j * kScatterBlock + threadIdx.x));
         }
     }
     // a chunk of several containers adds to its sources atomically: those that
@@ -1273,9 +1329,9 @@ __global__ void __launch_bounds__(256) k_runs(const Cont *cont0, const Cont *con
 // ---------------------------------------------------------------------------
 template <class T>
 __global__ void k_stage(int64_t n, const double *x, const double *up, const double *d,
-                        int64_t at, int64_t id0, Params p, MoverRec<T> *rec, int32_t *dest,
-                        int32_t *flags)
+                        int64_t at, int64_t id0, Params p, Staging<T> to, int32_t *flags)
 {
+    const StagingAt<T> staged(to);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         bool ok = true;
@@ -1310,9 +1366,9 @@ __global__ void k_stage(int64_t n, const double *x, const double *up, const doub
             if (!isfinite(v[a])) ok = false;
         if (!isfinite(dd) || !(dd > 0.0)) ok = false;
         const int64_t m = at + i;
-        rec[m] = MoverRec<T>{loc[0], loc[1], loc[2], (T)v[0], (T)v[1], (T)v[2], (T)dd,
+        *staged.at(m) = MoverRec<T>{loc[0], loc[1], loc[2], (T)v[0], (T)v[1], (T)v[2], (T)dd,
                                 (int32_t)(id0 + i)};
-        dest[m] = (int32_t)chunk_index(p, ch[0], ch[1], ch[2]);
+        staged.dest[m] = (int32_t)chunk_index(p, ch[0], ch[1], ch[2]);
         if (!ok) flags[F_BADINPUT] = 1;
     }
 }
@@ -1329,14 +1385,16 @@ __global__ void k_clear_staged(Cont *cont0, Cont *cont1, const int32_t *flags)
 
 // Adds the staged injections to the inbox counts of their chunks' first
 // containers (a full re-bin's layout counts a chunk's particles from these).
+template <class T>
 __global__ void __launch_bounds__(kScatterBlock) k_count_staged(Cont *cont0, Cont *cont1,
                                                                 const int32_t *first0,
                                                                 const int32_t *first1,
                                                                 const int32_t *flags,
-                                                                const int32_t *dest, int64_t n,
-                                                                int64_t C)
+                                                                Staging<T> from, int64_t at,
+                                                                int64_t n, int64_t C)
 {
     __shared__ int32_t hist[kHistMax];
+    const int32_t *const dest = StagingAt<T>(from).dest + at;
     const int cur = flags[F_CUR], t = flags[F_TICK];
     Cont *const ct = cur ? cont1 : cont0;
     const int32_t *const first = cur ? first1 : first0;
@@ -1426,38 +1484,12 @@ __global__ void __launch_bounds__(256) k_get_particles(Store<T> st, Params p, in
 // Read-out of many particles in two passes: one scattered write per particle
 // (its record with its chunk, by id), then the records in id order into the
 // outputs, whole lines at a time.  The records lie in the re-bin's second
-// store, which holds nothing between re-bins: seven arrays of slots T, each a
-// run of slots / 8 records of eight T, together at least 7/8 * 5/4 of the
-// capacity.  1e7 binary32 particles, all outputs: 0.67 ms (0.075 ms clearing,
+// store, which holds nothing between re-bins.  1e7 binary32 particles, all outputs: 0.67 ms (0.075 ms clearing,
 // 0.38 ms the scattered records, 0.22 ms out), against 2.06 ms directly.
-template <class T>
-struct RecordArrays {
-    View<T> W;
-    int64_t per;   // records per array
-
-    __device__ __forceinline__ RecordArrays(const Store<T> &s, int64_t slots)
-        : W(s.V.pick(s.flags[F_CUR] ^ 1)), per(slots / 8)
-    {
-    }
-    __device__ __forceinline__ MoverRec<T> *at(int64_t k) const
-    {
-        T *const a[7] = {W.ox, W.oy, W.oz, W.vx, W.vy, W.vz, W.d};
-        T *b = a[0];
-        int64_t j = k;
-#pragma unroll
-        for (int i = 1; i < 7; ++i)
-            if (k >= i * per) {
-                b = a[i];
-                j = k - i * per;
-            }
-        return reinterpret_cast<MoverRec<T> *>(b) + j;
-    }
-};
-
 template <class T>
 __global__ void __launch_bounds__(256) k_records_clear(Store<T> st, int64_t slots, int64_t count)
 {
-    const RecordArrays<T> r(st, slots);
+    const RecordArrays<T> r(st.V.pick(st.flags[F_CUR] ^ 1), slots);
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < count) *r.at(k) = MoverRec<T>{T(0), T(0), T(0), T(0), T(0), T(0), T(0), -1};
 }
@@ -1465,7 +1497,7 @@ __global__ void __launch_bounds__(256) k_records_clear(Store<T> st, int64_t slot
 template <class T>
 __global__ void __launch_bounds__(256) k_records_by_id(Store<T> st, int64_t slots, int64_t count)
 {
-    const RecordArrays<T> to(st, slots);
+    const RecordArrays<T> to(st.V.pick(st.flags[F_CUR] ^ 1), slots);
     const Current<T> S(st);
     each_particle(S, [&](int32_t c, MoverRec<T> r) {
         const int64_t k = r.id;
@@ -1484,7 +1516,7 @@ __global__ void __launch_bounds__(256) k_records_out(Store<T> st, int64_t slots,
     __shared__ double sx[768], su[768];
     __shared__ int32_t sc[768];
     __shared__ int there[256];
-    const RecordArrays<T> r(st, slots);
+    const RecordArrays<T> r(st.V.pick(st.flags[F_CUR] ^ 1), slots);
     const int64_t k0 = (int64_t)blockIdx.x * 256;
     const int64_t k = k0 + threadIdx.x;
     MoverRec<T> m;
@@ -1743,6 +1775,13 @@ hipError_t launch_step_e(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
                               : launch_step_d<T, A, E, 0>(c, a, s, ev);
 }
 
+template <class T>
+Staging<T> staging_of(st_ctx *c)
+{
+    return Staging<T>{views_of<T>(c), c->flags, (MoverRec<T> *)c->rec, c->stage_dest, c->slots,
+                      c->stage_in_store};
+}
+
 // everything after the step kernel (or, npend > 0, after staged injections):
 // the gate, and the full re-bin's scatter
 template <class T>
@@ -1757,7 +1796,7 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
                      dead_limit(c), npend == 0};
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
     const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
-                           (const MoverRec<T> *)c->rec, c->nrec, c->stage_dest, npend, c->lay,
+                           (const MoverRec<T> *)c->rec, c->nrec, staging_of<T>(c), npend, c->lay,
                            c->cursor, c->flags, c->C, c->whole_inbox, c->prm,
                            (int4 *)c->src,
                            (int32_t)(3 * c->prm.E * c->prm.E * c->prm.E * c->asize / 16),
@@ -1814,12 +1853,13 @@ hipError_t launch_settle(st_ctx *c, hipStream_t s)
 }
 
 namespace {
+template <class T>
 hipError_t count_staged(st_ctx *c, int64_t at, int64_t n, hipStream_t s)
 {
     if (n > 0) {
         const int64_t g = std::min<int64_t>((n + kTile - 1) / kTile, 512);
-        hipLaunchKernelGGL(k_count_staged, dim3(g), dim3(kScatterBlock), 0, s, c->cont[0],
-                           c->cont[1], c->first[0], c->first[1], c->flags, c->stage_dest + at, n,
+        hipLaunchKernelGGL((k_count_staged<T>), dim3(g), dim3(kScatterBlock), 0, s, c->cont[0],
+                           c->cont[1], c->first[0], c->first[1], c->flags, staging_of<T>(c), at, n,
                            c->C);
     }
     return hipGetLastError();
@@ -1917,8 +1957,8 @@ hipError_t launch_stage_inject(st_ctx *c, int64_t n, const double *x, const doub
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         hipLaunchKernelGGL((k_stage<T>), dim3(grid_for(n)), dim3(256), 0, s, n, x, up, d, at,
-                           c->next_id, c->prm, (MoverRec<T> *)c->rec, c->stage_dest, c->flags);
-        return count_staged(c, at, n, s);
+                           c->next_id, c->prm, staging_of<T>(c), c->flags);
+        return count_staged<T>(c, at, n, s);
     });
 }
 
@@ -1926,7 +1966,9 @@ hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s)
 {
     hipLaunchKernelGGL(k_clear_staged, dim3(grid_for(c->max_items)), dim3(256), 0, s, c->cont[0],
                        c->cont[1], c->flags);
-    return count_staged(c, 0, keep, s);
+    return dispatch(c, [&](auto t, auto) -> hipError_t {
+        return count_staged<decltype(t)>(c, 0, keep, s);
+    });
 }
 
 // The two-pass read-out from this many particles on (below it the outputs stay

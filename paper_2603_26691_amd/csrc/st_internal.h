@@ -215,6 +215,7 @@ struct st_ctx {
     void *rec = nullptr;       // [2][nrec] inboxes, by the tick's parity; also the
                                // staging area of injections
     int32_t *stage_dest = nullptr; // [mcap] chunks of the staged injections
+    int32_t stage_in_store = 0;    // they are staged in the (empty) store instead
     int32_t *cursor = nullptr;     // [C] scatter cursors of the full re-bin
     int32_t *new_cnt = nullptr;    // [C] particles per chunk at a full re-bin
     int4 *lay = nullptr;           // [C] its layout: first slot, per container, room, containers

@@ -140,3 +140,31 @@ def test_captured_step_replays():
     assert a.stats()["movers"] == b.stats()["movers"] > 0
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("P", [1000, 200_000])
+def test_first_load_in_parts(form, P):
+    """A first load in several injections (host and device arrays), staged in
+    the empty store, is the one in a single injection; so is one that follows
+    a flush, staged in the inboxes' memory over several re-bins."""
+    import torch
+    w = workload("tg32", n=(32, 16, 24), L=(0.1, 0.05, 0.075), P=P, noise=0.1)
+    x, up, d = w.particles()
+    up = np.random.default_rng(2).normal(0.0, 0.3, up.shape)
+    g = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    whole = tracker(w, form)
+    whole.inject(x, up, d)
+    want = state(whole)
+    for cuts, read in [([0, P // 3, P // 2, P], False), ([0, 10, P], True)]:
+        t = tracker(w, form)
+        for k, (a, b) in enumerate(zip(cuts, cuts[1:])):
+            part = (x[a:b], up[a:b], d[a:b])
+            t.inject(*(part if k % 2 else (g(v) for v in part)))
+            if read:
+                t.particles()      # places what is staged
+        got = state(t)
+        for key in want:
+            assert np.array_equal(got[key], want[key]), (cuts, key)
+        t.close()
+    whole.close()
