@@ -14,8 +14,8 @@
 //             read-modify-write (or one atomic, for chunks of several
 //             containers) per cell.  A mover's slot becomes a hole (binary32:
 //             an offset no particle has, written by the step's own store;
-//             binary64: its diameter negated, its state left in place).  The container's
-//             own arrivals of the step before are taken from its inbox into
+//             binary64: its diameter negated, its state left in place).  The
+//             container's own arrivals of the step before are taken from its inbox into
 //             the holes the stream passes, then past its last slot, where the
 //             step's own vector stores write them: no pass of their own, and
 //             no scattered writes but their diameters and ids;
@@ -335,14 +335,14 @@ __device__ __forceinline__ float sn_re_pow(float re2)
 }
 __device__ __forceinline__ double sn_re_pow(double re2) { return pow(re2, 0.3435); }
 
-// Workgroups are dispatched round-robin over the 8 XCDs.  Work items are
+// Workgroups are dispatched round-robin over the 8 XCDs.  Containers are
 // dealt to the XCDs in blocks of kXcdBlock consecutive items (neighbouring
 // chunks, which share halo cells through the XCD's L2), block j to XCD
-// j mod 8, so that every XCD gets a share of every region of the item list
+// j mod 8, so that every XCD gets a share of every region of their list
 // and of its work, however uneven the chunk occupancy.  A bijection of
-// [0, R), R the item count rounded up to whole rounds of 8 blocks; ids that
-// map past the items exit.  Blocks of 16 items measured best (1.8 % less
-// step-kernel time than 64 on 128^3; one item per block, the hardware's own
+// [0, R), R their number rounded up to whole rounds of 8 blocks; ids that
+// map past them exit.  Blocks of 16 measured best (1.8 % less
+// step-kernel time than 64 on 128^3; one container per block, the hardware's own
 // dealing, 7 % more).
 constexpr int64_t kXcdBlock = 16;
 __device__ __forceinline__ int64_t xcd_remap(int64_t bid)
@@ -354,7 +354,7 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid)
 // G consecutive values at a G*sizeof(T)-aligned address, as one 16-byte
 // access with the non-temporal hint: the particle state is streamed, read
 // once and written once per step, so it should not displace what the caches
-// hold (the tile, the counters, the mover lists).  Measured: 13 % less step
+// hold (the tile, the counters, the inboxes).  Measured: 13 % less step
 // kernel time on 1e7 particles, 11 % on 1.4e9.
 template <class T, int G>
 __device__ __forceinline__ void vld(const T *p, T (&v)[G])
@@ -450,6 +450,18 @@ static_assert(kRoomMax <= (1 << kSlotBits) && kMoverStage <= (1 << (32 - 1 - kSl
               "staged mover fields must fit one int32");
 static_assert(kDirBits * 4 <= 32, "direction classes of a group must fit one uint32");
 
+// Bound by HBM where the chunks are full: 13 streams of 16-byte accesses and
+// the records reach 4.5-4.9 TB/s of the 6.2 that a copy does (1e7 droplets on
+// 128^3: 138 us); by the chain of tile, flush and records where they are sparse
+// (1500 droplets a container, 4e8 on 512^3: 7.8 ms for 31 GB); and by that chain
+// alone on meshes that leave CUs idle.  The arrivals ride in the stream that the
+// container writes anyway: a pass of their own, eight scattered 4-byte writes
+// each, and the counts it needed took 10 + 7 of 153 us a step at 1e7 (148 now),
+// 4.9 + 4.7 of 53 at 777777 (33 now, the LDS sums in binary64 included) and 1.2
+// of 8.7 ms at 4e8.  Four workgroups share a CU in binary32 (40 KB of LDS, at
+// most 124 VGPRs); five without the prefetched group (32 KB, 95 VGPRs) were
+// slower (167 against 158 us a step with its sources), and fewer, larger
+// workgroups too, but for small meshes (launch_step_t).
 template <class T, class A, int E, int INTERP, int DRAG, bool SAVE, int NB>
 __global__ void __launch_bounds__(NB)
      k_step(StepArgs<T, A> a)
@@ -1127,15 +1139,20 @@ __device__ __forceinline__ int64_t slot_of_rank(const int4 &l, int32_t rank)
     return (int64_t)l.x + (int64_t)i * l.z + (rank - i * l.y);
 }
 
-constexpr int kScatterBlock = 256;
-constexpr int kScatterGroups = 2048;   // they run every step and usually exit at the gate
+// 512 threads: larger tiles take fewer reservations of a crowded chunk and
+// leave fewer partial lines, smaller workgroups hide more latency (tiles of
+// 2048, 4096 and, with 512 and 1024 threads, 8192 and 16384 droplets: 321, 203,
+// 187 and 211 us of scatter for 3e6; a re-bin of 4e8: 28.0 ms at 256 threads,
+// 25.2 at 512, 29.3 at 1024).
+constexpr int kScatterBlock = 512;
+constexpr int kScatterGroups = 1024;   // they run every step and usually exit at the gate
 
 // Staged injections per chunk are counted, and placed, in tiles of kTile per
 // workgroup through LDS counters of every chunk while there are at most
 // kHistMax chunks, so that the counter of a crowded chunk is taken once per
 // tile: device atomics on one address are served one after the other (8 x
-// 375e3 droplets in two plumes on 1728 chunks: 0.53 ms a count and 0.57 ms a
-// scatter with an atomic per droplet).  With more chunks the counters are
+// 375e3 droplets in two plumes on 1728 chunks: 8 x 0.53 ms of counts and 8 x
+// 0.57 ms of scatters with an atomic per droplet, 16 and 187 us in all now).  With more chunks the counters are
 // less crowded, and a droplet takes its own atomic.
 constexpr int kHistMax = 8192;
 constexpr int kTilePer = 16, kTile = kTilePer * kScatterBlock;
@@ -1216,8 +1233,26 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
         }
         if (a.C <= kHistMax) {
             __syncthreads();
-            for (int32_t i = threadIdx.x; i < a.C; i += kScatterBlock)
-                if (hist[i]) hist[i] = atomicAdd(&a.cursor[i], hist[i]);
+            // a thread's reservations are in flight together, and the
+            // workgroups start at different chunks
+            const int32_t C = (int32_t)a.C;
+            const int32_t rot = (int32_t)((int64_t)(r0 / kTile) * 97 % C);
+            constexpr int kBatch = 8;
+            for (int32_t i0 = threadIdx.x; i0 < C; i0 += kBatch * kScatterBlock) {
+                int32_t h[kBatch], at[kBatch];
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k) {
+                    const int32_t i = i0 + k * kScatterBlock;
+                    at[k] = i < C ? (i + rot < C ? i + rot : i + rot - C) : -1;
+                    h[k] = at[k] < 0 ? 0 : hist[at[k]];
+                }
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k)
+                    if (h[k]) h[k] = atomicAdd(&a.cursor[at[k]], h[k]);
+#pragma unroll
+                for (int k = 0; k < kBatch; ++k)
+                    if (at[k] >= 0) hist[at[k]] = h[k];
+            }
             __syncthreads();
         }
 #pragma unroll
@@ -1484,8 +1519,9 @@ __global__ void __launch_bounds__(256) k_get_particles(Store<T> st, Params p, in
 // Read-out of many particles in two passes: one scattered write per particle
 // (its record with its chunk, by id), then the records in id order into the
 // outputs, whole lines at a time.  The records lie in the re-bin's second
-// store, which holds nothing between re-bins.  1e7 binary32 particles, all outputs: 0.67 ms (0.075 ms clearing,
-// 0.38 ms the scattered records, 0.22 ms out), against 2.06 ms directly.
+// store, which holds nothing between re-bins.  1e7 binary32 particles, all
+// outputs: 0.67 ms (0.075 ms clearing, 0.38 ms the scattered records, 0.22 ms
+// out), against 2.06 ms directly.
 template <class T>
 __global__ void __launch_bounds__(256) k_records_clear(Store<T> st, int64_t slots, int64_t count)
 {
