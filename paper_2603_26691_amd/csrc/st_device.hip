@@ -389,15 +389,27 @@ __device__ __forceinline__ const T *at_byte(const T *base, uint32_t byte_off)
     return (const T *)((const char *)base + byte_off);
 }
 
-// A slot holds a particle unless its offset is the hole mark (binary32 forms:
-// the step kernel stores it for a particle that left) or its diameter is not
-// positive (binary64 form: the diameter of a particle that left is negated).
+// A slot holds a particle unless its offset is the hole mark (the step kernel
+// stores it for a particle that left, in the binary32 forms, and for one whose
+// new position is not finite, in all) or its diameter is not positive
+// (binary64 form: the diameter of a particle that left is negated).  The
+// containers' counts of holes are these slots exactly: arrivals and the places
+// of a full re-bin are reckoned from them.
 // (A particle whose inbox was full stays in place with the un-rebased, perhaps
 // negative, offsets of its new position.)
 template <class T>
 __device__ __forceinline__ bool occupied(T ox, T d)
 {
     return ox > T(kHoleMark) && d > T(0);
+}
+
+// Chunk-local offsets outside [0, E) on some axis: those of a mover.  (An
+// offset that is not a number is not outside: such a particle, its first
+// offset aside, stays in its chunk, where the next step drops it.)
+template <class T>
+__device__ __forceinline__ bool left_chunk(T x, T y, T z, T fe)
+{
+    return x < T(0) || x >= fe || y < T(0) || y >= fe || z < T(0) || z >= fe;
 }
 
 // Where a container takes arrivals of the step with state index m (the state
@@ -483,7 +495,7 @@ __global__ void __launch_bounds__(NB)
     constexpr bool kStageVals = sizeof(T) == 4;
     __shared__ T mval[kStageVals ? 6 * kMoverStage : 1];
     __shared__ MoverRec<T> pool[kPool];   // the first arrivals
-    __shared__ int32_t mcount, apop;
+    __shared__ int32_t mcount, apop, nlost;
     __shared__ int32_t dcount[28], dbase[27];
     __shared__ int32_t nbj[27];           // the neighbouring chunks' containers
     __shared__ Inbox nbin[27];
@@ -612,7 +624,7 @@ __global__ void __launch_bounds__(NB)
 #pragma unroll
         for (int u = 0; u < RV; ++u) reinterpret_cast<int4 *>(pool + threadIdx.x)[u] = arr[u];
     }
-    if (threadIdx.x == 0) mcount = apop = 0;
+    if (threadIdx.x == 0) mcount = apop = nlost = 0;
     __syncthreads();
     bool pool_open = n_in > 0;   // of the wave: arrivals may be left
 
@@ -769,7 +781,7 @@ __global__ void __launch_bounds__(NB)
             }
 
             // relocate: a particle whose new offset left [0, E) on some axis
-            // crossed into another chunk; it keeps the un-rebased offsets
+            // (left_chunk) crossed into another chunk; it keeps the un-rebased offsets
             // (relative to this chunk) until it is emitted and re-based.  A
             // particle that stays needs no re-basing.  FP32-everywhere form:
             // the new position in metres, wrapped, and its chunk from its cells
@@ -796,6 +808,8 @@ __global__ void __launch_bounds__(NB)
                 }
                 mover = (gk[0] | gk[1] | gk[2]) != 0;
             } else {
+                // (written out: through left_chunk the binary64 kernel takes 30
+                // registers more, one wave a SIMD less)
                 mover = xn[0] < T(0) || xn[0] >= fe || xn[1] < T(0) || xn[1] >= fe ||
                         xn[2] < T(0) || xn[2] >= fe;
             }
@@ -809,6 +823,8 @@ __global__ void __launch_bounds__(NB)
             }
             if (valid && mover) {
                 movers |= 1u << k;
+                // (a hole's mark in place would not be told from such an offset)
+                if (xn[0] <= T(kHoleMark)) X[k] = -T(INFINITY);
                 int kx = gk[0], ky = gk[1], kz = gk[2];
                 if constexpr (!GLOBAL) {
                     T tx = xn[0], ty = xn[1], tz = xn[2];
@@ -816,10 +832,29 @@ __global__ void __launch_bounds__(NB)
                     ky = rebase(ty, fe, inv_e);
                     kz = rebase(tz, fe, inv_e);
                 }
-                const int dir = (abs(kx) <= 1 && abs(ky) <= 1 && abs(kz) <= 1)
+                auto near = [](int v) { return (uint32_t)v + 1u <= 2u; };
+                const int dir = near(kx) && near(ky) && near(kz)
                                     ? (kx + 1) + 3 * (ky + 1) + 9 * (kz + 1) : 27;
                 dirs |= (uint32_t)dir << (kDirBits * k);
             }
+        }
+        // A first offset that is not finite (from a field or a velocity that is
+        // not): the droplet has no place any more, and its slot is a hole like
+        // any other.  One sum tells whether the group has one (a hole's own
+        // offset is finite).  It costs 2 % of the binary64 step with
+        // Schiller-Naumann drag (1e7 on 128^3: 320 -> 327 us), as do the other
+        // places tried for it, and nothing that can be measured in other steps.
+        T sum = X[0];
+#pragma unroll
+        for (int k = 1; k < G; ++k) sum += X[k];
+        if (!(fabs(sum) < T(INFINITY))) {
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+                if ((int)o + k < nq && DD[k] > T(0) && !(fabs(X[k]) < T(INFINITY))) {
+                    movers &= ~(1u << k);
+                    X[k] = T(2 * kHoleMark);
+                    atomicAdd(&nlost, 1);
+                }
         }
         // stage the movers with their direction class: one reservation of
         // stage entries per wave (their ranks within the direction classes
@@ -961,7 +996,7 @@ __global__ void __launch_bounds__(NB)
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         const int n = lane < 27 ? dcount[lane] : 0;
-        const int32_t h_new = h_left + mcount;
+        const int32_t h_new = h_left + mcount + nlost;
         if (lane == 0) ct[item].s[m] = {nq, h_new};
         // one atomic instruction (the counters differ per lane)
         int32_t *ctr = nullptr;
@@ -1195,11 +1230,9 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
                 if (occupied(r.ox, r.d)) {
                     // (a particle can leave its chunk and still be in it: one
                     // chunk along a periodic axis)
-                    const T fe = T(a.p.E);
-                    home = a.p.global || (r.ox >= T(0) && r.ox < fe && r.oy >= T(0) &&
-                                          r.oy < fe && r.oz >= T(0) && r.oz < fe);
-                    cn = chunk_of_stored(a.p, c, r.ox, r.oy, r.oz);
-                    home = home && cn == c;
+                    home = !a.p.global && !left_chunk(r.ox, r.oy, r.oz, T(a.p.E));
+                    cn = home ? c : chunk_of_stored(a.p, c, r.ox, r.oy, r.oz);
+                    home = home || (a.p.global && cn == c);
                 }
             }
             const uint64_t stay = __ballot(home);

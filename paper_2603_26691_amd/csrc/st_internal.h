@@ -5,10 +5,11 @@
 // containers (one per kSeg particles at the last full re-bin): container j
 // owns the slot range [base, base + room); its particles sit in the first cnt
 // slots of that range, among h holes: slots a particle left (an offset of
-// kHoleMark or below in binary32, a negative diameter in binary64).  Particles that crossed into the
-// chunk in the last step wait as `in` records in the container's inbox; the
-// next step's kernel takes them up as it streams the container (into the
-// holes, then past the last slot).
+// kHoleMark or below in binary32, a negative diameter in binary64) or was in
+// when its position ceased to be finite (the offset, in both).  Particles that
+// crossed into the chunk in the last step wait as `in` records in the
+// container's inbox; the next step's kernel takes them up as it streams the
+// container (into the holes, then past the last slot).
 // Positions are stored as chunk-local offsets in cell units, xi in [0, E)
 // per axis; the chunk origin is exact (the chunk index times E cells).  The
 // FP32-everywhere form stores binary32 coordinates in metres instead, and

@@ -1,0 +1,93 @@
+"""Droplets whose state stops being finite, on the GPU: a field with cells that
+are no numbers or infinite takes the droplets that read them out of the store,
+and every other droplet and cell stays what the FP64 oracle says, across
+arrivals into the slots they leave and full re-bins."""
+import numpy as np
+import pytest
+
+from gpu_helpers import (FORMS, band, face_distance, fields, min_image, oracle_mesh, state,
+                         tracker, workload)
+from oracle.oracle import load as load_oracle
+
+pytestmark = pytest.mark.gpu
+
+TOL = {   # as in the lockstep parity tests
+    "fp64": {"pos": 1e-13, "vel": 1e-12, "src": 1e-10},
+    "fp32_local": {"pos": 1e-5, "vel": 1e-5, "src": 1e-6},
+    "fp32": {"pos": 1e-5, "vel": 1e-5, "src": 1e-4},
+}
+
+
+def _finite(*arrays):
+    return np.logical_and.reduce([np.isfinite(a).all(axis=1) for a in arrays])
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("P,interp", [(40_000, "trilinear"), (150_000, "trilinear"),
+                                      (40_000, "ngp")])
+def test_field_with_cells_that_are_not_finite(form, P, interp):
+    import torch
+    orc = load_oracle()
+    w = workload("tg32", P=P, noise=0.1)
+    mesh = oracle_mesh(w, interp=1 if interp == "ngp" else 0)
+    rng = np.random.default_rng(P)
+    x, _, d = w.particles()
+    up = rng.normal(0.0, 3.0, (P, 3))       # about a cell a step, 3 in 10 change chunk
+    d[:] = 60e-6                            # and keep their velocity
+    vmax = float(np.abs(up).max())
+    Udev, Uor = fields(w, form)
+    Uor = Uor.copy()
+    for c, v in [(0, np.nan), (0, np.inf), (0, -np.inf), (1, np.nan), (2, np.inf)]:
+        k, j, i = rng.integers(0, 32, (3, 4))
+        Uor[c, k, j, i] = v
+    Udev = torch.from_numpy(Uor).to(Udev.dtype).cuda()
+    t = tracker(w, form, capacity=P + 4000, interp=interp)
+    t.inject(x, up, d)
+    h, L = w.h, np.array(w.L)
+    bnd = band(form, w.n)
+    if form == "fp32":   # the binary32 rounding of the largest position
+        bnd = max(bnd, 2.0 ** -21 * (max(w.L) + vmax * 1e-3) / min(h))
+    gone = 0
+    for step in range(10):
+        if step in (4, 7):                  # a full re-bin; new droplets read the same cells
+            n = 1500
+            t.inject(rng.random((n, 3)) * L, rng.normal(0.0, 3.0, (n, 3)), np.full(n, 60e-6))
+        s0 = state(t)
+        live = (s0["id"] >= 0) & _finite(s0["x"], s0["up"])
+        ill = (s0["id"] >= 0) & ~live     # a finite first coordinate keeps them in the store
+        q = {k: v[live] for k, v in s0.items()}
+        t.sources(reset=True)
+        t.step(Udev, 1e-3)
+        s1 = state(t)
+        S = t.sources(reset=True).cpu().numpy()
+        xo, uo, So = orc.run(mesh, Uor, q["x"], q["up"], q["d"], 1e-3, 1)
+        # droplets that the two sides may give another cell or stencil
+        c0 = orc.cells(mesh, q["x"])
+        split = (c0 != q["cell"]).any(axis=1)
+        assert not (split & ~(face_distance(q["x"], h) < bnd).any(axis=1)).any()
+        edge = split | (face_distance(q["x"] - 0.5 * h, h) < bnd).any(axis=1)
+        # the first coordinate decides whether a droplet is still there
+        at = np.nonzero(live)[0]
+        assert np.array_equal(s1["id"][at][~edge] >= 0, np.isfinite(xo[:, 0])[~edge])
+        gone += int((s1["id"][at] < 0).sum())
+        ok = _finite(xo, uo) & ~edge
+        there = {k: v[at][ok] for k, v in s1.items()}
+        assert np.array_equal(there["id"], at[ok])
+        assert np.array_equal(there["d"], q["d"][ok])
+        assert np.abs(min_image(there["x"] - xo[ok], L)).max() <= TOL[form]["pos"] * L.max()
+        assert np.abs(there["up"] - uo[ok]).max() <= TOL[form]["vel"] * vmax
+        # and no droplet but these adds to the sources
+        keep = np.ones(S.shape[1:], dtype=bool)
+        for c in s0["cell"][ill]:
+            keep[c[2], c[1], c[0]] = False
+        for p in np.nonzero(edge)[0]:
+            for c in (c0[p], q["cell"][p]):
+                keep[c[2], c[1], c[0]] = False
+        for comp in range(3):
+            fin = keep & np.isfinite(So[comp])
+            assert np.isfinite(S[comp][fin]).all()
+            err = np.abs(S[comp][fin] - So[comp][fin]).max() / np.abs(So[comp][fin]).max()
+            assert err <= TOL[form]["src"], (step, comp, err)
+    assert gone > 50, gone
+    assert t.stats()["repacks"] >= 3
+    t.close()
