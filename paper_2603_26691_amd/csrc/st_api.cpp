@@ -457,8 +457,8 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
             ST_HIP(hipMemcpyAsync(&badflag, c->flags + st::F_BADINPUT, 4, hipMemcpyDeviceToHost, s));
             ST_HIP(hipStreamSynchronize(s));
             if (badflag) {
-                // only possible when no flush happened in between (n <= mcap);
-                // otherwise the state already holds the batch
+                // undone when no flush happened in between; otherwise the store
+                // already holds the batch, its bad droplets left out
                 if (c->count == count0) {
                     ST_HIP(st::launch_unstage(c, pend0, s));
                     c->pending = pend0;

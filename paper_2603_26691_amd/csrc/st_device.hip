@@ -1436,7 +1436,10 @@ __global__ void k_stage(int64_t n, const double *x, const double *up, const doub
         const int64_t m = at + i;
         *staged.at(m) = MoverRec<T>{loc[0], loc[1], loc[2], (T)v[0], (T)v[1], (T)v[2], (T)dd,
                                 (int32_t)(id0 + i)};
-        staged.dest[m] = (int32_t)chunk_index(p, ch[0], ch[1], ch[2]);
+        // (a diameter that the state's precision rounds to zero is accepted,
+        // but no slot can hold it)
+        staged.dest[m] =
+            ok && (T)dd > T(0) ? (int32_t)chunk_index(p, ch[0], ch[1], ch[2]) : -1;
         if (!ok) flags[F_BADINPUT] = 1;
     }
 }
@@ -1453,6 +1456,8 @@ __global__ void k_clear_staged(Cont *cont0, Cont *cont1, const int32_t *flags)
 
 // Adds the staged injections to the inbox counts of their chunks' first
 // containers (a full re-bin's layout counts a chunk's particles from these).
+// Those without a chunk (a bad value in a batch that was staged in parts)
+// are neither counted nor placed.
 template <class T>
 __global__ void __launch_bounds__(kScatterBlock) k_count_staged(Cont *cont0, Cont *cont1,
                                                                 const int32_t *first0,
@@ -1474,7 +1479,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_count_staged(Cont *cont0, Con
     }
     for (int64_t i = (int64_t)blockIdx.x * kScatterBlock + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kScatterBlock)
-        atomicAdd(lds ? &hist[dest[i]] : &ct[first[dest[i]]].in[m], 1);
+        if (dest[i] >= 0) atomicAdd(lds ? &hist[dest[i]] : &ct[first[dest[i]]].in[m], 1);
     if (lds) {
         __syncthreads();
         for (int32_t i = threadIdx.x; i < C; i += kScatterBlock)

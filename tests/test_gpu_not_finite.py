@@ -1,7 +1,8 @@
-"""Droplets whose state stops being finite, on the GPU: a field with cells that
-are no numbers or infinite takes the droplets that read them out of the store,
-and every other droplet and cell stays what the FP64 oracle says, across
-arrivals into the slots they leave and full re-bins."""
+"""Droplets that no slot can hold, on the GPU: a field with cells that are no
+numbers or infinite takes the droplets that read them out of the store, and a
+batch injected in parts leaves its bad droplets out.  Every other droplet and
+cell stays what it would be without them, across arrivals into the slots they
+leave and full re-bins."""
 import numpy as np
 import pytest
 
@@ -91,3 +92,48 @@ def test_field_with_cells_that_are_not_finite(form, P, interp):
     assert gone > 50, gone
     assert t.stats()["repacks"] >= 3
     t.close()
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_batch_in_parts_with_bad_droplets(form):
+    """A device batch larger than the staging area is partly in the store when
+    its bad values are found; in binary32 a diameter can round to zero.  The
+    store then holds the others, as if the bad ones had never been there."""
+    import torch
+    from paper_2603_26691_amd._native import STError
+    P, first = 240_000, 5_000
+    w = workload("tg32", P=P, noise=0.2)
+    x, _, d = w.particles()
+    up = np.random.default_rng(4).normal(0.0, 2.0, (P, 3))
+    g = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    bad = {10: ("d", -1.0), 11: ("x", np.nan), 70_000: ("up", np.inf), 200_001: ("d", 0.0),
+           P - first - 1: ("d", np.nan)}
+    tiny = [] if form == "fp64" else [300, 170_000]       # below binary32's least value
+    ill = {"x": x[first:].copy(), "up": up[first:].copy(), "d": d[first:].copy()}
+    for i, (k, v) in bad.items():
+        ill[k][i] = v
+    ill["d"][tiny] = 1e-60
+    gone = np.zeros(P, dtype=bool)
+    gone[[first + i for i in list(bad) + tiny]] = True
+    a, b = tracker(w, form), tracker(w, form)
+    a.inject(x[:first], up[:first], d[:first])
+    a.particles()                                          # places them
+    with pytest.raises(STError, match="partially"):
+        a.inject(g(ill["x"]), g(ill["up"]), g(ill["d"]))
+    b.inject(g(x[~gone]), g(up[~gone]), g(d[~gone]))
+    Udev, _ = fields(w, form)
+    for t in (a, b):
+        t.sources(reset=True)
+    for step in range(6):
+        sa, sb = state(a), state(b)
+        assert np.array_equal(sa["id"], np.where(gone, -1, np.arange(P))[: len(sa["id"])])
+        for k in ("x", "up", "d", "cell"):
+            assert np.array_equal(sa[k][~gone], sb[k]), (step, k)
+        a.step(Udev, 1e-3)
+        b.step(Udev, 1e-3)
+        Sa, Sb = a.sources(reset=True), b.sources(reset=True)
+        # (sums ordered by atomics; stored in binary32 in the FP32-everywhere form)
+        tol = 1e-5 if form == "fp32" else 1e-12
+        assert float((Sa - Sb).abs().max() / Sb.abs().max()) < tol
+    a.close()
+    b.close()
