@@ -24,7 +24,9 @@
 // and, up to a bound in memory, the states of the steps between them, as the
 // forward run's own step kernel streams them.  A segment with all its steps'
 // states is reversed from these, and consecutive such segments share the
-// anchors of the newest one's checkpoint (below), looked up by particle id (the
+// anchors of the newest one's checkpoint (below), looked up by particle id; a
+// particle that this checkpoint no longer holds (its position ceased to be
+// finite) keeps its record by id (the
 // records by id itself would be scattered over the whole array: 69 us a step
 // against 55 us on 1e6 particles; in a recomputed segment, whose
 // ids are the anchors, 45 us).  Any other segment is recomputed from its checkpoint (deposit off), each step
@@ -63,7 +65,7 @@ struct AdjArgs {
     T *adj;                  // adjoint records by anchor, [nrec][8]: xbar[3], ubar[3], dbar, unused
     double *Ubar;            // dL/du [3][n2][n1][n0]
     double *tacc;            // per-chunk tile sums of dL/du over the steps, [C][3][S3], or null
-    const int32_t *anchor;   // anchors by id of the saved ids, or null (these are anchors)
+    const int32_t *anchor;   // records by id of the saved ids, or null (these are anchors)
     int64_t nids;            // particles
     int64_t nrec;            // records (the store's slots)
     Params p;
@@ -119,13 +121,14 @@ __device__ __forceinline__ void stage_tile(const Params &p, const T *u, int cx, 
     }
 }
 
-// A saved slot holds a particle unless its anchor is -1 (no particle at
-// that slot of the checkpoint) or it is a hole (its mark for an offset in
-// binary32, a negated diameter in binary64).
+// A saved slot holds a particle unless it has no record (its anchor is -1: no
+// particle at that slot of the checkpoint) or it is a hole (its mark for an
+// offset in binary32, a negated diameter in binary64).
+constexpr int32_t kNoRecord = INT32_MIN;
 template <class T>
-__device__ __forceinline__ bool adj_live(int64_t anchor, int64_t nrec, const T (&st)[7])
+__device__ __forceinline__ bool adj_live(int32_t record, const T (&st)[7])
 {
-    return anchor >= 0 && anchor < nrec && st[0] >= T(0) && st[6] > T(0);
+    return record != kNoRecord && st[0] >= T(0) && st[6] > T(0);
 }
 
 // Trilinear stencil of a chunk-local position [cells]: lowest corner i0 per
@@ -141,12 +144,12 @@ __device__ __forceinline__ void stencil(const double (&xi)[3], int (&i0)[3], dou
     }
 }
 
-// the anchor of a saved slot's particle
+// the record of a saved slot's particle, relative to the first by anchor
 template <class T>
-__device__ __forceinline__ int64_t anchor_of(const AdjArgs<T> &a, int32_t id)
+__device__ __forceinline__ int32_t record_of(const AdjArgs<T> &a, int32_t id)
 {
-    if (!a.anchor) return id;
-    return id >= 0 && id < a.nids ? a.anchor[id] : -1;
+    if (!a.anchor) return id >= 0 && id < a.nrec ? id : kNoRecord;
+    return id >= 0 && id < a.nids ? a.anchor[id] : kNoRecord;
 }
 
 // The reverse of one particle's step.  st: its saved state (chunk-local
@@ -292,15 +295,15 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
         const int np = (first && shift) ? 1 : PPT;
         const int64_t q0 = s0 + j * kAdjBlock;
         j += np;
-        int64_t an[PPT];
+        int32_t an[PPT];
         T st[PPT][7];
         double rc[PPT][7];
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
             const int64_t q = q0 + threadIdx.x + (int64_t)u * kAdjBlock;
-            an[u] = -1;
+            an[u] = kNoRecord;
             if (u < np && q < s1) {
-                an[u] = anchor_of(a, V.id[q]);
+                an[u] = record_of(a, V.id[q]);
                 st[u][0] = V.ox[q];
                 st[u][1] = V.oy[q];
                 st[u][2] = V.oz[q];
@@ -313,9 +316,9 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
         bool live[PPT];
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
-            live[u] = adj_live(an[u], a.nrec, st[u]);
+            live[u] = adj_live(an[u], st[u]);
             if (live[u])
-                for (int k = 0; k < 7; ++k) rc[u][k] = (double)a.adj[8 * an[u] + k];
+                for (int k = 0; k < 7; ++k) rc[u][k] = (double)a.adj[8 * (int64_t)an[u] + k];
         }
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
@@ -323,7 +326,7 @@ __global__ void __launch_bounds__(kAdjBlock, 2) k_adjoint_tri(AdjArgs<T> a)
             double ufb[3], fr[3];
             int i0[3], t0;
             reverse_particle<T, E, true>(p, a.dt, tile, lam, st[u], rc[u], ufb, i0, fr, t0);
-            T *rec = a.adj + 8 * an[u];
+            T *rec = a.adj + 8 * (int64_t)an[u];
             for (int k = 0; k < 7; ++k) rec[k] = (T)rc[u][k];
             const T f[3] = {(T)fr[0], (T)fr[1], (T)fr[2]};
             const T ub[3] = {(T)ufb[0], (T)ufb[1], (T)ufb[2]};
@@ -404,16 +407,16 @@ __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
     __syncthreads();
     const double *lam = a.lamC + c * 3 * E3;
     for (int64_t q = s0 + threadIdx.x; q < s1; q += kAdjBlock) {
-        const int64_t an = anchor_of(a, V.id[q]);
+        const int32_t an = record_of(a, V.id[q]);
         const T st[7] = {V.ox[q], V.oy[q], V.oz[q], V.vx[q], V.vy[q], V.vz[q], V.d[q]};
-        if (!adj_live(an, a.nrec, st)) continue;
+        if (!adj_live(an, st)) continue;
         double rc[7];
-        for (int k = 0; k < 7; ++k) rc[k] = (double)a.adj[8 * an + k];
+        for (int k = 0; k < 7; ++k) rc[k] = (double)a.adj[8 * (int64_t)an + k];
         double ufb[3], fr[3];
         int i0[3], t0;
         reverse_particle<T, E, false>(p, a.dt, tile, lam, st, rc, ufb, i0, fr, t0);
         for (int comp = 0; comp < 3; ++comp) atomicAdd(&ubt[comp * S3 + t0], ufb[comp]);
-        T *rec = a.adj + 8 * an;
+        T *rec = a.adj + 8 * (int64_t)an;
         for (int k = 0; k < 7; ++k) rec[k] = (T)rc[k];
     }
     __syncthreads();
@@ -537,6 +540,15 @@ hipError_t launch_checkpoint_records(st_ctx *c, const char *ck, const char *ok, 
                        c->count, (int32_t *)c->store[0][7], (int32_t *)c->store[1][7], c->flags,
                        (T *)by_id, (T *)rec, map, mode);
     return hipGetLastError();
+}
+
+// The records of a map's particles before a checkpoint sets theirs: by id,
+// which lie `before` records ahead of those by anchor.
+__global__ void k_map_by_id(int32_t *map, int64_t P, int64_t before)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P;
+         i += (int64_t)gridDim.x * blockDim.x)
+        map[i] = (int32_t)(i - before);
 }
 
 // dL/dd of every particle out of the adjoint records by id
@@ -747,6 +759,8 @@ hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd,
         if (segment_saved(c, sg)) {
             if (!group) {   // the newest of some
                 group = (const char *)c->snaps[(size_t)sg].buf;
+                hipLaunchKernelGGL(k_map_by_id, dim3(grid_of(P)), dim3(256), 0, s, map, P,
+                                   (int64_t)((W.o_adj - W.o_rid) / (8 * c->tsize)));
                 e = records(group, nullptr, kMap | kToAnchor);
             }
             for (int64_t k = k1 - 1; k >= k0 && e == hipSuccess; --k)

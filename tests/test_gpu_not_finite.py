@@ -137,3 +137,51 @@ def test_batch_in_parts_with_bad_droplets(form):
         assert float((Sa - Sb).abs().max() / Sb.abs().max()) < tol
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("form,tol", [("fp64", 1e-9), ("fp32_local", 1e-4)])
+def test_adjoint_of_a_run_that_loses_droplets(form, tol):
+    """Taped steps over a field with cells that are not finite: droplets that a
+    checkpoint holds are not in later ones.  The gradients of the others' diameters
+    are the oracle's, from kept states and (on a tracker whose states are too large to
+    keep) from recomputed ones, and these two agree in every entry."""
+    import torch
+    orc = load_oracle()
+    P, nsteps, K, dt = 20_000, 9, 3, 5e-4
+    w = workload("tg32", P=P, noise=0.1)
+    rng = np.random.default_rng(8)
+    x, _, d = w.particles()
+    up = rng.normal(0.0, 3.0, (P, 3))
+    Udev, Uor = fields(w, form)
+    Uor = Uor.copy()
+    k, j, i = rng.integers(0, 32, (3, 40))
+    Uor[0, k, j, i] = np.nan
+    Udev = torch.from_numpy(Uor).to(Udev.dtype).cuda()
+    lam = torch.from_numpy(rng.normal(size=Uor.shape)).cuda()
+    # about 1 GB a state: two of them are kept
+    big = 14_000_000 if form == "fp64" else 26_000_000
+    got = []
+    for capacity in (P, big):
+        t = tracker(w, form, capacity=capacity)
+        t.inject(x, up, d)
+        s0 = state(t)
+        for _ in range(nsteps):
+            t.step(Udev, dt, tape=K)
+        there = t.particles()["id"].cpu().numpy() >= 0
+        assert (~there).sum() > 100
+        got.append([v.cpu().numpy() for v in t.backward(lam)])
+        after = t.particles()["id"].cpu().numpy() >= 0
+        assert np.array_equal(after, there)
+        t.close()
+    q = {k: v[there] for k, v in s0.items()}
+    mesh = oracle_mesh(w)
+    Uz = np.where(np.isfinite(Uor), Uor, 0.0)      # (the others never read those cells)
+    _, od = orc.adjoint_run(mesh, np.stack([Uz]), [0] * nsteps, [dt] * nsteps, 1, q["x"], q["up"],
+                            q["d"], lam.cpu().numpy())
+    for dU, dd in got:
+        assert np.isfinite(dd[there]).all()
+        assert np.linalg.norm(dd[there] - od) <= tol * np.linalg.norm(od)
+    for a, b in zip(*got):
+        fin = np.isfinite(a)
+        assert np.array_equal(fin, np.isfinite(b))
+        assert np.linalg.norm(a[fin] - b[fin]) <= 1e-6 * np.linalg.norm(b[fin])
