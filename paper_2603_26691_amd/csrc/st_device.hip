@@ -147,9 +147,8 @@ struct GateArgs {
     int32_t *flags, *spread;
     int64_t C;
     int32_t nc[3];
-    int64_t spare;           // slots to share out beyond the particles
+    int64_t slots;           // slots to share out among the particles and the spare ones
     int32_t whole;           // inboxes hold whole rooms
-    int32_t hole_limit;      // more holes than this force a full re-bin at the next step
     int32_t advance;         // after a step (not after an injection)
 };
 
@@ -201,7 +200,7 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
                 f[F_TICK] = t == 5 ? 0 : t + 1;
             }
             // holes are streamed like particles until a full re-bin drops them
-            f[F_FORCE] = !full && holes - movers > a.hole_limit;
+            f[F_FORCE] = !full && holes - movers > f[F_HOLE_LIMIT];
             if (full) {
                 f[F_OVERFLOW] = 0;
                 f[F_TICKET] = 0;
@@ -236,9 +235,18 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
         a.cursor[c] = n;
     }
     __syncthreads();
-    int64_t w = 0, denom;
-    for (int64_t c = threadIdx.x; c < a.C; c += 1024) w += room_weight(a.new_cnt, a.nc, c);
+    // The particles are counted here, not by the host: a captured step may be
+    // replayed after more have been put in.
+    int64_t w = 0, np = 0, denom, total;
+    for (int64_t c = threadIdx.x; c < a.C; c += 1024) {
+        w += room_weight(a.new_cnt, a.nc, c);
+        np += a.new_cnt[c];
+    }
     block_excl_scan<int64_t>(w, denom);
+    block_excl_scan<int64_t>(np, total);
+    const int64_t spare = a.slots - total;
+    // (of the steps until the next full re-bin: a sixteenth of the particles)
+    if (threadIdx.x == 0) f[F_HOLE_LIMIT] = (int32_t)(total / 16 + 1024);
     int64_t slot0 = 0;
     int32_t cont_0 = 0, rec0 = 0;
     for (int64_t r0 = 0; r0 < a.C; r0 += 1024) {
@@ -248,7 +256,7 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
             n = a.new_cnt[c];
             k = n > kSeg ? (n + kSeg - 1) / kSeg : 1;
             per = ((n + k - 1) / k + kAlign - 1) / kAlign * kAlign;
-            const int64_t extra = a.spare * room_weight(a.new_cnt, a.nc, c) / denom / k;
+            const int64_t extra = spare * room_weight(a.new_cnt, a.nc, c) / denom / k;
             room = (int32_t)min((int64_t)kRoomMax, per + extra / kAlign * kAlign);
         }
         const int32_t icap = c < a.C ? inbox_cap(room, a.whole) : 0;
@@ -1779,13 +1787,6 @@ inline int64_t grid_for(int64_t n, int64_t cap = 8192)
     return g > cap ? cap : g;
 }
 
-// more holes than this force a full re-bin (a sixteenth of the particles)
-inline int32_t dead_limit(const st_ctx *c)
-{
-    const int64_t v = c->count / 16 + 1024;
-    return (int32_t)(v < 0x7fffffff ? v : 0x7fffffff);
-}
-
 template <class F>
 hipError_t dispatch(st_ctx *c, F &&f)
 {
@@ -1862,12 +1863,10 @@ template <class T>
 hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 {
     c->store_stream = s;
-    const int64_t total = c->count + npend;
     const GateArgs g{c->cont[0], c->cont[1], c->first[0], c->first[1], c->new_cnt, c->cursor,
                      c->lay, c->flags, c->spread, c->C,
                      {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]},
-                     c->slots - total - (int64_t)kAlign * c->max_items, c->whole_inbox,
-                     dead_limit(c), npend == 0};
+                     c->slots - (int64_t)kAlign * c->max_items, c->whole_inbox, npend == 0};
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
     const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
                            (const MoverRec<T> *)c->rec, c->nrec, staging_of<T>(c), npend, c->lay,

@@ -133,10 +133,11 @@ struct Params {
 // needs a full re-bin; F_FORCE: so does the next one; F_GO: the full re-bin's
 // layout is made, its scatter is due; F_TICKET counts the scatter's finished
 // workgroups; F_CUR: the store (0 or 1); F_TICK: the tick of the next step,
-// modulo 6; F_NITEMS, F_NITEMS1: the containers of either store's layout.
+// modulo 6; F_NITEMS, F_NITEMS1: the containers of either store's layout;
+// F_HOLE_LIMIT: more holes than this force a full re-bin at the next step.
 enum DevFlag { F_OVERFLOW = 0, F_FORCE = 1, F_GO = 2, F_CUR = 3, F_TICK = 4, F_NITEMS = 5,
                F_NITEMS1 = 6, F_BADINPUT = 7, F_REPACKS = 8, F_LASTMOV = 9, F_TICKET = 10,
-               F_STAT_ITEMS = 11, F_STAT_HOLES = 12, F_COUNT = 16 };
+               F_STAT_ITEMS = 11, F_STAT_HOLES = 12, F_HOLE_LIMIT = 13, F_COUNT = 16 };
 
 // Counts of holes and of a step's movers, spread over kSpread 64-byte lines
 // (hundreds of thousands of workgroups add to them).

@@ -143,6 +143,48 @@ def test_captured_step_replays():
 
 
 @pytest.mark.parametrize("form", FORMS)
+def test_captured_step_replays_after_more_droplets(form):
+    """A step captured with a quarter of the droplets in the store is replayed
+    with all of them, through full re-bins: their layout is made for what the
+    store holds by then."""
+    import torch
+    P, P0 = 24_000, 6_000
+    w = workload("tg32", P=P, noise=0.3)
+    x, _, d = w.particles()
+    d = np.full(P, 60e-6)
+    up = np.random.default_rng(5).normal(0.0, 6.0, (P, 3))
+    a, b = tracker(w, form), tracker(w, form)
+    U = fields(w, form)[0]
+    for t in (a, b):
+        t.inject(x[:P0], up[:P0], d[:P0])
+        t.step(U, 1e-3)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        a.step(U, 1e-3)
+    torch.cuda.synchronize()
+    for t in (a, b):
+        t.inject(x[P0:], up[P0:], d[P0:])
+        t.particles()                     # places them
+    before = a.stats()["repacks"]
+    for k in range(24):
+        graph.replay()
+        b.step(U, 1e-3)
+        torch.cuda.synchronize()
+        if k % 4 == 3:
+            sa, sb = state(a), state(b)
+            assert np.array_equal(sa["id"], np.arange(P))
+            for key in sa:
+                assert np.array_equal(sa[key], sb[key]), (k, key)
+    Sa, Sb = a.sources(), b.sources()
+    tol = 1e-5 if form == "fp32" else 1e-12      # (sums ordered by atomics)
+    assert float((Sa - Sb).norm() / Sb.norm()) < tol
+    assert a.stats()["repacks"] == b.stats()["repacks"] > before
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("P", [1000, 200_000])
 def test_first_load_in_parts(form, P):
     """A first load in several injections (host and device arrays), staged in
