@@ -129,7 +129,12 @@ const char *st_last_error(const st_ctx *ctx);
  * arrays are validated on the host (non-finite values or d <= 0 give
  * ST_ERR_INVALID); device arrays are validated on the device and the call
  * waits for the result.  ST_ERR_CAPACITY if the count would exceed the
- * capacity (state unchanged). */
+ * capacity (state unchanged).  Particles are staged until the next call that
+ * needs them (st_step, st_get_particles, st_bounding_boxes, ...) or a full
+ * staging area places them; until then the ones in the store are neither moved
+ * nor written, so a read-out may still run on another stream.  A device batch
+ * that does not fit the staging area is placed in parts: when it holds bad
+ * values, its other particles stay (and the call says so). */
 st_status st_inject(st_ctx *ctx, int64_t n, const double *x, const double *up,
                     const double *d, int on_device, void *hip_stream);
 
@@ -147,7 +152,11 @@ st_status st_count(const st_ctx *ctx, int64_t *n);
  * borrowed until st_backward or st_tape_clear; a checkpoint of the
  * particle state is kept every `tape` sub-steps (the value of the first
  * taped call fixes the interval; ST_ERR_INVALID in the form
- * ST_FORM_FP32).  dt must be finite and > 0, nsub >= 1. */
+ * ST_FORM_FP32).  dt must be finite and > 0, nsub >= 1.  A particle whose
+ * new position is not finite along x (a field or velocity that is not) leaves
+ * the store; its id stays its own.  An untaped call can be captured in a HIP
+ * graph and replayed: a replay advances the particles that are in the store by
+ * then, not those that are still staged. */
 st_status st_step(st_ctx *ctx, const void *u_cells, double dt, int32_t nsub,
                   int32_t tape, void *hip_stream);
 

@@ -310,7 +310,9 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
     // inboxes: whole rooms in a small store, else an eighth of them
     c->whole_inbox = c->slots <= (1 << 17);
     c->nrec = c->whole_inbox ? c->slots : c->slots / 8 + 16 * c->max_items;
-    c->mcap = std::min<int64_t>(d.capacity, 2 * c->nrec);
+    // staging of injections into a store that holds particles: a full re-bin
+    // places them, so a load should fill it few times
+    c->mcap = std::min<int64_t>(d.capacity, std::max<int64_t>(1 << 17, d.capacity / 16 * 5));
     if (c->slots >= ((int64_t)1 << 31) - 1 || c->max_items >= ((int64_t)1 << 30))
         return bad("capacity too large for 32-bit slot indices");
 
@@ -339,7 +341,10 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
         }
         A(&c->rec, (size_t)(2 * c->nrec) * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
                                                           : sizeof(st::MoverRec<float>)));
+        A(&c->stage, (size_t)c->mcap * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
+                                                      : sizeof(st::MoverRec<float>)));
         A(&c->stage_dest, (size_t)c->mcap * 4);
+        A(&c->staged, (size_t)C * 4);
         A(&c->cursor, (size_t)C * 4);
         A(&c->new_cnt, (size_t)C * 4);
         A(&c->lay, (size_t)C * 16);
@@ -412,11 +417,8 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
         if (on_device) {
             ST_HIP(st::launch_zero_i32(c->flags + st::F_BADINPUT, 1, s));
         }
-        // the staging area is the inboxes' memory, or the store while it is empty
-        if (c->pending == 0) {
-            c->stage_in_store = c->count == 0;
-            if (c->count > 0) ST_HIP(st::launch_settle(c, s));
-        }
+        // staged in the store while it is empty
+        if (c->pending == 0) c->stage_in_store = c->count == 0;
         const int64_t stage_batch = std::min<int64_t>(c->mcap, 1 << 22);
         if (!on_device && !c->stage64.buf) {
             size_t bytes = (size_t)stage_batch * 7 * 8;
@@ -469,7 +471,7 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
                             "st_inject: non-finite value or d <= 0 (partially injected)");
             }
         }
-        // no more than the inboxes' memory holds is left for the next call to place
+        // no more than the staging area holds is left for the next call to place
         if (c->stage_in_store && c->pending > c->mcap) return ensure_flushed(c, s);
         return ST_OK;
     } catch (...) {

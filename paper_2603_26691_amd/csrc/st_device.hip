@@ -149,7 +149,8 @@ struct GateArgs {
     int32_t nc[3];
     int64_t slots;           // slots to share out among the particles and the spare ones
     int32_t whole;           // inboxes hold whole rooms
-    int32_t advance;         // after a step (not after an injection)
+    int32_t advance;         // after a step (not for staged injections alone)
+    int32_t *staged;         // [C] staged injections to be placed too, or null
 };
 
 // Share of the spare slots a chunk asks for in a re-binned layout: the
@@ -228,8 +229,12 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
         all = n;
         for (int32_t j = j0; j < j1; ++j) {
             ct[j].place[1] = n;
-            n += a.advance ? min(ct[j].in[m], inbox_cap(ct[j].room, a.whole)) : 0;
+            n += min(ct[j].in[m], inbox_cap(ct[j].room, a.whole));
             all += ct[j].in[m];
+        }
+        if (a.staged) {
+            all += a.staged[c];
+            a.staged[c] = 0;
         }
         a.new_cnt[c] = all;
         a.cursor[c] = n;
@@ -1126,10 +1131,13 @@ struct RecordArrays {
     }
 };
 
-// Where injections are staged: the inboxes' memory (no arrivals wait there
-// then), or, while no particle has been placed, the empty store's own arrays,
+// Where injections are staged until a full re-bin places them: memory of their
+// own, or, while no particle has been placed, the empty store's arrays,
 // which hold them all, so that a first load in one call takes one re-bin (3e6
 // droplets: 0.45 to 0.12 ms).  Their chunks beside them (the store's id array).
+// Nothing of the store, its containers or its inboxes is written for them: a
+// read-out of the store may still run on another stream, and a captured step may
+// be replayed before they are placed.
 template <class T>
 struct Staging {
     Views<T> V;
@@ -1163,7 +1171,7 @@ struct ScatterArgs {
     const MoverRec<T> *rec;  // inboxes [2][nrec]
     int64_t nrec;
     Staging<T> staged;
-    int64_t npend;           // staged injections (then no inbox holds any)
+    int64_t npend;           // staged injections
     const int4 *lay;
     int32_t *cursor;
     int32_t *flags;
@@ -1219,7 +1227,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
     for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) {
         const ContState me = state_of(ct + it, m);
         const int32_t c = me.c, cnt = me.cnt;
-        const int32_t nin = a.npend ? 0 : min(me.in, inbox_cap(me.room, a.whole));
+        const int32_t nin = min(me.in, inbox_cap(me.room, a.whole));
         if (cnt == 0 && nin == 0) continue;   // uniform
         const int4 l = a.lay[c];
         if (threadIdx.x == 0) pos = ct[it].place[0];
@@ -1362,9 +1370,8 @@ __global__ void __launch_bounds__(256) k_settle(Views<T> VV, Cont *cont0, Cont *
 }
 
 // non-empty containers and holes (as they are once the arrivals are placed)
-// (without the inboxes when these count staged injections)
 __global__ void __launch_bounds__(256) k_stats(const Cont *cont0, const Cont *cont1,
-                                               int32_t *flags, int arrivals)
+                                               int32_t *flags)
 {
     const int cur = flags[F_CUR], t = flags[F_TICK];
     const int32_t ni = cur ? flags[F_NITEMS1] : flags[F_NITEMS];
@@ -1372,7 +1379,7 @@ __global__ void __launch_bounds__(256) k_stats(const Cont *cont0, const Cont *co
     const int m = (t + 2) % 3;
     int32_t items = 0, holes = 0;
     for (int32_t j = blockIdx.x * 256 + threadIdx.x; j < ni; j += gridDim.x * 256) {
-        const int32_t in = arrivals ? ct[j].in[m] : 0;
+        const int32_t in = ct[j].in[m];
         items += ct[j].s[m].cnt - ct[j].s[m].h + in > 0;
         holes += max(0, ct[j].s[m].h - in);
     }
@@ -1452,34 +1459,15 @@ __global__ void k_stage(int64_t n, const double *x, const double *up, const doub
     }
 }
 
-// (after a rejected injection)
-__global__ void k_clear_staged(Cont *cont0, Cont *cont1, const int32_t *flags)
-{
-    const int cur = flags[F_CUR], m = (flags[F_TICK] + 2) % 3;
-    const int32_t ni = cur ? flags[F_NITEMS1] : flags[F_NITEMS];
-    Cont *const ct = cur ? cont1 : cont0;
-    for (int32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < ni; j += gridDim.x * blockDim.x)
-        ct[j].in[m] = 0;
-}
-
-// Adds the staged injections to the inbox counts of their chunks' first
-// containers (a full re-bin's layout counts a chunk's particles from these).
-// Those without a chunk (a bad value in a batch that was staged in parts)
-// are neither counted nor placed.
+// Counts the staged injections of each chunk (for the layout of the full
+// re-bin that places them).  Those without a chunk (a bad value in a batch that
+// was staged in parts) are neither counted nor placed.
 template <class T>
-__global__ void __launch_bounds__(kScatterBlock) k_count_staged(Cont *cont0, Cont *cont1,
-                                                                const int32_t *first0,
-                                                                const int32_t *first1,
-                                                                const int32_t *flags,
-                                                                Staging<T> from, int64_t at,
-                                                                int64_t n, int64_t C)
+__global__ void __launch_bounds__(kScatterBlock) k_count_staged(int32_t *staged, Staging<T> from,
+                                                                int64_t at, int64_t n, int64_t C)
 {
     __shared__ int32_t hist[kHistMax];
     const int32_t *const dest = StagingAt<T>(from).dest + at;
-    const int cur = flags[F_CUR], t = flags[F_TICK];
-    Cont *const ct = cur ? cont1 : cont0;
-    const int32_t *const first = cur ? first1 : first0;
-    const int m = (t + 2) % 3;
     const bool lds = C <= kHistMax;
     if (lds) {
         for (int32_t i = threadIdx.x; i < C; i += kScatterBlock) hist[i] = 0;
@@ -1487,11 +1475,11 @@ __global__ void __launch_bounds__(kScatterBlock) k_count_staged(Cont *cont0, Con
     }
     for (int64_t i = (int64_t)blockIdx.x * kScatterBlock + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kScatterBlock)
-        if (dest[i] >= 0) atomicAdd(lds ? &hist[dest[i]] : &ct[first[dest[i]]].in[m], 1);
+        if (dest[i] >= 0) atomicAdd(lds ? &hist[dest[i]] : &staged[dest[i]], 1);
     if (lds) {
         __syncthreads();
         for (int32_t i = threadIdx.x; i < C; i += kScatterBlock)
-            if (hist[i]) atomicAdd(&ct[first[i]].in[m], hist[i]);
+            if (hist[i]) atomicAdd(&staged[i], hist[i]);
     }
 }
 
@@ -1853,12 +1841,12 @@ hipError_t launch_step_e(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
 template <class T>
 Staging<T> staging_of(st_ctx *c)
 {
-    return Staging<T>{views_of<T>(c), c->flags, (MoverRec<T> *)c->rec, c->stage_dest, c->slots,
+    return Staging<T>{views_of<T>(c), c->flags, (MoverRec<T> *)c->stage, c->stage_dest, c->slots,
                       c->stage_in_store};
 }
 
-// everything after the step kernel (or, npend > 0, after staged injections):
-// the gate, and the full re-bin's scatter
+// everything after the step kernel (or, npend > 0, the placing of the staged
+// injections): the gate, and the full re-bin's scatter
 template <class T>
 hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 {
@@ -1866,7 +1854,8 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
     const GateArgs g{c->cont[0], c->cont[1], c->first[0], c->first[1], c->new_cnt, c->cursor,
                      c->lay, c->flags, c->spread, c->C,
                      {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]},
-                     c->slots - (int64_t)kAlign * c->max_items, c->whole_inbox, npend == 0};
+                     c->slots - (int64_t)kAlign * c->max_items, c->whole_inbox, npend == 0,
+                     npend ? c->staged : nullptr};
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
     const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
                            (const MoverRec<T> *)c->rec, c->nrec, staging_of<T>(c), npend, c->lay,
@@ -1910,6 +1899,7 @@ hipError_t launch_init(st_ctx *c, hipStream_t s)
                        (int64_t)kSpreadInts, 0);
     hipLaunchKernelGGL(k_init, dim3(grid_for(c->C + 1)), dim3(256), 0, s, c->cont[0], c->first[0],
                        c->flags, c->C);
+    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->staged, c->C, 0);
     return hipGetLastError();
 }
 
@@ -1931,9 +1921,8 @@ hipError_t count_staged(st_ctx *c, int64_t at, int64_t n, hipStream_t s)
 {
     if (n > 0) {
         const int64_t g = std::min<int64_t>((n + kTile - 1) / kTile, 512);
-        hipLaunchKernelGGL((k_count_staged<T>), dim3(g), dim3(kScatterBlock), 0, s, c->cont[0],
-                           c->cont[1], c->first[0], c->first[1], c->flags, staging_of<T>(c), at, n,
-                           c->C);
+        hipLaunchKernelGGL((k_count_staged<T>), dim3(g), dim3(kScatterBlock), 0, s, c->staged,
+                           staging_of<T>(c), at, n, c->C);
     }
     return hipGetLastError();
 }
@@ -1943,7 +1932,7 @@ hipError_t launch_stats(st_ctx *c, hipStream_t s)
 {
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, c->flags + F_STAT_ITEMS, (int64_t)2, 0);
     hipLaunchKernelGGL(k_stats, dim3(grid_for(c->max_items, 1024)), dim3(256), 0, s, c->cont[0],
-                       c->cont[1], c->flags, c->pending == 0);
+                       c->cont[1], c->flags);
     return hipGetLastError();
 }
 
@@ -2037,8 +2026,8 @@ hipError_t launch_stage_inject(st_ctx *c, int64_t n, const double *x, const doub
 
 hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_clear_staged, dim3(grid_for(c->max_items)), dim3(256), 0, s, c->cont[0],
-                       c->cont[1], c->flags);
+    const hipError_t e = launch_zero_i32(c->staged, c->C, s);
+    if (e != hipSuccess) return e;
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         return count_staged<decltype(t)>(c, 0, keep, s);
     });

@@ -93,8 +93,7 @@ __host__ __device__ __forceinline__ int32_t inbox_cap(int32_t room, int32_t whol
     return whole ? room : room / 8 + 16;
 }
 
-// One particle in flight between chunks (also the staging area of
-// st_inject), kept together so that moving it reads and writes whole
+// One particle in flight between chunks (also staged by st_inject), kept together so that moving it reads and writes whole
 // 16-byte vectors: 32 bytes in binary32, 64 in binary64.
 template <class T>
 struct alignas(16) MoverRec {
@@ -214,9 +213,10 @@ struct st_ctx {
     std::vector<st::Block> blocks;  // allocations that hold the buffers below
     st::Cont *cont[2] = {};    // [max_items] containers of either store
     int32_t *first[2] = {};    // [C+1] first container of each chunk
-    void *rec = nullptr;       // [2][nrec] inboxes, by the tick's parity; also the
-                               // staging area of injections
-    int32_t *stage_dest = nullptr; // [mcap] chunks of the staged injections
+    void *rec = nullptr;       // [2][nrec] inboxes, by the tick's parity
+    void *stage = nullptr;         // [mcap] staged injections
+    int32_t *stage_dest = nullptr; // [mcap] their chunks
+    int32_t *staged = nullptr;     // [C] their number by chunk
     int32_t stage_in_store = 0;    // they are staged in the (empty) store instead
     int32_t *cursor = nullptr;     // [C] scatter cursors of the full re-bin
     int32_t *new_cnt = nullptr;    // [C] particles per chunk at a full re-bin
@@ -268,7 +268,7 @@ hipError_t launch_settle(st_ctx *c, hipStream_t s);
 hipError_t launch_stats(st_ctx *c, hipStream_t s);
 // the runs of the (settled) store's containers and their count
 hipError_t launch_runs(st_ctx *c, RunItem *items, int32_t *nitems, hipStream_t s);
-// takes staged injections from `keep` on out of the inbox counts again
+// takes staged injections from `keep` on out of the counts by chunk again
 hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s);
 hipError_t launch_flush_pending(st_ctx *c, hipStream_t s);
 hipError_t launch_zero_sources(st_ctx *c, hipStream_t s);

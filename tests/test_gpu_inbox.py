@@ -185,6 +185,90 @@ def test_captured_step_replays_after_more_droplets(form):
 
 
 @pytest.mark.parametrize("form", FORMS)
+def test_captured_step_replays_beside_staged_droplets(form):
+    """Droplets that are staged while a captured step is replayed change
+    nothing of what the replays do, and are placed by the next call that
+    needs them; a rejected batch leaves no trace either."""
+    import torch
+    from paper_2603_26691_amd._native import STError
+    P, P0 = 24_000, 10_000
+    w = workload("tg32", P=P, noise=0.3)
+    x, _, d = w.particles()
+    d = np.full(P, 60e-6)
+    up = np.random.default_rng(6).normal(0.0, 6.0, (P, 3))
+    g = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    a, b = tracker(w, form), tracker(w, form)
+    U = fields(w, form)[0]
+    for t in (a, b):
+        t.inject(x[:P0], up[:P0], d[:P0])
+        t.step(U, 1e-3)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        a.step(U, 1e-3)
+    torch.cuda.synchronize()
+    bad = d[:100].copy()
+    bad[7] = -1.0
+    cuts = [P0, P0 + 3000, P0 + 3100, P]
+    for p, q in zip(cuts, cuts[1:]):
+        a.inject(g(x[p:q]), g(up[p:q]), g(d[p:q]))         # staged
+        with pytest.raises(STError):
+            a.inject(g(x[:100]), g(up[:100]), g(bad))
+        for _ in range(6):
+            graph.replay()
+            b.step(U, 1e-3)
+        torch.cuda.synchronize()
+        Sa, Sb = a.sources(reset=True), b.sources(reset=True)
+        tol = 1e-5 if form == "fp32" else 1e-12            # (sums ordered by atomics)
+        assert float((Sa - Sb).norm() / Sb.norm()) < tol
+        assert a.stats()["movers"] == b.stats()["movers"] > 0
+        b.inject(x[p:q], up[p:q], d[p:q])
+        sa, sb = state(a), state(b)                        # places them
+        assert np.array_equal(sa["id"], np.arange(q))
+        for key in sa:
+            assert np.array_equal(sa[key], sb[key]), (q, key)
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_injection_beside_a_read_out_on_another_stream(form):
+    """Boxes and particles that another stream is still to read are those of the
+    store, not of droplets injected meanwhile."""
+    import torch
+    P, P0 = 100_000, 70_000
+    w = workload("tg32", P=P, noise=0.3)
+    x, _, d = w.particles()
+    d = np.full(P, 60e-6)
+    up = np.random.default_rng(7).normal(0.0, 6.0, (P, 3))
+    g = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    t = tracker(w, form)
+    U = fields(w, form)[0]
+    late = (g(x[P0:]), g(up[P0:]), g(d[P0:]))
+    t.inject(x[:P0], up[:P0], d[:P0])
+    for _ in range(3):
+        t.step(U, 1e-3)                                    # arrivals wait in the inboxes
+    want, box = state(t), t.bounding_boxes(0, 1000, 200).cpu().numpy()
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(400_000_000)                     # some 0.2 s
+        late_box = t.bounding_boxes(0, 1000, 200)
+        late_state = t.particles()
+    t.inject(*late)
+    waiting = not side.query()
+    side.synchronize()
+    assert waiting, "the injection was to end before the read-out began"
+    assert np.array_equal(late_box.cpu().numpy(), box)
+    for k in want:
+        assert np.array_equal(late_state[k].cpu().numpy(), want[k]), k
+    s = state(t)
+    assert np.array_equal(s["id"], np.arange(P))
+    assert np.array_equal(s["x"][:P0], want["x"])
+    t.close()
+
+
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("P", [1000, 200_000])
 def test_first_load_in_parts(form, P):
     """A first load in several injections (host and device arrays), staged in
