@@ -195,9 +195,9 @@ st_status st_get_particles(st_ctx *ctx, double *x, double *up, double *d,
  * fields, which are one tensor when every step used the same field) and
  * dL/dd (device, [count] binary64, by id; may be NULL when count is 0).
  * The states of the steps between checkpoints are kept by the forward run, one
- * more copy of the store each, up to 2 GiB in all and while device memory
- * lasts; where they are not kept, the checkpoint is restored and the steps
- * after it recomputed.  The tape is consumed; its checkpoint and state buffers
+ * more copy of the store each, for as many whole segments of `tape` sub-steps as
+ * fit in 2 GiB (and while device memory lasts); elsewhere the checkpoint is
+ * restored and the steps after it recomputed.  The tape is consumed; its checkpoint and state buffers
  * and the call's workspace (the adjoint records: 8 values of the state precision
  * per particle and per slot; where steps are recomputed, about tape copies of
  * the particle store more) stay allocated for the next taped run until

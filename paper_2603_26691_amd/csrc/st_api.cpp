@@ -89,6 +89,7 @@ hipError_t block_alloc(int device, size_t bytes, Block *out)
         e = hipMalloc(&p, bytes);
     }
     if (e == hipSuccess) *out = Block{p, bytes};
+    else (void)hipGetLastError();   // reported here, not by the next launch
     return e;
 }
 
@@ -114,21 +115,39 @@ void block_free(int device, Block *b)
     (void)hipFree(mine.buf);
 }
 
+bool saved_fit(const st_ctx *c, int64_t n)
+{
+    const size_t left = c->saved_max > c->saved_bytes ? c->saved_max - c->saved_bytes : 0;
+    return (int64_t)(c->saved_spare.size() + left / snapshot_bytes(c)) >= n;
+}
+
 Block take_saved(st_ctx *c)
 {
     Block b;
     if (!c->saved_spare.empty()) {
         b = c->saved_spare.back();
         c->saved_spare.pop_back();
-    } else if (c->saved_bytes + snapshot_bytes(c) <= kSavedBytes) {
-        if (block_alloc(c->device, snapshot_bytes(c), &b) == hipSuccess) c->saved_bytes += b.bytes;
-        else (void)hipGetLastError();
+    } else if (saved_fit(c, 1)) {
+        if (block_alloc(c->device, snapshot_bytes(c), &b) == hipSuccess) {
+            c->saved_bytes += b.bytes;
+        } else {
+            c->saved_max = c->saved_bytes;   // no more than there are
+        }
     }
     return b;
 }
 
+void untake_saved(st_ctx *c, size_t n)
+{
+    for (size_t k = c->saved.size() - n; k < c->saved.size(); ++k) {
+        if (c->saved[k].buf) c->saved_spare.push_back(c->saved[k]);
+        c->saved[k] = Block{};
+    }
+}
+
 bool drop_saved(st_ctx *c)
 {
+    c->saved_max = 0;
     const bool any = c->saved_bytes > 0;
     if (!any || hipDeviceSynchronize() != hipSuccess) return false;
     for (auto *v : {&c->saved, &c->saved_spare})
@@ -222,6 +241,15 @@ st_status ensure_flushed(st_ctx *c, hipStream_t s)
     c->count += c->pending;
     c->pending = 0;
     return ST_OK;
+}
+
+// A buffer for one more checkpoint; the kept states make room for it.
+hipError_t alloc_checkpoint(st_ctx *c, st::Snapshot *sn)
+{
+    hipError_t e = st::block_alloc(c->device, st::snapshot_bytes(c), sn);
+    if (e == hipErrorOutOfMemory && st::drop_saved(c))
+        e = st::block_alloc(c->device, st::snapshot_bytes(c), sn);
+    return e;
 }
 
 bool finite3(const double *v)
@@ -509,15 +537,17 @@ st_status st_step(st_ctx *c, const void *u_cells, double dt, int32_t nsub, int32
                         sn = c->spare.back();
                         c->spare.pop_back();
                     } else {
-                        hipError_t e = st::block_alloc(c->device, st::snapshot_bytes(c), &sn);
-                        if (e == hipErrorOutOfMemory && st::drop_saved(c))
-                            e = st::block_alloc(c->device, st::snapshot_bytes(c), &sn);
-                        if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_step: checkpoint");
+                        if (alloc_checkpoint(c, &sn) != hipSuccess)
+                            return fail(c, ST_ERR_OOM, "st_step: checkpoint");
                     }
                     c->snaps.push_back(sn);
                     ST_HIP(st::launch_snapshot(c, sn.buf, 0, s));
-                } else if (pos == 1 || c->saved.back().buf) {   // a segment's states, or none
+                } else if (pos == 1 ? st::saved_fit(c, c->tape_every - 1)
+                                    : c->saved.back().buf != nullptr) {
+                    // a segment's states are kept if all of them fit: one
+                    // that lacks some is recomputed whole
                     state = st::take_saved(c);
+                    if (!state.buf) st::untake_saved(c, pos - 1);
                 }
                 c->saved.push_back(state);
                 c->tape.push_back(st::TapeStep{u_cells, dts});
@@ -610,7 +640,10 @@ void tape_reset(st_ctx *c, bool keep_buffers)
     for (auto &b : c->saved)
         if (b.buf) c->saved_spare.push_back(b);
     c->saved.clear();
-    if (!keep_buffers) (void)st::drop_saved(c);
+    if (!keep_buffers) {
+        (void)st::drop_saved(c);
+        c->saved_max = st::kSavedBytes;
+    }
     c->tape.clear();
     c->tape_every = 0;
 }
@@ -638,22 +671,37 @@ st_status st_tape_reserve(st_ctx *c, int32_t tape, int64_t substeps)
         const int64_t need = (substeps + tape - 1) / tape;
         while ((int64_t)c->spare.size() < need) {
             st::Snapshot sn;
-            if (st::block_alloc(c->device, st::snapshot_bytes(c), &sn) != hipSuccess)
+            if (alloc_checkpoint(c, &sn) != hipSuccess)
                 return fail(c, ST_ERR_OOM, "st_tape_reserve: checkpoint");
             c->spare.push_back(sn);
         }
-        // the states of the steps between the checkpoints, as far as they are kept
-        const int64_t between = substeps - need;
-        while ((int64_t)c->saved_spare.size() < between) {
+        // the states of the steps between the checkpoints, for the segments that
+        // the run will keep them for
+        int64_t states = 0;
+        auto kept = [&]() {   // (whether that is all of them)
+            states = 0;
+            for (int64_t left = substeps; left > 0; left -= tape) {
+                const int64_t n = std::min<int64_t>(left, tape) - 1;
+                if (n > 0 && !st::saved_fit(c, states + tape - 1)) return false;
+                states += n;
+            }
+            return true;
+        };
+        bool all = kept();
+        while ((int64_t)c->saved_spare.size() < states) {
+            c->saved_spare.reserve(c->saved_spare.size() + 1);
             std::vector<st::Block> held;
             held.swap(c->saved_spare);
             const st::Block b = st::take_saved(c);
             held.swap(c->saved_spare);
-            if (!b.buf) break;
-            c->saved_spare.push_back(b);
+            if (b.buf) c->saved_spare.push_back(b);
+            else all = kept();   // fewer than they were to be
         }
-        if (st::reserve_backward(c, tape, (int64_t)c->saved_spare.size() < between) != hipSuccess)
-            return fail(c, ST_ERR_OOM, "st_tape_reserve: backward workspace");
+        // they are given up where they leave no room for the rest
+        hipError_t e = st::reserve_backward(c, tape, !all);
+        if (e == hipErrorOutOfMemory && st::drop_saved(c))
+            e = st::reserve_backward(c, tape, substeps > need);
+        if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_tape_reserve: backward workspace");
         return ST_OK;
     } catch (...) {
         return fail(c, ST_ERR_OOM, "st_tape_reserve: host allocation failed");

@@ -148,6 +148,8 @@ struct TapeStep {
     double dt;         // sub-step length
 };
 
+constexpr size_t kSavedBytes = (size_t)2 << 30;
+
 struct Block {         // device memory from block_alloc
     void *buf = nullptr;
     size_t bytes = 0;
@@ -240,6 +242,7 @@ struct st_ctx {
     // not kept), and buffers for them from a consumed tape; their bytes in all
     std::vector<st::Block> saved, saved_spare;
     size_t saved_bytes = 0;
+    size_t saved_max = st::kSavedBytes;   // less where memory ran out
     st::Block bwd_ws;
 
     // coupled run
@@ -291,11 +294,13 @@ size_t snapshot_bytes(const st_ctx *c);
 hipError_t launch_backward(st_ctx *c, const double *lam, double *dU, double *dd, hipStream_t s);
 // allocates st_backward's workspace for checkpoints every K sub-steps, if smaller
 hipError_t reserve_backward(st_ctx *c, int64_t K, bool recompute);
-// A buffer for one more taped step's state, or none when they would take more
-// than kSavedBytes or memory has run out.
-constexpr size_t kSavedBytes = (size_t)2 << 30;
+// The states of taped steps take at most kSavedBytes (until st_tape_clear less,
+// once memory ran out).  Whether n more fit; a buffer for one more, or none;
+// takes the last n steps' back; gives all of them up (their steps are
+// recomputed), and whether there were any.
+bool saved_fit(const st_ctx *c, int64_t n);
 Block take_saved(st_ctx *c);
-// Gives all of them up (their steps are recomputed); whether there were any.
+void untake_saved(st_ctx *c, size_t n);
 bool drop_saved(st_ctx *c);
 hipError_t launch_hilbert_positions(int32_t order, int64_t nseg, int64_t seg_begin,
                                     int64_t per_seg, const double L[3], int64_t first, int64_t n,

@@ -70,3 +70,80 @@ def test_kept_and_recomputed(form, interp, tol, K, nsteps, nsub, reserve):
                              s0["d"], lam)
     for g in (a, b):
         assert _rel(g[0], oU) < tol and _rel(g[1], od) < tol, (_rel(g[0], oU), _rel(g[1], od))
+
+
+def _free():
+    """Free device memory once it has settled (freed memory comes back late)."""
+    import time
+    import torch
+    torch.cuda.synchronize()
+    seen = []
+    while len(seen) < 4 or len(set(seen[-4:])) > 1:
+        assert len(seen) < 100
+        seen.append(torch.cuda.mem_get_info()[0])
+        time.sleep(0.05)
+    return seen[-1]
+
+
+@pytest.mark.parametrize("K,steps,kept", [(3, 4, 2), (4, 4, 0), (2, 6, 2), (5, 3, 0)])
+def test_states_of_whole_segments_only(K, steps, kept):
+    """States of about 1 GiB, two of which may be kept: a segment keeps its
+    states only where all of them fit."""
+    import torch
+    w = workload("tg32", n=(16, 16, 16), P=2000, noise=0.2, dt=4e-4)
+    x, up, d = w.particles()
+    U = fields(w, "fp32_local")[0]
+    t = tracker(w, "fp32_local", capacity=26_000_000)
+    t.inject(x, up, d)
+    t.step(U, w.dt)
+    t.sources(reset=True)
+    for reserve in (False, True):
+        t.tape_clear()
+        free0 = _free()
+        if reserve:
+            t.tape_reserve(K, steps)
+            reserved = _free()
+        for _ in range(steps):
+            t.step(U, w.dt, tape=K)
+        states = -(-steps // K) + kept     # checkpoints too
+        if reserve:
+            assert _free() == reserved      # the run allocates nothing
+        else:
+            used = (free0 - _free()) / 2**30
+            assert 0.95 * states < used < 1.35 * states, (used, states)
+        lam = torch.cos(t.sources()).contiguous()
+        dU, dd = t.backward(lam)
+        if reserve:
+            assert _free() == reserved      # nor does its reverse
+        assert torch.isfinite(dU).all() and torch.isfinite(dd).all()
+    t.close()
+
+
+def test_reserve_gives_up_states_for_the_workspace():
+    """Where the kept states leave no room for the reverse's workspace, the
+    reservation gives them up instead of failing."""
+    import torch
+    w = workload("tg32", n=(16, 16, 16), P=2000, noise=0.2, dt=4e-4)
+    x, up, d = w.particles()
+    U = fields(w, "fp32_local")[0]
+    ref = tracker(w, "fp32_local")
+    t = tracker(w, "fp32_local", capacity=26_000_000)
+    for v in (ref, t):
+        v.inject(x, up, d)
+        v.step(U, w.dt)
+        v.sources(reset=True)
+    # two checkpoints, then two states of the first segment and a workspace of
+    # three states and the records: with the states it does not fit
+    fill = torch.empty(_free() - (27 << 28), dtype=torch.uint8, device="cuda")
+    t.tape_reserve(3, 6)
+    del fill
+    torch.cuda.empty_cache()
+    for v in (ref, t):
+        for _ in range(6):
+            v.step(U, w.dt, tape=3)
+    lam = torch.cos(ref.sources() * 1e3).contiguous()
+    got, want = t.backward(lam), ref.backward(lam)
+    for a, b in zip(got, want):
+        assert float((a - b).norm()) < 1e-6 * float(b.norm())
+    t.close()
+    ref.close()
