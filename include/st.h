@@ -111,9 +111,16 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out);
 /* Outside the paper (lifetime of a context).
  * Frees every buffer of the context (after synchronising its device).  Up to
  * 512 MiB of device memory that contexts free, here and in st_tape_clear, are
- * kept for the buffers of later ones; they are given back when later frees
- * pass them by, or when device memory runs out. */
+ * kept for the buffers of later ones.  They are given back when later frees
+ * pass them by, when an allocation of the library finds no device memory, and
+ * by st_release_memory (which a program calls that needs the memory for its own
+ * allocations; those do not bring it back). */
 st_status st_destroy(st_ctx *ctx);
+
+/* Outside the paper (lifetime of device memory).
+ * Gives the device memory back that destroyed contexts left for later ones.
+ * Safe beside calls on other threads. */
+st_status st_release_memory(void);
 
 /* Outside the paper (error reporting).
  * Message describing the last error of this context ("" if none);

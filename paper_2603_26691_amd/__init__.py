@@ -13,4 +13,7 @@ def __getattr__(name):
     if name == "DepositFn":
         from .autograd import DepositFn
         return DepositFn
+    if name == "release_memory":
+        from .tracker import release_memory
+        return release_memory
     raise AttributeError(name)

@@ -50,6 +50,7 @@ _D = ctypes.c_double
 SIGNATURES = {
     "st_create_mesh": (_I, [ctypes.POINTER(MeshDesc), _I, ctypes.POINTER(_P)]),
     "st_destroy": (_I, [_P]),
+    "st_release_memory": (_I, []),
     "st_last_error": (ctypes.c_char_p, [_P]),
     "st_inject": (_I, [_P, _I64, _P, _P, _P, _I, _P]),
     "st_count": (_I, [_P, ctypes.POINTER(_I64)]),

@@ -22,7 +22,8 @@ namespace {
 
 // Blocks kept for the next context: at most kKeepBytes in all, for all devices
 // and threads, and none that the last kKeepFrees calls of block_free have passed
-// by; all of them are given back when the device has no memory left.  Making
+// by; all of them are given back when one of the library's allocations finds no
+// memory, and by st_release_memory.  Making
 // and freeing device memory can cost more than a short-lived context's work:
 // memory is cleared on its way through the driver, so a program that makes a
 // context per iteration waits for that.  3e6 droplets put in, read back and
@@ -58,6 +59,25 @@ void drop(Keeper &k, size_t i)
 
 }  // namespace
 
+void release_kept()
+{
+    Keeper &k = keeper();
+    std::lock_guard<std::mutex> lock(k.mu);
+    while (!k.kept.empty()) drop(k, 0);
+}
+
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        release_kept();
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) (void)hipGetLastError();   // reported here, not by the next launch
+    return e;
+}
+
 hipError_t block_alloc(int device, size_t bytes, Block *out)
 {
     if (bytes == 0) bytes = 8;
@@ -80,16 +100,8 @@ hipError_t block_alloc(int device, size_t bytes, Block *out)
         }
     }
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        Keeper &k = keeper();
-        std::lock_guard<std::mutex> lock(k.mu);
-        while (!k.kept.empty()) drop(k, 0);
-        e = hipMalloc(&p, bytes);
-    }
+    const hipError_t e = device_malloc(&p, bytes);
     if (e == hipSuccess) *out = Block{p, bytes};
-    else (void)hipGetLastError();   // reported here, not by the next launch
     return e;
 }
 
@@ -243,12 +255,22 @@ st_status ensure_flushed(st_ctx *c, hipStream_t s)
     return ST_OK;
 }
 
-// A buffer for one more checkpoint; the kept states make room for it.
+// Device memory that the kept states of taped steps make room for: a buffer for
+// one more checkpoint, and a call's temporary or a context's later buffer (for
+// hipFree).
 hipError_t alloc_checkpoint(st_ctx *c, st::Snapshot *sn)
 {
     hipError_t e = st::block_alloc(c->device, st::snapshot_bytes(c), sn);
     if (e == hipErrorOutOfMemory && st::drop_saved(c))
         e = st::block_alloc(c->device, st::snapshot_bytes(c), sn);
+    return e;
+}
+
+template <class P>
+hipError_t alloc(st_ctx *c, P **p, size_t bytes)
+{
+    hipError_t e = st::device_malloc((void **)p, bytes);
+    if (e == hipErrorOutOfMemory && st::drop_saved(c)) e = st::device_malloc((void **)p, bytes);
     return e;
 }
 
@@ -410,6 +432,16 @@ st_status st_destroy(st_ctx *c)
     return ST_OK;
 }
 
+st_status st_release_memory(void)
+{
+    try {
+        st::release_kept();
+        return ST_OK;
+    } catch (...) {
+        return ST_ERR_DEVICE;
+    }
+}
+
 const char *st_last_error(const st_ctx *c)
 {
     if (!c) return g_create_err.c_str();
@@ -451,6 +483,8 @@ st_status st_inject(st_ctx *c, int64_t n, const double *x, const double *up, con
         if (!on_device && !c->stage64.buf) {
             size_t bytes = (size_t)stage_batch * 7 * 8;
             hipError_t e = st::block_alloc(c->device, bytes, &c->stage64);
+            if (e == hipErrorOutOfMemory && st::drop_saved(c))
+                e = st::block_alloc(c->device, bytes, &c->stage64);
             if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_inject: staging buffer");
         }
         const int64_t pend0 = c->pending, id0 = c->next_id, count0 = c->count;
@@ -574,7 +608,7 @@ st_status st_get_sources(st_ctx *c, double *out, int32_t reset, int on_device, v
         return ST_OK;
     }
     double *tmp = nullptr;
-    hipError_t e = hipMalloc((void **)&tmp, n * 8);
+    hipError_t e = alloc(c, &tmp, n * 8);
     if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_get_sources: temporary");
     e = st::launch_get_sources(c, tmp, reset, s);
     if (e == hipSuccess) e = hipMemcpyAsync(out, tmp, n * 8, hipMemcpyDeviceToHost, s);
@@ -601,7 +635,7 @@ st_status st_get_particles(st_ctx *c, double *x, double *up, double *d, int64_t 
     // one device temporary laid out as x, up, d, id, cell
     size_t bytes = n * (24 + 24 + 8 + 8 + 12);
     char *tmp = nullptr;
-    hipError_t e = hipMalloc((void **)&tmp, bytes);
+    hipError_t e = alloc(c, &tmp, bytes);
     if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_get_particles: temporary");
     double *tx = (double *)tmp, *tu = tx + 3 * n, *td = tu + 3 * n;
     int64_t *ti = (int64_t *)(td + n);
@@ -653,8 +687,12 @@ void tape_reset(st_ctx *c, bool keep_buffers)
 st_status st_tape_clear(st_ctx *c)
 {
     if (!c) return ST_ERR_INVALID;
-    tape_reset(c, false);
-    return ST_OK;
+    try {
+        tape_reset(c, false);
+        return ST_OK;
+    } catch (...) {
+        return fail(c, ST_ERR_OOM, "st_tape_clear: host allocation failed");
+    }
 }
 
 st_status st_tape_reserve(st_ctx *c, int32_t tape, int64_t substeps)
@@ -716,9 +754,13 @@ st_status st_backward(st_ctx *c, const double *dL_dSint, double *dL_du, double *
         return fail(c, ST_ERR_INVALID, "st_backward: null pointer");
     if (c->tape.empty()) return fail(c, ST_ERR_STATE, "st_backward: nothing taped");
     ST_HIP(hipSetDevice(c->device));
-    ST_HIP(st::launch_backward(c, dL_dSint, dL_du, dL_dd, (hipStream_t)hip_stream));
-    tape_reset(c, true);
-    return ST_OK;
+    try {
+        ST_HIP(st::launch_backward(c, dL_dSint, dL_du, dL_dd, (hipStream_t)hip_stream));
+        tape_reset(c, true);
+        return ST_OK;
+    } catch (...) {
+        return fail(c, ST_ERR_OOM, "st_backward: host allocation failed");
+    }
 }
 
 st_status st_run_coupled(st_ctx *c, const void *u0, const double *cs, int32_t nsteps, double dt,
@@ -740,7 +782,7 @@ st_status st_run_coupled(st_ctx *c, const void *u0, const double *cs, int32_t ns
     const size_t fbytes = 3 * (size_t)c->prm.n[0] * c->prm.n[1] * c->prm.n[2] * c->tsize;
     for (int b = 0; b < 2; ++b)
         if (!c->fieldbuf[b]) {
-            hipError_t e = hipMalloc(&c->fieldbuf[b], fbytes);
+            hipError_t e = alloc(c, &c->fieldbuf[b], fbytes);
             if (e != hipSuccess) return fail(c, ST_ERR_OOM, "st_run_coupled: field buffers");
         }
     if (!c->side) ST_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
@@ -829,9 +871,9 @@ st_status st_ec_reset(st_ctx *c, void *hip_stream)
     hipStream_t s = (hipStream_t)hip_stream;
     const int64_t n = 3 * (int64_t)c->prm.n[0] * c->prm.n[1] * c->prm.n[2];
     if (!c->ec_prev) {
-        if (hipMalloc((void **)&c->ec_prev, (size_t)n * 8) != hipSuccess)
+        if (alloc(c, &c->ec_prev, (size_t)n * 8) != hipSuccess)
             return fail(c, ST_ERR_OOM, "st_ec_reset: history buffers");
-        if (hipMalloc((void **)&c->ec_ext, (size_t)n * 8) != hipSuccess) {
+        if (alloc(c, &c->ec_ext, (size_t)n * 8) != hipSuccess) {
             (void)hipFree(c->ec_prev);
             c->ec_prev = nullptr;
             return fail(c, ST_ERR_OOM, "st_ec_reset: history buffers");
@@ -861,7 +903,7 @@ st_status st_ec_estimate(st_ctx *c, int32_t kind, const double *S_last, double *
         return ST_OK;
     }
     double *tmp = nullptr;
-    if (hipMalloc((void **)&tmp, 2 * n * 8) != hipSuccess)
+    if (alloc(c, &tmp, 2 * n * 8) != hipSuccess)
         return fail(c, ST_ERR_OOM, "st_ec_estimate: temporaries");
     hipError_t e = hipMemcpyAsync(tmp, S_last, n * 8, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = st::launch_ec(c, kind, tmp, tmp + n, s);
@@ -961,7 +1003,7 @@ st_status st_hilbert_positions(st_ctx *c, int32_t order, int64_t nseg, int64_t s
             return ST_OK;
         }
         double *tmp = nullptr;
-        if (hipMalloc((void **)&tmp, (size_t)n * 48) != hipSuccess)
+        if (alloc(c, &tmp, (size_t)n * 48) != hipSuccess)
             return fail(c, ST_ERR_OOM, "st_hilbert_positions: temporaries");
         hipError_t e = hipMemcpyAsync(tmp, u, (size_t)n * 24, hipMemcpyHostToDevice, s);
         if (e == hipSuccess)
@@ -1011,7 +1053,7 @@ st_status st_inject_hilbert(st_ctx *c, int32_t order, int64_t nseg, int64_t seg_
         const int64_t batch = std::min<int64_t>(n, (int64_t)1 << 22);
         double *tmp = nullptr;
         const size_t per = on_device ? 24 : 24 + 24 + 24 + 8;
-        if (hipMalloc((void **)&tmp, (size_t)batch * per) != hipSuccess)
+        if (alloc(c, &tmp, (size_t)batch * per) != hipSuccess)
             return fail(c, ST_ERR_OOM, "st_inject_hilbert: temporaries");
         st_status r = ST_OK;
         hipError_t e = hipSuccess;
@@ -1058,7 +1100,7 @@ st_status st_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64_t np
         return ST_OK;
     }
     double *tmp = nullptr;
-    if (hipMalloc((void **)&tmp, (size_t)nparts * 48) != hipSuccess)
+    if (alloc(c, &tmp, (size_t)nparts * 48) != hipSuccess)
         return fail(c, ST_ERR_OOM, "st_bounding_boxes: temporaries");
     hipError_t e = st::launch_bounding_boxes(c, id0, per_part, nparts, tmp, s);
     if (e == hipSuccess) e = hipMemcpyAsync(boxes, tmp, (size_t)nparts * 48, hipMemcpyDeviceToHost, s);

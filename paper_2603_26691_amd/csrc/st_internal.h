@@ -161,6 +161,10 @@ using Snapshot = Block;   // particle store and layout at a checkpoint
 hipError_t block_alloc(int device, size_t bytes, Block *b);
 // Takes a block back; nothing on the device may use it any more.
 void block_free(int device, Block *b);
+// hipMalloc for memory that is not kept; the kept blocks make room for it.
+hipError_t device_malloc(void **p, size_t bytes);
+// Gives the kept blocks back.
+void release_kept();
 
 // One container's run in a saved step or checkpoint.
 struct alignas(16) RunItem {

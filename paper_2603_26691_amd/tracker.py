@@ -20,6 +20,11 @@ def _dptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def release_memory():
+    """Gives the device memory back that closed trackers left for new ones."""
+    N.check(N.lib().st_release_memory(), what="st_release_memory")
+
+
 class Tracker:
     """Particles on a uniform periodic mesh (see include/st.h).
 

@@ -1,7 +1,9 @@
 """Device memory that closed trackers leave for new ones, on the GPU: a tracker
 on kept memory gives what one on fresh memory gives, from several threads and
 streams, and what is kept is bounded."""
+import ctypes
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -69,3 +71,104 @@ def test_kept_memory_is_bounded():
         tracker(w, "fp32_local", capacity=capacity).close()
     free1 = torch.cuda.mem_get_info()[0]
     assert free0 - free1 <= KEEP + (64 << 20), (free0, free1)
+
+
+def _free():
+    """Free device memory once it has settled (freed memory comes back late)."""
+    import torch
+    torch.cuda.synchronize()
+    seen = []
+    while len(seen) < 4 or len(set(seen[-4:])) > 1:
+        assert len(seen) < 100
+        seen.append(torch.cuda.mem_get_info()[0])
+        time.sleep(0.05)
+    return seen[-1]
+
+
+def _fill():
+    """Tensors that leave 64 to 128 MiB of device memory."""
+    import torch
+    held = [torch.empty(_free() - (1 << 30), dtype=torch.uint8, device="cuda")]
+    try:
+        while len(held) < 200:
+            held.append(torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
+    except torch.OutOfMemoryError:
+        pass
+    assert 3 < len(held) < 200
+    del held[-1:]
+    torch.cuda.empty_cache()
+    return held
+
+
+def _leave_kept():
+    """Closes a tracker that leaves some 400 MiB; returns the bytes."""
+    import paper_2603_26691_amd as pkg
+    pkg.release_memory()
+    free0 = _free()
+    tracker(workload("tg32", P=1, n=(16, 16, 16)), "fp32_local", capacity=3_500_000).close()
+    kept = free0 - _free()
+    assert (300 << 20) < kept <= KEEP + (16 << 20), kept
+    return kept
+
+
+def test_release_memory():
+    import paper_2603_26691_amd as pkg
+    w = workload("tg32", P=1, n=(16, 16, 16))
+    tracker(w, "fp32_local").close()       # (the library's own memory is there)
+    kept = _leave_kept()
+    free1 = _free()
+    pkg.release_memory()
+    assert _free() - free1 >= 0.95 * kept
+
+
+@pytest.mark.parametrize("call", ["sources", "particles", "coupled", "ec"])
+def test_kept_memory_makes_room(call):
+    """With nearly no device memory left, the library's calls take what closed
+    trackers left."""
+    import torch
+    from paper_2603_26691_amd import _native as N
+    P = 3_000_000
+    w = workload("tg32", P=P, n=(192, 192, 192), L=(0.1, 0.1, 0.1))
+    t = tracker(w, "fp32_local", capacity=2 * P)
+    rng = np.random.default_rng(1)
+    x, d = rng.random((P, 3)) * 0.1, np.full(P, 20e-6)
+    up = np.zeros((P, 3))
+    g = [torch.from_numpy(a).cuda() for a in (x, up, d)]
+    U = torch.zeros(t.field_shape, dtype=torch.float32, device="cuda")
+    host = np.empty(t.field_shape)
+    rows = np.empty((P, 3)), np.empty((P, 3)), np.empty(P), np.empty(P, np.int64), \
+        np.empty((P, 3), np.int32)
+    ptr = lambda a: ctypes.c_void_p(a.ctypes.data)  # noqa: E731
+    t.inject(*g)
+    t.particles()
+    torch.cuda.empty_cache()
+    _leave_kept()
+    fill = _fill()
+    lib = N.lib()
+    if call == "sources":
+        st = lib.st_get_sources(t.ctx, ptr(host), 0, 0, None)
+    elif call == "particles":
+        st = lib.st_get_particles(t.ctx, *(ptr(a) for a in rows), 0, None)
+        assert np.array_equal(rows[3], np.arange(P))
+    elif call == "coupled":
+        t.run_coupled(U, [1.0, 0.0], 1e-4)
+        st = 0
+    else:
+        st = lib.st_ec_reset(t.ctx, None)
+    assert st == 0, st
+    torch.cuda.synchronize()
+    del fill
+    torch.cuda.empty_cache()
+    t.close()
+    # and a call that finds none says so, and leaves no error behind
+    if call == "sources":
+        t = tracker(w, "fp32_local", capacity=1000)
+        from paper_2603_26691_amd import release_memory
+        release_memory()
+        fill = _fill()
+        assert lib.st_get_sources(t.ctx, ptr(host), 0, 0, None) == N.ST_ERR_OOM
+        t.step(U, 1e-4)
+        torch.cuda.synchronize()
+        del fill
+        torch.cuda.empty_cache()
+        t.close()
