@@ -398,6 +398,8 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
         A(&c->cursor, (size_t)C * 4);
         A(&c->new_cnt, (size_t)C * 4);
         A(&c->lay, (size_t)C * 16);
+        A(&c->lay_sums, 16);
+        A(&c->lay_part, (size_t)(C / 1024 + 1) * 16);
         A(&c->flags, (size_t)st::F_COUNT * 4);
         A(&c->spread, (size_t)st::kSpreadInts * 4);
         A(&c->src, (size_t)3 * ncell * c->asize);

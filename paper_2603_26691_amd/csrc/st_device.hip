@@ -22,7 +22,8 @@
 //   gate      one workgroup: the next tick; and, when a container ran out of
 //             room, an inbox was too small, particles were injected or too
 //             many holes gathered, the layout of a full re-bin (counts per
-//             chunk, rooms, containers);
+//             chunk, rooms, containers; on meshes of many chunks in three
+//             more launches);
 //   scatter   only then: a counting sort into the second store, which becomes
 //             the store.
 #include "st_internal.h"
@@ -145,21 +146,76 @@ struct GateArgs {
     int32_t *new_cnt, *cursor;
     int4 *lay;
     int32_t *flags, *spread;
+    int64_t *sums;           // layout in several launches: particles, weights
+    int4 *part;              // and its blocks' sums: slots (64 bits), containers, records
     int64_t C;
     int32_t nc[3];
     int64_t slots;           // slots to share out among the particles and the spare ones
     int32_t whole;           // inboxes hold whole rooms
     int32_t advance;         // after a step (not for staged injections alone)
     int32_t *staged;         // [C] staged injections to be placed too, or null
+    int32_t one;             // the layout is made by the gate's own workgroup
 };
+
+// The layouts of a full re-bin, the present one and the new, and the state
+// index after the step.
+struct Layouts {
+    Cont *ct, *nct;
+    const int32_t *cf;
+    int32_t *ncf;
+    int cur, m;
+    __device__ __forceinline__ Layouts(const GateArgs &a, int cur_, int m_) : cur(cur_), m(m_)
+    {
+        ct = cur ? a.cont1 : a.cont0;
+        cf = cur ? a.first1 : a.first0;
+        nct = cur ? a.cont0 : a.cont1;
+        ncf = cur ? a.first0 : a.first1;
+    }
+};
+
+// A chunk's particles: those of its containers (their holes out, their inboxes
+// and the movers that found them full in), and staged ones.
+__device__ __forceinline__ int32_t chunk_total(const GateArgs &a, const Layouts &L, int64_t c)
+{
+    int32_t n = a.staged ? a.staged[c] : 0;
+    const int32_t j1 = L.cf[c + 1];
+    for (int32_t j = L.cf[c]; j < j1; ++j) {
+        const ContState s = state_of(L.ct + j, L.m);
+        n += s.cnt - s.h + s.in;
+    }
+    return n;
+}
+
+// Counts them, and sets their places: those that stay in its containers,
+// container by container, then its inboxes' records, then (from the cursor
+// on) injections and the movers whose inbox was full.
+__device__ __forceinline__ int32_t count_chunk(const GateArgs &a, const Layouts &L, int64_t c)
+{
+    const int32_t j0 = L.cf[c], j1 = L.cf[c + 1];
+    int32_t n = 0, all = 0;
+    for (int32_t j = j0; j < j1; ++j) {
+        L.ct[j].place[0] = n;
+        n += L.ct[j].s[L.m].cnt - L.ct[j].s[L.m].h;
+    }
+    all = n;
+    for (int32_t j = j0; j < j1; ++j) {
+        L.ct[j].place[1] = n;
+        n += min(L.ct[j].in[L.m], inbox_cap(L.ct[j].room, a.whole));
+        all += L.ct[j].in[L.m];
+    }
+    if (a.staged) all += a.staged[c];
+    a.new_cnt[c] = all;
+    a.cursor[c] = n;
+    return all;
+}
 
 // Share of the spare slots a chunk asks for in a re-binned layout: the
 // largest count among the chunk and its six face neighbours (periodic), plus
 // kSlackMin.  What a chunk can gain before the next re-bin is bounded by what
 // its neighbours can send, so a sparse chunk at the edge of a dense region
 // gets room for the arrivals from the dense side.
-__device__ __forceinline__ int64_t room_weight(const int32_t *cnt, const int32_t (&nc)[3],
-                                               int64_t i)
+template <class F>
+__device__ __forceinline__ int64_t room_weight(const F &cnt, const int32_t (&nc)[3], int64_t i)
 {
     const int32_t j = (int32_t)i;
     const int32_t sx = 1, sy = nc[0], sz = nc[0] * nc[1];
@@ -168,18 +224,67 @@ __device__ __forceinline__ int64_t room_weight(const int32_t *cnt, const int32_t
         j + (x == nc[0] - 1 ? -(nc[0] - 1) * sx : sx), j + (x == 0 ? (nc[0] - 1) * sx : -sx),
         j + (y == nc[1] - 1 ? -(nc[1] - 1) * sy : sy), j + (y == 0 ? (nc[1] - 1) * sy : -sy),
         j + (z == nc[2] - 1 ? -(nc[2] - 1) * sz : sz), j + (z == 0 ? (nc[2] - 1) * sz : -sz)};
-    int32_t m = cnt[j];
+    int32_t m = cnt(j);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) m = max(m, cnt[nb[k]]);
+    for (int k = 0; k < 6; ++k) m = max(m, cnt(nb[k]));
     return (int64_t)m + kSlackMin;
 }
 
+// A chunk's containers in the new layout: k of at most kSeg particles, equal
+// rooms of whole groups of kAlign slots, the spare slots shared out in
+// proportion to the chunks' weights and rounded down.
+struct Room {
+    int32_t n, k, per, room, icap;
+};
+__device__ __forceinline__ Room chunk_room(const GateArgs &a, int64_t c, int64_t spare,
+                                           int64_t denom)
+{
+    Room r;
+    r.n = a.new_cnt[c];
+    r.k = r.n > kSeg ? (r.n + kSeg - 1) / kSeg : 1;
+    r.per = ((r.n + r.k - 1) / r.k + kAlign - 1) / kAlign * kAlign;
+    const int64_t w = room_weight([&](int32_t j) { return a.new_cnt[j]; }, a.nc, c);
+    const int64_t extra = spare * w / denom / r.k;
+    r.room = (int32_t)min((int64_t)kRoomMax, r.per + extra / kAlign * kAlign);
+    r.icap = inbox_cap(r.room, a.whole);
+    return r;
+}
+
+__device__ __forceinline__ void write_chunk(const GateArgs &a, const Layouts &L, int64_t c,
+                                            const Room &r, int64_t base, int32_t j0, int32_t ib)
+{
+    L.ncf[c] = j0;
+    a.lay[c] = int4{(int32_t)base, r.per, r.room, r.k};
+    if (a.staged) a.staged[c] = 0;
+    for (int32_t i = 0; i < r.k; ++i) {
+        Cont d;
+        d.c = (int32_t)c;
+        d.base = (int32_t)base + i * r.room;
+        d.room = r.room;
+        d.ibase = ib + i * r.icap;
+        d.k = r.k;
+        for (int u = 0; u < 3; ++u) {
+            d.in[u] = 0;
+            d.s[u].cnt = u == L.m ? min(max(r.n - i * r.per, 0), r.per) : 0;
+            d.s[u].h = 0;
+        }
+        d.place[0] = d.place[1] = 0;
+        L.nct[j0 + i] = d;
+    }
+}
+
+__device__ __forceinline__ void finish_layout(const GateArgs &a, const Layouts &L, int32_t ni,
+                                              int64_t total)
+{
+    L.ncf[a.C] = ni;
+    a.flags[L.cur ? F_NITEMS : F_NITEMS1] = ni;
+    // (of the steps until the next full re-bin: a sixteenth of the particles)
+    a.flags[F_HOLE_LIMIT] = (int32_t)(total / 16 + 1024);
+}
+
 // One workgroup.  Without a full re-bin (nearly always) it only turns the
-// tick and sums the spread counters.  With one: each chunk's particles are
-// those of its containers (their holes out, their inboxes in); the chunk gets
-// k containers of at most kSeg particles, equal rooms of whole groups of
-// kAlign slots, the spare slots shared out in proportion to the chunks'
-// weights and rounded down.
+// tick and sums the spread counters.  With one, it makes the new layout too, or
+// (many chunks) leaves it to the launches below.
 __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
 {
     int32_t *const f = a.flags;
@@ -206,97 +311,123 @@ __global__ void __launch_bounds__(1024) k_gate(GateArgs a)
                 f[F_OVERFLOW] = 0;
                 f[F_TICKET] = 0;
                 f[F_GO] = 1;
+                if (!a.one) a.sums[0] = a.sums[1] = 0;
             }
         }
     }
-    if (!full) return;
+    if (!full || !a.one) return;
 
-    const int m = a.advance ? t % 3 : (t + 2) % 3;   // state index after the step
-    Cont *const ct = cur ? a.cont1 : a.cont0;
-    const int32_t *const cf = cur ? a.first1 : a.first0;
-    Cont *const nct = cur ? a.cont0 : a.cont1;
-    int32_t *const ncf = cur ? a.first0 : a.first1;
-    for (int64_t c = threadIdx.x; c < a.C; c += 1024) {
-        // the places of a chunk's particles: those that stay in its containers,
-        // container by container, then its inboxes' records, then (from the
-        // cursor on) injections and the movers whose inbox was full
-        const int32_t j0 = cf[c], j1 = cf[c + 1];
-        int32_t n = 0, all = 0;
-        for (int32_t j = j0; j < j1; ++j) {
-            ct[j].place[0] = n;
-            n += ct[j].s[m].cnt - ct[j].s[m].h;
-        }
-        all = n;
-        for (int32_t j = j0; j < j1; ++j) {
-            ct[j].place[1] = n;
-            n += min(ct[j].in[m], inbox_cap(ct[j].room, a.whole));
-            all += ct[j].in[m];
-        }
-        if (a.staged) {
-            all += a.staged[c];
-            a.staged[c] = 0;
-        }
-        a.new_cnt[c] = all;
-        a.cursor[c] = n;
-    }
+    const Layouts L(a, cur, a.advance ? t % 3 : (t + 2) % 3);
+    for (int64_t c = threadIdx.x; c < a.C; c += 1024) count_chunk(a, L, c);
     __syncthreads();
     // The particles are counted here, not by the host: a captured step may be
     // replayed after more have been put in.
     int64_t w = 0, np = 0, denom, total;
     for (int64_t c = threadIdx.x; c < a.C; c += 1024) {
-        w += room_weight(a.new_cnt, a.nc, c);
+        w += room_weight([&](int32_t j) { return a.new_cnt[j]; }, a.nc, c);
         np += a.new_cnt[c];
     }
     block_excl_scan<int64_t>(w, denom);
     block_excl_scan<int64_t>(np, total);
-    const int64_t spare = a.slots - total;
-    // (of the steps until the next full re-bin: a sixteenth of the particles)
-    if (threadIdx.x == 0) f[F_HOLE_LIMIT] = (int32_t)(total / 16 + 1024);
     int64_t slot0 = 0;
     int32_t cont_0 = 0, rec0 = 0;
     for (int64_t r0 = 0; r0 < a.C; r0 += 1024) {
         const int64_t c = r0 + threadIdx.x;
-        int32_t n = 0, k = 0, per = 0, room = 0;
-        if (c < a.C) {
-            n = a.new_cnt[c];
-            k = n > kSeg ? (n + kSeg - 1) / kSeg : 1;
-            per = ((n + k - 1) / k + kAlign - 1) / kAlign * kAlign;
-            const int64_t extra = spare * room_weight(a.new_cnt, a.nc, c) / denom / k;
-            room = (int32_t)min((int64_t)kRoomMax, per + extra / kAlign * kAlign);
-        }
-        const int32_t icap = c < a.C ? inbox_cap(room, a.whole) : 0;
+        Room r = {0, 0, 0, 0, 0};
+        if (c < a.C) r = chunk_room(a, c, a.slots - total, denom);
         int64_t slots_r;
         int32_t conts_r, recs_r;
-        const int64_t base = slot0 + block_excl_scan<int64_t>((int64_t)k * room, slots_r);
-        const int32_t j0 = cont_0 + block_excl_scan<int32_t>(k, conts_r);
-        const int32_t ib = rec0 + block_excl_scan<int32_t>(k * icap, recs_r);
-        if (c < a.C) {
-            ncf[c] = j0;
-            a.lay[c] = int4{(int32_t)base, per, room, k};
-            for (int32_t i = 0; i < k; ++i) {
-                Cont d;
-                d.c = (int32_t)c;
-                d.base = (int32_t)base + i * room;
-                d.room = room;
-                d.ibase = ib + i * icap;
-                d.k = k;
-                for (int u = 0; u < 3; ++u) {
-                    d.in[u] = 0;
-                    d.s[u].cnt = u == m ? min(max(n - i * per, 0), per) : 0;
-                    d.s[u].h = 0;
-                }
-                d.place[0] = d.place[1] = 0;
-                nct[j0 + i] = d;
-            }
-        }
+        const int64_t base = slot0 + block_excl_scan<int64_t>((int64_t)r.k * r.room, slots_r);
+        const int32_t j0 = cont_0 + block_excl_scan<int32_t>(r.k, conts_r);
+        const int32_t ib = rec0 + block_excl_scan<int32_t>(r.k * r.icap, recs_r);
+        if (c < a.C) write_chunk(a, L, c, r, base, j0, ib);
         slot0 += slots_r;
         cont_0 += conts_r;
         rec0 += recs_r;
     }
-    if (threadIdx.x == 0) {
-        ncf[a.C] = cont_0;
-        f[cur ? F_NITEMS : F_NITEMS1] = cont_0;
+    if (threadIdx.x == 0) finish_layout(a, L, cont_0, total);
+}
+
+// The same layout over many workgroups, 1024 chunks each, behind the gate: the
+// counts and the two sums of them, then each block's slots, containers and
+// records, then the layout.  Bound by latency, then by the containers' lines
+// (64 B read, 64 B written): 27 + 7 + 14 us at 262144 chunks.
+constexpr int kLayBlock = 1024;
+
+__device__ __forceinline__ Layouts gated_layouts(const GateArgs &a)
+{
+    return Layouts(a, a.flags[F_CUR], (a.flags[F_TICK] + 2) % 3);
+}
+
+__global__ void __launch_bounds__(kLayBlock) k_lay_count(GateArgs a)
+{
+    if (!a.flags[F_GO]) return;
+    const Layouts L = gated_layouts(a);
+    const int64_t c = (int64_t)blockIdx.x * kLayBlock + threadIdx.x;
+    int64_t np = 0, w = 0;
+    if (c < a.C) {
+        np = count_chunk(a, L, c);
+        w = room_weight([&](int32_t j) { return chunk_total(a, L, j); }, a.nc, c);
     }
+    int64_t npb, wb;
+    block_excl_scan<int64_t>(np, npb);
+    block_excl_scan<int64_t>(w, wb);
+    if (threadIdx.x == 0) {
+        atomicAdd((unsigned long long *)a.sums, (unsigned long long)npb);
+        atomicAdd((unsigned long long *)a.sums + 1, (unsigned long long)wb);
+    }
+}
+
+__device__ __forceinline__ int4 pack_part(int64_t slots, int32_t conts, int32_t recs)
+{
+    return int4{(int32_t)slots, (int32_t)(slots >> 32), conts, recs};
+}
+__device__ __forceinline__ int64_t part_slots(const int4 &p)
+{
+    return (int64_t)(uint32_t)p.x | (int64_t)p.y << 32;
+}
+
+__global__ void __launch_bounds__(kLayBlock) k_lay_rooms(GateArgs a)
+{
+    if (!a.flags[F_GO]) return;
+    const int64_t c = (int64_t)blockIdx.x * kLayBlock + threadIdx.x;
+    Room r = {0, 0, 0, 0, 0};
+    if (c < a.C) r = chunk_room(a, c, a.slots - a.sums[0], a.sums[1]);
+    int64_t slots;
+    int32_t conts, recs;
+    block_excl_scan<int64_t>((int64_t)r.k * r.room, slots);
+    block_excl_scan<int32_t>(r.k, conts);
+    block_excl_scan<int32_t>(r.k * r.icap, recs);
+    if (threadIdx.x == 0) a.part[blockIdx.x] = pack_part(slots, conts, recs);
+}
+
+__global__ void __launch_bounds__(kLayBlock) k_lay_write(GateArgs a)
+{
+    if (!a.flags[F_GO]) return;
+    const Layouts L = gated_layouts(a);
+    // where the block begins: the blocks before it
+    int64_t s = 0, slot0;
+    int32_t j = 0, i = 0, cont_0, rec0;
+    for (int32_t b = threadIdx.x; b < (int32_t)blockIdx.x; b += kLayBlock) {
+        const int4 p = a.part[b];
+        s += part_slots(p);
+        j += p.z;
+        i += p.w;
+    }
+    block_excl_scan<int64_t>(s, slot0);
+    block_excl_scan<int32_t>(j, cont_0);
+    block_excl_scan<int32_t>(i, rec0);
+    const int64_t c = (int64_t)blockIdx.x * kLayBlock + threadIdx.x;
+    Room r = {0, 0, 0, 0, 0};
+    if (c < a.C) r = chunk_room(a, c, a.slots - a.sums[0], a.sums[1]);
+    int64_t slots_r;
+    int32_t conts_r, recs_r;
+    const int64_t base = slot0 + block_excl_scan<int64_t>((int64_t)r.k * r.room, slots_r);
+    const int32_t j0 = cont_0 + block_excl_scan<int32_t>(r.k, conts_r);
+    const int32_t ib = rec0 + block_excl_scan<int32_t>(r.k * r.icap, recs_r);
+    if (c < a.C) write_chunk(a, L, c, r, base, j0, ib);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        finish_layout(a, L, cont_0 + conts_r, a.sums[0]);
 }
 
 __global__ void k_set_flag(int32_t *flags, int which, int32_t v) { flags[which] = v; }
@@ -1845,18 +1976,33 @@ Staging<T> staging_of(st_ctx *c)
                       c->stage_in_store};
 }
 
+// Up to this many chunks the gate's own workgroup makes the layout.  Behind a
+// step the three launches of the other way nearly always find nothing to do and
+// cost it 13 us all the same; behind injections there is always a layout to
+// make.  Layout of 4096 chunks in one workgroup 40 us, of 32768 0.27 ms against
+// 0.031 in three launches, of 262144 2.3 ms against 0.048, of 2097152 20 ms
+// against 0.23: at 32768 the launches pay from a full re-bin every 18 steps on.
+constexpr int64_t kLayoutOneStep = 32768, kLayoutOneFlush = 4096;
+
 // everything after the step kernel (or, npend > 0, the placing of the staged
 // injections): the gate, and the full re-bin's scatter
 template <class T>
 hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 {
     c->store_stream = s;
+    const bool one = c->C <= (npend ? kLayoutOneFlush : kLayoutOneStep);
     const GateArgs g{c->cont[0], c->cont[1], c->first[0], c->first[1], c->new_cnt, c->cursor,
-                     c->lay, c->flags, c->spread, c->C,
+                     c->lay, c->flags, c->spread, c->lay_sums, c->lay_part, c->C,
                      {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]},
                      c->slots - (int64_t)kAlign * c->max_items, c->whole_inbox, npend == 0,
-                     npend ? c->staged : nullptr};
+                     npend ? c->staged : nullptr, one};
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
+    if (!one) {
+        const dim3 lb((c->C + kLayBlock - 1) / kLayBlock);
+        hipLaunchKernelGGL(k_lay_count, lb, dim3(kLayBlock), 0, s, g);
+        hipLaunchKernelGGL(k_lay_rooms, lb, dim3(kLayBlock), 0, s, g);
+        hipLaunchKernelGGL(k_lay_write, lb, dim3(kLayBlock), 0, s, g);
+    }
     const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
                            (const MoverRec<T> *)c->rec, c->nrec, staging_of<T>(c), npend, c->lay,
                            c->cursor, c->flags, c->C, c->whole_inbox, c->prm,

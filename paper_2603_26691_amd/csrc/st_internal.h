@@ -227,6 +227,8 @@ struct st_ctx {
     int32_t *cursor = nullptr;     // [C] scatter cursors of the full re-bin
     int32_t *new_cnt = nullptr;    // [C] particles per chunk at a full re-bin
     int4 *lay = nullptr;           // [C] its layout: first slot, per container, room, containers
+    int64_t *lay_sums = nullptr;   // [2] and [C/1024+1]: sums of a layout made in several
+    int4 *lay_part = nullptr;      // launches
     int32_t *flags = nullptr;      // DevFlag
     int32_t *spread = nullptr;     // spread counters
     void *src = nullptr;           // [C][3][E^3] accumulator (double or float)

@@ -1,0 +1,45 @@
+"""The layout of a full re-bin on the GPU, made by one workgroup and by several
+launches, at chunk counts on either side of where they meet (behind injections
+and behind steps) and at ones that fill no whole blocks, with a chunk of two
+containers that empties into its neighbours: lockstep against the FP64 oracle."""
+import numpy as np
+import pytest
+
+from gpu_helpers import fields, lockstep_check, oracle_mesh, state, tracker, workload
+from oracle.oracle import load as load_oracle
+
+pytestmark = pytest.mark.gpu
+
+TOL = {   # as in the lockstep parity tests
+    "fp64": {"pos": 1e-13, "vel": 1e-12, "src": 1e-10},
+    "fp32_local": {"pos": 1e-5, "vel": 1e-5, "src": 1e-6},
+}
+
+
+@pytest.mark.parametrize("form", sorted(TOL))
+@pytest.mark.parametrize("n,chunks", [((32, 32, 32), 4096), ((32, 34, 32), 4352),
+                                      ((64, 64, 64), 32768), ((64, 66, 64), 33792),
+                                      ((66, 70, 62), 35805)])
+def test_layouts(form, n, chunks):
+    orc = load_oracle()
+    P = 60_000
+    w = workload("tg32", n=n, L=tuple(0.1 * v / 64 for v in n), P=P, noise=0.3, chunk_edge=2)
+    assert n[0] * n[1] * n[2] // 8 == chunks
+    rng = np.random.default_rng(chunks)
+    x = rng.random((P, 3)) * np.array(w.L)
+    x[:20_000] = rng.random((20_000, 3)) * 2 * w.h         # one chunk
+    up = rng.normal(0.0, 1.0, (P, 3))
+    d = np.full(P, 60e-6)
+    t = tracker(w, form, capacity=P + 100)
+    Udev, Uor = fields(w, form)
+    vmax = float(np.abs(up).max())
+    tol = dict(TOL[form], vel=TOL[form]["vel"] * vmax)
+    t.inject(x[:40_000], up[:40_000], d[:40_000])
+    lockstep_check(t, orc, oracle_mesh(w), Udev, Uor, 1e-3, 2, tol)
+    t.inject(x[40_000:], up[40_000:], d[40_000:])
+    before = t.stats()["repacks"]
+    lockstep_check(t, orc, oracle_mesh(w), Udev, Uor, 1e-3, 4, tol)
+    st = t.stats()
+    assert st["repacks"] > before + 1, st                  # (one places the injection)
+    assert np.array_equal(state(t)["id"], np.arange(P))
+    t.close()
