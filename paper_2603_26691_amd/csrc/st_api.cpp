@@ -357,12 +357,6 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
     // plus what rounding every room up to kAlign can take
     c->slots = d.capacity + std::max<int64_t>(d.capacity / 4, (int64_t)st::kSlackMin * p.C) +
                (int64_t)st::kAlign * c->max_items;
-    // inboxes: whole rooms in a small store, else an eighth of them
-    c->whole_inbox = c->slots <= (1 << 17);
-    c->nrec = c->whole_inbox ? c->slots : c->slots / 8 + 16 * c->max_items;
-    // staging of injections into a store that holds particles: a full re-bin
-    // places them, so a load should fill it few times
-    c->mcap = std::min<int64_t>(d.capacity, std::max<int64_t>(1 << 17, d.capacity / 16 * 5));
     if (c->slots >= ((int64_t)1 << 31) - 1 || c->max_items >= ((int64_t)1 << 30))
         return bad("capacity too large for 32-bit slot indices");
 
@@ -378,34 +372,54 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
     size_t total = 0;
     const int64_t C = p.C;
     auto stagger = [](int b, int k) { return (size_t)(8 * b + k) * st::kStagger; };
+    // The inboxes, and the staging area of injections into a store that holds
+    // particles (a full re-bin places them, so a load should fill it few times).
+    // Where these do not fit beside the store, smaller ones: the steps then take
+    // the full re-bin more often.
+    const st::InboxRule rules[3] = {c->slots <= (1 << 17) ? st::InboxRule{0, 0}
+                                                          : st::InboxRule{3, 16},
+                                    {3, 4}, {5, 0}};
+    auto sizes = [&](int level) {
+        c->inbox = rules[level];
+        c->nrec = (c->slots >> c->inbox.shift) + c->inbox.plus * c->max_items;
+        const int64_t stage = level ? std::max<int64_t>(1 << 16, d.capacity / 8)
+                                    : std::max<int64_t>(1 << 17, d.capacity / 16 * 5);
+        c->mcap = std::min<int64_t>(d.capacity, stage);
+    };
     hipError_t ok = hipErrorOutOfMemory;
     try {
-        std::vector<Wanted> want;
-        auto A = [&](auto **ptr, size_t bytes) { want.push_back({(void **)ptr, bytes}); };
-        for (int b = 0; b < 2; ++b)
-            for (int k = 0; k < 8; ++k)
-                A(&c->store[b][k], (size_t)c->slots * (k < 7 ? c->tsize : 4) + stagger(b, k));
-        for (int b = 0; b < 2; ++b) {
-            A(&c->cont[b], (size_t)c->max_items * sizeof(st::Cont));
-            A(&c->first[b], (size_t)(C + 1) * 4);
+        const size_t rec = c->tsize == 8 ? sizeof(st::MoverRec<double>)
+                                         : sizeof(st::MoverRec<float>);
+        for (int level = 0; level < 3 && ok == hipErrorOutOfMemory; ++level) {
+            for (auto &b : c->blocks) st::block_free(device, &b);
+            c->blocks.clear();
+            sizes(level);
+            std::vector<Wanted> want;
+            auto A = [&](auto **ptr, size_t bytes) { want.push_back({(void **)ptr, bytes}); };
+            for (int b = 0; b < 2; ++b)
+                for (int k = 0; k < 8; ++k)
+                    A(&c->store[b][k], (size_t)c->slots * (k < 7 ? c->tsize : 4) + stagger(b, k));
+            for (int b = 0; b < 2; ++b) {
+                A(&c->cont[b], (size_t)c->max_items * sizeof(st::Cont));
+                A(&c->first[b], (size_t)(C + 1) * 4);
+            }
+            A(&c->rec, (size_t)(2 * c->nrec) * rec);
+            A(&c->stage, (size_t)c->mcap * rec);
+            A(&c->stage_dest, (size_t)c->mcap * 4);
+            A(&c->staged, (size_t)C * 4);
+            A(&c->cursor, (size_t)C * 4);
+            A(&c->new_cnt, (size_t)C * 4);
+            A(&c->lay, (size_t)C * 16);
+            A(&c->lay_sums, 16);
+            A(&c->lay_part, (size_t)(C / 1024 + 1) * 16);
+            A(&c->flags, (size_t)st::F_COUNT * 4);
+            A(&c->spread, (size_t)st::kSpreadInts * 4);
+            A(&c->src, (size_t)3 * ncell * c->asize);
+            A(&c->written, (size_t)C * 4);
+            ok = allocate(c, want, total);
         }
-        A(&c->rec, (size_t)(2 * c->nrec) * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
-                                                          : sizeof(st::MoverRec<float>)));
-        A(&c->stage, (size_t)c->mcap * (c->tsize == 8 ? sizeof(st::MoverRec<double>)
-                                                      : sizeof(st::MoverRec<float>)));
-        A(&c->stage_dest, (size_t)c->mcap * 4);
-        A(&c->staged, (size_t)C * 4);
-        A(&c->cursor, (size_t)C * 4);
-        A(&c->new_cnt, (size_t)C * 4);
-        A(&c->lay, (size_t)C * 16);
-        A(&c->lay_sums, 16);
-        A(&c->lay_part, (size_t)(C / 1024 + 1) * 16);
-        A(&c->flags, (size_t)st::F_COUNT * 4);
-        A(&c->spread, (size_t)st::kSpreadInts * 4);
-        A(&c->src, (size_t)3 * ncell * c->asize);
-        A(&c->written, (size_t)C * 4);
-        ok = allocate(c, want, total);
     } catch (...) {   // host memory
+        ok = hipErrorOutOfMemory;
     }
     if (ok != hipSuccess)
         return dev_bad(ST_ERR_OOM, "device allocation of " + std::to_string(total) +

@@ -151,7 +151,7 @@ struct GateArgs {
     int64_t C;
     int32_t nc[3];
     int64_t slots;           // slots to share out among the particles and the spare ones
-    int32_t whole;           // inboxes hold whole rooms
+    InboxRule inbox;
     int32_t advance;         // after a step (not for staged injections alone)
     int32_t *staged;         // [C] staged injections to be placed too, or null
     int32_t one;             // the layout is made by the gate's own workgroup
@@ -200,7 +200,7 @@ __device__ __forceinline__ int32_t count_chunk(const GateArgs &a, const Layouts 
     all = n;
     for (int32_t j = j0; j < j1; ++j) {
         L.ct[j].place[1] = n;
-        n += min(L.ct[j].in[L.m], inbox_cap(L.ct[j].room, a.whole));
+        n += min(L.ct[j].in[L.m], inbox_cap(L.ct[j].room, a.inbox));
         all += L.ct[j].in[L.m];
     }
     if (a.staged) all += a.staged[c];
@@ -246,7 +246,7 @@ __device__ __forceinline__ Room chunk_room(const GateArgs &a, int64_t c, int64_t
     const int64_t w = room_weight([&](int32_t j) { return a.new_cnt[j]; }, a.nc, c);
     const int64_t extra = spare * w / denom / r.k;
     r.room = (int32_t)min((int64_t)kRoomMax, r.per + extra / kAlign * kAlign);
-    r.icap = inbox_cap(r.room, a.whole);
+    r.icap = inbox_cap(r.room, a.inbox);
     return r;
 }
 
@@ -446,7 +446,7 @@ struct StepArgs {
     MoverRec<T> *rec;        // inboxes [2][nrec]
     int64_t nrec;
     int32_t *flags, *spread;
-    int32_t whole;           // inboxes hold whole rooms
+    InboxRule inbox;
     int32_t deposit;         // 0: move and re-bin only (tape recompute)
     // taped steps and their recomputation: what the reverse of the step reads,
     // saved into a snapshot buffer at the store's slot indices: the state each slot
@@ -562,10 +562,10 @@ __device__ __forceinline__ bool left_chunk(T x, T y, T z, T fe)
 struct Inbox {
     int32_t free, cap, base;
 };
-__device__ __forceinline__ Inbox inbox_of(const Cont *d, int pm, int32_t whole)
+__device__ __forceinline__ Inbox inbox_of(const Cont *d, int pm, InboxRule rule)
 {
     const int32_t room = d->room;
-    return Inbox{room - (d->s[pm].cnt - d->s[pm].h) - d->in[pm], inbox_cap(room, whole), d->ibase};
+    return Inbox{room - (d->s[pm].cnt - d->s[pm].h) - d->in[pm], inbox_cap(room, rule), d->ibase};
 }
 
 // The container of chunk c that container `item` sends its movers to.
@@ -587,7 +587,7 @@ __device__ __forceinline__ bool send_mover(const StepArgs<T, A> &a, Cont *ct,
 {
     const int64_t cn = chunk_of_stored(a.p, c, x, y, z);
     const int32_t j = container_for(first, cn, item);
-    const Inbox in = inbox_of(ct + j, pm, a.whole);
+    const Inbox in = inbox_of(ct + j, pm, a.inbox);
     const int32_t r = atomicAdd(&ct[j].in[m], 1);
     if (r >= in.free) a.flags[F_OVERFLOW] = 1;
     if (r >= in.cap) {
@@ -752,7 +752,7 @@ __global__ void __launch_bounds__(NB)
                                        wrap1(cy + (l / 3) % 3 - 1, p.nc[1]),
                                        wrap1(cz + l / 9 - 1, p.nc[2]));
         nb = ni == (int32_t)p.C ? (int32_t)dc : container_for(first, dc, (int32_t)item);
-        const Inbox in = inbox_of(ct + nb, pm, a.whole);
+        const Inbox in = inbox_of(ct + nb, pm, a.inbox);
         nb_free = in.free;
         nb_cap = in.cap;
         nb_base = in.base;
@@ -1307,7 +1307,7 @@ struct ScatterArgs {
     int32_t *cursor;
     int32_t *flags;
     int64_t C;
-    int32_t whole;
+    InboxRule inbox;
     Params p;
     int4 *src;               // sources, and a chunk's size in 16-byte pieces
     int32_t src_pieces;
@@ -1358,7 +1358,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
     for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) {
         const ContState me = state_of(ct + it, m);
         const int32_t c = me.c, cnt = me.cnt;
-        const int32_t nin = min(me.in, inbox_cap(me.room, a.whole));
+        const int32_t nin = min(me.in, inbox_cap(me.room, a.inbox));
         if (cnt == 0 && nin == 0) continue;   // uniform
         const int4 l = a.lay[c];
         if (threadIdx.x == 0) pos = ct[it].place[0];
@@ -1994,7 +1994,7 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
     const GateArgs g{c->cont[0], c->cont[1], c->first[0], c->first[1], c->new_cnt, c->cursor,
                      c->lay, c->flags, c->spread, c->lay_sums, c->lay_part, c->C,
                      {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]},
-                     c->slots - (int64_t)kAlign * c->max_items, c->whole_inbox, npend == 0,
+                     c->slots - (int64_t)kAlign * c->max_items, c->inbox, npend == 0,
                      npend ? c->staged : nullptr, one};
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
     if (!one) {
@@ -2005,7 +2005,7 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
     }
     const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
                            (const MoverRec<T> *)c->rec, c->nrec, staging_of<T>(c), npend, c->lay,
-                           c->cursor, c->flags, c->C, c->whole_inbox, c->prm,
+                           c->cursor, c->flags, c->C, c->inbox, c->prm,
                            (int4 *)c->src,
                            (int32_t)(3 * c->prm.E * c->prm.E * c->prm.E * c->asize / 16),
                            c->written};
@@ -2117,7 +2117,7 @@ hipError_t launch_step(st_ctx *c, const void *u, double dt, int deposit, hipStre
         a.nrec = c->nrec;
         a.flags = c->flags;
         a.spread = c->spread;
-        a.whole = c->whole_inbox;
+        a.inbox = c->inbox;
         a.deposit = deposit;
         a.p = c->prm;
         a.dt = (T)dt;

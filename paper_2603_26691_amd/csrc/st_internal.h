@@ -86,11 +86,19 @@ struct alignas(64) Cont {
 };
 static_assert(sizeof(Cont) == 64, "a container is one 64-byte line");
 
-// records an inbox holds: a container's whole room in a small store, else an
-// eighth of it (more arrivals in one step take the full re-bin)
-__host__ __device__ __forceinline__ int32_t inbox_cap(int32_t room, int32_t whole)
+// Records an inbox holds (more arrivals in one step take the full re-bin): a
+// share of its container's room, 1 / 2^shift, and some.  The whole rooms in a
+// small store; else an eighth and 16, which on meshes of many sparse chunks is
+// a large part of a context (512^3 cells in chunks of 2^3: 22 GB of 67 in
+// binary32); where that does not fit, an eighth and 4, and then a 32nd.  (Not less
+// at once: with an eighth and 4, 3e7 droplets in 2 097 152 chunks took a full
+// re-bin every step, 33.9 ms a step against 25.6.)
+struct InboxRule {
+    int32_t shift, plus;
+};
+__host__ __device__ __forceinline__ int32_t inbox_cap(int32_t room, InboxRule rule)
 {
-    return whole ? room : room / 8 + 16;
+    return (room >> rule.shift) + rule.plus;
 }
 
 // One particle in flight between chunks (also staged by st_inject), kept together so that moving it reads and writes whole
@@ -206,7 +214,7 @@ struct st_ctx {
     int64_t slots = 0;         // slots per store
     int64_t mcap = 0;          // staging capacity of injections
     int64_t nrec = 0;          // records of one tick's inboxes
-    int32_t whole_inbox = 0;   // inboxes hold their containers' whole rooms
+    st::InboxRule inbox = {0, 0};
     int64_t max_items = 0;     // upper bound of containers
     int64_t count = 0;         // particles in the store (host mirror)
     int64_t pending = 0;       // injected particles waiting in the staging area

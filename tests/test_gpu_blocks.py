@@ -85,8 +85,8 @@ def _free():
     return seen[-1]
 
 
-def _fill():
-    """Tensors that leave 64 to 128 MiB of device memory."""
+def _fill(leave=1):
+    """Tensors that leave `leave` to `leave` + 1 times 64 MiB of device memory."""
     import torch
     held = [torch.empty(_free() - (1 << 30), dtype=torch.uint8, device="cuda")]
     try:
@@ -94,8 +94,8 @@ def _fill():
             held.append(torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
     except torch.OutOfMemoryError:
         pass
-    assert 3 < len(held) < 200
-    del held[-1:]
+    assert leave + 1 < len(held) < 200
+    del held[-leave:]
     torch.cuda.empty_cache()
     return held
 

@@ -43,3 +43,47 @@ def test_layouts(form, n, chunks):
     assert st["repacks"] > before + 1, st                  # (one places the injection)
     assert np.array_equal(state(t)["id"], np.arange(P))
     t.close()
+
+
+def _lockstep_mixing(form, n, P, steps, t_of):
+    """A tracker of a sparse mesh of 2-cell chunks, a few thousand droplets in one
+    of them, most droplets in another chunk after every step."""
+    orc = load_oracle()
+    w = workload("tg32", n=n, L=tuple(0.1 * v / 64 for v in n), P=P, noise=0.3, chunk_edge=2)
+    rng = np.random.default_rng(P)
+    x = rng.random((P, 3)) * np.array(w.L)
+    x[:3000] = rng.random((3000, 3)) * 2 * w.h
+    up = rng.normal(0.0, 2.0, (P, 3))
+    d = np.full(P, 60e-6)
+    Udev, Uor = fields(w, form)
+    t = t_of(w)
+    vmax = float(np.abs(up).max())
+    tol = dict(TOL[form], vel=TOL[form]["vel"] * vmax)
+    t.inject(x, up, d)
+    lockstep_check(t, orc, oracle_mesh(w), Udev, Uor, 1e-3, steps, tol)
+    assert np.array_equal(state(t)["id"], np.arange(P))
+    st = t.stats()
+    assert st["movers"] > P // 3, st
+    t.close()
+    return st
+
+
+@pytest.mark.parametrize("form,n,leave,least", [("fp64", 96, 10, 1), ("fp64", 128, 20, 3),
+                                                ("fp32_local", 128, 11, 3)])
+def test_small_inboxes_where_memory_is_short(form, n, leave, least):
+    """A device that has room for the store, but only for smaller inboxes beside
+    it (of the first or the second smaller size), holds the tracker all the same."""
+    import torch
+    from test_gpu_blocks import _fill
+    import paper_2603_26691_amd as pkg
+    pkg.release_memory()
+
+    def make(w):
+        held = _fill(leave)
+        t = tracker(w, form)
+        del held
+        torch.cuda.empty_cache()
+        return t
+
+    st = _lockstep_mixing(form, (n, n, n), 30_000, 3, make)
+    assert st["repacks"] >= least        # (the smallest inboxes mostly hold one record)
