@@ -127,6 +127,38 @@ void block_free(int device, Block *b)
     (void)hipFree(mine.buf);
 }
 
+namespace {
+// the capture that s takes part in (0: none; the default stream takes part in none)
+unsigned long long capture_of(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (!s) return 0;
+    if (hipStreamGetCaptureInfo(s, &status, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return status == hipStreamCaptureStatusNone ? 0 : id + 1;
+}
+}  // namespace
+
+void wrote_store(st_ctx *c, hipStream_t s)
+{
+    const unsigned long long id = capture_of(s);
+    if (id) {
+        c->capture = id;
+        c->capture_stream = s;
+    } else {
+        c->store_stream = s;
+    }
+}
+
+bool second_store_free(const st_ctx *c, hipStream_t s)
+{
+    const unsigned long long id = capture_of(s);
+    return id ? id == c->capture && s == c->capture_stream : s == c->store_stream;
+}
+
 bool saved_fit(const st_ctx *c, int64_t n)
 {
     const size_t left = c->saved_max > c->saved_bytes ? c->saved_max - c->saved_bytes : 0;

@@ -1989,7 +1989,7 @@ constexpr int64_t kLayoutOneStep = 32768, kLayoutOneFlush = 4096;
 template <class T>
 hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
 {
-    c->store_stream = s;
+    wrote_store(c, s);
     const bool one = c->C <= (npend ? kLayoutOneFlush : kLayoutOneStep);
     const GateArgs g{c->cont[0], c->cont[1], c->first[0], c->first[1], c->new_cnt, c->cursor,
                      c->lay, c->flags, c->spread, c->lay_sums, c->lay_part, c->C,
@@ -2051,7 +2051,7 @@ hipError_t launch_init(st_ctx *c, hipStream_t s)
 
 hipError_t launch_settle(st_ctx *c, hipStream_t s)
 {
-    c->store_stream = s;
+    wrote_store(c, s);
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         using T = decltype(t);
         hipLaunchKernelGGL((k_settle<T>), dim3(std::min<int64_t>(c->max_items, 4096)), dim3(256), 0,
@@ -2191,10 +2191,7 @@ hipError_t launch_get_particles(st_ctx *c, double *x, double *up, double *d, int
         const int64_t gi = c->max_items < 65536 ? c->max_items : 65536;
         const Store<T> st = store_of<T>(c);
         const ParticleOut out{x, up, d, id, cell};
-        // The second store is this stream's to use when this stream wrote the
-        // store last: whoever writes the store or reads it from another
-        // stream has ordered that stream against this one first.
-        if (c->count < kRecordsMin || s != c->store_stream) {
+        if (c->count < kRecordsMin || !second_store_free(c, s)) {
             hipLaunchKernelGGL((k_get_particles<T>), dim3(gi), dim3(256), 0, s, st, c->prm,
                                c->count, out);
             return hipGetLastError();
@@ -2328,7 +2325,7 @@ hipError_t launch_snapshot(st_ctx *c, void *dst, int restore, hipStream_t s)
         const hipError_t e = launch_settle(c, s);
         if (e != hipSuccess) return e;
     } else {
-        c->store_stream = s;
+        wrote_store(c, s);
         hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(kSpreadInts)), dim3(256), 0, s, c->spread,
                            (int64_t)kSpreadInts, 0);
     }

@@ -382,15 +382,14 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
 {
     unsigned long long *b = (unsigned long long *)box;
     // Tables when the partitions fit a few of them and the re-bin's second
-    // store (nothing lies in it between re-bins; it is this stream's to use when
-    // this stream wrote the store last) has room for at least 32 workgroups'.
+    // store (second_store_free) has room for at least 32 workgroups'.
     // Beyond that each further table reads the store again, and a store too
     // small for the tables has few atomics to make.
     const int64_t passes = (nparts + kBoxTable - 1) / kBoxTable;
     const int64_t Kp = (nparts + passes - 1) / passes;
     const int64_t room = c->slots * (int64_t)c->tsize / (passes * Kp * 48);
     const int64_t groups = std::min(std::min<int64_t>(kBoxGroups, room), c->max_items);
-    const bool tables = passes <= kBoxPasses && s == c->store_stream &&
+    const bool tables = passes <= kBoxPasses && second_store_free(c, s) &&
                         groups >= std::min<int64_t>(32, c->max_items);
     auto run = [&](auto t) -> hipError_t {
         using T = decltype(t);

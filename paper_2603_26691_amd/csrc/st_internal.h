@@ -164,6 +164,16 @@ struct Block {         // device memory from block_alloc
 };
 using Snapshot = Block;   // particle store and layout at a checkpoint
 
+// Notes that a launch on s writes the store.
+void wrote_store(st_ctx *c, hipStream_t s);
+// Whether a read-out on s may use the re-bin's second store (nothing lies in it
+// between re-bins): where s wrote the store last, for whoever writes the store or
+// reads it from another stream has ordered that stream against s first.  A
+// captured read-out may where its capture wrote the store before it, for then
+// a replay is ordered as a writer; what is captured changes nothing for calls
+// outside.
+bool second_store_free(const st_ctx *c, hipStream_t s);
+
 // Device memory of the current device, at least `bytes` of it, perhaps one that
 // block_free kept (its contents are anything).
 hipError_t block_alloc(int device, size_t bytes, Block *b);
@@ -219,7 +229,10 @@ struct st_ctx {
     int64_t count = 0;         // particles in the store (host mirror)
     int64_t pending = 0;       // injected particles waiting in the staging area
     int64_t next_id = 0;
-    hipStream_t store_stream = nullptr;   // stream of the last launch that wrote the store
+    // stream of the last launch that wrote the store, and, of the last such launch
+    // that was captured, stream and capture
+    hipStream_t store_stream = nullptr, capture_stream = nullptr;
+    unsigned long long capture = 0;
 
     // device memory
     void *store[2][8] = {};    // SoA arrays of the store and the re-bin's target (F_CUR)

@@ -196,3 +196,72 @@ def test_hilbert_large_per_segment():
     b = t.hilbert_positions(order, nseg, 3, 4, 4 * per, v)
     assert torch.equal(a, b[::4])
     t.close()
+
+
+def _kernels(call):
+    """Names of the kernels that run during call()."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return " ".join(e.name for e in p.events())
+
+
+def test_read_out_beside_captures():
+    """Steps and read-outs captured in graphs leave the way of other read-outs
+    alone; a captured read-out takes the fast way (through the second store) where its
+    own capture stepped first, and only there."""
+    import torch
+    P = 100_000
+    w = workload("tg32", P=P, noise=0.3)
+    a, b = tracker(w, "fp32_local"), tracker(w, "fp32_local")
+    U = fields(w, "fp32_local")[0]
+    for t in (a, b):
+        t.inject(*w.particles())
+        t.step(U, 1e-3)
+    fast = ("k_records_out", "k_bbox_tables")
+    got = {}
+
+    def read(t):
+        got["s"] = t.particles()
+        got["box"] = t.bounding_boxes(0, 1000, 100)
+
+    names = _kernels(lambda: read(a))
+    assert all(k in names for k in fast), names
+    torch.cuda.synchronize()
+    step, both, only = (torch.cuda.CUDAGraph() for _ in range(3))
+    with torch.cuda.graph(step):
+        a.step(U, 1e-3)
+    with torch.cuda.graph(both):
+        a.step(U, 1e-3)
+        read(a)
+    in_both = got.copy()
+    with torch.cuda.graph(only):
+        read(a)
+    in_only = got.copy()
+    torch.cuda.synchronize()
+
+    def same(out):
+        want = {}
+        want["s"], want["box"] = b.particles(), b.bounding_boxes(0, 1000, 100)
+        for k in want["s"]:
+            assert torch.equal(out["s"][k], want["s"][k]), k
+        assert torch.equal(out["box"], want["box"])
+
+    for k in range(3):
+        step.replay()
+        b.step(U, 1e-3)
+        names = _kernels(lambda: read(a))
+        assert all(n in names for n in fast), names
+        same(got)
+        names = _kernels(both.replay)
+        b.step(U, 1e-3)
+        assert all(n in names for n in fast), names
+        same(in_both)
+        names = _kernels(only.replay)
+        assert not any(n in names for n in fast) and "k_get_particles" in names, names
+        same(in_only)
+    a.close()
+    b.close()
