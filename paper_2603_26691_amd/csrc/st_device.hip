@@ -2131,7 +2131,7 @@ hipError_t launch_step(st_ctx *c, const void *u, double dt, int deposit, hipStre
         a.inv_V = (T)c->prm.inv_V;
         a.re2_coef = (T)(c->prm.re_coef * c->prm.re_coef);
         hipEvent_t ev[2] = {nullptr, nullptr};
-        if (c->timing) {
+        if (c->timing && deposit) {   // (not a step that the reverse recomputes)
             for (int k = 0; k < 2; ++k) {
                 hipError_t ee = hipEventCreate(&ev[k]);
                 if (ee != hipSuccess) return ee;

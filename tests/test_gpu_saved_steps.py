@@ -72,6 +72,25 @@ def test_kept_and_recomputed(form, interp, tol, K, nsteps, nsub, reserve):
         assert _rel(g[0], oU) < tol and _rel(g[1], od) < tol, (_rel(g[0], oU), _rel(g[1], od))
 
 
+@pytest.mark.parametrize("K", [1, 4])
+def test_timing_counts_the_steps_of_the_run(K):
+    """The step-kernel timing counts a taped run's steps, and none of those
+    that its reverse recomputes (states of about 1 GB: those of 4 steps are not
+    kept)."""
+    w = workload("tg32", n=(16, 16, 16), P=2000, noise=0.2, dt=4e-4)
+    U = fields(w, "fp32_local")[0]
+    t = tracker(w, "fp32_local", capacity=26_000_000)
+    t.inject(*w.particles())
+    t.timing(True)
+    for _ in range(6):
+        t.step(U, w.dt, tape=K)
+    ms, n = t.timing(True)
+    assert n == 6 and ms > 0.0
+    t.backward(t.sources())
+    assert t.timing(False) == (0.0, 0)
+    t.close()
+
+
 def _free():
     """Free device memory once it has settled (freed memory comes back late)."""
     import time
