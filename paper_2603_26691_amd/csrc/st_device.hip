@@ -626,19 +626,21 @@ __global__ void __launch_bounds__(NB)
     constexpr int S3 = S * S * S;
     constexpr int E3 = E * E * E;
     constexpr int G = 16 / sizeof(T);   // consecutive particles per thread
+    constexpr int MS = NB < 256 ? kMoverStage / 3 : kMoverStage;   // movers staged
+    constexpr int KP = NB < kPool ? NB : kPool;                    // arrivals staged
     static_assert(kAlign % G == 0, "chunk rooms must hold whole particle groups");
     __shared__ T tile[3 * S3];
     // (binary64 in every form: LDS adds of binary32 values take twice as long on
     // this chip; 777777 droplets with Schiller-Naumann drag in the FP32-everywhere
     // form: 47 against 55 us)
     __shared__ double acc[3 * E3];
-    __shared__ int32_t mstage[kMoverStage];
+    __shared__ int32_t mstage[MS];
     // binary32 state: the staged movers' new positions and velocities (9 KB,
     // which with the arrivals still lets four workgroups share a CU; the
     // binary64 form re-reads them instead)
     constexpr bool kStageVals = sizeof(T) == 4;
-    __shared__ T mval[kStageVals ? 6 * kMoverStage : 1];
-    __shared__ MoverRec<T> pool[kPool];   // the first arrivals
+    __shared__ T mval[kStageVals ? 6 * MS : 1];
+    __shared__ MoverRec<T> pool[KP];   // the first arrivals
     __shared__ int32_t mcount, apop, nlost;
     __shared__ int32_t dcount[28], dbase[27];
     __shared__ int32_t nbj[27];           // the neighbouring chunks' containers
@@ -669,9 +671,10 @@ __global__ void __launch_bounds__(NB)
     const bool multi = me.k > 1;
     if constexpr (SAVE)
         if (threadIdx.x == 0) a.sitems[item] = RunItem{me.c, me.base, nq, me.k};
-    if (threadIdx.x == 0) ct[item].in[qm] = 0;
-    if (nq == 0) {
-        if (threadIdx.x == 0) ct[item].s[m] = {0, 0};
+    if (threadIdx.x == 0 && ct[item].in[qm] != 0) ct[item].in[qm] = 0;
+    if (nq == 0) {   // (mostly as it has been: its line stays clean)
+        if (threadIdx.x == 0 && (ct[item].s[m].cnt | ct[item].s[m].h) != 0)
+            ct[item].s[m] = {0, 0};
         return;
     }
     const Params &p = a.p;
@@ -735,7 +738,7 @@ __global__ void __launch_bounds__(NB)
     // the container's first arrivals, in 16-byte pieces
     constexpr int RV = sizeof(MoverRec<T>) / 16;
     int4 arr[RV];
-    const bool have_arr = (int)threadIdx.x < min(n_in, kPool);
+    const bool have_arr = (int)threadIdx.x < min(n_in, KP);
 #pragma unroll
     for (int u = 0; u < RV; ++u)
         arr[u] = have_arr ? reinterpret_cast<const int4 *>(rec_in + me.ibase + threadIdx.x)[u]
@@ -743,20 +746,23 @@ __global__ void __launch_bounds__(NB)
     int gi = threadIdx.x;
     T X[G], Y[G], Z[G], UX[G], UY[G], UZ[G], DD[G];
     if (gi < ngroups) load_group(gi, X, Y, Z, UX, UY, UZ, DD);
-    // the neighbouring chunks' inboxes, needed after the loop
-    int32_t nb = 0, nb_free = 0, nb_cap = 0, nb_base = 0;
-    if (threadIdx.x < 27) {
+    // The neighbouring chunks' inboxes, a lane each, needed after the loop: read
+    // ahead of it for 8^3-cell chunks, which nearly always have movers, and for
+    // smaller ones only when there are some (27 lines a container: 3 to 10 % of a
+    // step of 1 to 60 droplets a chunk).
+    constexpr bool kEarly = E == 8;
+    int32_t nb = 0;
+    Inbox nb_in = {0, 0, 0};
+    auto neighbour = [&]() {
         const int l = threadIdx.x;
         auto wrap1 = [](int i, int n) { return i < 0 ? i + n : i >= n ? i - n : i; };
         const int64_t dc = chunk_index(p, wrap1(cx + l % 3 - 1, p.nc[0]),
                                        wrap1(cy + (l / 3) % 3 - 1, p.nc[1]),
                                        wrap1(cz + l / 9 - 1, p.nc[2]));
         nb = ni == (int32_t)p.C ? (int32_t)dc : container_for(first, dc, (int32_t)item);
-        const Inbox in = inbox_of(ct + nb, pm, a.inbox);
-        nb_free = in.free;
-        nb_cap = in.cap;
-        nb_base = in.base;
-    }
+        nb_in = inbox_of(ct + nb, pm, a.inbox);
+    };
+    if (kEarly && threadIdx.x < 27) neighbour();
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
         const int t = threadIdx.x + u * NB;
@@ -827,7 +833,7 @@ __global__ void __launch_bounds__(NB)
                             pd[o + k] = rc.d;
                             pid[o + k] = rc.id;
                         };
-                        if (r < kPool) take(pool[r]);
+                        if (r < KP) take(pool[r]);
                         else take(rec_in[me.ibase + r]);
                     }
                     ++r;
@@ -1024,15 +1030,15 @@ __global__ void __launch_bounds__(NB)
 #pragma unroll
                 for (int k = 0; k < G; ++k) {
                     if (!((movers >> k) & 1)) continue;
-                    if (j < kMoverStage) {
+                    if (j < MS) {
                         const int dir = (dirs >> (kDirBits * k)) & ((1 << kDirBits) - 1);
                         mstage[j] = (int32_t)(o + k) | (dir << kSlotBits);
                         mval[j] = X[k];
-                        mval[kMoverStage + j] = Y[k];
-                        mval[2 * kMoverStage + j] = Z[k];
-                        mval[3 * kMoverStage + j] = UX[k];
-                        mval[4 * kMoverStage + j] = UY[k];
-                        mval[5 * kMoverStage + j] = UZ[k];
+                        mval[MS + j] = Y[k];
+                        mval[2 * MS + j] = Z[k];
+                        mval[3 * MS + j] = UX[k];
+                        mval[4 * MS + j] = UY[k];
+                        mval[5 * MS + j] = UZ[k];
                         X[k] = T(2 * kHoleMark);   // the slot becomes a hole
                     } else {  // more movers than the LDS stage holds
                         if (send_mover(a, ct, first, rec_out, m, pm, (int32_t)item, c, X[k], Y[k],
@@ -1045,7 +1051,7 @@ __global__ void __launch_bounds__(NB)
                 while (movers) {
                     const int k = __ffs(movers) - 1;
                     movers &= movers - 1;
-                    if (j < kMoverStage) {
+                    if (j < MS) {
                         const int dir = (dirs >> (kDirBits * k)) & ((1 << kDirBits) - 1);
                         mstage[j] = (int32_t)(o + k) | (dir << kSlotBits);
                     } else {  // more movers than the LDS stage holds
@@ -1090,17 +1096,22 @@ __global__ void __launch_bounds__(NB)
             old[u] = add && t < 3 * E3 ? src_c[t] : A(0);
         }
     }
-    if (threadIdx.x < 27) {
+    if (kEarly && threadIdx.x < 27) {
         nbj[threadIdx.x] = nb;
-        nbin[threadIdx.x] = Inbox{nb_free, nb_cap, nb_base};
+        nbin[threadIdx.x] = nb_in;
     }
     __syncthreads();
+    if (!kEarly && threadIdx.x < 27 && mcount > 0) {
+        neighbour();
+        nbj[threadIdx.x] = nb;
+        nbin[threadIdx.x] = nb_in;
+    }
 
     // Mover reservations, all issued by one wave at once: one reservation per
     // neighbouring destination instead of one per mover, which would serialise
     // on the counters of crowded chunks, and the workgroup's share of the
     // spread counters.  The movers' state is read in the same round trip.
-    const int nm = min(mcount, kMoverStage);
+    const int nm = min(mcount, MS);
     // ranks of the staged movers within their direction classes
     if (nm > 0) {
         for (int j = threadIdx.x; j < nm; j += NB) {
@@ -1110,7 +1121,7 @@ __global__ void __launch_bounds__(NB)
         }
         __syncthreads();
     }
-    constexpr int NM = (kMoverStage + NB - 1) / NB;   // staged movers per thread
+    constexpr int NM = (MS + NB - 1) / NB;   // staged movers per thread
     T mx[NM], my[NM], mz[NM], mvx[NM], mvy[NM], mvz[NM], md[NM];
     int32_t mid[NM];
 #pragma unroll
@@ -1120,11 +1131,11 @@ __global__ void __launch_bounds__(NB)
             const int64_t q = s0 + (mstage[j] & ((1 << kSlotBits) - 1));
             if constexpr (kStageVals) {
                 mx[u] = mval[j];
-                my[u] = mval[kMoverStage + j];
-                mz[u] = mval[2 * kMoverStage + j];
-                mvx[u] = mval[3 * kMoverStage + j];
-                mvy[u] = mval[4 * kMoverStage + j];
-                mvz[u] = mval[5 * kMoverStage + j];
+                my[u] = mval[MS + j];
+                mz[u] = mval[2 * MS + j];
+                mvx[u] = mval[3 * MS + j];
+                mvy[u] = mval[4 * MS + j];
+                mvz[u] = mval[5 * MS + j];
             } else {
                 mx[u] = V.ox[q];
                 my[u] = V.oy[q];
@@ -1949,6 +1960,19 @@ hipError_t launch_step_t(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
     // and hold more than one pass of 256 threads (32^3 mesh, 1e5 droplets in
     // binary64: 24.7 against 27.4 us a step with its sources; with 270
     // containers and more the larger workgroups lose 3 % and more).
+    // Half the threads on large meshes of sparse small chunks: a workgroup's time
+    // is latency there, and twice as many are in flight (64^3 cells in chunks of
+    // 2^3, 1 and 8 droplets a chunk in binary32: 196 -> 141 and 275 -> 189 us; 128^3,
+    // 2 a chunk, 1.48 -> 0.91 ms; 192^3 in chunks of 4^3, 10 a chunk, 0.75 -> 0.50
+    // ms).  Above that plumes' chunks can be crowded (64^3 in chunks of 2^3, 40 a
+    // chunk, most in one plume: 293 -> 311 us; 64^3 in chunks of 4^3, 300 a chunk,
+    // 131 -> 222), and meshes of fewer chunks are soon through.  The
+    // FP32-everywhere form (whose state takes the most registers) gains longer: 40
+    // and 60 a chunk 0.375 -> 0.24 and 0.36 -> 0.23 ms, in a plume 0.36 -> 0.37 and
+    // 0.36 -> 0.33.
+    if constexpr (E < 8)
+        if (c->C >= 32768 && c->count <= c->C * (sizeof(A) == 4 ? 64 : 12))
+            return launch_step_n<T, A, E, I, D, 128>(c, a, s, ev);
     if constexpr (E == 8)
         if (c->max_items <= 128 && c->count > c->C * 256 * (16 / (int64_t)sizeof(T)))
             return launch_step_n<T, A, E, I, D, 512>(c, a, s, ev);

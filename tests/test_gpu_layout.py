@@ -5,7 +5,7 @@ containers that empties into its neighbours: lockstep against the FP64 oracle.""
 import numpy as np
 import pytest
 
-from gpu_helpers import fields, lockstep_check, oracle_mesh, state, tracker, workload
+from gpu_helpers import band, fields, lockstep_check, oracle_mesh, state, tracker, workload
 from oracle.oracle import load as load_oracle
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +14,7 @@ TOL = {   # as in the lockstep parity tests
     "fp64": {"pos": 1e-13, "vel": 1e-12, "src": 1e-10},
     "fp32_local": {"pos": 1e-5, "vel": 1e-5, "src": 1e-6},
 }
+TOL_FP32 = {"pos": 1e-5, "vel": 1e-5, "src": 1e-4}
 
 
 @pytest.mark.parametrize("form", sorted(TOL))
@@ -87,3 +88,56 @@ def test_small_inboxes_where_memory_is_short(form, n, leave, least):
 
     st = _lockstep_mixing(form, (n, n, n), 30_000, 3, make)
     assert st["repacks"] >= least        # (the smallest inboxes mostly hold one record)
+
+
+@pytest.mark.parametrize("form,n,edge,P,crowd", [
+    ("fp32", (64, 66, 64), 2, 100_000, 5000), ("fp32_local", (64, 66, 64), 2, 33_792 * 12, 5000),
+    ("fp32_local", (64, 66, 64), 2, 33_792 * 12 + 1, 5000),      # on either side of the line
+    ("fp64", (128, 132, 128), 4, 60_000, 20_000), ("fp32", (128, 128, 128), 4, 90_000, 20_000)])
+def test_steps_of_sparse_small_chunks(form, n, edge, P, crowd):
+    """Few droplets a chunk but for one that holds more than a workgroup stages
+    of movers and arrivals."""
+    orc = load_oracle()
+    w = workload("tg32", n=n, L=tuple(0.1 * v / 64 for v in n), P=P, noise=0.3, chunk_edge=edge)
+    rng = np.random.default_rng(P)
+    x = rng.random((P, 3)) * np.array(w.L)
+    x[:crowd] = rng.random((crowd, 3)) * edge * w.h
+    up = rng.normal(0.0, 1.0, (P, 3))
+    up[:crowd] += 1.5                                   # most of them leave it together
+    d = np.full(P, 60e-6)
+    t = tracker(w, form)
+    Udev, Uor = fields(w, form)
+    vmax = float(np.abs(up).max())
+    tol = dict(TOL.get(form, TOL_FP32))
+    tol["vel"] *= vmax
+    bnd = band(form, w.n)
+    if form == "fp32":   # the binary32 rounding of the largest position
+        bnd = max(bnd, 2.0 ** -21 * (max(w.L) + vmax * 1e-3) / min(w.h))
+    t.inject(x, up, d)
+    lockstep_check(t, orc, oracle_mesh(w), Udev, Uor, 1e-3, 3, tol, band_=bnd)
+    assert np.array_equal(state(t)["id"], np.arange(P))
+    assert t.stats()["movers"] > P // 4
+    t.close()
+
+
+@pytest.mark.parametrize("form,interp,tol", [("fp64", "trilinear", 1e-9), ("fp32_local", "ngp", 1e-4)])
+def test_adjoint_of_sparse_small_chunks(form, interp, tol):
+    import torch
+    orc = load_oracle()
+    n, P, steps, dt = (64, 66, 64), 4000, 6, 5e-4
+    w = workload("tg32", n=n, L=tuple(0.1 * v / 64 for v in n), P=P, noise=0.2, chunk_edge=2)
+    x, up, d = w.particles()
+    Udev, Uor = fields(w, form)
+    t = tracker(w, form, interp=interp)
+    t.inject(x, up, d)
+    s0 = state(t)
+    for _ in range(steps):
+        t.step(Udev, dt, tape=3)
+    lam = torch.from_numpy(np.random.default_rng(1).normal(size=Uor.shape)).cuda()
+    dU, dd = (v.cpu().numpy() for v in t.backward(lam))
+    oU, od = orc.adjoint_run(oracle_mesh(w, interp=1 if interp == "ngp" else 0), np.stack([Uor]),
+                             [0] * steps, [dt] * steps, 1, s0["x"], s0["up"], s0["d"],
+                             lam.cpu().numpy())
+    assert np.linalg.norm(dU - oU[0]) <= tol * np.linalg.norm(oU)
+    assert np.linalg.norm(dd - od) <= tol * np.linalg.norm(od)
+    t.close()
