@@ -305,9 +305,14 @@ __global__ void __launch_bounds__(256) k_bbox(BoxArgs<T> a)
         const int64_t cc[3] = {c % p.nc[0], (c / p.nc[0]) % p.nc[1],
                                c / ((int64_t)p.nc[0] * p.nc[1])};
         const int32_t cnt = me.cnt, all = cnt + me.in;   // the arrivals last
+        if (all == 0) continue;
+        // A container's particles lie about in the order of their ids, so
+        // workgroups that all began with the first would meet at the same boxes.
+        const int32_t shift = (int32_t)((uint32_t)it * 2654435761u % (uint32_t)all);
         // every lane of the workgroup runs the same number of rounds
         for (int32_t o0 = 0; o0 < all; o0 += blockDim.x) {
-            const int32_t o = o0 + threadIdx.x;
+            int32_t o = o0 + threadIdx.x;
+            o = o < all ? (o + shift < all ? o + shift : o + shift - all) : all;
             int64_t part = -1;
             double xg[3] = {0.0, 0.0, 0.0};
             if (o < cnt) {
@@ -381,15 +386,18 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
                                  double *box, hipStream_t s)
 {
     unsigned long long *b = (unsigned long long *)box;
-    // Tables when the partitions fit a few of them and the re-bin's second
-    // store (second_store_free) has room for at least 32 workgroups'.
-    // Beyond that each further table reads the store again, and a store too
-    // small for the tables has few atomics to make.
+    // Tables when the partitions fit a few of them, the re-bin's second
+    // store (second_store_free) has room for at least 32 workgroups' of them, and the
+    // atomics that they save are worth their 23 to 27 us: particles enough for each
+    // box to be in demand (P / nparts = 78: 18 us directly, 234: 41, 312: 49) or in
+    // all (2e5 in 1000 boxes 68 us directly, 36 by tables).  Beyond kBoxPasses each
+    // further table reads the store again.
     const int64_t passes = (nparts + kBoxTable - 1) / kBoxTable;
     const int64_t Kp = (nparts + passes - 1) / passes;
     const int64_t room = c->slots * (int64_t)c->tsize / (passes * Kp * 48);
     const int64_t groups = std::min(std::min<int64_t>(kBoxGroups, room), c->max_items);
-    const bool tables = passes <= kBoxPasses && second_store_free(c, s) &&
+    const bool many = c->count >= 150 * nparts || c->count >= 1 << 17;
+    const bool tables = many && passes <= kBoxPasses && second_store_free(c, s) &&
                         groups >= std::min<int64_t>(32, c->max_items);
     auto run = [&](auto t) -> hipError_t {
         using T = decltype(t);

@@ -163,6 +163,25 @@ def test_boxes_of_more_partitions_than_one_table():
     t.close()
 
 
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("P,nparts", [(15_000, 100), (14_999, 100), (131_072, 4000),
+                                      (131_071, 4000)])
+def test_boxes_where_their_way_changes(form, P, nparts):
+    """Particles per box, and in all, on either side of where tables take over
+    from updates in memory."""
+    import torch
+    t, _ = _moved(P, form, capacity=600_000)
+    x = t.particles()["x"]
+    per = -(-P // nparts)
+    at = (torch.arange(P, device="cuda") // per)[:, None].expand(-1, 3)
+    inf = float("inf")
+    lo = torch.full((nparts, 3), inf, dtype=torch.float64, device="cuda")
+    hi = torch.full((nparts, 3), -inf, dtype=torch.float64, device="cuda")
+    want = torch.cat([lo.scatter_reduce(0, at, x, "amin"), hi.scatter_reduce(0, at, x, "amax")], 1)
+    assert torch.equal(t.bounding_boxes(0, per, nparts), want)
+    t.close()
+
+
 # (64-bit divisions from 65536 segments, or where per_seg times a segment's
 # voxels reaches 2^32)
 @pytest.mark.parametrize("order,nseg,seg_begin,seg_end,per_seg", [
