@@ -2203,9 +2203,11 @@ hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s)
     });
 }
 
-// The two-pass read-out from this many particles on (below it the outputs stay
-// in the caches and its two launches more cost more than they save).
-constexpr int64_t kRecordsMin = 1 << 16;
+// The two-pass read-out from this many particles on.  Below it the outputs stay
+// in the caches, and its two launches more cost more than they save: 65536
+// particles 20 us directly, 25 in two passes; 131072 22 and 25; 262144 40 and 25
+// (binary64 40 and 32).
+constexpr int64_t kRecordsMin = 5 << 15;
 
 hipError_t launch_get_particles(st_ctx *c, double *x, double *up, double *d, int64_t *id,
                                 int32_t *cell, hipStream_t s)

@@ -217,6 +217,24 @@ def test_hilbert_large_per_segment():
     t.close()
 
 
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("P", [163_839, 163_840])
+def test_read_out_where_its_way_changes(form, P):
+    """The two ways of the read-out give the same droplets as another stream's,
+    which is always direct."""
+    import torch
+    t, _ = _moved(P, form)
+    mine = t.particles()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        other = t.particles()
+    torch.cuda.synchronize()
+    assert torch.equal(mine["id"], torch.arange(P, device="cuda"))
+    for k in mine:
+        assert torch.equal(mine[k], other[k]), k
+    t.close()
+
+
 def _kernels(call):
     """Names of the kernels that run during call()."""
     import torch
@@ -233,7 +251,7 @@ def test_read_out_beside_captures():
     alone; a captured read-out takes the fast way (through the second store) where its
     own capture stepped first, and only there."""
     import torch
-    P = 100_000
+    P = 200_000
     w = workload("tg32", P=P, noise=0.3)
     a, b = tracker(w, "fp32_local"), tracker(w, "fp32_local")
     U = fields(w, "fp32_local")[0]
