@@ -1319,6 +1319,7 @@ struct ScatterArgs {
     int32_t *flags;
     int64_t C;
     InboxRule inbox;
+    int32_t sparse;          // containers hold few particles: a wave for each
     Params p;
     int4 *src;               // sources, and a chunk's size in 16-byte pieces
     int32_t src_pieces;
@@ -1350,15 +1351,23 @@ constexpr int kScatterGroups = 1024;   // they run every step and usually exit a
 constexpr int kHistMax = 8192;
 constexpr int kTilePer = 16, kTile = kTilePer * kScatterBlock;
 
+// Containers of more slots than kWaveSlots are never a wave's, up to kBigMax of a
+// workgroup's (a wave takes 64 slots in the time of a workgroup's 512).
+constexpr int kWaveSlots = 1024, kBigMax = 256;
+
 // Full re-bin: the occupied slots and the records, chunk by chunk, into the
 // second store, which the last workgroup makes the store.  A container's
-// particles that stay in its chunk get consecutive places (one reservation
-// per container), and so do its arrivals.
+// particles that stay in its chunk get the consecutive places that the layout
+// set for them, and so do its arrivals.  A workgroup takes a container at a
+// time, or, where they hold few particles (`sparse`), each of its waves does: the
+// time of a small container is latency (an injection of 1000 and a step of 1e6
+// droplets in 32 768 containers 588 us by workgroups, 380 by waves; of 1e5 in
+// 32 768, 440 and 257).
 template <class T>
 __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
 {
     if (!a.flags[F_GO]) return;
-    __shared__ int32_t pos, hist[kHistMax];
+    __shared__ int32_t pos, nbig, big[kBigMax], hist[kHistMax];
     __shared__ bool last;
     const int cur = a.flags[F_CUR], t = a.flags[F_TICK];
     const int32_t ni = cur ? a.flags[F_NITEMS1] : a.flags[F_NITEMS];
@@ -1366,19 +1375,15 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
     const Cont *const ct = cur ? a.cont1 : a.cont0;
     const int m = (t + 2) % 3;
     const MoverRec<T> *const rec = a.rec + ((t + 1) & 1) * a.nrec;
-    for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) {
-        const ContState me = state_of(ct + it, m);
+    // Moves the slots first, first + step, ... of a container (lanes' slots
+    // consecutive) and its inbox's records; take(n) reserves places of those that stay.
+    auto move = [&](int32_t it, const ContState &me, int32_t nin, int32_t first, int32_t step,
+                    auto take) {
         const int32_t c = me.c, cnt = me.cnt;
-        const int32_t nin = min(me.in, inbox_cap(me.room, a.inbox));
-        if (cnt == 0 && nin == 0) continue;   // uniform
         const int4 l = a.lay[c];
-        if (threadIdx.x == 0) pos = ct[it].place[0];
         const int32_t in0 = ct[it].place[1];
-        __syncthreads();
-        const int64_t s0 = me.base;
-        for (int32_t o = 0; o < cnt; o += kScatterBlock) {   // every lane the same rounds
-            const int32_t o1 = o + threadIdx.x;
-            const int64_t q = s0 + o1;
+        for (int32_t o1 = first; o1 - (int32_t)__lane_id() < cnt; o1 += step) {   // every lane
+            const int64_t q = (int64_t)me.base + o1;
             MoverRec<T> r;
             int64_t cn = -1;
             bool home = false;
@@ -1394,17 +1399,60 @@ __global__ void __launch_bounds__(kScatterBlock) k_scatter(ScatterArgs<T> a)
                 }
             }
             const uint64_t stay = __ballot(home);
-            int32_t b = 0;
-            if (__lane_id() == 0) b = stay ? atomicAdd(&pos, __popcll(stay)) : 0;
-            b = __shfl(b, 0);
+            const int32_t b = take(__popcll(stay));
             if (home)
                 put_slot(W, slot_of_rank(l, b + __popcll(stay & lanes_below_mask())), r);
             else if (cn >= 0)   // a mover whose inbox was full
                 put_slot(W, slot_of_rank(a.lay[cn], atomicAdd(&a.cursor[cn], 1)), r);
         }
-        for (int32_t r = threadIdx.x; r < nin; r += kScatterBlock)
+        for (int32_t r = first; r < nin; r += step)
             put_slot(W, slot_of_rank(l, in0 + r), rec[me.ibase + r]);
+    };
+    auto arrivals = [&](const ContState &me) { return min(me.in, inbox_cap(me.room, a.inbox)); };
+    auto by_workgroup = [&](int32_t it) {
+        const ContState me = state_of(ct + it, m);
+        const int32_t nin = arrivals(me);
+        if (me.cnt == 0 && nin == 0) return;   // uniform
+        if (threadIdx.x == 0) pos = ct[it].place[0];
         __syncthreads();
+        move(it, me, nin, threadIdx.x, kScatterBlock, [&](int32_t n) {
+            int32_t b = 0;
+            if (__lane_id() == 0) b = n ? atomicAdd(&pos, n) : 0;
+            return __shfl(b, 0);
+        });
+        __syncthreads();
+    };
+    if (a.sparse) {
+        // a container per wave, those of more slots than kWaveSlots left to the
+        // workgroup (as many as it can note)
+        if (threadIdx.x == 0) nbig = 0;
+        __syncthreads();
+        const int32_t waves = kScatterBlock / 64;
+        for (int32_t w = blockIdx.x * waves + (threadIdx.x >> 6); w < ni; w += gridDim.x * waves) {
+            const int32_t it = __builtin_amdgcn_readfirstlane(w);
+            const ContState me = state_of(ct + it, m);
+            const int32_t nin = arrivals(me);
+            if (me.cnt == 0 && nin == 0) continue;
+            if (me.cnt > kWaveSlots) {
+                int32_t k = 0;
+                if (__lane_id() == 0) k = atomicAdd(&nbig, 1);
+                k = __shfl(k, 0);
+                if (k < kBigMax) {
+                    if (__lane_id() == 0) big[k] = it;
+                    continue;
+                }
+            }
+            int32_t at = ct[it].place[0];
+            move(it, me, nin, __lane_id(), 64, [&](int32_t n) {
+                at += n;
+                return at - n;
+            });
+        }
+        __syncthreads();
+        const int32_t nb = min(nbig, kBigMax);
+        for (int32_t k = 0; k < nb; ++k) by_workgroup(big[k]);
+    } else {
+        for (int32_t it = blockIdx.x; it < ni; it += gridDim.x) by_workgroup(it);
     }
     const StagingAt<T> staged(a.staged);
     for (int64_t r0 = (int64_t)blockIdx.x * kTile; r0 < a.npend;
@@ -2003,10 +2051,16 @@ Staging<T> staging_of(st_ctx *c)
 // Up to this many chunks the gate's own workgroup makes the layout.  Behind a
 // step the three launches of the other way nearly always find nothing to do and
 // cost it 13 us all the same; behind injections there is always a layout to
-// make.  Layout of 4096 chunks in one workgroup 40 us, of 32768 0.27 ms against
+// make.  Layout of 4096 chunks in one workgroup 40 us against 20, of 32768 0.27 ms against
 // 0.031 in three launches, of 262144 2.3 ms against 0.048, of 2097152 20 ms
 // against 0.23: at 32768 the launches pay from a full re-bin every 18 steps on.
-constexpr int64_t kLayoutOneStep = 32768, kLayoutOneFlush = 4096;
+constexpr int64_t kLayoutOneStep = 32768, kLayoutOneFlush = 2048;
+
+// The scatter's containers are taken by waves up to this many particles for each
+// on the average (placing an injection, 40 a container 0.67 by workgroups and 0.49
+// ms by waves, in a plume 0.73 and 0.56; 100 a container 0.205 and 0.182, but in a
+// plume 0.227 and 0.262).
+constexpr int64_t kSparsePer = 64;
 
 // everything after the step kernel (or, npend > 0, the placing of the staged
 // injections): the gate, and the full re-bin's scatter
@@ -2029,7 +2083,8 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
     }
     const ScatterArgs<T> a{views_of<T>(c), c->cont[0], c->cont[1],
                            (const MoverRec<T> *)c->rec, c->nrec, staging_of<T>(c), npend, c->lay,
-                           c->cursor, c->flags, c->C, c->inbox, c->prm,
+                           c->cursor, c->flags, c->C, c->inbox,
+                           c->count + npend <= kSparsePer * c->max_items, c->prm,
                            (int4 *)c->src,
                            (int32_t)(3 * c->prm.E * c->prm.E * c->prm.E * c->asize / 16),
                            c->written};

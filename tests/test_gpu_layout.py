@@ -18,7 +18,7 @@ TOL_FP32 = {"pos": 1e-5, "vel": 1e-5, "src": 1e-4}
 
 
 @pytest.mark.parametrize("form", sorted(TOL))
-@pytest.mark.parametrize("n,chunks", [((32, 32, 32), 4096), ((32, 34, 32), 4352),
+@pytest.mark.parametrize("n,chunks", [((32, 32, 16), 2048), ((32, 34, 16), 2176),
                                       ((64, 64, 64), 32768), ((64, 66, 64), 33792),
                                       ((66, 70, 62), 35805)])
 def test_layouts(form, n, chunks):
@@ -140,4 +140,43 @@ def test_adjoint_of_sparse_small_chunks(form, interp, tol):
                              lam.cpu().numpy())
     assert np.linalg.norm(dU - oU[0]) <= tol * np.linalg.norm(oU)
     assert np.linalg.norm(dd - od) <= tol * np.linalg.norm(od)
+    t.close()
+
+
+@pytest.mark.parametrize("form", ["fp64", "fp32_local", "fp32"])
+@pytest.mark.parametrize("per", [64, 65])
+def test_scatter_by_waves_and_workgroups(form, per):
+    """Particles a container on either side of where the re-bin's scatter goes by
+    waves, with containers of more slots than a wave takes, of one wave's and of none;
+    droplets whose inbox is full among them."""
+    orc = load_oracle()
+    n, edge = (32, 32, 40), 4
+    w = workload("tg32", n=n, L=tuple(0.1 * v / 32 for v in n), P=1, noise=0.3, chunk_edge=edge)
+    chunks = n[0] * n[1] * n[2] // edge ** 3
+    # (particles per container: a container more per 16384 of the capacity)
+    P = per * (chunks + 3)
+    assert -(-P // 16384) == 3
+    w = workload("tg32", n=n, L=w.L, P=P, noise=0.3, chunk_edge=edge)
+    rng = np.random.default_rng(per)
+    x = rng.random((P, 3)) * np.array(w.L)
+    k = P // 2
+    x[:k] = rng.random((k, 3)) * (8 * w.h) + 5 * w.h          # a few crowded chunks
+    x[k: k + P // 4, 0] *= 0.05                               # and a thin layer
+    up = rng.normal(0.0, 2.0, (P, 3))
+    d = np.full(P, 60e-6)
+    t = tracker(w, form)
+    Udev, Uor = fields(w, form)
+    vmax = float(np.abs(up).max())
+    tol = dict(TOL.get(form, TOL_FP32))
+    tol["vel"] *= vmax
+    bnd = band(form, w.n)
+    if form == "fp32":   # the binary32 rounding of the largest position
+        bnd = max(bnd, 2.0 ** -21 * (max(w.L) + vmax * 1e-3) / min(w.h))
+    t.inject(x[:P - 500], up[:P - 500], d[:P - 500])
+    lockstep_check(t, orc, oracle_mesh(w), Udev, Uor, 1e-3, 2, tol, band_=bnd)
+    t.inject(x[P - 500:], up[P - 500:], d[P - 500:])
+    before = t.stats()["repacks"]
+    lockstep_check(t, orc, oracle_mesh(w), Udev, Uor, 1e-3, 3, tol, band_=bnd)
+    assert t.stats()["repacks"] > before
+    assert np.array_equal(state(t)["id"], np.arange(P))
     t.close()
