@@ -415,8 +415,9 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
         c->inbox = rules[level];
         c->nrec = (c->slots >> c->inbox.shift) + c->inbox.plus * c->max_items;
         const int64_t stage = level ? std::max<int64_t>(1 << 16, d.capacity / 8)
-                                    : std::max<int64_t>(1 << 17, d.capacity / 16 * 5);
+                                    : std::max<int64_t>(1 << 17, d.capacity / 3 + 1);
         c->mcap = std::min<int64_t>(d.capacity, stage);
+        c->staged_stride = level ? 1 : 16;
     };
     hipError_t ok = hipErrorOutOfMemory;
     try {
@@ -438,7 +439,7 @@ st_status st_create_mesh(const st_mesh_desc *desc, int device, st_ctx **out)
             A(&c->rec, (size_t)(2 * c->nrec) * rec);
             A(&c->stage, (size_t)c->mcap * rec);
             A(&c->stage_dest, (size_t)c->mcap * 4);
-            A(&c->staged, (size_t)C * 4);
+            A(&c->staged, (size_t)(C * c->staged_stride) * 4);
             A(&c->cursor, (size_t)C * 4);
             A(&c->new_cnt, (size_t)C * 4);
             A(&c->lay, (size_t)C * 16);

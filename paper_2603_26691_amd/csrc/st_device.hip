@@ -153,7 +153,8 @@ struct GateArgs {
     int64_t slots;           // slots to share out among the particles and the spare ones
     InboxRule inbox;
     int32_t advance;         // after a step (not for staged injections alone)
-    int32_t *staged;         // [C] staged injections to be placed too, or null
+    int32_t *staged;         // [C] staged injections to be placed too, or null,
+    int64_t stride;          // so many apart
     int32_t one;             // the layout is made by the gate's own workgroup
 };
 
@@ -177,7 +178,7 @@ struct Layouts {
 // and the movers that found them full in), and staged ones.
 __device__ __forceinline__ int32_t chunk_total(const GateArgs &a, const Layouts &L, int64_t c)
 {
-    int32_t n = a.staged ? a.staged[c] : 0;
+    int32_t n = a.staged ? a.staged[c * a.stride] : 0;
     const int32_t j1 = L.cf[c + 1];
     for (int32_t j = L.cf[c]; j < j1; ++j) {
         const ContState s = state_of(L.ct + j, L.m);
@@ -203,7 +204,7 @@ __device__ __forceinline__ int32_t count_chunk(const GateArgs &a, const Layouts 
         n += min(L.ct[j].in[L.m], inbox_cap(L.ct[j].room, a.inbox));
         all += L.ct[j].in[L.m];
     }
-    if (a.staged) all += a.staged[c];
+    if (a.staged) all += a.staged[c * a.stride];
     a.new_cnt[c] = all;
     a.cursor[c] = n;
     return all;
@@ -255,7 +256,7 @@ __device__ __forceinline__ void write_chunk(const GateArgs &a, const Layouts &L,
 {
     L.ncf[c] = j0;
     a.lay[c] = int4{(int32_t)base, r.per, r.room, r.k};
-    if (a.staged) a.staged[c] = 0;
+    if (a.staged) a.staged[c * a.stride] = 0;
     for (int32_t i = 0; i < r.k; ++i) {
         Cont d;
         d.c = (int32_t)c;
@@ -1653,7 +1654,8 @@ __global__ void k_stage(int64_t n, const double *x, const double *up, const doub
 // re-bin that places them).  Those without a chunk (a bad value in a batch that
 // was staged in parts) are neither counted nor placed.
 template <class T>
-__global__ void __launch_bounds__(kScatterBlock) k_count_staged(int32_t *staged, Staging<T> from,
+__global__ void __launch_bounds__(kScatterBlock) k_count_staged(int32_t *staged,
+                                                                int64_t stride, Staging<T> from,
                                                                 int64_t at, int64_t n, int64_t C)
 {
     __shared__ int32_t hist[kHistMax];
@@ -1665,11 +1667,11 @@ __global__ void __launch_bounds__(kScatterBlock) k_count_staged(int32_t *staged,
     }
     for (int64_t i = (int64_t)blockIdx.x * kScatterBlock + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kScatterBlock)
-        if (dest[i] >= 0) atomicAdd(lds ? &hist[dest[i]] : &staged[dest[i]], 1);
+        if (dest[i] >= 0) atomicAdd(lds ? &hist[dest[i]] : &staged[dest[i] * stride], 1);
     if (lds) {
         __syncthreads();
         for (int32_t i = threadIdx.x; i < C; i += kScatterBlock)
-            if (hist[i]) atomicAdd(&staged[i], hist[i]);
+            if (hist[i]) atomicAdd(&staged[i * stride], hist[i]);
     }
 }
 
@@ -2073,7 +2075,7 @@ hipError_t launch_rebin(st_ctx *c, int64_t npend, hipStream_t s)
                      c->lay, c->flags, c->spread, c->lay_sums, c->lay_part, c->C,
                      {c->prm.nc[0], c->prm.nc[1], c->prm.nc[2]},
                      c->slots - (int64_t)kAlign * c->max_items, c->inbox, npend == 0,
-                     npend ? c->staged : nullptr, one};
+                     npend ? c->staged : nullptr, c->staged_stride, one};
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1024), 0, s, g);
     if (!one) {
         const dim3 lb((c->C + kLayBlock - 1) / kLayBlock);
@@ -2124,7 +2126,8 @@ hipError_t launch_init(st_ctx *c, hipStream_t s)
                        (int64_t)kSpreadInts, 0);
     hipLaunchKernelGGL(k_init, dim3(grid_for(c->C + 1)), dim3(256), 0, s, c->cont[0], c->first[0],
                        c->flags, c->C);
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C)), dim3(256), 0, s, c->staged, c->C, 0);
+    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->C * c->staged_stride)), dim3(256), 0, s,
+                       c->staged, c->C * c->staged_stride, 0);
     return hipGetLastError();
 }
 
@@ -2147,7 +2150,7 @@ hipError_t count_staged(st_ctx *c, int64_t at, int64_t n, hipStream_t s)
     if (n > 0) {
         const int64_t g = std::min<int64_t>((n + kTile - 1) / kTile, 512);
         hipLaunchKernelGGL((k_count_staged<T>), dim3(g), dim3(kScatterBlock), 0, s, c->staged,
-                           staging_of<T>(c), at, n, c->C);
+                           c->staged_stride, staging_of<T>(c), at, n, c->C);
     }
     return hipGetLastError();
 }
@@ -2251,7 +2254,7 @@ hipError_t launch_stage_inject(st_ctx *c, int64_t n, const double *x, const doub
 
 hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s)
 {
-    const hipError_t e = launch_zero_i32(c->staged, c->C, s);
+    const hipError_t e = launch_zero_i32(c->staged, c->C * c->staged_stride, s);
     if (e != hipSuccess) return e;
     return dispatch(c, [&](auto t, auto) -> hipError_t {
         return count_staged<decltype(t)>(c, 0, keep, s);

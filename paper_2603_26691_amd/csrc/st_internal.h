@@ -243,7 +243,8 @@ struct st_ctx {
     void *rec = nullptr;       // [2][nrec] inboxes, by the tick's parity
     void *stage = nullptr;         // [mcap] staged injections
     int32_t *stage_dest = nullptr; // [mcap] their chunks
-    int32_t *staged = nullptr;     // [C] their number by chunk
+    int32_t *staged = nullptr;     // [C] their number by chunk, so many apart: a line each,
+    int64_t staged_stride = 16;    // since neighbouring chunks are crowded together
     int32_t stage_in_store = 0;    // they are staged in the (empty) store instead
     int32_t *cursor = nullptr;     // [C] scatter cursors of the full re-bin
     int32_t *new_cnt = nullptr;    // [C] particles per chunk at a full re-bin
