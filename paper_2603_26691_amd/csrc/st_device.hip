@@ -557,6 +557,25 @@ __device__ __forceinline__ bool left_chunk(T x, T y, T z, T fe)
     return x < T(0) || x >= fe || y < T(0) || y >= fe || z < T(0) || z >= fe;
 }
 
+// Whether no value is NaN or infinite: binary64 by the exponents, binary32 by one
+// sum (which may overflow: then this is false too).
+template <class T, int G>
+__device__ __forceinline__ bool all_finite(const T (&v)[G])
+{
+    if constexpr (sizeof(T) == 8) {
+        uint32_t top = 0;
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            top = max(top, (uint32_t)__double2hiint(v[k]) & 0x7fffffffu);
+        return top < 0x7ff00000u;
+    } else {
+        T sum = v[0];
+#pragma unroll
+        for (int k = 1; k < G; ++k) sum += v[k];
+        return fabs(sum) < T(INFINITY);
+    }
+}
+
 // Where a container takes arrivals of the step with state index m (the state
 // before it: index pm): slots free for them whatever the step's departures
 // (more force the full re-bin), the records its inbox holds, and its first.
@@ -991,14 +1010,10 @@ __global__ void __launch_bounds__(NB)
         }
         // A first offset that is not finite (from a field or a velocity that is
         // not): the droplet has no place any more, and its slot is a hole like
-        // any other.  One sum tells whether the group has one (a hole's own
-        // offset is finite).  It costs 2 % of the binary64 step with
-        // Schiller-Naumann drag (1e7 on 128^3: 320 -> 327 us), as do the other
-        // places tried for it, and nothing that can be measured in other steps.
-        T sum = X[0];
-#pragma unroll
-        for (int k = 1; k < G; ++k) sum += X[k];
-        if (!(fabs(sum) < T(INFINITY))) {
+        // any other (a hole's own offset is finite).  It costs 1 % of the binary64
+        // step with Schiller-Naumann drag (1e7 on 128^3: 320 -> 325 us; a binary64
+        // sum or a test per droplet 327), and nothing that can be measured elsewhere.
+        if (!all_finite(X)) {
 #pragma unroll
             for (int k = 0; k < G; ++k)
                 if ((int)o + k < nq && DD[k] > T(0) && !(fabs(X[k]) < T(INFINITY))) {
