@@ -26,12 +26,12 @@
 // states is reversed from these, and consecutive such segments share the
 // anchors of the newest one's checkpoint (below), looked up by particle id; a
 // particle that this checkpoint no longer holds (its position ceased to be
-// finite) keeps its record by id (the
-// records by id itself would be scattered over the whole array: 69 us a step
-// against 55 us on 1e6 particles; in a recomputed segment, whose
-// ids are the anchors, 45 us).  Any other segment is recomputed from its checkpoint (deposit off), each step
-// saving the state it starts from, the ids and its layout as it streams
-// them, and then reversed newest first (the newest from the store itself).
+// finite) keeps its record by id (the records by id itself would be scattered
+// over the whole array: 69 us a step against 49 us on 1e6 particles; in a
+// recomputed segment, whose ids are the anchors, 45 us).  Any other segment is
+// recomputed from its checkpoint (deposit off), each step saving the state it
+// starts from, the ids and its layout as it streams them, and then reversed newest
+// first (the newest from the store itself).
 // The per-particle adjoint state is kept in one record of eight values of
 // the state precision per particle, indexed within a segment by the
 // particle's slot in the segment's checkpoint (its anchor): the restored
@@ -381,7 +381,8 @@ __global__ void k_fold_tiles(const double *tacc, Params p, int64_t C, double *Ub
 // Nearest grid point: the reverse of each particle adds its ufbar to its
 // cell of the tile with one LDS atomic per component, in binary64 (LDS adds of
 // binary32 values take longer on this chip); per chunk each tile cell's
-// sum goes to the chunk's binary64 tile sums (or, for a chunk split over several items, to dL/du with one atomic).
+// sum goes to the chunk's binary64 tile sums (or, for a chunk split over several
+// items, to dL/du with one atomic).
 template <class T, int E>
 __global__ void __launch_bounds__(kAdjBlock) k_adjoint_ngp(AdjArgs<T> a)
 {

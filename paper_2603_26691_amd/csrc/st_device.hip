@@ -1169,7 +1169,8 @@ __global__ void __launch_bounds__(NB)
         const int n = lane < 27 ? dcount[lane] : 0;
         const int32_t h_new = h_left + mcount + nlost;
         if (lane == 0) ct[item].s[m] = {nq, h_new};
-        // one atomic instruction (the counters differ per lane)
+        // one atomic instruction (the counters differ per lane, but for those
+        // of a mesh of one or two chunks along an axis)
         int32_t *ctr = nullptr;
         int add = n;
         if (n > 0) ctr = &ct[nbj[lane]].in[m];
@@ -1362,8 +1363,11 @@ constexpr int kScatterGroups = 1024;   // they run every step and usually exit a
 // kHistMax chunks, so that the counter of a crowded chunk is taken once per
 // tile: device atomics on one address are served one after the other (8 x
 // 375e3 droplets in two plumes on 1728 chunks: 8 x 0.53 ms of counts and 8 x
-// 0.57 ms of scatters with an atomic per droplet, 16 and 187 us in all now).  With more chunks the counters are
-// less crowded, and a droplet takes its own atomic.
+// 0.57 ms of scatters with an atomic per droplet, 16 and 187 us in all now; on
+// 8000 chunks, putting in 3e6 uniform droplets 0.74 against 1.16 ms, in two plumes
+// 0.50 against 3.7, 3e5 uniform ones 0.34 against 0.36).  More chunks than these do
+// not fit 32 KB of LDS, and their counters are less crowded: a droplet takes its
+// own atomic.
 constexpr int kHistMax = 8192;
 constexpr int kTilePer = 16, kTile = kTilePer * kScatterBlock;
 
@@ -1890,13 +1894,6 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
         p[i] = v;
 }
 
-__global__ void k_fill_i64(int64_t *p, int64_t n, int64_t v)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 // synthetic fluid update: U^k = R_z(theta_k) U^0, rounded once to T
 template <class T>
 __global__ void k_rotate(const T *u0, T *u, int64_t ncell, double cs, double sn)
@@ -2023,8 +2020,11 @@ hipError_t launch_step_t(st_ctx *c, const StepArgs<T, A> &a, hipStream_t s, hipE
 {
     // Twice the threads where the containers fill at most half of the 256 CUs
     // and hold more than one pass of 256 threads (32^3 mesh, 1e5 droplets in
-    // binary64: 24.7 against 27.4 us a step with its sources; with 270
-    // containers and more the larger workgroups lose 3 % and more).
+    // binary64: 24.7 against 27.4 us a step with its sources; 100 containers of
+    // 1600 droplets 18.8 against 21.3, in binary32 15.2 against 17.6).  Not with
+    // 270 containers in the FP32-everywhere form (3 % slower).  Between the two the
+    // line could lie higher: 125 to 252 containers of 800 to 4000 droplets are 8 to
+    // 20 % faster with twice the threads in the other forms.
     // Half the threads on large meshes of sparse small chunks: a workgroup's time
     // is latency there, and twice as many are in flight (64^3 cells in chunks of
     // 2^3, 1 and 8 droplets a chunk in binary32: 196 -> 141 and 275 -> 189 us; 128^3,

@@ -172,7 +172,7 @@ __device__ __forceinline__ int64_t box_particle(const BoxArgs<T> &a, int32_t id,
                                                 T d, const int64_t (&cc)[3], double (&xg)[3])
 {
     const Params &p = a.p;
-    // a hole has the mark for an offset (binary32) or a negated diameter (binary64)
+    // a hole has the mark for an offset, or a negated diameter (binary64)
     if (!(x > T(kHoleMark) && d > T(0)) || id < a.id0) return -1;
     const int64_t rel = id - a.id0;    // below 2^31
     const int64_t part = a.per_part > 0x7fffffff ? 0 : (uint32_t)rel / (uint32_t)a.per_part;
@@ -259,8 +259,8 @@ __global__ void __launch_bounds__(1024) k_bbox_tables(BoxArgs<T> a, int32_t Kp)
 
 // the tables of `groups` workgroups into the boxes
 template <class T>
-__global__ void __launch_bounds__(256) k_bbox_reduce(Store<T> st, int32_t groups, int32_t Kp, int64_t nparts,
-                                                     unsigned long long *box)
+__global__ void __launch_bounds__(256) k_bbox_reduce(Store<T> st, int32_t groups, int32_t Kp,
+                                                     int64_t nparts, unsigned long long *box)
 {
     const unsigned long long *const tables = box_tables(st);
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -410,7 +410,7 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
             hipLaunchKernelGGL((k_bbox_tables<T>), dim3(groups, passes), dim3(1024),
                                (size_t)Kp * 48, s, a, (int32_t)Kp);
             hipLaunchKernelGGL((k_bbox_reduce<T>), dim3((6 * nparts + 255) / 256), dim3(256), 0, s,
-                               a.st,                               (int32_t)groups, (int32_t)Kp, nparts, b);
+                               a.st, (int32_t)groups, (int32_t)Kp, nparts, b);
             return hipGetLastError();
         }
         hipLaunchKernelGGL(k_bbox_init, dim3(blocks_for(6 * nparts)), dim3(256), 0, s, b, nparts);

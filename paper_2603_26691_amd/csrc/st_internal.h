@@ -101,8 +101,9 @@ __host__ __device__ __forceinline__ int32_t inbox_cap(int32_t room, InboxRule ru
     return (room >> rule.shift) + rule.plus;
 }
 
-// One particle in flight between chunks (also staged by st_inject), kept together so that moving it reads and writes whole
-// 16-byte vectors: 32 bytes in binary32, 64 in binary64.
+// One particle in flight between chunks (also staged by st_inject), kept together
+// so that moving it reads and writes whole 16-byte vectors: 32 bytes in binary32,
+// 64 in binary64.
 template <class T>
 struct alignas(16) MoverRec {
     T ox, oy, oz, vx, vy, vz, d;
