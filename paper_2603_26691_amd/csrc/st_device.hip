@@ -2276,11 +2276,13 @@ hipError_t launch_unstage(st_ctx *c, int64_t keep, hipStream_t s)
     });
 }
 
-// The two-pass read-out from this many particles on.  Below it the outputs stay
-// in the caches, and its two launches more cost more than they save: 65536
-// particles 20 us directly, 25 in two passes; 131072 22 and 25; 262144 40 and 25
-// (binary64 40 and 32).
-constexpr int64_t kRecordsMin = 5 << 15;
+// The two-pass read-out from this many particles on.  Droplets that lie evenly and
+// are read again stay in the caches, where its two launches more cost some 8 us
+// (binary32, 66 000 in 512 chunks: 21.5 us directly, 31 in two passes); where they
+// have mixed or lie close together the direct one's scattered writes cost more
+// (four plumes in 4096 chunks, 66 000: 40 and 25, 130 000: 65 and 40; one: 110 and
+// 40, 212 and 89; in 32 768 chunks, evenly: 52 and 42).
+constexpr int64_t kRecordsMin = 1 << 16;
 
 hipError_t launch_get_particles(st_ctx *c, double *x, double *up, double *d, int64_t *id,
                                 int32_t *cell, hipStream_t s)

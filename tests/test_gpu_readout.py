@@ -218,12 +218,14 @@ def test_hilbert_large_per_segment():
 
 
 @pytest.mark.parametrize("form", FORMS)
-@pytest.mark.parametrize("P", [163_839, 163_840])
+@pytest.mark.parametrize("P", [65_535, 65_536, 163_839, 163_840])
 def test_read_out_where_its_way_changes(form, P):
     """The two ways of the read-out give the same droplets as another stream's,
     which is always direct."""
     import torch
     t, _ = _moved(P, form)
+    names = _kernels(lambda: t.particles())
+    assert ("k_records_out" in names) == (P >= 65_536), names
     mine = t.particles()
     torch.cuda.synchronize()
     with torch.cuda.stream(torch.cuda.Stream()):
