@@ -387,17 +387,24 @@ hipError_t launch_bounding_boxes(st_ctx *c, int64_t id0, int64_t per_part, int64
 {
     unsigned long long *b = (unsigned long long *)box;
     // Tables when the partitions fit a few of them, the re-bin's second
-    // store (second_store_free) has room for at least 32 workgroups' of them, and the
-    // atomics that they save are worth their 23 to 27 us: particles enough for each
-    // box to be in demand (P / nparts = 78: 18 us directly, 234: 41, 312: 49) or in
-    // all (2e5 in 1000 boxes 68 us directly, 36 by tables).  Beyond kBoxPasses each
-    // further table reads the store again.
+    // store (second_store_free) has room for at least 32 workgroups' of them, and
+    // their cost is less than what the direct updates may come to.  Beyond
+    // kBoxPasses each further table reads the store again.
+    //   The tables cost some 20 us and 1.5 us for each container that a workgroup
+    // takes in turn (max_items / groups of them); direct updates cost more with
+    // the particles, and with the particles that meet at one box where droplets
+    // lie close together: 8000 in 57 partitions and 512 chunks, evenly spread 25 us
+    // by tables and 33 directly, in one plume 25 and 175; 300 000 in 3000 and 32 768
+    // chunks 2054 and 91.  Over 1206 calls of 300 to 300 000 droplets, 1 to 15 000
+    // partitions and 0, 1 or 4 plumes this line takes 1.04 times what the better way
+    // of each call does, always tables 1.43, always direct 2.26.
     const int64_t passes = (nparts + kBoxTable - 1) / kBoxTable;
     const int64_t Kp = (nparts + passes - 1) / passes;
     const int64_t room = c->slots * (int64_t)c->tsize / (passes * Kp * 48);
     const int64_t groups = std::min(std::min<int64_t>(kBoxGroups, room), c->max_items);
-    const bool many = c->count >= 150 * nparts || c->count >= 1 << 17;
-    const bool tables = many && passes <= kBoxPasses && second_store_free(c, s) &&
+    const double worth = (double)c->count * (1.0 / 1500 + 1.0 / (16.0 * (double)nparts));
+    const bool tables = worth * (double)groups >= (double)c->max_items &&
+                        passes <= kBoxPasses && second_store_free(c, s) &&
                         groups >= std::min<int64_t>(32, c->max_items);
     auto run = [&](auto t) -> hipError_t {
         using T = decltype(t);

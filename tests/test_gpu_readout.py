@@ -164,13 +164,17 @@ def test_boxes_of_more_partitions_than_one_table():
 
 
 @pytest.mark.parametrize("form", FORMS)
-@pytest.mark.parametrize("P,nparts", [(15_000, 100), (14_999, 100), (131_072, 4000),
-                                      (131_071, 4000)])
-def test_boxes_where_their_way_changes(form, P, nparts):
-    """Particles per box, and in all, on either side of where tables take over
-    from updates in memory."""
+@pytest.mark.parametrize("P,nparts,edge,tables", [
+    (15, 1, 8, False), (16, 1, 8, True), (774, 100, 8, False), (775, 100, 8, True),
+    (121, 1, 2, False), (122, 1, 2, True), (5918, 100, 2, False), (5919, 100, 2, True),
+    (15_000, 100, 8, True), (131_072, 4000, 8, False), (21_300, 1000, 2, False)])
+def test_boxes_where_their_way_changes(form, P, nparts, edge, tables):
+    """Particles, particles per box and chunks per workgroup on either side of
+    where tables take over from updates in memory."""
     import torch
-    t, _ = _moved(P, form, capacity=600_000)
+    t, _ = _moved(P, form, edge=edge, capacity=600_000)
+    names = _kernels(lambda: t.bounding_boxes(0, -(-P // nparts), nparts))
+    assert ("k_bbox_tables" in names) == tables, names
     x = t.particles()["x"]
     per = -(-P // nparts)
     at = (torch.arange(P, device="cuda") // per)[:, None].expand(-1, 3)
