@@ -2068,10 +2068,12 @@ Staging<T> staging_of(st_ctx *c)
 // Up to this many chunks the gate's own workgroup makes the layout.  Behind a
 // step the three launches of the other way nearly always find nothing to do and
 // cost it 13 us all the same; behind injections there is always a layout to
-// make.  Layout of 4096 chunks in one workgroup 40 us against 20, of 32768 0.27 ms against
-// 0.031 in three launches, of 262144 2.3 ms against 0.048, of 2097152 20 ms
-// against 0.23: at 32768 the launches pay from a full re-bin every 18 steps on.
-constexpr int64_t kLayoutOneStep = 32768, kLayoutOneFlush = 2048;
+// make (an injection placed and read: 3072 chunks 166 us in one workgroup, 177 in three
+// launches, 4096 187 and 184, 6144 223 and 201).  Layout of 32768 chunks in one
+// workgroup 0.27 ms against 0.031 in three launches, of 262144 2.3 ms against 0.048, of
+// 2097152 20 ms against 0.23: at 32768 the launches pay from a full re-bin every 18
+// steps on.
+constexpr int64_t kLayoutOneStep = 32768, kLayoutOneFlush = 4096;
 
 // The scatter's containers are taken by waves up to this many particles for each
 // on the average (placing an injection, 40 a container 0.67 by workgroups and 0.49

@@ -19,6 +19,7 @@ TOL_FP32 = {"pos": 1e-5, "vel": 1e-5, "src": 1e-4}
 
 @pytest.mark.parametrize("form", sorted(TOL))
 @pytest.mark.parametrize("n,chunks", [((32, 32, 16), 2048), ((32, 34, 16), 2176),
+                                      ((32, 32, 32), 4096), ((32, 34, 32), 4352),
                                       ((64, 64, 64), 32768), ((64, 66, 64), 33792),
                                       ((66, 70, 62), 35805)])
 def test_layouts(form, n, chunks):
